@@ -274,7 +274,7 @@ int osc_rmsnorm_quantize_act(const void *X, const void *gamma, float eps, int64_
  * SwiGLU fused with the MXFP8 quantiser of the W_2 fallback (the W_2 inputs, position 4 of
  * Section 2.1, are silu(gate) * up; Section 4.1 quantises them to MXFP8): what
  * osc_quantize_act(fmt = OSC_FMT_MXFP8) returns for y = bf16(bf16(silu(g)) * u), without y
- * passing through memory.  silu(g) = g / (1 + exp(-g)) is computed as a fixed sequence of
+ * passing through memory.  silu(g) = g / (1 + exp(-g)) is defined as a fixed sequence of
  * correctly rounded single-precision operations: z = clamp(-g, -86, 86); n = rint(z * log2 e);
  * r = fma(n, -LN2_HI, z), r = fma(n, -LN2_LO, r) with LN2_HI = 0x1.62e4p-1, LN2_LO =
  * 0x1.7f7d1cp-20; p = Horner of 1 + r + r^2/2 + ... + r^6/720, one fma per step from the
@@ -283,11 +283,7 @@ int osc_rmsnorm_quantize_act(const void *X, const void *gamma, float eps, int64_
  *         halves of one fused GEMM output are fine: pass the pointers and the common stride)
  *   Xq    uint8 [M, K] E4M3 codes; Xs E8M0 scales as for OSC_FMT_MXFP8
  *   Yn    bf16 [M, K] (device) or NULL: receives y when given
- * From a few million elements on, this call and osc_swiglu_quantize_act_fp8 first tabulate
- * bf16(silu(g)) for all 65536 bf16 values of g with the arithmetic above (a second small kernel on
- * the same stream, into 128 KB of device memory that the library owns) and look the values up;
- * the results are the same bits.  Calls that overlap on one device rewrite the table with
- * identical contents.
+ * (The kernels evaluate a shorter sequence that has the same bf16 rounding for every finite bf16 g.)
  * Errors as osc_quantize_act.
  */
 int osc_swiglu_quantize_act(const void *G, const void *U, int64_t M, int64_t K, int64_t ldg,

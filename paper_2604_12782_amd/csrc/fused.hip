@@ -11,6 +11,7 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int FT = 256;  // four wavefronts, one row each at a time
+constexpr int64_t MAX_GRID = 1 << 22;  // workgroups of a one-trip launch (the kernels walk on from there)
 
 // bf16(a * r) for the two halves of a packed word, one single-precision multiplication each
 __device__ __forceinline__ uint32_t scale_pair(uint32_t w, float r) {
@@ -42,11 +43,6 @@ __device__ __forceinline__ void f64_round_mode(double& a, double& b) {
 __device__ __forceinline__ void sq_add(double& acc, uint32_t fbits) {
     const double x = (double)__builtin_bit_cast(float, fbits);
     asm volatile("v_fma_f64 %0, %1, %1, %0" : "+v"(acc) : "v"(x));
-}
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
-// element-wise maximum of two pairs of 16-bit magnitudes (one packed instruction)
-__device__ __forceinline__ uint32_t max_pair(uint32_t a, uint32_t b) {
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 
 // A wavefront owns a whole row: lane l holds the 16-byte chunks l, l + 64, ... (NCI of them), so
@@ -212,82 +208,49 @@ int launch_rmsnorm_quant_mxfp4(const uint16_t* X, const uint16_t* gamma, float e
 // ------------------------------------------------------------------------------------------
 // SwiGLU fused with the MXFP8 quantiser of the W_2 fallback (position 4 of Section 2.1; Section
 // 3.4; Section 4.1: MXFP8 for the W_2 inputs): y = bf16(bf16(silu(g)) * u) goes straight from
-// registers into E4M3 codes and E8M0 scales.  silu is a fixed sequence of correctly rounded single
-// precision operations (range reduction by ln 2, degree-6 Horner polynomial, one division), so the
-// codes are reproducible bit for bit.  Streaming kernel, same work split as the quantisers.
+// registers into E4M3 codes and E8M0 scales.
+//
+// silu is defined as a fixed sequence of correctly rounded single-precision operations (osc.h), but only
+// its bf16 rounding is ever used and its argument is a bf16 value, so there are 65536 cases.  The
+// sequence below (hardware exp2 and reciprocal, one Newton step on the reciprocal) gives the defined
+// sequence's bf16 result in every one of them with a finite gate (compared value by value on the
+// device; without the Newton step g = 5.9375, whose silu lies on a rounding boundary, comes out one
+// step high).  Eight vector instructions, two of them at quarter rate, instead of 28: the kernels
+// below are streams bound by HBM again at every size.  They replaced a 128 KB table in LDS
+// (one workgroup per CU, and a 4.7 us launch in front of every call to fill it).
 // ------------------------------------------------------------------------------------------
-__device__ __forceinline__ float silu_f32(float g) {
-    const float LOG2E = 0x1.715476p+0f, LN2_HI = 0x1.62e400p-1f, LN2_LO = 0x1.7f7d1cp-20f;
-    const float z = fminf(fmaxf(-g, -86.0f), 86.0f);
-    const float n = __builtin_rintf(__fmul_rn(z, LOG2E));
-    float r = __fmaf_rn(n, -LN2_HI, z);
-    r = __fmaf_rn(n, -LN2_LO, r);
-    float p = 1.0f / 720.0f;
-    p = __fmaf_rn(p, r, 1.0f / 120.0f);
-    p = __fmaf_rn(p, r, 1.0f / 24.0f);
-    p = __fmaf_rn(p, r, 1.0f / 6.0f);
-    p = __fmaf_rn(p, r, 0.5f);
-    p = __fmaf_rn(p, r, 1.0f);
-    p = __fmaf_rn(p, r, 1.0f);
-    const float e = __builtin_ldexpf(p, (int)n);
-    return __fdiv_rn(g, __fadd_rn(1.0f, e));
+__device__ __forceinline__ float silu_bf16_exact(float g) {
+    const float z = __builtin_amdgcn_fmed3f(g, -86.0f, 86.0f);
+    const float d = 1.0f + __builtin_amdgcn_exp2f(z * -0x1.715476p+0f);
+    float r = __builtin_amdgcn_rcpf(d);
+    r = __builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r);
+    return g * r;
 }
 // bf16(bf16(silu(g)) * u) for the two halves of a packed word
 __device__ __forceinline__ uint32_t swiglu_pair(uint32_t g, uint32_t u) {
     const uint32_t gl = g << 16, gh = g & 0xffff0000u;
-    const v2f s = {silu_f32(__builtin_bit_cast(float, gl)), silu_f32(__builtin_bit_cast(float, gh))};
+    const v2f s = {silu_bf16_exact(__builtin_bit_cast(float, gl)), silu_bf16_exact(__builtin_bit_cast(float, gh))};
     const uint32_t t = __builtin_bit_cast(uint32_t, __builtin_convertvector(s, v2bf));
     return mul_pair(t, u);
 }
-
-// bf16(silu(g)) is a function of the 16 bits of g: 65536 values, 128 KB.  For large inputs the
-// kernels below tabulate it once per call with the arithmetic above (every CU takes a slice), copy
-// the table into LDS (one workgroup per CU) and replace ~28 vector operations per element by one
-// LDS read; the results are the same bits by construction.  The table lives in device memory owned
-// by the library (128 KB per process and device); concurrent calls rewrite it with identical values.
-__device__ __attribute__((aligned(256))) uint16_t g_silu_tab[65536];
-
-__global__ void __launch_bounds__(256) silu_table_kernel() {
-    const uint32_t i = (blockIdx.x * 256u + threadIdx.x) * 2u;  // two neighbouring entries per thread
-    const v2f s = {silu_f32(__builtin_bit_cast(float, i << 16)), silu_f32(__builtin_bit_cast(float, (i + 1u) << 16))};
-    reinterpret_cast<uint32_t*>(g_silu_tab)[i >> 1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(s, v2bf));
+__device__ __forceinline__ uint32_t max_mag4(const uint32_t (&w)[4]) {  // two 16-bit maxima
+    return max_pair(max_pair(w[0] & 0x7fff7fffu, w[1] & 0x7fff7fffu), max_pair(w[2] & 0x7fff7fffu, w[3] & 0x7fff7fffu));
 }
-// the table from device memory into this workgroup's LDS (blockDim threads, 16 bytes each per trip)
-__device__ __forceinline__ void load_silu_table(uint16_t* tab) {
-    const u32x4* src = reinterpret_cast<const u32x4*>(g_silu_tab);
-    u32x4* dst = reinterpret_cast<u32x4*>(tab);
-    for (int i = threadIdx.x; i < 65536 * 2 / 16; i += blockDim.x) dst[i] = src[i];
-    __syncthreads();
-}
-template <bool TAB>
-__device__ __forceinline__ uint32_t swiglu_pair_t(uint32_t g, uint32_t u, const uint16_t* tab) {
-    if constexpr (TAB) {
-        const uint32_t t = (uint32_t)tab[g & 0xffffu] | ((uint32_t)tab[g >> 16] << 16);
-        return mul_pair(t, u);
-    } else {
-        return swiglu_pair(g, u);
-    }
-}
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
-// TAB: 1024 threads, the silu table in LDS; every four wavefronts act as one of the 256-thread
-// workgroups of the work split
-template <bool TAB>
-__global__ void __launch_bounds__(TAB ? 1024 : FT) swiglu_quant_mxfp8_kernel(const uint16_t* __restrict__ G,
+// 4 B read and 1 B written per element.  One (row, 1024-channel segment) per wavefront and trip as in
+// the quantisers; a lane's four 16-byte loads per trip on up to eight wavefronts per SIMD keep enough
+// bytes in flight.  8192 x 12288: 98.9 -> 79.0 us (6.4 TB/s), 1000 x 12288: 16.9 -> 12.9 us, table launch
+// included in the old figures.
+__global__ void __launch_bounds__(FT) swiglu_quant_mxfp8_kernel(const uint16_t* __restrict__ G,
                                                                 const uint16_t* __restrict__ U, int M, int K,
                                                                 int64_t ldg, int64_t ldu, uint8_t* __restrict__ Xq,
                                                                 uint8_t* __restrict__ Xs, uint16_t* __restrict__ Yn,
                                                                 int nseg, int total_wg) {
-    extern __shared__ uint16_t silu_lds[];
-    if (TAB) load_silu_table(silu_lds);
     const int Kg = K >> 5, Kg4 = (Kg + 3) >> 2;
     const int nchunk = K >> 3;
-    const int t = threadIdx.x, lane = t & 63, wave = (t >> 6) & 3;
-    const int sub = TAB ? (t >> 8) : 0, nsub = TAB ? 4 : 1;
-    // virtual workgroup number: keeps "number % 8 = XCD of the real workgroup", which the work split uses
-    // to give one XCD the 32 rows that share lines of scale words
-    const int b = blockIdx.x;
-    const int first = (gridDim.x & 7) == 0 ? (b & 7) + 8 * ((b >> 3) * nsub + sub) : b * nsub + sub;
-    for (int wg = first; wg < total_wg; wg += gridDim.x * nsub) {
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    for (int wg = blockIdx.x; wg < total_wg; wg += gridDim.x) {
         const QItem it = quant_item(wg, wave, nseg, M);
         if (it.m < 0) continue;  // uniform over the wavefront
         const int m = it.m;
@@ -301,20 +264,18 @@ __global__ void __launch_bounds__(TAB ? 1024 : FT) swiglu_quant_mxfp8_kernel(con
                 gv[i] = __builtin_nontemporal_load(gsrc + c0 + 64 * i);
                 uv[i] = __builtin_nontemporal_load(usrc + c0 + 64 * i);
             }
-        typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
         u32x2* dst = reinterpret_cast<u32x2*>(Xq + (int64_t)m * K);
         uint8_t* sdst = Xs + (int64_t)(m >> 5) * Kg4 * 128 + (m & 31) * 4;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int c = c0 + 64 * i;
-            const uint32_t ww[4] = {swiglu_pair_t<TAB>(gv[i].x, uv[i].x, silu_lds), swiglu_pair_t<TAB>(gv[i].y, uv[i].y, silu_lds),
-                                    swiglu_pair_t<TAB>(gv[i].z, uv[i].z, silu_lds), swiglu_pair_t<TAB>(gv[i].w, uv[i].w, silu_lds)};
+            const uint32_t ww[4] = {swiglu_pair(gv[i].x, uv[i].x), swiglu_pair(gv[i].y, uv[i].y),
+                                    swiglu_pair(gv[i].z, uv[i].z), swiglu_pair(gv[i].w, uv[i].w)};
             if (Yn && c < nchunk)
                 __builtin_nontemporal_store((u32x4){ww[0], ww[1], ww[2], ww[3]},
                                             reinterpret_cast<u32x4*>(Yn + (int64_t)m * K) + c);
-            uint32_t a = 0;
-#pragma unroll
-            for (int k = 0; k < 4; ++k) a = max(a, max(ww[k] & 0x7fffu, (ww[k] >> 16) & 0x7fffu));
+            const uint32_t a2 = max_mag4(ww);
+            uint32_t a = max(a2 & 0xffffu, a2 >> 16);
             a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0xB1, 0xF, 0xF, true));  // lane ^ 1
             a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x4E, 0xF, 0xF, true));  // lane ^ 2
             const uint32_t code = (uint32_t)max((int)(a >> 7) - 8, 0);  // E8M0 code = max(E - 8, 0)
@@ -323,35 +284,10 @@ __global__ void __launch_bounds__(TAB ? 1024 : FT) swiglu_quant_mxfp8_kernel(con
             word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x108, 0xF, 0xF, true) << 16;
             word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x10C, 0xF, 0xF, true) << 24;
             if ((lane & 15) == 0 && c < nchunk) *reinterpret_cast<uint32_t*>(sdst + (c >> 4) * 128) = word;
-            const float inv = __builtin_bit_cast(float, (254u - code) << 23);  // 2^-(code - 127)
-            float p[8];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const uint32_t lo = ww[k] << 16, hi = ww[k] & 0xffff0000u;
-                p[2 * k] = fminf(fmaxf(__fmul_rn(__builtin_bit_cast(float, lo), inv), -448.0f), 448.0f);
-                p[2 * k + 1] = fminf(fmaxf(__fmul_rn(__builtin_bit_cast(float, hi), inv), -448.0f), 448.0f);
-            }
-            int r0 = 0, r1 = 0;
-            r0 = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], r0, false);
-            r0 = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], r0, true);
-            r1 = __builtin_amdgcn_cvt_pk_fp8_f32(p[4], p[5], r1, false);
-            r1 = __builtin_amdgcn_cvt_pk_fp8_f32(p[6], p[7], r1, true);
-            if (c < nchunk) __builtin_nontemporal_store((u32x2){(uint32_t)r0, (uint32_t)r1}, dst + c);
+            const u32x2 out = mxfp8_codes(ww, code);
+            if (c < nchunk) __builtin_nontemporal_store(out, dst + c);
         }
     }
-}
-
-constexpr int SILU_TAB_BYTES = 65536 * 2;
-// The table pays for itself (its 128 KB are copied into every CU's LDS, about 2 us) from a few
-// million elements on.  The OSC_TUNE_SWIGLU_TABLE override forces the choice (a tuning and test aid; the results
-// are the same bits either way).
-static bool use_silu_table(int64_t M, int64_t K) {
-    if (const int t = tuning(TUNE_SWIGLU_TABLE); t >= 0) return t == 1;
-    return M * K >= ((int64_t)4 << 20);
-}
-static int launch_silu_table(hipStream_t st) {
-    hipLaunchKernelGGL(silu_table_kernel, dim3(128), dim3(256), 0, st);
-    return check_launch("silu_table_kernel");
 }
 
 int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, int64_t K, int64_t ldg, int64_t ldu,
@@ -361,136 +297,104 @@ int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, i
     const int64_t blocks = (M + 31) / 32;
     const int64_t total_wg = (blocks + 7) / 8 * 8 * (8 * nseg);
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "swiglu+quantize: M=%lld too large", (long long)M);
-    if (use_silu_table(M, K)) {
-        int rc = launch_silu_table(st);
-        if (rc) return rc;
-        auto kern = swiglu_quant_mxfp8_kernel<true>;
-        static unsigned char lds_done[MAX_DEVICES];
-        static size_t lds_reserved[MAX_DEVICES];
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), SILU_TAB_BYTES, lds_done, lds_reserved)) return rc;
-        const int64_t need = (total_wg + 3) / 4;
-        const int grid = (int)(need < 256 ? need : 256);
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(1024), SILU_TAB_BYTES, st, G, U, (int)M, (int)K, ldg, ldu, Xq, Xs, Yn,
-                           nseg, (int)total_wg);
-        return check_launch("swiglu_quant_mxfp8_kernel<table>");
-    }
-    const int grid = (int)(total_wg < 8192 ? total_wg : 8192);
-    hipLaunchKernelGGL(swiglu_quant_mxfp8_kernel<false>, dim3(grid), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, Xq,
+    // One trip per workgroup: the hardware hands out new workgroups as old ones drain, which beats walking a
+    // fixed grid at every size of whole segments (8192 x 12288: 79 us, a grid of 8192 86 us, of 2048 92 us).
+    // Rows of less than a segment leave lanes idle and are the exception (32768 x 768: 26.4 us against 24.7).
+    const int64_t cap = K >= SEG_CH ? MAX_GRID : 4096;
+    const int grid = (int)(total_wg < cap ? total_wg : cap);
+    hipLaunchKernelGGL(swiglu_quant_mxfp8_kernel, dim3(grid), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, Xq,
                        Xs, Yn, nseg, (int)total_wg);
     return check_launch("swiglu_quant_mxfp8_kernel");
 }
 
 // ------------------------------------------------------------------------------------------
 // SwiGLU fused with the per-token FP8 quantiser (Section 3.4: the W_2 inputs stay in 8 bits; this
-// is the per-token e4m3 form of that fallback): one wavefront per row, y = bf16(bf16(silu(g)) * u)
-// stays in registers between the row's amax reduction and the conversion, so gate and up are read
-// once and y is never written unless asked for.
+// is the per-token e4m3 form of that fallback): y = bf16(bf16(silu(g)) * u) stays in registers between
+// the row's amax reduction and the conversion, so gate and up are read once and y is never written
+// unless asked for.  WPR wavefronts share a row (thread t of them holds chunks t, t + 64 WPR, ...): one
+// for rows of at most 2048 channels (no barrier), four for longer ones, so that a few hundred rows
+// still occupy the chip and the row's values fit few registers (with a wavefront per row and the table
+// 1000 x 12288 took 30.9 us, now 13.0; 8192 x 12288 95.5 -> 84.6 us, 32768 x 768 37.3 -> 24.7 us).
 // ------------------------------------------------------------------------------------------
-// TAB: 768 threads (twelve rows at a time), the silu table in LDS
-template <int NCI, bool TAB>
-__global__ void __launch_bounds__(TAB ? 768 : FT) swiglu_quant_fp8_kernel(const uint16_t* __restrict__ G,
+template <int CPT, int WPR>
+__global__ void __launch_bounds__(FT) swiglu_quant_fp8_kernel(const uint16_t* __restrict__ G,
                                                               const uint16_t* __restrict__ U, int M, int K,
                                                               int64_t ldg, int64_t ldu, uint8_t* __restrict__ X8,
                                                               float* __restrict__ xs, uint16_t* __restrict__ Yn) {
-    typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-    extern __shared__ uint16_t silu_lds[];
-    if (TAB) load_silu_table(silu_lds);
-    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: row and segment arithmetic stays on the scalar unit
-    const int nwave = TAB ? 12 : 4;
+    static_assert(WPR == 1 || WPR == 4, "a wavefront or the workgroup per row");
+    __shared__ uint32_t red[2][4];  // two copies by parity of the trip: one barrier per row
+    const int t = WPR == 1 ? threadIdx.x & 63 : threadIdx.x, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nchunk = K >> 3;
-    // a wavefront owns a whole row (lane l holds chunks l, l + 64, ...): the row's amax is register work
-    // plus one 64-lane reduction, no barrier
-    for (int m = blockIdx.x * nwave + wave; m < M; m += gridDim.x * nwave) {
+    int par = 0;
+    for (int m = WPR == 1 ? blockIdx.x * 4 + wave : blockIdx.x; m < M; m += gridDim.x * (4 / WPR), par ^= 1) {
         const u32x4* gsrc = reinterpret_cast<const u32x4*>(G + (int64_t)m * ldg);
         const u32x4* usrc = reinterpret_cast<const u32x4*>(U + (int64_t)m * ldu);
-        uint32_t y[NCI][4];
-        uint32_t a = 0;
+        u32x4 gv[CPT], uv[CPT];
+        uint32_t y[CPT][4];
+        uint32_t a2 = 0;
 #pragma unroll
-        for (int i = 0; i < NCI; ++i) {
-            const int c = lane + 64 * i;
-            u32x4 gv = {0u, 0u, 0u, 0u}, uv = {0u, 0u, 0u, 0u};
+        for (int i = 0; i < CPT; ++i) {
+            const int c = t + 64 * WPR * i;
+            gv[i] = uv[i] = (u32x4){0u, 0u, 0u, 0u};
             if (c < nchunk) {
-                gv = __builtin_nontemporal_load(gsrc + c);
-                uv = __builtin_nontemporal_load(usrc + c);
+                gv[i] = __builtin_nontemporal_load(gsrc + c);
+                uv[i] = __builtin_nontemporal_load(usrc + c);
             }
-            y[i][0] = swiglu_pair_t<TAB>(gv.x, uv.x, silu_lds);
-            y[i][1] = swiglu_pair_t<TAB>(gv.y, uv.y, silu_lds);
-            y[i][2] = swiglu_pair_t<TAB>(gv.z, uv.z, silu_lds);
-            y[i][3] = swiglu_pair_t<TAB>(gv.w, uv.w, silu_lds);
+        }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) a = max(a, max(y[i][k] & 0x7fffu, (y[i][k] >> 16) & 0x7fffu));
+        for (int i = 0; i < CPT; ++i) {
+            const int c = t + 64 * WPR * i;
+            y[i][0] = swiglu_pair(gv[i].x, uv[i].x);
+            y[i][1] = swiglu_pair(gv[i].y, uv[i].y);
+            y[i][2] = swiglu_pair(gv[i].z, uv[i].z);
+            y[i][3] = swiglu_pair(gv[i].w, uv[i].w);
+            a2 = max_pair(a2, max_mag4(y[i]));
             if (Yn && c < nchunk)
                 __builtin_nontemporal_store((u32x4){y[i][0], y[i][1], y[i][2], y[i][3]},
                                             reinterpret_cast<u32x4*>(Yn + (int64_t)m * K) + c);
         }
-        a = wave_max_u32(a);
+        uint32_t a = wave_max_u32(max(a2 & 0xffffu, a2 >> 16));
+        if constexpr (WPR == 4) {
+            if ((t & 63) == 0) red[par][wave] = a;
+            __syncthreads();
+            a = max(max(red[par][0], red[par][1]), max(red[par][2], red[par][3]));
+        }
         const float amax = __builtin_bit_cast(float, a << 16);
         float scale = 1.0f, inv = 1.0f;
         if (amax >= 0x1p-100f) {
             scale = __fdiv_rn(amax, 448.0f);
             inv = __fdiv_rn(448.0f, amax);
         }
-        if (lane == 0) xs[m] = scale;
+        if (t == 0) xs[m] = scale;
         u32x2* dst = reinterpret_cast<u32x2*>(X8 + (int64_t)m * K);
 #pragma unroll
-        for (int i = 0; i < NCI; ++i) {
-            const int c = lane + 64 * i;
-            if (c < nchunk) {
-                float p[8];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const float lo = __builtin_bit_cast(float, y[i][k] << 16);
-                    const float hi = __builtin_bit_cast(float, y[i][k] & 0xffff0000u);
-                    p[2 * k] = fminf(fmaxf(__fmul_rn(lo, inv), -448.0f), 448.0f);
-                    p[2 * k + 1] = fminf(fmaxf(__fmul_rn(hi, inv), -448.0f), 448.0f);
-                }
-                int r0 = 0, r1 = 0;
-                r0 = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], r0, false);
-                r0 = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], r0, true);
-                r1 = __builtin_amdgcn_cvt_pk_fp8_f32(p[4], p[5], r1, false);
-                r1 = __builtin_amdgcn_cvt_pk_fp8_f32(p[6], p[7], r1, true);
-                __builtin_nontemporal_store((u32x2){(uint32_t)r0, (uint32_t)r1}, dst + c);
-            }
+        for (int i = 0; i < CPT; ++i) {
+            const int c = t + 64 * WPR * i;
+            if (c < nchunk) __builtin_nontemporal_store(fp8_codes(y[i], inv), dst + c);
         }
     }
 }
 
 int launch_swiglu_quant_fp8(const uint16_t* G, const uint16_t* U, int64_t M, int64_t K, int64_t ldg, int64_t ldu,
                             uint8_t* X8, float* xs, uint16_t* Yn, hipStream_t st) {
-    const int64_t nci = (K / 8 + 63) / 64;
-    if (nci > 32) return fail(OSC_ERR_UNSUPPORTED, "swiglu+fp8 quantize: K=%lld exceeds 16384", (long long)K);
-    if (use_silu_table(M, K)) {
-        int rc = launch_silu_table(st);
-        if (rc) return rc;
-        const int64_t need = (M + 11) / 12;
-        const int tgrid = (int)(need < 256 ? need : 256);
-#define OSC_TLAUNCH(C)                                                                                          \
-    {                                                                                                           \
-        auto kern = swiglu_quant_fp8_kernel<C, true>;                                                           \
-        static unsigned char lds_done[MAX_DEVICES];                                                             \
-        static size_t lds_reserved[MAX_DEVICES];                                                                \
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), SILU_TAB_BYTES, lds_done, lds_reserved)) return rc; \
-        hipLaunchKernelGGL(kern, dim3(tgrid), dim3(768), SILU_TAB_BYTES, st, G, U, (int)M, (int)K, ldg, ldu, X8, xs, Yn); \
-    }
-        if (nci <= 4) OSC_TLAUNCH(4)
-        else if (nci <= 8) OSC_TLAUNCH(8)
-        else if (nci <= 16) OSC_TLAUNCH(16)
-        else if (nci <= 24) OSC_TLAUNCH(24)
-        else OSC_TLAUNCH(32)
-#undef OSC_TLAUNCH
-        return check_launch("swiglu_quant_fp8_kernel<table>");
-    }
-    const int64_t want = (M + 3) / 4;
-    const int grid = (int)(want < 4096 ? want : 4096);
-#define OSC_SLAUNCH(C)                                                                                      \
-    hipLaunchKernelGGL((swiglu_quant_fp8_kernel<C, false>), dim3(grid), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, X8, \
+    const int64_t nchunk = K / 8;
+    if (nchunk > 8 * FT) return fail(OSC_ERR_UNSUPPORTED, "swiglu+fp8 quantize: K=%lld exceeds 16384", (long long)K);
+    const bool wave_rows = nchunk <= 4 * 64;
+    // one row (four short rows) per workgroup, as above: 8192 x 12288 85 us, 89 us on a grid of 2048
+    const int64_t want = wave_rows ? (M + 3) / 4 : M;
+    const int grid = (int)(want < MAX_GRID ? want : MAX_GRID);
+    const int64_t cpt = wave_rows ? (nchunk + 63) / 64 : (nchunk + FT - 1) / FT;
+#define OSC_SLAUNCH(C, W)                                                                                   \
+    hipLaunchKernelGGL((swiglu_quant_fp8_kernel<C, W>), dim3(grid), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, X8, \
                        xs, Yn)
-    if (nci <= 4) OSC_SLAUNCH(4);
-    else if (nci <= 8) OSC_SLAUNCH(8);
-    else if (nci <= 16) OSC_SLAUNCH(16);
-    else if (nci <= 24) OSC_SLAUNCH(24);
-    else if (nci <= 32) OSC_SLAUNCH(32);
-    else return fail(OSC_ERR_UNSUPPORTED, "swiglu+fp8 quantize: K=%lld exceeds 16384", (long long)K);
+    if (wave_rows) {
+        if (cpt <= 1) OSC_SLAUNCH(1, 1);
+        else if (cpt <= 2) OSC_SLAUNCH(2, 1);
+        else OSC_SLAUNCH(4, 1);
+    } else if (cpt <= 2) OSC_SLAUNCH(2, 4);
+    else if (cpt <= 4) OSC_SLAUNCH(4, 4);
+    else if (cpt <= 6) OSC_SLAUNCH(6, 4);
+    else OSC_SLAUNCH(8, 4);
 #undef OSC_SLAUNCH
     return check_launch("swiglu_quant_fp8_kernel");
 }

@@ -49,6 +49,53 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     return max(max(a, b), max(c, d));
 }
 
+// ---- packed 16-bit magnitudes and 8-bit codes ------------------------------------------------
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+// element-wise maximum of two pairs of 16-bit magnitudes (one packed instruction)
+__device__ __forceinline__ uint32_t max_pair(uint32_t a, uint32_t b) {
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+typedef unsigned int codes8 __attribute__((ext_vector_type(2)));  // eight one-byte codes
+// E4M3 codes of eight bf16 values (four packed words) with E8M0 scale code `code`, of which no value's
+// exponent exceeds code + 8: the scaled conversion rounds x * 2^(127 - code) to nearest even but does not
+// saturate, so magnitudes are clamped to 448 * 2^(code - 127) first, as bit patterns, two at a time
+// (the same codes as multiply, clamp to +-448, convert for every value and scale, at half the instructions)
+__device__ __forceinline__ codes8 mxfp8_codes(const uint32_t (&w)[4], uint32_t code) {
+    typedef __bf16 v2bf_ __attribute__((ext_vector_type(2)));
+    typedef short v2s_ __attribute__((ext_vector_type(2)));
+    const uint32_t lim = ((code + 8u) << 7 | 0x60u) * 0x00010001u;
+    const float scale = __builtin_bit_cast(float, code << 23);
+    uint32_t c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t mag = w[k] & 0x7fff7fffu;
+        c[k] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, mag), __builtin_bit_cast(u16x2, lim)));
+        c[k] |= w[k] & 0x80008000u;
+    }
+    v2s_ lo = {0, 0}, hi = {0, 0};
+    lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(lo, __builtin_bit_cast(v2bf_, c[0]), scale, false);
+    lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(lo, __builtin_bit_cast(v2bf_, c[1]), scale, true);
+    hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(v2bf_, c[2]), scale, false);
+    hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(v2bf_, c[3]), scale, true);
+    return (codes8){__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
+}
+// E4M3 codes of eight bf16 values times `inv` (one rounded multiplication each), saturating at +-448
+__device__ __forceinline__ codes8 fp8_codes(const uint32_t (&w)[4], float inv) {
+    float p[8];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t lo = w[k] << 16, hi = w[k] & 0xffff0000u;
+        p[2 * k] = __builtin_amdgcn_fmed3f(__fmul_rn(__builtin_bit_cast(float, lo), inv), -448.0f, 448.0f);
+        p[2 * k + 1] = __builtin_amdgcn_fmed3f(__fmul_rn(__builtin_bit_cast(float, hi), inv), -448.0f, 448.0f);
+    }
+    int r0 = 0, r1 = 0;
+    r0 = __builtin_amdgcn_cvt_pk_fp8_f32(p[0], p[1], r0, false);
+    r0 = __builtin_amdgcn_cvt_pk_fp8_f32(p[2], p[3], r0, true);
+    r1 = __builtin_amdgcn_cvt_pk_fp8_f32(p[4], p[5], r1, false);
+    r1 = __builtin_amdgcn_cvt_pk_fp8_f32(p[6], p[7], r1, true);
+    return (codes8){(uint32_t)r0, (uint32_t)r1};
+}
+
 // ---- work split of the row-streaming kernels: (row, 1024-channel segment) items --------------
 constexpr int SEG_CHUNKS = 128;             // chunks per segment (two per lane)
 constexpr int SEG_CH = SEG_CHUNKS * 8;      // channels per segment

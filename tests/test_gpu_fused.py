@@ -168,3 +168,19 @@ def test_swiglu_fp8_every_gate_value(osc, tuning, table):
     G = np.concatenate([bits, np.zeros(pad, np.uint16)]).reshape(-1, K)
     U = to_bf16_bits((0.5 + wl.rng(1801).random(G.shape)).astype(np.float32))
     check_swiglu_fp8(osc, G, U)
+
+
+# row lengths around every change of form: wavefront or workgroup per row (2048), chunks per thread
+# (4096, 8192, 12288), and more short rows than the MXFP8 form's fixed grid holds at once
+@pytest.mark.parametrize("M,K", [(5, 2048), (3, 4104), (2, 8200), (2, 12296), (1, 512), (6, 520)])
+def test_swiglu_fp8_row_forms(osc, M, K):
+    gen = wl.rng(1900 + K)
+    check_swiglu_fp8(osc, to_bf16_bits((gen.standard_normal((M, K)) * 3).astype(np.float32)),
+                     wl.activations_diffuse(1950 + K, M, K, p=0.01))
+
+
+@pytest.mark.parametrize("M,K", [(16450, 32), (33, 992), (33, 1024)])
+def test_swiglu_mxfp8_grid_forms(osc, M, K):
+    gen = wl.rng(2000 + K)
+    check_swiglu(osc, to_bf16_bits((gen.standard_normal((M, K)) * 3).astype(np.float32)),
+                 wl.activations_diffuse(2050 + K, M, K, p=0.01))
