@@ -58,6 +58,9 @@ __device__ __forceinline__ float chunk_abs_sum(u32x4 w) {
     return ((e0 + e1) + (e2 + e3)) + ((e4 + e5) + (e6 + e7));
 }
 
+// PARTIAL: every workgroup stores its own sum to abs_sum[blockIdx.x] instead of adding it to *abs_sum
+// (additions to one address are performed one after the other, about 9 ns each: 2.3 us for 256 of them).
+template <bool PARTIAL>
 __global__ void __launch_bounds__(PT) profile_abs_sum_kernel(const uint16_t* __restrict__ X, int64_t S,
                                                              int H, int64_t ldx, int nseg, int nslots,
                                                              double* __restrict__ abs_sum) {
@@ -85,7 +88,8 @@ __global__ void __launch_bounds__(PT) profile_abs_sum_kernel(const uint16_t* __r
     if (t == 0) {
         double s = 0.0;
         for (int i = 0; i < PW; ++i) s += part[i];
-        if (s != 0.0) atomicAdd(abs_sum, s);  // one atomic per workgroup: same-address atomics serialise
+        if constexpr (PARTIAL) abs_sum[blockIdx.x] = s;
+        else if (s != 0.0) atomicAdd(abs_sum, s);  // one atomic per workgroup: same-address atomics serialise
     }
 }
 
@@ -127,11 +131,26 @@ __device__ __forceinline__ void hist_chunk(u32x4 w, int c, int nchunk, int lane,
     }
 }
 
+// What osc_profile_calibrate adds to the counting pass: a column strip's counts become table entries in the
+// workgroup that adds to them last, and the strip that is finished last forms the mean density.
+struct CalibrateTail {
+    uint32_t* ended;    // one arrival counter per set of strips, zero at the start ...
+    uint32_t* strips;   // ... and one for the sets
+    int nsets;          // strip s belongs to set s % nsets
+    int R;
+    int16_t* table;
+    uint32_t *n_total, *n_hit;
+    float *density, *cbar, *T_out;
+};
+
 template <int G>
+__device__ void calibrate_tail(const CalibrateTail& ct, uint32_t* hist, int H, int nseg, int set);
+
+template <int G, bool CALIBRATE>
 __global__ void __launch_bounds__(PT) profile_hist_kernel(const uint16_t* __restrict__ X, int64_t S, int H,
                                                           int64_t ldx, int nseg, int nslots,
                                                           const float* __restrict__ Tptr,
-                                                          uint32_t* __restrict__ hist) {
+                                                          uint32_t* hist, CalibrateTail ct) {
     __shared__ uint32_t lhist[P_SEG_CH];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: row and segment arithmetic stays on the scalar unit
     const int seg = blockIdx.x % nseg, slot = blockIdx.x / nseg;
@@ -144,6 +163,7 @@ __global__ void __launch_bounds__(PT) profile_hist_kernel(const uint16_t* __rest
     // threshold as a bound on magnitude bit patterns: negative T admits everything (zeros too),
     // NaN or infinite T nothing
     const float T = *Tptr;
+    if (CALIBRATE && ct.T_out && blockIdx.x == 0 && t == 0) *ct.T_out = T;
     const uint32_t tbits = __builtin_bit_cast(uint32_t, T);
     int tb = (int)(tbits >> 16);
     if (tbits & 0x80000000u) tb = -1;
@@ -164,7 +184,21 @@ __global__ void __launch_bounds__(PT) profile_hist_kernel(const uint16_t* __rest
     for (int i = t; i < P_SEG_CH; i += PT) {
         const uint32_t v = lhist[i];
         const int ch = seg * P_SEG_CH + i;
-        if (v && ch < H) atomicAdd(&hist[ch], v);
+        if (v && ch < H) {
+            const uint32_t old = __hip_atomic_fetch_add(&hist[ch], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if constexpr (CALIBRATE) asm volatile("" ::"v"(old));  // the value is back, so the addition is done
+        }
+    }
+    if constexpr (CALIBRATE) {
+        // Every workgroup's additions have been performed before its own arrival, so the last arrival reads
+        // them all.  Only device-scope atomics cross workgroups here: no fence, because a device-scope
+        // release writes the whole L2 of the die back (with one the call took 210 us).
+        __shared__ int last;
+        const int set = seg % ct.nsets, members = (nseg - set + ct.nsets - 1) / ct.nsets;
+        __syncthreads();
+        if (t == 0) last = __hip_atomic_fetch_add(ct.ended + set, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(members * nslots - 1);
+        __syncthreads();
+        if (last) calibrate_tail<G>(ct, hist, H, nseg, set);
     }
 }
 
@@ -247,6 +281,85 @@ __global__ void __launch_bounds__(PT) profile_cbar_kernel(const uint32_t* __rest
     if (t == 0) *cbar = dcnt[0] ? (float)(dsum[0] / (double)dcnt[0]) : 0.0f;
 }
 
+// The same results at the end of osc_profile_calibrate's counting pass, for the strips of one set: 64 / G
+// groups per wavefront, one counter per lane.  A group's density replaces its first two counters (the
+// counts are the call's own scratch), where the last set to finish finds it for the mean: place t of a
+// workgroup adds groups t, t + PT, ... and the places are added in a fixed order.
+template <int G>
+__device__ void calibrate_tail(const CalibrateTail& ct, uint32_t* hist, int H, int nseg, int set) {
+    constexpr int GPW = 64 / G, GPS = P_SEG_CH / G;  // groups per wavefront, per strip
+    constexpr int NB = GPS / (PW * GPW);             // wavefront steps per strip (one for every G)
+    static_assert(GPS == NB * PW * GPW, "a strip is whole steps of the workgroup");
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6, l = lane & (G - 1), Kg = H / G;
+    for (int seg = set; seg < nseg; seg += ct.nsets) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const int k = seg * GPS + (b * PW + wave) * GPW + lane / G;
+            uint32_t v = k < Kg ? __hip_atomic_load(hist + (int64_t)k * G + l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+            uint32_t total = v;
+#pragma unroll
+            for (int o = G / 2; o; o >>= 1) total += (uint32_t)__shfl_xor((int)total, o);
+            for (int r = 0; r == 0 || r < ct.R; ++r) {
+                uint32_t top = v;
+#pragma unroll
+                for (int o = G / 2; o; o >>= 1) top = max(top, (uint32_t)__shfl_xor((int)top, o));
+                // lowest lane of the group that holds the largest count
+                const uint64_t who = __ballot(v == top && v != 0u) >> (lane & ~(G - 1));
+                const int pick = top ? __ffsll((unsigned long long)who) - 1 : -1;
+                if (l == 0 && k < Kg) {
+                    if (r < ct.R) ct.table[(int64_t)k * ct.R + r] = (int16_t)pick;
+                    if (r == 0) {
+                        const double c = total ? (double)top / (double)total : -1.0;  // -1: empty, not part of the mean
+                        if (ct.cbar)
+                            __hip_atomic_store(reinterpret_cast<uint64_t*>(hist + (int64_t)k * G), __builtin_bit_cast(uint64_t, c),
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (ct.n_total) ct.n_total[k] = total;
+                        if (ct.n_hit) ct.n_hit[k] = top;
+                        if (ct.density) ct.density[k] = total ? (float)c : 0.0f;
+                    }
+                }
+                if (l == pick) v = 0u;  // taken
+            }
+        }
+    }
+    if (!ct.cbar) return;
+    __shared__ int final_set;
+    __shared__ double dsum[PW];
+    __shared__ int dcnt[PW];
+    __builtin_amdgcn_s_waitcnt(0);  // this wavefront's densities have been stored
+    __syncthreads();
+    if (t == 0) final_set = __hip_atomic_fetch_add(ct.strips, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (uint32_t)(ct.nsets - 1);
+    __syncthreads();
+    if (!final_set) return;
+    double sum = 0.0;
+    int cnt = 0;
+    for (int k = t; k < Kg; k += PT) {
+        const double c = __builtin_bit_cast(double, __hip_atomic_load(reinterpret_cast<uint64_t*>(hist + (int64_t)k * G), __ATOMIC_RELAXED,
+                                                                      __HIP_MEMORY_SCOPE_AGENT));
+        if (c >= 0.0) {
+            sum += c;
+            ++cnt;
+        }
+    }
+#pragma unroll
+    for (int o = 32; o; o >>= 1) {
+        sum += __shfl_xor(sum, o);
+        cnt += __shfl_xor(cnt, o);
+    }
+    if (lane == 0) {
+        dsum[wave] = sum;
+        dcnt[wave] = cnt;
+    }
+    __syncthreads();
+    if (t == 0) {
+        for (int w = 1; w < PW; ++w) {
+            sum += dsum[w];
+            cnt += dcnt[w];
+        }
+        *ct.cbar = cnt ? (float)(sum / (double)cnt) : 0.0f;
+    }
+}
+
 // ---- launchers ---------------------------------------------------------------------------
 
 // Grid of the streaming kernels: nseg column strips x nslots row slots; enough workgroups to keep
@@ -264,7 +377,7 @@ int launch_profile_abs_sum(const uint16_t* X, int64_t S, int64_t H, int64_t ldx,
                            hipStream_t st) {
     int nseg, nslots;
     profile_grid(S, H, &nseg, &nslots);
-    hipLaunchKernelGGL(profile_abs_sum_kernel, dim3(nseg * nslots), dim3(PT), 0, st, X, S, (int)H, ldx, nseg,
+    hipLaunchKernelGGL(profile_abs_sum_kernel<false>, dim3(nseg * nslots), dim3(PT), 0, st, X, S, (int)H, ldx, nseg,
                        nslots, abs_sum);
     return check_launch("profile_abs_sum_kernel");
 }
@@ -275,18 +388,19 @@ int launch_profile_threshold(const double* abs_sum, int64_t count, float alpha, 
     return check_launch("profile_threshold_kernel");
 }
 
-int launch_profile_hist(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int32_t G, const float* T,
-                        uint32_t* hist, hipStream_t st) {
+template <bool CALIBRATE>
+static int launch_hist(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int32_t G, const float* T, uint32_t* hist,
+                       const CalibrateTail& ct, hipStream_t st) {
     int nseg, nslots;
     profile_grid(S, H, &nseg, &nslots);
-    const dim3 grid(nseg * nslots), block(PT);
-    if (G == 16)
-        hipLaunchKernelGGL(profile_hist_kernel<16>, grid, block, 0, st, X, S, (int)H, ldx, nseg, nslots, T, hist);
-    else if (G == 32)
-        hipLaunchKernelGGL(profile_hist_kernel<32>, grid, block, 0, st, X, S, (int)H, ldx, nseg, nslots, T, hist);
-    else
-        hipLaunchKernelGGL(profile_hist_kernel<64>, grid, block, 0, st, X, S, (int)H, ldx, nseg, nslots, T, hist);
+    auto kern = G == 16 ? profile_hist_kernel<16, CALIBRATE> : G == 32 ? profile_hist_kernel<32, CALIBRATE> : profile_hist_kernel<64, CALIBRATE>;
+    hipLaunchKernelGGL(kern, dim3(nseg * nslots), dim3(PT), 0, st, X, S, (int)H, ldx, nseg, nslots, T, hist, ct);
     return check_launch("profile_hist_kernel");
+}
+
+int launch_profile_hist(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int32_t G, const float* T,
+                        uint32_t* hist, hipStream_t st) {
+    return launch_hist<false>(X, S, H, ldx, G, T, hist, CalibrateTail{}, st);
 }
 
 int launch_profile_table(const uint32_t* hist, int32_t Kg, int32_t G, int32_t R, int16_t* table,
@@ -304,37 +418,60 @@ int launch_profile_table(const uint32_t* hist, int32_t Kg, int32_t G, int32_t R,
 }
 
 // ---- Alg. 1 in one call: threshold, candidate counts, table -------------------------------------
-// Scratch layout (caller's workspace): double abs_sum at 0, float T at 8, uint32 hist[H] at 256.
-__global__ void profile_clear_kernel(uint32_t* words, int64_t n) {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        words[i] = 0u;
+// Two readings of X are the work (the second finds most of it in the last-level cache); everything else is
+// launches and latency, so it is folded into three launches: 8192 x 4096 41.1 -> 31.9 us, 1024 x 4096
+// 24.2 -> 15.7 us against clear, sum, threshold, counts, table, mean and copy as kernels of their own.
+// Scratch layout (caller's workspace): float T at 0, arrival counters at 4, uint32 hist[H] at 256.  Until the
+// threshold is known the hist area holds the workgroups' partial sums (double, at most H / 2 of them).
+constexpr int CAL_SETS = 62;  // counters at 8 .. 255, the one for the sets at 4
+
+// Threshold from the partial sums (added in a fixed order), then counters and counts set to zero: workgroup 0
+// alone touches the area that held the sums.  (A kernel and not a memset: callers may record the call.)
+__global__ void __launch_bounds__(PT) profile_calibrate_mid_kernel(uint8_t* scratch, int npart, double count, double alpha, int64_t H) {
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    uint32_t* const hist = reinterpret_cast<uint32_t*>(scratch + 256);
+    if (blockIdx.x == 0) {
+        __shared__ double part[PW];
+        const double* sums = reinterpret_cast<const double*>(hist);
+        double s = 0.0;
+        for (int i = t; i < npart; i += PT) s += sums[i];
+#pragma unroll
+        for (int o = 32; o; o >>= 1) s += __shfl_xor(s, o);
+        if (lane == 0) part[wave] = s;
+        __syncthreads();  // also: every partial sum has been read
+        if (t == 0) {
+            for (int w = 1; w < PW; ++w) s += part[w];
+            *reinterpret_cast<float*>(scratch) = (float)(alpha * (s / count));
+        } else if (t < 64) {
+            reinterpret_cast<uint32_t*>(scratch)[t] = 0u;
+        }
+        for (int i = t; i < 2 * npart; i += PT) hist[i] = 0u;
+    }
+    for (int64_t i = 2 * npart + (int64_t)blockIdx.x * PT + t; i < H; i += (int64_t)gridDim.x * PT) hist[i] = 0u;
 }
-__global__ void profile_copy_float_kernel(const float* src, float* dst) { *dst = *src; }
 
 size_t profile_scratch_bytes(int64_t H) { return 256 + (size_t)H * 4; }
 
 int launch_profile_calibrate(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int32_t G, float alpha, int32_t R,
                              int16_t* table, uint32_t* n_total, uint32_t* n_hit, float* density, float* cbar,
                              float* T_out, uint8_t* scratch, hipStream_t st) {
-    double* abs_sum = reinterpret_cast<double*>(scratch);
-    float* T = reinterpret_cast<float*>(scratch + 8);
     uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + 256);
-    // a fill kernel, not a memset: callers may record this call into a graph
-    const int64_t words = (int64_t)(profile_scratch_bytes(H) / 4);
-    const int64_t wgs = (words + 255) / 256;
-    hipLaunchKernelGGL(profile_clear_kernel, dim3((unsigned)(wgs < 1024 ? wgs : 1024)), dim3(256), 0, st,
-                       reinterpret_cast<uint32_t*>(scratch), words);
-    int rc = check_launch("profile_clear_kernel");
+    int nseg, nslots;
+    profile_grid(S, H, &nseg, &nslots);
+    const int64_t room = H / 2 / nseg;  // partial sums fit the area of the counts
+    if (nslots > room) nslots = (int)room;
+    const int npart = nseg * nslots;
+    hipLaunchKernelGGL(profile_abs_sum_kernel<true>, dim3(npart), dim3(PT), 0, st, X, S, (int)H, ldx, nseg, nslots,
+                       reinterpret_cast<double*>(hist));
+    int rc = check_launch("profile_abs_sum_kernel");
     if (rc) return rc;
-    if ((rc = launch_profile_abs_sum(X, S, H, ldx, abs_sum, st))) return rc;
-    if ((rc = launch_profile_threshold(abs_sum, S * H, alpha, T, st))) return rc;
-    if ((rc = launch_profile_hist(X, S, H, ldx, G, T, hist, st))) return rc;
-    if ((rc = launch_profile_table(hist, (int32_t)(H / G), G, R, table, n_total, n_hit, density, cbar, st))) return rc;
-    if (T_out) {
-        hipLaunchKernelGGL(profile_copy_float_kernel, dim3(1), dim3(1), 0, st, T, T_out);
-        rc = check_launch("profile_copy_float_kernel");
-    }
-    return rc;
+    const int64_t wgs = (H + 4 * PT - 1) / (4 * PT);
+    hipLaunchKernelGGL(profile_calibrate_mid_kernel, dim3((unsigned)(wgs < 256 ? wgs : 256)), dim3(PT), 0, st, scratch, npart,
+                       (double)(S * H), (double)alpha, H);
+    if ((rc = check_launch("profile_calibrate_mid_kernel"))) return rc;
+    const CalibrateTail ct{reinterpret_cast<uint32_t*>(scratch + 8), reinterpret_cast<uint32_t*>(scratch + 4),
+                           nseg < CAL_SETS ? nseg : CAL_SETS, R, table, n_total, n_hit, density, cbar, T_out};
+    return launch_hist<true>(X, S, H, ldx, G, reinterpret_cast<const float*>(scratch), hist, ct, st);
 }
 
 // ---- the same call for callers that cannot allocate -----------------------------------------------

@@ -166,3 +166,17 @@ def test_calibrate_in_one_call(osc, S, H, G, R):
     T4 = osc.osc_profile_threshold(acc, S * H, 5.0)
     t4 = osc.osc_profile_table(osc.osc_profile_hist(bf(X), T4, G), R)
     assert torch.equal(t4[0], table) and torch.equal(t4[1], n_total) and torch.equal(t4[2], n_hit)
+
+
+# the one-call form at the edges of its scratch and of its arrival counters: fewer partial sums than
+# workgroups, more column strips than counters, every slot of a group asked for
+@pytest.mark.parametrize("S,H,G,R", [(700, 16, 16, 16), (3, 64, 64, 64), (40, 1040, 16, 2), (18, 65600, 32, 1), (2100, 2048, 64, 2)])
+def test_calibrate_scratch_edges(osc, S, H, G, R):
+    X = wl.activations_diffuse(9600 + H, S, H, p=0.02)
+    table, n_total, n_hit, density, cbar, T = osc.osc_profile_calibrate(bf(X), G, 5.0, R)
+    ref_T = oracle.profile_threshold(X, 5.0)
+    assert abs(T.item() - ref_T) <= 1e-6 * ref_T
+    rt, rn, rh, rd, rc = oracle.profile_table(oracle.profile_hist(X, T.item(), G), R)
+    assert np.array_equal(table.cpu().numpy(), rt)
+    assert np.array_equal(as_u32(n_total), rn.astype(np.uint32)) and np.array_equal(as_u32(n_hit), rh.astype(np.uint32))
+    assert np.allclose(density.cpu().numpy(), rd, rtol=1e-6, atol=0) and abs(cbar.item() - rc) <= 1e-6
