@@ -28,6 +28,8 @@
 //   gemm_pipe2_kernel  the same data path, persistent workgroups, slot-pinned instruction order,
 //                      early buffer release; one problem (dual path, FP8 or MXFP8) of more than one whole
 //                      256x256 tile per CU (a ragged row tail goes to the DMA kernel);
+//   gemm_stream_kernel few rows: single problems of up to 32 (more where N is small), experts of up to eight on
+//                      average; 16-row instructions, any legal row length;
 //   gemm_skinny_kernel M <= 64 (decode) and other launches of at most 512 blocks of 32x32 outputs: one
 //                      workgroup per 32 output channels streams the weights once, its wavefronts split
 //                      the reduction axis;
@@ -2185,6 +2187,274 @@ static int launch_skinny(KArgs a, hipStream_t st) {
     return launch_skinny_cfg<MODE, 3, 3>(a, (unsigned)grid, mtiles, st);
 }
 
+// ------------------------------------------------------------------------------------------
+// Streaming kernel (few rows: decode batches, single problems and experts), dual path, FP8 and MXFP8.
+// The work is reading the weights once, so what counts is that every CU has requests to HBM in flight from
+// the first moment on and that every CU has a share.  A workgroup owns 16 NT output channels and 16 MT
+// rows; its NW wavefronts take the 128-byte lines of the reduction axis (FP4 or 8-bit lines, then lines of
+// the bf16 branch) in turn and add their partial results through LDS in a fixed order at the end.  A
+// wavefront loads the next line (eight lanes per row and line: 16-byte pieces of whole lines; loads in
+// matrix-core layout, where neighbouring lanes hold different rows, ran at a quarter of the rate) into one
+// of two register sets while it takes the current one through a strip of LDS of its own into
+// matrix-core layout: no barrier, and the waits are the compiler's counted ones.  Against the kernel below
+// (32 channels and 32 rows per workgroup, operands by DMA through LDS rings), weights from HBM, us:
+//   M x N x K          dual path        FP8              MXFP8
+//   1 x 1024 x 4096    4.50 -> 3.71
+//   1 x 4096 x 4096    5.15 -> 4.42     6.53 -> 5.36     6.51 -> 5.89
+//   16 x 12288 x 4096  9.45 -> 8.4      14.2 -> 10.9     14.5 -> 11.7
+//   16 x 24576 x 4096  14.9 -> 12.3
+//   16 x 4096 x 12288                   16.2 -> 11.4     16.5 -> 12.3     (50 MB: 4.5 TB/s with the launch)
+//   32 x 4096 x 4096   5.9 -> 5.3       K = 12288: 19.1 -> 14.4
+// and, grouped, 128 experts of 1536 x 2048 (dual) and 2048 x 768 (FP8) with two rows each on average against
+// tiles of 64 x 128: 50.5 -> 38.1 us and 42.1 -> 31.0 us (6 TB/s).
+// Layout of the 16-row instructions (lane = 16 q + r): v_mfma_scale_f32_16x16x128_f8f6f4 takes from lane
+// (q, r) of row r, FP4: the 32 elements (16 bytes) of scale block q and its scale byte; 8 bits: elements
+// 16q .. 16q+15 of each half of the 128 (registers 0-3, 4-7), and the scale of the 32-element block q.
+// v_mfma_f32_16x16x32_bf16: 8 elements (16 bytes).  Result register k: row 4q + k, column r.
+// An FP4 or bf16 line is two instructions, instruction i taking piece 2q + i for lane block q (its two scale
+// bytes are then one 16-bit word); an 8-bit line is one, pieces q and 4 + q.
+// GROUPED: blockIdx.y is the expert; its rows are taken 16 MT at a time (an expert without rows leaves
+// at once).  RAGGED: rows need not be whole lines; pieces past the end of a row come from the block of
+// zeros in the packed weight.
+// ------------------------------------------------------------------------------------------
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+template <int MODE, int MT, int NT, int NW, bool GROUPED, bool RAGGED>
+__global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(KArgs a) {
+    constexpr bool DUAL = MODE == MODE_DUAL, MX = MODE == MODE_MX8;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int q = lane >> 4, r = lane & 15;
+    const int n0 = blockIdx.x * (16 * NT);
+    int m_begin = blockIdx.y * (16 * MT), m_end = min(a.M, m_begin + 16 * MT);
+    const uint8_t* wp = a.Wpack;
+    if constexpr (GROUPED) {
+        m_begin = a.off[blockIdx.y];
+        m_end = a.off[blockIdx.y + 1];
+        if (m_begin >= m_end) return;
+        wp += (size_t)blockIdx.y * a.pack_stride;
+    }
+    const int Kg4 = ((a.K >> 5) + 3) >> 2;
+    const int rowbytes = DUAL ? a.K >> 1 : a.K;
+    const int nL = (rowbytes + 127) >> 7;
+    const int nLT = nL + (DUAL ? (a.K_o * 2 + 127) >> 7 : 0);
+    const uint8_t* const wq = wp + a.off_q;
+    const uint8_t* const wl = wp + a.off_l;
+    const uint8_t* const wsb = wp + a.off_s;
+    const uint8_t* const zeros = wp + a.off_z;
+    // instruction h of a 16-row tile loads rows 8h .. 8h+7, eight lanes per line; piece ^ swizzle = place in LDS
+    const int lrow = lane >> 3;
+    const uint32_t p0 = (uint32_t)(lane & 7) * 16u;
+    // scale bytes of a lane inside a line's words: FP4 bytes 2(q%2), +1 of word q/2 of two; MXFP8 byte q of one
+    const uint32_t sc_lane = DUAL ? (uint32_t)(q >> 1) * 128u + 2u * (q & 1) : (uint32_t)q;
+    uint32_t ow[NT][2], owb[NT][2], osw[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t n = (uint32_t)min(n0 + 16 * j + 8 * h + lrow, a.N - 1);
+            ow[j][h] = n * (uint32_t)rowbytes + p0;
+            owb[j][h] = n * (uint32_t)a.wlpitch + p0;
+        }
+        const uint32_t n = (uint32_t)min(n0 + 16 * j + r, a.N - 1);
+        osw[j] = (n >> 5) * (uint32_t)Kg4 * 128u + (n & 31u) * 4u + sc_lane;
+    }
+    // one line of the workgroup's rows per wavefront (rows 0 .. 16 NT - 1 weights, then X); later the partial sums
+    constexpr int STRIP = 16 * (NT + MT) * 128;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_s[NW * (STRIP > MT * NT * 1024 ? STRIP : MT * NT * 1024)];
+    uint8_t* const strip = lds_s + wave * STRIP;
+    float* const red = reinterpret_cast<float*>(lds_s);
+    uint32_t wpos[2], rpos[2];  // places in a 16-row tile: written (instruction h), read (piece p of lane block q)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        wpos[h] = (uint32_t)st128_off(8 * h + lrow, lane & 7);
+        rpos[h] = (uint32_t)st128_off(r, DUAL ? 2 * q + h : q + 4 * h);
+    }
+
+    struct Line {
+        u32x4 w[NT][2], x[MT][2];
+        uint32_t sw[NT], sx[MT];
+    };
+    // line L_ (clamped by the caller) into S_; a branch line fetches the last scale words again (unused)
+#define STREAM_AT(BASE_, OFF_, POS_, VALID_) (RAGGED && (POS_) >= (uint32_t)(VALID_) ? zeros : (BASE_) + (OFF_))
+#define STREAM_LOAD(L_, S_)                                                                               \
+    {                                                                                                     \
+        const int l__ = (L_);                                                                             \
+        const bool main__ = !DUAL || l__ < nL;                                                            \
+        const uint32_t lo__ = (uint32_t)(main__ ? l__ : l__ - nL) * 128u;                                 \
+        const uint8_t* wb__ = (main__ ? wq : wl) + lo__;                                                  \
+        const uint8_t* xb__ = (main__ ? a.Xq : a.B) + lo__;                                               \
+        const uint32_t vw__ = (uint32_t)(main__ ? rowbytes : (int)a.wlpitch), vx__ = (uint32_t)(main__ ? rowbytes : (int)a.bpitch); \
+        _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                    \
+            _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
+                S_.w[j][p] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(                   \
+                    STREAM_AT(wb__, (main__ ? ow[j][p] : owb[j][p]), lo__ + p0, vw__)));      \
+        _Pragma("unroll") for (int i = 0; i < MT; ++i)                                                    \
+            _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
+                S_.x[i][p] = *reinterpret_cast<const u32x4*>(                                             \
+                    STREAM_AT(xb__, (main__ ? ox[i][p] : oxb[i][p]), lo__ + p0, vx__));       \
+        if (DUAL || MX) {                                                                                 \
+            const int ls__ = min(l__, nL - 1);                                                            \
+            uint32_t so__ = (uint32_t)ls__ * (DUAL ? 256u : 128u);                                        \
+            if (RAGGED && DUAL && 2 * ls__ + 1 >= Kg4) so__ -= (q >> 1) * 128u; /* one word only */       \
+            _Pragma("unroll") for (int j = 0; j < NT; ++j)                                                \
+                S_.sw[j] = DUAL ? (uint32_t)*reinterpret_cast<const uint16_t*>(wsb + (so__ + osw[j])) : (uint32_t)wsb[so__ + osw[j]]; \
+            _Pragma("unroll") for (int i = 0; i < MT; ++i)                                                \
+                S_.sx[i] = DUAL ? (uint32_t)*reinterpret_cast<const uint16_t*>(a.Xs + (so__ + osx[i])) : (uint32_t)a.Xs[so__ + osx[i]]; \
+        }                                                                                                 \
+    }
+#define STREAM_COMPUTE(L_, S_)                                                                            \
+    {                                                                                                     \
+        /* through the wavefront's strip into matrix-core layout (LDS runs a wavefront's operations in order) */ \
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                                            \
+        __builtin_amdgcn_wave_barrier();                                                                  \
+        _Pragma("unroll") for (int p = 0; p < 2; ++p) {                                                   \
+            _Pragma("unroll") for (int j = 0; j < NT; ++j) *reinterpret_cast<u32x4*>(strip + j * 2048 + wpos[p]) = S_.w[j][p]; \
+            _Pragma("unroll") for (int i = 0; i < MT; ++i) *reinterpret_cast<u32x4*>(strip + (NT + i) * 2048 + wpos[p]) = S_.x[i][p]; \
+        }                                                                                                 \
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");                                            \
+        __builtin_amdgcn_wave_barrier();                                                                  \
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");                                            \
+        u32x4 fw__[NT][2], fx__[MT][2];                                                                   \
+        _Pragma("unroll") for (int p = 0; p < 2; ++p) {                                                   \
+            _Pragma("unroll") for (int j = 0; j < NT; ++j) fw__[j][p] = *reinterpret_cast<const u32x4*>(strip + j * 2048 + rpos[p]); \
+            _Pragma("unroll") for (int i = 0; i < MT; ++i) fx__[i][p] = *reinterpret_cast<const u32x4*>(strip + (NT + i) * 2048 + rpos[p]); \
+        }                                                                                                 \
+        if (!DUAL || (L_) < nL) {                                                                         \
+            _Pragma("unroll") for (int p = 0; p < (DUAL ? 2 : 1); ++p)                                    \
+                _Pragma("unroll") for (int i = 0; i < MT; ++i)                                            \
+                    _Pragma("unroll") for (int j = 0; j < NT; ++j) {                                      \
+                        const u32x4 x0__ = fx__[i][p], w0__ = fw__[j][p], x1__ = fx__[i][1], w1__ = fw__[j][1]; \
+                        if constexpr (DUAL) {                                                             \
+                            const v8i av__ = {(int)x0__.x, (int)x0__.y, (int)x0__.z, (int)x0__.w, 0, 0, 0, 0}; \
+                            const v8i bv__ = {(int)w0__.x, (int)w0__.y, (int)w0__.z, (int)w0__.w, 0, 0, 0, 0}; \
+                            if (p == 0) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av__, bv__, acc[i][j], 4, 4, 0, (int)S_.sx[i], 0, (int)S_.sw[j]); \
+                            else acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av__, bv__, acc[i][j], 4, 4, 1, (int)S_.sx[i], 1, (int)S_.sw[j]); \
+                        } else {                                                                          \
+                            const v8i av__ = {(int)x0__.x, (int)x0__.y, (int)x0__.z, (int)x0__.w, (int)x1__.x, (int)x1__.y, (int)x1__.z, (int)x1__.w}; \
+                            const v8i bv__ = {(int)w0__.x, (int)w0__.y, (int)w0__.z, (int)w0__.w, (int)w1__.x, (int)w1__.y, (int)w1__.z, (int)w1__.w}; \
+                            acc[i][j] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(av__, bv__, acc[i][j], 0, 0, 0, \
+                                MX ? (int)S_.sx[i] : 0x7f7f7f7f, 0, MX ? (int)S_.sw[j] : 0x7f7f7f7f);     \
+                        }                                                                                 \
+                    }                                                                                     \
+        } else {                                                                                          \
+            _Pragma("unroll") for (int p = 0; p < 2; ++p)                                                 \
+                _Pragma("unroll") for (int i = 0; i < MT; ++i)                                            \
+                    _Pragma("unroll") for (int j = 0; j < NT; ++j)                                        \
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, fx__[i][p]), \
+                                                                            __builtin_bit_cast(v8bf, fw__[j][p]), acc[i][j], 0, 0, 0); \
+        }                                                                                                 \
+    }
+    for (int mb = m_begin; mb < m_end; mb += 16 * MT) {
+        uint32_t ox[MT][2], oxb[MT][2], osx[MT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                int g = min(mb + 16 * i + 8 * h + lrow, m_end - 1);
+                if (GROUPED && DUAL && a.row_map) g = a.row_map[g];
+                ox[i][h] = (uint32_t)g * (uint32_t)rowbytes + p0;
+                oxb[i][h] = (uint32_t)g * (uint32_t)a.bpitch + p0;
+            }
+            int g = min(mb + 16 * i + r, m_end - 1);
+            if (GROUPED && DUAL && a.row_map) g = a.row_map[g];
+            osx[i] = (uint32_t)(g >> 5) * (uint32_t)Kg4 * 128u + (uint32_t)(g & 31) * 4u + sc_lane;
+        }
+        v4f acc[MT][NT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+        if (wave < nLT) {
+            // two sets written out in turn: a copy from one to the other would wait for the loads in flight
+            Line sa, sb;
+            int L = wave;
+            STREAM_LOAD(L, sa)
+#pragma unroll 1
+            for (; L + 2 * NW < nLT; L += 2 * NW) {
+                STREAM_LOAD(L + NW, sb)
+                STREAM_COMPUTE(L, sa)
+                STREAM_LOAD(L + 2 * NW, sa)
+                STREAM_COMPUTE(L + NW, sb)
+            }
+            if (L + NW < nLT) {
+                STREAM_LOAD(L + NW, sb)
+                STREAM_COMPUTE(L, sa)
+                STREAM_COMPUTE(L + NW, sb)
+            } else {
+                STREAM_COMPUTE(L, sa)
+            }
+        }
+        // ---- sum the NW partial results in a fixed order, store ----
+        __syncthreads();  // every wavefront is done with its strip
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) red[((wave * MT * NT + i * NT + j) * 4 + k) * 64 + lane] = acc[i][j][k];
+        __syncthreads();
+        for (int u = t; u < MT * NT * 256; u += 64 * NW) {
+            const int l = u & 63, k = (u >> 6) & 3, ij = u >> 8;
+            const int row = mb + 16 * (ij / NT) + 4 * (l >> 4) + k, col = n0 + 16 * (ij % NT) + (l & 15);
+            if (row >= m_end || col >= a.N) continue;
+            float v = red[u];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) v += red[w * MT * NT * 256 + u];
+            if (MODE == MODE_FP8) v *= a.xs[row] * reinterpret_cast<const float*>(wsb)[col];  // per-token and per-channel scales
+            if (a.y_bf16) reinterpret_cast<uint16_t*>(a.Y)[(int64_t)row * a.ldy + col] = f32_to_bf16_rne(v);
+            else reinterpret_cast<float*>(a.Y)[(int64_t)row * a.ldy + col] = v;
+        }
+        if (GROUPED) __syncthreads();  // the sums have been read before the next rows' lines arrive
+    }
+#undef STREAM_COMPUTE
+#undef STREAM_LOAD
+#undef STREAM_AT
+}
+
+template <int MODE, int MT, int NT, int NW, bool GROUPED>
+static int launch_stream_cfg(const KArgs& a, bool ragged, hipStream_t st) {
+    const unsigned gx = (unsigned)((a.N + 16 * NT - 1) / (16 * NT));
+    const unsigned gy = GROUPED ? (unsigned)a.E : (unsigned)((a.M + 16 * MT - 1) / (16 * MT));
+    if (gx == 0 || gy == 0) return OSC_OK;
+    auto kern = ragged ? gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, MODE != MODE_MX8> : gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, false>;
+    hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(64 * NW), 0, st, a);
+    return check_launch("gemm_stream_kernel");
+}
+
+// Tile of the streaming kernel for one problem.  A workgroup reads (MT + NT) x 16 rows of the reduction axis
+// and the launch lasts as long as the CU with the most workgroups: take the tile with the smallest
+// ceil(workgroups / CUs) x (MT + NT), the smaller one among equals (it predicts the measured order at
+// N = 1024 .. 24576, M = 16 .. 64).  Eight wavefronts as long as all workgroups of a CU are resident, else four.
+struct StreamTile {
+    int mt, nt, nw, cost;
+};
+static StreamTile stream_tile(int64_t M, int64_t N, int ncu) {
+    static const int shapes[5][2] = {{1, 1}, {1, 2}, {1, 4}, {2, 2}, {2, 4}};
+    StreamTile best{0, 0, 0, 0x7fffffff};
+    for (const auto& sh : shapes) {
+        if (sh[0] > 1 && M <= 16) continue;
+        const int64_t wgs = ((N + 16 * sh[1] - 1) / (16 * sh[1])) * ((M + 16 * sh[0] - 1) / (16 * sh[0]));
+        const int64_t per = (wgs + ncu - 1) / ncu, cost = per * (sh[0] + sh[1]);
+        if (cost >= best.cost) continue;
+        best = StreamTile{sh[0], sh[1], per <= 4 && per * 8 * (sh[0] + sh[1]) * 2048 <= 160 * 1024 ? 8 : 4, (int)cost};
+    }
+    return best;
+}
+template <int MODE>
+static int launch_stream(const KArgs& a, const StreamTile& tile, bool ragged, hipStream_t st) {
+#define STREAM_CASE(MT_, NT_)                                                                          \
+    if (tile.mt == MT_ && tile.nt == NT_)                                                              \
+        return tile.nw == 8 ? launch_stream_cfg<MODE, MT_, NT_, 8, false>(a, ragged, st)               \
+                            : launch_stream_cfg<MODE, MT_, NT_, 4, false>(a, ragged, st);
+    STREAM_CASE(1, 1)
+    STREAM_CASE(1, 2)
+    STREAM_CASE(1, 4)
+    STREAM_CASE(2, 2)
+    STREAM_CASE(2, 4)
+#undef STREAM_CASE
+    return fail(OSC_ERR_UNSUPPORTED, "gemm: no streaming tile of %d x %d", tile.mt, tile.nt);
+}
+
 template <int MODE, int TM, int TN, bool RAGGED>
 static int launch_cfg(KArgs a, int64_t rows_total, bool grouped, hipStream_t st) {
     constexpr int BM = 64 * TM, BN = 64 * TN;
@@ -2353,11 +2623,23 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     const int64_t skinny_wgs = ((p.N + 31) / 32) * ((p.M + 31) / 32);
     const bool skinny_ok = lines && !grouped && !p.row_map && p.M >= 1 && (p.M <= 64 || skinny_wgs <= 512);
     if (skinny_ok) kind = 3;
+    // The streaming kernel up to 32 rows at any N, and above that while its tile costs at most three 16-row
+    // panels per CU (64 x 1024 x 4096: 3.9 us against 5.0 on the weight-streaming kernel; at four panels,
+    // 64 x 4096 x 4096, 6.35 against 6.1).  Rows that are not whole lines have only the staged kernel otherwise,
+    // which eight panels still beat (64 x 4096 x 4128: 8.2 us against 26, 333 x 1000 x 2080: 7.5 against 12.7, 256 x 2048 x 8224:
+    // 17 against 43) and twelve no longer do (256 x 4096 x 1056: 11.1 against 8.8, 500 x 2048 x 4128: 20.4 against 18.6)
+    StreamTile stile = stream_tile(p.M, p.N, ncu_hint > 0 ? ncu_hint : 256);
+    const bool stream_ok = !p.row_map && p.M >= 1 && (lines || MODE != MODE_MX8);
+    if (stream_ok && !grouped && (p.M <= 32 || stile.cost <= (lines ? 3 : 8))) kind = 6;
+    // Experts of a few rows (at most eight on average: 46 us against 56 on the tiles at 1024 rows in 128 experts;
+    // at sixteen most experts need a second pass over their weights, 63 against 57)
+    if (grouped && p.E > 0 && (lines || MODE != MODE_MX8) && p.M <= 8 * (int64_t)p.E) kind = 6;
     if (const int t_tile = tuning(TUNE_GEMM_TILE), t_kern = tuning(TUNE_GEMM_KERNEL); t_tile >= 0 || t_kern >= 0) {
         // test and tuning overrides (osc_tuning.h); a kernel that cannot serve the shape is not forced
         if (t_tile >= 0) tm = (t_tile == 1 || t_tile == 2 || t_tile == 4) ? t_tile : 2;
-        int k2 = (t_kern >= 0 && t_kern <= 3) ? t_kern : kind;  // ids above 3 are handled before the launch below
-        if (t_tile >= 0 && t_kern < 0 && k2 == 3) k2 = lines ? 1 : 0;  // a forced tile means a tiled kernel
+        int k2 = ((t_kern >= 0 && t_kern <= 3) || t_kern == 6) ? t_kern : kind;  // ids 4 and 5 are handled before the launch below
+        if (t_tile >= 0 && t_kern < 0 && (k2 == 3 || k2 == 6)) k2 = lines ? 1 : 0;  // a forced tile means a tiled kernel
+        if (k2 == 6 && !(grouped ? lines || MODE != MODE_MX8 : stream_ok)) k2 = lines ? 1 : 0;
         if ((k2 == 1 || k2 == 2) && !lines) k2 = 0;
         if (k2 == 2 && (tm == 1 || (MODE != MODE_DUAL && tm != 4))) k2 = 1;
         if (k2 == 2 && !pipe_ok) k2 = 1;
@@ -2372,6 +2654,8 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         if ((t_kern == 4 || t_kern == 5) && ring_ok)
             return t_kern == 4 ? launch_ring<4, 2, 4, true>(a, st) : launch_ring<4, 2, 4, false>(a, st);
     }
+    if (kind == 6 && grouped) return launch_stream_cfg<MODE, 1, 2, 4, true>(a, !lines, st);
+    if (kind == 6) return launch_stream<MODE>(a, stile, !lines, st);
     if (kind == 3) return launch_skinny<MODE>(a, st);
     if (kind == 2 && p.N % (64 * tm) == 0 && p.M >= 64 * tm) {
         const int64_t m_full = p.M / (64 * tm) * (64 * tm);

@@ -1,0 +1,115 @@
+"""The streaming GEMM kernel (few rows): every tile shape and wavefront count its rule can choose, odd sizes, rows
+that are not whole 128-byte lines, one line and more lines than wavefronts, and experts with any number of rows.
+Against the oracle on selected output channels (an output depends on one weight row)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-3  # of the largest result; a bf16 result also half a unit in its last place
+
+
+@pytest.fixture(scope="module")
+def osc():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2604_12782_amd as m
+    m.lib()
+    return m
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def close(Y, ref, what, bf16=False):
+    Y = Y.float().cpu().numpy().astype(np.float64)
+    slack = TOL * np.abs(ref).max() + (2.0 ** -8 * np.abs(ref) if bf16 else 0.0)
+    assert np.isfinite(Y).all() and (np.abs(Y - ref) <= slack).all(), what
+
+
+def columns(N):
+    return np.arange(N) if N <= 300 else np.unique(np.concatenate([np.arange(0, N, N // 97), [15, 16, 31, 32, 63, 64, N - 1]]))
+
+
+# tiles of 16 x 16, 16 x 32, 16 x 64, 32 x 32 (four and eight wavefronts) and 32 x 64 (eight and four)
+SHAPES = [(1, 40, 256, 1), (16, 24576, 256, 2), (16, 12288, 512, 1), (32, 24576, 256, 0), (64, 4096, 512, 2), (32, 12288, 256, 2),
+          (100, 8192, 256, 1), (17, 33, 4352, 4), (5, 200, 32, 1), (33, 250, 2080, 3), (7, 1000, 96, 2), (70, 300, 8224, 1)]
+
+
+@pytest.mark.parametrize("M,N,K,r", SHAPES)
+def test_dual(osc, tuning, M, N, K, r):
+    tuning.gemm("1,6")
+    X, table = wl.activations_persistent(8000 + M, M, K, r) if r else (wl.activations_diffuse(8000 + M, M, K), None)
+    W = wl.weights(8100 + N, N, K)
+    oidx = oracle.table_to_index(table) if r else np.zeros(0, np.int32)
+    d_oidx = dev(oidx) if r else None
+    Wp = osc.osc_pack_weight(dev(W), d_oidx)
+    c = columns(N)
+    wq, ws, _ = oracle.quantize_mxfp4_osc(W[c])
+    for ldb in ((len(oidx) + 63) // 64 * 64, (len(oidx) + 7) // 8 * 8):
+        Xq, Xs, B = osc.osc_quantize_act(dev(X), d_oidx, ldb=ldb)
+        rq, rs, rb = oracle.quantize_mxfp4_osc(X, oidx, ldb=ldb)
+        ref = oracle.dual_gemm(rq, rs, rb if r else None, wq, ws, oracle.gather_wl(W[c], oidx))
+        for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
+            close(osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), ydt)[:, c], ref, f"{M}x{N}x{K} r={r} ldb={ldb} bf16={bf}", bf)
+
+
+@pytest.mark.parametrize("M,N,K", [(1, 40, 128), (16, 12288, 256), (33, 260, 4352), (64, 4096, 384), (32, 12288, 128), (9, 100, 16),
+                                   (20, 333, 2064), (100, 8192, 128)])
+def test_8bit(osc, tuning, M, N, K):
+    tuning.gemm("1,6")
+    X = wl.activations_diffuse(8200 + M, M, K)
+    W = wl.weights(8300 + N, N, K)
+    c = columns(N)
+    X8, xs = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_FP8_E4M3_TOKEN)
+    ref = oracle.fp8_gemm(*oracle.quantize_fp8_rows(X), *oracle.quantize_fp8_rows(W[c]))
+    Wp = osc.osc_pack_weight_fp8(dev(W))
+    for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
+        close(osc.osc_fp8_gemm(X8, xs, Wp, N, K, y_dtype=ydt)[:, c], ref, f"fp8 {M}x{N}x{K} bf16={bf}", bf)
+    if K % 128 == 0:
+        Xm, Xms = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_MXFP8)
+        ref = oracle.mxfp8_gemm(*oracle.quantize_mxfp8(X), *oracle.quantize_mxfp8(W[c]))
+        Y = osc.osc_mxfp8_gemm(Xm, Xms, osc.osc_pack_weight_mxfp8(dev(W)), N, K)
+        close(Y[:, c], ref, f"mxfp8 {M}x{N}x{K}")
+
+
+@pytest.mark.parametrize("K,r", [(512, 2), (256, 0), (1056, 1)])
+@pytest.mark.parametrize("sizes", [[0, 1, 15, 16, 17, 0, 33, 70, 2], [3], [0, 0, 5, 0]])
+def test_experts(osc, tuning, sizes, K, r):
+    """Experts of no rows, of one tile, of several; dual path with a row map, FP8 and MXFP8."""
+    tuning.gemm("1,6")
+    E, N, tokens = len(sizes), 200, 60
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    T = int(off[-1])
+    X, table = wl.activations_persistent(8500, tokens, K, r) if r else (wl.activations_diffuse(8500, tokens, K), None)
+    oidx = oracle.table_to_index(table) if r else np.zeros(0, np.int32)
+    d_oidx = dev(oidx) if r else None
+    rows = wl.rng(8501).integers(0, tokens, T).astype(np.int32)
+    Ws = [wl.weights(8510 + e, N, K) for e in range(E)]
+    pack = lambda f, b: torch.cat([f(dev(w))[:b] for w in Ws])  # noqa: E731
+    Xq, Xs, B = osc.osc_quantize_act(dev(X), d_oidx)
+    rq, rs, rb = oracle.quantize_mxfp4_osc(X, oidx, ldb=B.shape[1] if r else 0)
+    w4 = [oracle.quantize_mxfp4_osc(w) for w in Ws]
+    ref = oracle.grouped_dual_gemm(rq, rs, rb if r else None, rows, off, np.stack([a for a, _, _ in w4]), np.stack([b for _, b, _ in w4]),
+                                   np.stack([oracle.gather_wl(w, oidx) for w in Ws]))
+    Wp = pack(lambda w: osc.osc_pack_weight(w, d_oidx), osc.osc_packed_weight_bytes(N, K, len(oidx)))
+    for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
+        Y = osc.osc_grouped_dual_gemm(Xq, Xs, B, dev(rows), dev(off), T, Wp, N, K, len(oidx), ydt)
+        close(Y, ref, f"grouped dual {sizes} K={K} bf16={bf}", bf)
+    X2 = wl.activations_diffuse(8502, T, K)
+    X8, xs = osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_FP8_E4M3_TOKEN)
+    w8 = [oracle.quantize_fp8_rows(w) for w in Ws]
+    ref = oracle.grouped_fp8_gemm(*oracle.quantize_fp8_rows(X2), off, np.stack([a for a, _ in w8]), np.stack([b for _, b in w8]))
+    close(osc.osc_fp8_gemm(X8, xs, pack(osc.osc_pack_weight_fp8, osc.osc_packed_weight_fp8_bytes(N, K)), N, K, expert_offsets=dev(off)),
+          ref, f"grouped fp8 {sizes} K={K}")
+    if K % 128 == 0:
+        Xm, Xms = osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_MXFP8)
+        m8, m8s = oracle.quantize_mxfp8(X2)
+        ref = np.concatenate([oracle.mxfp8_gemm(m8[off[e]:off[e + 1]], m8s[off[e]:off[e + 1]], *oracle.quantize_mxfp8(Ws[e]))
+                              for e in range(E) if off[e + 1] > off[e]])
+        Y = osc.osc_mxfp8_gemm(Xm, Xms, pack(osc.osc_pack_weight_mxfp8, osc.osc_packed_weight_mxfp8_bytes(N, K)), N, K, expert_offsets=dev(off))
+        close(Y, ref, f"grouped mxfp8 {sizes} K={K}")
