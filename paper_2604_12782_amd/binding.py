@@ -1,5 +1,6 @@
-"""ctypes binding of libosc.  Argument marshalling only: torch tensors in, torch tensors out,
-each function named after the C entry point it calls (see include/osc.h for the contract).
+"""Binding of libosc.  Argument marshalling only: torch tensors in, torch tensors out, each function named
+after the C entry point it calls (see include/osc.h for the contract).  The calls of a layer's every step are
+marshalled in native code (csrc/native.cpp), set-up and profiling calls through ctypes.
 
 bf16 tensors may be torch.bfloat16 or raw torch.uint16/int16 bit patterns.
 """
@@ -87,6 +88,20 @@ def lib():
     return _lib
 
 
+_native = None
+
+
+def _load_native():
+    """The extension module of the per-step calls (built together with the library; there is no fallback)."""
+    global _native
+    if _native is None:
+        lib()
+        from . import _native as m
+        m.bind_error(OscError)
+        _native = m
+    return _native
+
+
 def osc_last_error():
     return lib().osc_last_error().decode()
 
@@ -105,7 +120,7 @@ def _ptr(t):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    return (_native or _load_native()).current_stream()
 
 
 def _rows16(t):
@@ -228,78 +243,24 @@ def osc_quantize_act(X, oidx=None, fmt=OSC_FMT_MXFP4_OSC, ldb=None, out=None):
     scales, B uint16 [M,ldb]);
     FP8_E4M3_TOKEN -> (X8 uint8 [M,K], xs float32 [M]);
     MXFP8 -> (X8 uint8 [M,K], Xs uint8 row-block-major scales).  `out` may hold preallocated outputs."""
-    X = _rows16(X)
-    M, K = X.shape
-    dev = X.device
-    if fmt == OSC_FMT_MXFP8:
-        X8, Xs = out if out is not None else (torch.empty((M, K), dtype=torch.uint8, device=dev),
-                                              torch.empty(osc_act_scale_bytes(M, K), dtype=torch.uint8, device=dev))
-        _check(lib().osc_quantize_act(_ptr(X), M, K, X.stride(0), None, 0, fmt, _ptr(X8), _ptr(Xs),
-                                      None, 0, _stream()))
-        return X8, Xs
-    if fmt == OSC_FMT_FP8_E4M3_TOKEN:
-        X8, xs = out if out is not None else (torch.empty((M, K), dtype=torch.uint8, device=dev),
-                                              torch.empty(M, dtype=torch.float32, device=dev))
-        _check(lib().osc_quantize_act(_ptr(X), M, K, X.stride(0), None, 0, fmt, _ptr(X8), _ptr(xs),
-                                      None, 0, _stream()))
-        return X8, xs
-    K_o = 0 if oidx is None else int(oidx.numel())
-    if out is not None:
-        Xq, Xs, B = out
-        ldb = 0 if B is None else B.stride(0)
-    else:
-        if ldb is None:
-            ldb = (K_o + 63) // 64 * 64
-        Xq = torch.empty((M, K // 2), dtype=torch.uint8, device=dev)
-        Xs = torch.empty(osc_act_scale_bytes(M, K), dtype=torch.uint8, device=dev)
-        B = torch.empty((M, ldb), dtype=torch.uint16, device=dev) if ldb else None
-    _check(lib().osc_quantize_act(_ptr(X), M, K, X.stride(0), _ptr(oidx) if K_o else None, K_o, fmt,
-                                  _ptr(Xq), _ptr(Xs), _ptr(B), ldb, _stream()))
-    return Xq, Xs, B
-
-
-def _y(M, N, y_dtype, dev, out):
-    if out is not None:
-        return out
-    return torch.empty((M, N), dtype=torch.float32 if y_dtype == OSC_DT_F32 else torch.bfloat16,
-                       device=dev)
+    return (_native or _load_native()).quantize_act(X, oidx, fmt, ldb, out)
 
 
 def osc_dual_gemm(Xq, Xs, B, Wpack, N, K, K_o, y_dtype=OSC_DT_F32, out=None):
-    M = Xq.shape[0]
-    Y = _y(M, N, y_dtype, Xq.device, out)
-    _check(lib().osc_dual_gemm(_ptr(Xq), _ptr(Xs), _ptr(B), 0 if B is None else B.stride(0),
-                               _ptr(Wpack), M, N, K, K_o, _ptr(Y), y_dtype, Y.stride(0) if M else N,
-                               _stream()))
-    return Y
+    return (_native or _load_native()).dual_gemm(Xq, Xs, B, Wpack, N, K, K_o, y_dtype, out)
 
 
 def osc_fp8_gemm(X8, xs, W8pack, N, K, expert_offsets=None, y_dtype=OSC_DT_F32, out=None):
-    M = X8.shape[0]
-    Y = _y(M, N, y_dtype, X8.device, out)
-    E = 0 if expert_offsets is None else int(expert_offsets.numel()) - 1
-    _check(lib().osc_fp8_gemm(_ptr(X8), _ptr(xs), _ptr(W8pack), M, N, K, _ptr(expert_offsets), E,
-                              _ptr(Y), y_dtype, Y.stride(0) if M else N, _stream()))
-    return Y
+    return (_native or _load_native()).fp8_gemm(X8, xs, W8pack, N, K, expert_offsets, y_dtype, out)
 
 
 def osc_mxfp8_gemm(X8, Xs, Wpack, N, K, expert_offsets=None, y_dtype=OSC_DT_F32, out=None):
-    M = X8.shape[0]
-    Y = _y(M, N, y_dtype, X8.device, out)
-    E = 0 if expert_offsets is None else int(expert_offsets.numel()) - 1
-    _check(lib().osc_mxfp8_gemm(_ptr(X8), _ptr(Xs), _ptr(Wpack), M, N, K, _ptr(expert_offsets), E,
-                                _ptr(Y), y_dtype, Y.stride(0) if M else N, _stream()))
-    return Y
+    return (_native or _load_native()).mxfp8_gemm(X8, Xs, Wpack, N, K, expert_offsets, y_dtype, out)
 
 
 def osc_grouped_dual_gemm(Xq, Xs, B, row_map, expert_offsets, T, Wpack, N, K, K_o,
                           y_dtype=OSC_DT_F32, out=None):
-    Y = _y(T, N, y_dtype, Xq.device, out)
-    E = int(expert_offsets.numel()) - 1
-    _check(lib().osc_grouped_dual_gemm(_ptr(Xq), _ptr(Xs), _ptr(B), 0 if B is None else B.stride(0),
-                                       _ptr(row_map), _ptr(expert_offsets), E, T, _ptr(Wpack), N, K,
-                                       K_o, _ptr(Y), y_dtype, Y.stride(0) if T else N, _stream()))
-    return Y
+    return (_native or _load_native()).grouped_dual_gemm(Xq, Xs, B, row_map, expert_offsets, T, Wpack, N, K, K_o, y_dtype, out)
 
 
 def osc_profile_abs_sum(X, abs_sum=None):
@@ -381,21 +342,7 @@ def osc_profile_calibrate_static(X, G=32, alpha=5.0, R=1, out=None):
 
 def osc_quantize_act_g16(X, oidx=None, fmt16=OSC_FMT16_E8M0, tensor_scale=1.0, ldb=None, out=None):
     """4-bit quantiser with one scale per 16 channels -> (Xq uint8 [M, K/2], Xs16 uint8 [M, K/16], B or None)."""
-    X = _rows16(X)
-    M, K = X.shape
-    dev = X.device
-    K_o = 0 if oidx is None else int(oidx.numel())
-    if ldb is None:
-        ldb = (K_o + 63) // 64 * 64
-    if out is not None:
-        Xq, Xs, B = out
-    else:
-        Xq = torch.empty((M, K // 2), dtype=torch.uint8, device=dev)
-        Xs = torch.empty((M, K // 16), dtype=torch.uint8, device=dev)
-        B = torch.empty((M, ldb), dtype=torch.uint16, device=dev) if ldb else None
-    _check(lib().osc_quantize_act_g16(_ptr(X), M, K, X.stride(0), _ptr(oidx), K_o, fmt16, float(tensor_scale), _ptr(Xq),
-                                      _ptr(Xs), _ptr(B), ldb, _stream()))
-    return Xq, Xs, B
+    return (_native or _load_native()).quantize_act_g16(X, oidx, fmt16, tensor_scale, ldb, out)
 
 
 def osc_packed_weight_g16_bytes(N, K, K_o):
@@ -424,53 +371,18 @@ def osc_unpack_weight_g16(Wpack, N, K, K_o):
 
 def osc_dual_gemm_g16(Xq, Xs16, B, Wpack, N, K, K_o, fmt16=OSC_FMT16_E8M0, x_tensor_scale=1.0, w_tensor_scale=1.0,
                       y_dtype=OSC_DT_F32, out=None):
-    M = Xq.shape[0]
-    if out is None:
-        out = torch.empty((M, N), dtype=torch.bfloat16 if y_dtype == OSC_DT_BF16 else torch.float32, device=Xq.device)
-    _check(lib().osc_dual_gemm_g16(_ptr(Xq), _ptr(Xs16), float(x_tensor_scale), _ptr(B), 0 if B is None else B.stride(0),
-                                   _ptr(Wpack), float(w_tensor_scale), M, N, K, K_o, fmt16, _ptr(out), y_dtype,
-                                   out.stride(0), _stream()))
-    return out
+    return (_native or _load_native()).dual_gemm_g16(Xq, Xs16, B, Wpack, N, K, K_o, fmt16, x_tensor_scale, w_tensor_scale, y_dtype,
+                                                         out)
 
 
 def osc_quantize_act_dynamic(X, ldb=None, want_idx=True, out=None):
     """Dynamic protection -> (Xq, Xs, Bd uint16 [M, ldb] dense, idx uint8 [M, K/32] or None)."""
-    X = _rows16(X)
-    M, K = X.shape
-    dev = X.device
-    if ldb is None:
-        ldb = K
-    if out is not None:
-        Xq, Xs, Bd, idx = out
-    else:
-        Xq = torch.empty((M, K // 2), dtype=torch.uint8, device=dev)
-        Xs = torch.empty(osc_act_scale_bytes(M, K), dtype=torch.uint8, device=dev)
-        Bd = torch.empty((M, ldb), dtype=torch.uint16, device=dev)
-        idx = torch.empty((M, K // 32), dtype=torch.uint8, device=dev) if want_idx else None
-    _check(lib().osc_quantize_act_dynamic(_ptr(X), M, K, X.stride(0), _ptr(Xq), _ptr(Xs), _ptr(Bd), ldb, _ptr(idx),
-                                          _stream()))
-    return Xq, Xs, Bd, idx
+    return (_native or _load_native()).quantize_act_dynamic(X, ldb, want_idx, out)
 
 
 def osc_rmsnorm_quantize_act(X, gamma, eps=1e-6, oidx=None, ldb=None, want_norm=False, out=None):
     """RMSNorm + OSC quantiser in one pass -> (Xq, Xs, B, Xn or None)."""
-    X = _rows16(X)
-    M, K = X.shape
-    dev = X.device
-    K_o = 0 if oidx is None else int(oidx.numel())
-    if out is not None:
-        Xq, Xs, B, Xn = out
-        ldb = 0 if B is None else B.stride(0)
-    else:
-        if ldb is None:
-            ldb = (K_o + 63) // 64 * 64
-        Xq = torch.empty((M, K // 2), dtype=torch.uint8, device=dev)
-        Xs = torch.empty(osc_act_scale_bytes(M, K), dtype=torch.uint8, device=dev)
-        B = torch.empty((M, ldb), dtype=torch.uint16, device=dev) if ldb else None
-        Xn = torch.empty((M, K), dtype=torch.uint16, device=dev) if want_norm else None
-    _check(lib().osc_rmsnorm_quantize_act(_ptr(X), _ptr(gamma), eps, M, K, X.stride(0), _ptr(oidx), K_o, _ptr(Xq),
-                                          _ptr(Xs), _ptr(B), ldb, _ptr(Xn), _stream()))
-    return Xq, Xs, B, Xn
+    return (_native or _load_native()).rmsnorm_quantize_act(X, gamma, eps, oidx, ldb, want_norm, out)
 
 
 OSC_TUNE_GEMM_TILE, OSC_TUNE_GEMM_KERNEL, OSC_TUNE_GROUPED_ONE_TILE, OSC_TUNE_SWIGLU_TABLE = 0, 1, 2, 3
@@ -488,33 +400,9 @@ def osc_tuning_get(knob):
 
 def osc_swiglu_quantize_act(G, U, want_y=False, out=None):
     """SwiGLU + MXFP8 quantiser in one pass -> (Xq uint8 [M, K], Xs, Yn uint16 [M, K] or None)."""
-    G, U = _rows16(G), _rows16(U)
-    M, K = G.shape
-    assert U.shape == G.shape
-    dev = G.device
-    if out is not None:
-        Xq, Xs, Yn = out
-    else:
-        Xq = torch.empty((M, K), dtype=torch.uint8, device=dev)
-        Xs = torch.empty(osc_act_scale_bytes(M, K), dtype=torch.uint8, device=dev)
-        Yn = torch.empty((M, K), dtype=torch.uint16, device=dev) if want_y else None
-    _check(lib().osc_swiglu_quantize_act(_ptr(G), _ptr(U), M, K, G.stride(0), U.stride(0), _ptr(Xq), _ptr(Xs),
-                                         _ptr(Yn), _stream()))
-    return Xq, Xs, Yn
+    return (_native or _load_native()).swiglu_quantize_act(G, U, want_y, out)
 
 
 def osc_swiglu_quantize_act_fp8(G, U, want_y=False, out=None):
     """SwiGLU + per-token FP8 quantiser in one pass -> (X8 uint8 [M, K], xs float32 [M], Yn uint16 [M, K] or None)."""
-    G, U = _rows16(G), _rows16(U)
-    M, K = G.shape
-    assert U.shape == G.shape
-    dev = G.device
-    if out is not None:
-        X8, xs, Yn = out
-    else:
-        X8 = torch.empty((M, K), dtype=torch.uint8, device=dev)
-        xs = torch.empty(M, dtype=torch.float32, device=dev)
-        Yn = torch.empty((M, K), dtype=torch.uint16, device=dev) if want_y else None
-    _check(lib().osc_swiglu_quantize_act_fp8(_ptr(G), _ptr(U), M, K, G.stride(0), U.stride(0), _ptr(X8), _ptr(xs),
-                                             _ptr(Yn), _stream()))
-    return X8, xs, Yn
+    return (_native or _load_native()).swiglu_quantize_act_fp8(G, U, want_y, out)

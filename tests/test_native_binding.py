@@ -1,0 +1,40 @@
+"""The native marshalling of the per-step calls: what it refuses, and that errors of the C ABI arrive as
+OscError with the library's code and text."""
+import pytest
+import torch
+
+import paper_2604_12782_amd as osc
+
+
+def test_refuses_what_is_not_a_row_major_bf16_matrix():
+    X = torch.zeros((4, 64), dtype=torch.bfloat16)
+    with pytest.raises(TypeError, match="torch tensor"):
+        osc.osc_quantize_act([1, 2, 3])
+    for bad in (X[0], X.t(), X.float()):
+        with pytest.raises(AssertionError, match="2-D bf16"):
+            osc.osc_quantize_act(bad)
+    with pytest.raises(AssertionError):
+        osc.osc_swiglu_quantize_act(X, X[:, :32])
+    with pytest.raises(ValueError, match="holds 1 tensors"):
+        osc.osc_quantize_act(X, out=(X,))
+    with pytest.raises(TypeError):
+        osc.osc_dual_gemm(X, X, None, X, 64, "64", 0, out=X)
+
+
+@pytest.mark.gpu
+def test_errors_and_outputs_on_the_device():
+    X = torch.zeros((4, 64), dtype=torch.bfloat16, device="cuda")
+    with pytest.raises(osc.OscError, match="multiple of 32") as e:
+        osc.osc_quantize_act(X[:, :40])
+    assert e.value.code == -2
+    out = (torch.empty((4, 32), dtype=torch.uint8, device="cuda"), torch.empty(osc.osc_act_scale_bytes(4, 64), dtype=torch.uint8, device="cuda"), None)
+    got = osc.osc_quantize_act(X, out=list(out))
+    assert got[0] is out[0] and got[1] is out[1] and got[2] is None
+    q = osc.osc_quantize_act(X, ldb=8)
+    assert q[2].shape == (4, 8) and q[2].dtype == torch.uint16 and int(q[2].to(torch.int32).sum()) == 0
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):  # the current stream is the one that is used
+        torch.cuda._sleep(1000000)
+        Y = osc.osc_quantize_act(torch.ones((1, 32), dtype=torch.bfloat16, device="cuda"))[1]
+    side.synchronize()
+    assert int(Y[0]) == 125
