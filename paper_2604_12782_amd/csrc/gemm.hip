@@ -2213,8 +2213,15 @@ static int launch_skinny(KArgs a, hipStream_t st) {
 // v_mfma_f32_16x16x32_bf16: 8 elements (16 bytes).  Result register k: row 4q + k, column r.
 // An FP4 or bf16 line is two instructions, instruction i taking piece 2q + i for lane block q (its two scale
 // bytes are then one 16-bit word); an 8-bit line is one, pieces q and 4 + q.
-// GROUPED: blockIdx.y is the expert; its rows are taken 16 MT at a time (an expert without rows leaves
-// at once).  RAGGED: rows need not be whole lines; pieces past the end of a row come from the block of
+// GROUPED: blockIdx.y < E is the expert, of which the workgroup takes the first 16 MT rows (an expert without
+// rows leaves at once); the M / (16 MT) values after them number the further row blocks of all experts, and the
+// workgroup finds the expert of its own (most leave).  One workgroup taking an expert's blocks one after the
+// other made uneven routing expensive.  Both
+// expert GEMMs of the layer above, weights from HBM, us (64 x 128 tiles / an expert's blocks in turn / this):
+//   256 rows, all of one expert    27 / 70 / 21      evenly drawn (2 an expert)   137 / 83 / 83
+//   512 rows, all of one expert    27 / 131 / 29     evenly drawn (4)             145 / 92 / 94
+//   512 rows over eight experts    32 / 45 / 35
+//   1024 rows                                        evenly drawn (8)             145 / 96 / 102  RAGGED: rows need not be whole lines; pieces past the end of a row come from the block of
 // zeros in the packed weight.
 // ------------------------------------------------------------------------------------------
 typedef float v4f __attribute__((ext_vector_type(4)));
@@ -2228,10 +2235,35 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(KArgs a) {
     int m_begin = blockIdx.y * (16 * MT), m_end = min(a.M, m_begin + 16 * MT);
     const uint8_t* wp = a.Wpack;
     if constexpr (GROUPED) {
-        m_begin = a.off[blockIdx.y];
-        m_end = a.off[blockIdx.y + 1];
+        int e = blockIdx.y, block = 0;
+        if (e >= a.E) {
+            // 64 experts at a time, one per lane: prefix sum of their further blocks (as in tile_at)
+            int j = e - a.E;
+            e = -1;
+            for (int e0 = 0; e0 < a.E; e0 += 64) {
+                const int n = e0 + lane < a.E ? a.off[e0 + lane + 1] - a.off[e0 + lane] : 0;
+                const int more = n > 16 * MT ? (n - 1) / (16 * MT) : 0;
+                int ps = more;
+#pragma unroll
+                for (int d = 1; d < 64; d <<= 1) {
+                    const int v = __shfl_up(ps, d);
+                    if (lane >= d) ps += v;
+                }
+                const int total = __shfl(ps, 63);
+                if (j < total) {
+                    const int l = __ffsll((unsigned long long)__ballot(ps > j)) - 1;
+                    e = __builtin_amdgcn_readfirstlane(e0 + l);
+                    block = __builtin_amdgcn_readfirstlane(1 + j - (__shfl(ps, l) - __shfl(more, l)));
+                    break;
+                }
+                j -= total;
+            }
+            if (e < 0) return;
+        }
+        m_begin = a.off[e] + block * (16 * MT);
+        m_end = min(a.off[e + 1], m_begin + 16 * MT);
         if (m_begin >= m_end) return;
-        wp += (size_t)blockIdx.y * a.pack_stride;
+        wp += (size_t)e * a.pack_stride;
     }
     const int Kg4 = ((a.K >> 5) + 3) >> 2;
     const int rowbytes = DUAL ? a.K >> 1 : a.K;
@@ -2344,67 +2376,64 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(KArgs a) {
                                                                             __builtin_bit_cast(v8bf, fw__[j][p]), acc[i][j], 0, 0, 0); \
         }                                                                                                 \
     }
-    for (int mb = m_begin; mb < m_end; mb += 16 * MT) {
-        uint32_t ox[MT][2], oxb[MT][2], osx[MT];
+    uint32_t ox[MT][2], oxb[MT][2], osx[MT];
 #pragma unroll
-        for (int i = 0; i < MT; ++i) {
+    for (int i = 0; i < MT; ++i) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                int g = min(mb + 16 * i + 8 * h + lrow, m_end - 1);
-                if (GROUPED && DUAL && a.row_map) g = a.row_map[g];
-                ox[i][h] = (uint32_t)g * (uint32_t)rowbytes + p0;
-                oxb[i][h] = (uint32_t)g * (uint32_t)a.bpitch + p0;
-            }
-            int g = min(mb + 16 * i + r, m_end - 1);
+        for (int h = 0; h < 2; ++h) {
+            int g = min(m_begin + 16 * i + 8 * h + lrow, m_end - 1);
             if (GROUPED && DUAL && a.row_map) g = a.row_map[g];
-            osx[i] = (uint32_t)(g >> 5) * (uint32_t)Kg4 * 128u + (uint32_t)(g & 31) * 4u + sc_lane;
+            ox[i][h] = (uint32_t)g * (uint32_t)rowbytes + p0;
+            oxb[i][h] = (uint32_t)g * (uint32_t)a.bpitch + p0;
         }
-        v4f acc[MT][NT];
+        int g = min(m_begin + 16 * i + r, m_end - 1);
+        if (GROUPED && DUAL && a.row_map) g = a.row_map[g];
+        osx[i] = (uint32_t)(g >> 5) * (uint32_t)Kg4 * 128u + (uint32_t)(g & 31) * 4u + sc_lane;
+    }
+    v4f acc[MT][NT];
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
-        if (wave < nLT) {
-            // two sets written out in turn: a copy from one to the other would wait for the loads in flight
-            Line sa, sb;
-            int L = wave;
-            STREAM_LOAD(L, sa)
+        for (int j = 0; j < NT; ++j) acc[i][j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    if (wave < nLT) {
+        // two sets written out in turn: a copy from one to the other would wait for the loads in flight
+        Line sa, sb;
+        int L = wave;
+        STREAM_LOAD(L, sa)
 #pragma unroll 1
-            for (; L + 2 * NW < nLT; L += 2 * NW) {
-                STREAM_LOAD(L + NW, sb)
-                STREAM_COMPUTE(L, sa)
-                STREAM_LOAD(L + 2 * NW, sa)
-                STREAM_COMPUTE(L + NW, sb)
-            }
-            if (L + NW < nLT) {
-                STREAM_LOAD(L + NW, sb)
-                STREAM_COMPUTE(L, sa)
-                STREAM_COMPUTE(L + NW, sb)
-            } else {
-                STREAM_COMPUTE(L, sa)
-            }
+        for (; L + 2 * NW < nLT; L += 2 * NW) {
+            STREAM_LOAD(L + NW, sb)
+            STREAM_COMPUTE(L, sa)
+            STREAM_LOAD(L + 2 * NW, sa)
+            STREAM_COMPUTE(L + NW, sb)
         }
-        // ---- sum the NW partial results in a fixed order, store ----
-        __syncthreads();  // every wavefront is done with its strip
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) red[((wave * MT * NT + i * NT + j) * 4 + k) * 64 + lane] = acc[i][j][k];
-        __syncthreads();
-        for (int u = t; u < MT * NT * 256; u += 64 * NW) {
-            const int l = u & 63, k = (u >> 6) & 3, ij = u >> 8;
-            const int row = mb + 16 * (ij / NT) + 4 * (l >> 4) + k, col = n0 + 16 * (ij % NT) + (l & 15);
-            if (row >= m_end || col >= a.N) continue;
-            float v = red[u];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) v += red[w * MT * NT * 256 + u];
-            if (MODE == MODE_FP8) v *= a.xs[row] * reinterpret_cast<const float*>(wsb)[col];  // per-token and per-channel scales
-            if (a.y_bf16) reinterpret_cast<uint16_t*>(a.Y)[(int64_t)row * a.ldy + col] = f32_to_bf16_rne(v);
-            else reinterpret_cast<float*>(a.Y)[(int64_t)row * a.ldy + col] = v;
+        if (L + NW < nLT) {
+            STREAM_LOAD(L + NW, sb)
+            STREAM_COMPUTE(L, sa)
+            STREAM_COMPUTE(L + NW, sb)
+        } else {
+            STREAM_COMPUTE(L, sa)
         }
-        if (GROUPED) __syncthreads();  // the sums have been read before the next rows' lines arrive
+    }
+    // ---- sum the NW partial results in a fixed order, store ----
+    __syncthreads();  // every wavefront is done with its strip
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) red[((wave * MT * NT + i * NT + j) * 4 + k) * 64 + lane] = acc[i][j][k];
+    __syncthreads();
+    for (int u = t; u < MT * NT * 256; u += 64 * NW) {
+        const int l = u & 63, k = (u >> 6) & 3, ij = u >> 8;
+        const int row = m_begin + 16 * (ij / NT) + 4 * (l >> 4) + k, col = n0 + 16 * (ij % NT) + (l & 15);
+        if (row >= m_end || col >= a.N) continue;
+        float v = red[u];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += red[w * MT * NT * 256 + u];
+        if (MODE == MODE_FP8) v *= a.xs[row] * reinterpret_cast<const float*>(wsb)[col];  // per-token and per-channel scales
+        if (a.y_bf16) reinterpret_cast<uint16_t*>(a.Y)[(int64_t)row * a.ldy + col] = f32_to_bf16_rne(v);
+        else reinterpret_cast<float*>(a.Y)[(int64_t)row * a.ldy + col] = v;
     }
 #undef STREAM_COMPUTE
 #undef STREAM_LOAD
@@ -2414,7 +2443,7 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(KArgs a) {
 template <int MODE, int MT, int NT, int NW, bool GROUPED>
 static int launch_stream_cfg(const KArgs& a, bool ragged, hipStream_t st) {
     const unsigned gx = (unsigned)((a.N + 16 * NT - 1) / (16 * NT));
-    const unsigned gy = GROUPED ? (unsigned)a.E : (unsigned)((a.M + 16 * MT - 1) / (16 * MT));
+    const unsigned gy = GROUPED ? (unsigned)(a.E + a.M / (16 * MT)) : (unsigned)((a.M + 16 * MT - 1) / (16 * MT));
     if (gx == 0 || gy == 0) return OSC_OK;
     auto kern = ragged ? gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, MODE != MODE_MX8> : gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, false>;
     hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(64 * NW), 0, st, a);
@@ -2631,15 +2660,16 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     StreamTile stile = stream_tile(p.M, p.N, ncu_hint > 0 ? ncu_hint : 256);
     const bool stream_ok = !p.row_map && p.M >= 1 && (lines || MODE != MODE_MX8);
     if (stream_ok && !grouped && (p.M <= 32 || stile.cost <= (lines ? 3 : 8))) kind = 6;
-    // Experts of a few rows (at most eight on average: 46 us against 56 on the tiles at 1024 rows in 128 experts;
-    // at sixteen most experts need a second pass over their weights, 63 against 57)
-    if (grouped && p.E > 0 && (lines || MODE != MODE_MX8) && p.M <= 8 * (int64_t)p.E) kind = 6;
+    // Experts of a few rows (at most eight on average: both GEMMs of 128 experts at 1024 rows 102 us against 145 on the
+    // tiles, 88 against 96 with half the weights in the last-level cache; at ten 96 against 96 there, beyond it the tiles are ahead)
+    const bool stream_grp = grouped && p.E > 0 && (lines || MODE != MODE_MX8) && p.E + p.M / 16 <= 65535;  // its grid's second extent
+    if (stream_grp && p.M <= 8 * (int64_t)p.E) kind = 6;
     if (const int t_tile = tuning(TUNE_GEMM_TILE), t_kern = tuning(TUNE_GEMM_KERNEL); t_tile >= 0 || t_kern >= 0) {
         // test and tuning overrides (osc_tuning.h); a kernel that cannot serve the shape is not forced
         if (t_tile >= 0) tm = (t_tile == 1 || t_tile == 2 || t_tile == 4) ? t_tile : 2;
         int k2 = ((t_kern >= 0 && t_kern <= 3) || t_kern == 6) ? t_kern : kind;  // ids 4 and 5 are handled before the launch below
         if (t_tile >= 0 && t_kern < 0 && (k2 == 3 || k2 == 6)) k2 = lines ? 1 : 0;  // a forced tile means a tiled kernel
-        if (k2 == 6 && !(grouped ? lines || MODE != MODE_MX8 : stream_ok)) k2 = lines ? 1 : 0;
+        if (k2 == 6 && !(grouped ? stream_grp : stream_ok)) k2 = lines ? 1 : 0;
         if ((k2 == 1 || k2 == 2) && !lines) k2 = 0;
         if (k2 == 2 && (tm == 1 || (MODE != MODE_DUAL && tm != 4))) k2 = 1;
         if (k2 == 2 && !pipe_ok) k2 = 1;

@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -8,6 +9,19 @@ if ROOT not in sys.path:
 
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X (run with -m gpu)")
+
+
+_module = None
+
+
+def pytest_runtest_setup(item):
+    """What earlier modules' failed calls left in reference cycles (an expected error holds its frame and the
+    frame's tensors) goes before the next module starts: a test that compares the memory in use around a call
+    must not see it released in between."""
+    global _module
+    if item.module is not _module:
+        _module = item.module
+        gc.collect()
 
 
 class _Tuning:

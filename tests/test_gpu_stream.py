@@ -78,9 +78,11 @@ def test_8bit(osc, tuning, M, N, K):
 
 
 @pytest.mark.parametrize("K,r", [(512, 2), (256, 0), (1056, 1)])
-@pytest.mark.parametrize("sizes", [[0, 1, 15, 16, 17, 0, 33, 70, 2], [3], [0, 0, 5, 0]])
+@pytest.mark.parametrize("sizes", [[0, 1, 15, 16, 17, 0, 33, 70, 2], [3], [0, 0, 5, 0], [0] * 62 + [17, 0, 33] + [1] * 64 + [48]],
+                         ids=["any", "one", "few", "past_64"])
 def test_experts(osc, tuning, sizes, K, r):
-    """Experts of no rows, of one tile, of several; dual path with a row map, FP8 and MXFP8."""
+    """Experts of no rows, of one tile, of several (whose further blocks are looked up 64 experts at a time); dual path
+    with a row map, FP8 and MXFP8."""
     tuning.gemm("1,6")
     E, N, tokens = len(sizes), 200, 60
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
