@@ -29,6 +29,11 @@ float real(PyObject* o) {
     return (float)v;
 }
 bool none(PyObject* o) { return o == Py_None; }
+bool truth(PyObject* o) {
+    const int v = PyObject_IsTrue(o);
+    if (v < 0) throw PyFailed();
+    return v != 0;
+}
 const at::Tensor& tensor(PyObject* o) {
     if (!THPVariable_Check(o)) {
         PyErr_Format(PyExc_TypeError, "expected a torch tensor, got %s", Py_TYPE(o)->tp_name);
@@ -239,7 +244,7 @@ PyObject* rmsnorm_quantize_act(PyObject* const* a) {
     Ref q, s, b, xn;
     const int64_t ldb = mx4_outputs(outs, a[4], K_o, X, M, K, q, s, b);
     if (outs) xn.share(outs.item[3]);
-    else if (PyObject_IsTrue(a[5]) == 1) xn.own(fresh(X, {M, K}, at::kUInt16));
+    else if (truth(a[5])) xn.own(fresh(X, {M, K}, at::kUInt16));
     else xn.share(Py_None);
     void *x = X.data_ptr(), *g = ptr(a[1]), *pi = ptr(a[3]), *pq = ptr(q.o), *ps = ptr(s.o), *pb = ptr(b.o), *pn = ptr(xn.o);
     enqueue([&](void* st) {
@@ -267,7 +272,7 @@ PyObject* swiglu(PyObject* const* a) {
         q.own(fresh(G, {M, K}, at::kByte));
         if (MX) s.own(fresh(G, {(int64_t)osc_act_scale_bytes(M, K)}, at::kByte));
         else s.own(fresh(G, {M}, at::kFloat));
-        if (PyObject_IsTrue(a[2]) == 1) y.own(fresh(G, {M, K}, at::kUInt16));
+        if (truth(a[2])) y.own(fresh(G, {M, K}, at::kUInt16));
         else y.share(Py_None);
     }
     void *g = G.data_ptr(), *u = U.data_ptr(), *pq = ptr(q.o), *ps = ptr(s.o), *py = ptr(y.o);
@@ -338,7 +343,7 @@ PyObject* quantize_act_dynamic(PyObject* const* a) {
         q.own(fresh(X, {M, K / 2}, at::kByte));
         s.own(fresh(X, {(int64_t)osc_act_scale_bytes(M, K)}, at::kByte));
         b.own(fresh(X, {M, ldb}, at::kUInt16));
-        if (PyObject_IsTrue(a[2]) == 1) idx.own(fresh(X, {M, K / 32}, at::kByte));
+        if (truth(a[2])) idx.own(fresh(X, {M, K / 32}, at::kByte));
         else idx.share(Py_None);
     }
     void *x = X.data_ptr(), *pq = ptr(q.o), *ps = ptr(s.o), *pb = ptr(b.o), *pi = ptr(idx.o);

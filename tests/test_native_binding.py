@@ -21,6 +21,16 @@ def test_refuses_what_is_not_a_row_major_bf16_matrix():
         osc.osc_dual_gemm(X, X, None, X, 64, "64", 0, out=X)
 
 
+def test_error_of_a_truth_value_arrives():
+    """A flag whose truth value raises (a tensor of several elements): that error, before anything is launched."""
+    X = torch.zeros((4, 64), dtype=torch.bfloat16)
+    flag = torch.ones(2)
+    for call in (lambda: osc.osc_rmsnorm_quantize_act(X, X[0], want_norm=flag), lambda: osc.osc_swiglu_quantize_act(X, X, want_y=flag),
+                 lambda: osc.osc_swiglu_quantize_act_fp8(X, X, want_y=flag), lambda: osc.osc_quantize_act_dynamic(X, want_idx=flag)):
+        with pytest.raises(RuntimeError, match="ambiguous"):
+            call()
+
+
 @pytest.mark.gpu
 def test_errors_and_outputs_on_the_device():
     X = torch.zeros((4, 64), dtype=torch.bfloat16, device="cuda")
