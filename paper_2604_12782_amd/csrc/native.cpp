@@ -8,6 +8,7 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/device_lazy_init.h>
 #include <torch/types.h>
 
 #include "../../include/osc.h"
@@ -55,9 +56,12 @@ int32_t count(PyObject* o) { return none(o) ? 0 : (int32_t)tensor(o).numel(); }
 int64_t pitch(PyObject* o) { return none(o) ? 0 : tensor(o).stride(0); }
 int64_t up64(int64_t n) { return (n + 63) / 64 * 64; }
 
-// an owned reference to a new tensor on t's device
+// an owned reference to a new tensor on t's device; like torch.empty, it asks torch whether the device may be
+// used first (in a process forked after the GPU was, torch refuses)
 PyObject* fresh(const at::Tensor& t, at::IntArrayRef size, at::ScalarType dtype) {
-    PyObject* o = THPVariable_Wrap(at::empty(size, t.options().dtype(dtype)));
+    const at::TensorOptions options = t.options().dtype(dtype);
+    torch::utils::maybe_initialize_device(options);
+    PyObject* o = THPVariable_Wrap(at::empty(size, options));
     if (!o) throw PyFailed();
     return o;
 }
@@ -81,9 +85,15 @@ struct Ref {
     }
 };
 
+// torch's current stream, with the checks of torch.cuda.current_stream()
+void* stream() {
+    torch::utils::device_lazy_init(at::kCUDA);
+    return c10::hip::getCurrentHIPStream().stream();
+}
+
 template <class F>
 void enqueue(F&& call) {
-    void* st = c10::hip::getCurrentHIPStream().stream();
+    void* st = stream();
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = call(st);
@@ -351,7 +361,7 @@ PyObject* quantize_act_dynamic(PyObject* const* a) {
     return tuple({&q, &s, &b, &idx});
 }
 
-PyObject* current_stream(PyObject* const*) { return PyLong_FromVoidPtr(c10::hip::getCurrentHIPStream().stream()); }
+PyObject* current_stream(PyObject* const*) { return PyLong_FromVoidPtr(stream()); }
 
 PyObject* bind_error(PyObject* const* a) {
     Py_INCREF(a[0]);

@@ -1,5 +1,9 @@
 """The native marshalling of the per-step calls: what it refuses, and that errors of the C ABI arrive as
 OscError with the library's code and text."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -29,6 +33,32 @@ def test_error_of_a_truth_value_arrives():
                  lambda: osc.osc_swiglu_quantize_act_fp8(X, X, want_y=flag), lambda: osc.osc_quantize_act_dynamic(X, want_idx=flag)):
         with pytest.raises(RuntimeError, match="ambiguous"):
             call()
+
+
+def test_asks_torch_before_using_the_device():
+    """Before its first use of the device a process asks torch, which refuses in a process forked after the GPU was
+    used: that refusal arrives, from the native calls and from the stream of the others.  (In a process of its
+    own, where nothing has used the device yet.)"""
+    code = """
+import torch
+import paper_2604_12782_amd as osc
+def refuse(): raise RuntimeError("refused by torch")
+torch.cuda._lazy_init = refuse
+X = torch.zeros((4, 64), dtype=torch.bfloat16)
+out = (X, X, None)
+for call in (lambda: osc.osc_quantize_act(X, out=out), lambda: osc.osc_dual_gemm(X, X, None, X, 64, 64, 0, out=X),
+             lambda: osc.osc_pack_weight(X, None), lambda: osc.osc_swiglu_quantize_act(X, X)):
+    try:
+        call()
+    except RuntimeError as e:
+        assert str(e) == "refused by torch", e
+    else:
+        raise AssertionError("not refused")
+print("all refused")
+"""
+    run = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), capture_output=True,
+                         text=True, timeout=300)
+    assert run.returncode == 0 and "all refused" in run.stdout, run.stdout + run.stderr
 
 
 @pytest.mark.gpu
