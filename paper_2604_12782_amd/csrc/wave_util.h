@@ -56,29 +56,6 @@ __device__ __forceinline__ uint32_t max_pair(uint32_t a, uint32_t b) {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
 }
 typedef unsigned int codes8 __attribute__((ext_vector_type(2)));  // eight one-byte codes
-// E4M3 codes of eight bf16 values (four packed words) with E8M0 scale code `code`, of which no value's
-// exponent exceeds code + 8: the scaled conversion rounds x * 2^(127 - code) to nearest even but does not
-// saturate, so magnitudes are clamped to 448 * 2^(code - 127) first, as bit patterns, two at a time
-// (the same codes as multiply, clamp to +-448, convert for every value and scale, at half the instructions)
-__device__ __forceinline__ codes8 mxfp8_codes(const uint32_t (&w)[4], uint32_t code) {
-    typedef __bf16 v2bf_ __attribute__((ext_vector_type(2)));
-    typedef short v2s_ __attribute__((ext_vector_type(2)));
-    const uint32_t lim = ((code + 8u) << 7 | 0x60u) * 0x00010001u;
-    const float scale = __builtin_bit_cast(float, code << 23);
-    uint32_t c[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t mag = w[k] & 0x7fff7fffu;
-        c[k] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, mag), __builtin_bit_cast(u16x2, lim)));
-        c[k] |= w[k] & 0x80008000u;
-    }
-    v2s_ lo = {0, 0}, hi = {0, 0};
-    lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(lo, __builtin_bit_cast(v2bf_, c[0]), scale, false);
-    lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(lo, __builtin_bit_cast(v2bf_, c[1]), scale, true);
-    hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(v2bf_, c[2]), scale, false);
-    hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(v2bf_, c[3]), scale, true);
-    return (codes8){__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
-}
 // E4M3 codes of eight bf16 values times `inv` (one rounded multiplication each), saturating at +-448
 __device__ __forceinline__ codes8 fp8_codes(const uint32_t (&w)[4], float inv) {
     float p[8];
@@ -94,6 +71,32 @@ __device__ __forceinline__ codes8 fp8_codes(const uint32_t (&w)[4], float inv) {
     r1 = __builtin_amdgcn_cvt_pk_fp8_f32(p[4], p[5], r1, false);
     r1 = __builtin_amdgcn_cvt_pk_fp8_f32(p[6], p[7], r1, true);
     return (codes8){(uint32_t)r0, (uint32_t)r1};
+}
+// E4M3 codes of eight bf16 values (four packed words) with E8M0 scale code `code`, of which no value's
+// exponent exceeds code + 8: the scaled conversion rounds x * 2^(127 - code) to nearest even but does not
+// saturate, so magnitudes are clamped to 448 * 2^(code - 127) first, as bit patterns, two at a time
+// (the codes of multiply, clamp to +-448, convert for every finite value and scale, at half the instructions).
+// Products that left the bf16 range come out of exponent 255, where no bf16 pattern is the limit (448 * 2^120):
+// such a block takes the multiplication and saturates as everywhere else (infinities to +-448, NaN to -448).
+__device__ __forceinline__ codes8 mxfp8_codes(const uint32_t (&w)[4], uint32_t code) {
+    typedef __bf16 v2bf_ __attribute__((ext_vector_type(2)));
+    typedef short v2s_ __attribute__((ext_vector_type(2)));
+    const uint32_t lim = ((code + 8u) << 7 | 0x60u) * 0x00010001u;
+    const float scale = __builtin_bit_cast(float, code << 23);
+    if (__builtin_expect(code == 247u, 0)) return fp8_codes(w, 0x1p-120f);
+    uint32_t c[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t mag = w[k] & 0x7fff7fffu;
+        c[k] = __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(u16x2, mag), __builtin_bit_cast(u16x2, lim)));
+        c[k] |= w[k] & 0x80008000u;
+    }
+    v2s_ lo = {0, 0}, hi = {0, 0};
+    lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(lo, __builtin_bit_cast(v2bf_, c[0]), scale, false);
+    lo = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(lo, __builtin_bit_cast(v2bf_, c[1]), scale, true);
+    hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(v2bf_, c[2]), scale, false);
+    hi = __builtin_amdgcn_cvt_scalef32_pk_fp8_bf16(hi, __builtin_bit_cast(v2bf_, c[3]), scale, true);
+    return (codes8){__builtin_bit_cast(uint32_t, lo), __builtin_bit_cast(uint32_t, hi)};
 }
 
 // ---- work split of the row-streaming kernels: (row, 1024-channel segment) items --------------

@@ -184,3 +184,30 @@ def test_swiglu_mxfp8_grid_forms(osc, M, K):
     gen = wl.rng(2000 + K)
     check_swiglu(osc, to_bf16_bits((gen.standard_normal((M, K)) * 3).astype(np.float32)),
                  wl.activations_diffuse(2050 + K, M, K, p=0.01))
+
+
+@pytest.mark.parametrize("K", [64, 2048])
+def test_swiglu_saturates_beyond_bf16(osc, K):
+    """Finite gates and ups whose product leaves the bf16 range, infinite gates and ups, and NaN, beside finite values
+    of the same block and of other blocks: the codes and scales are those of the quantiser on the values that the
+    call returns (infinities saturate at +-448, no NaN code), in both 8-bit formats.  Exact."""
+    gen = wl.rng(2100 + K)
+    edge = np.array([0x7F7F, 0xFF7F, 0x7F80, 0xFF80, 0x7FC0, 0x7E96, 0xFE96, 0x3F80, 0xBF80, 0x0000], np.uint16)  # +-max, inf, nan, 1e38, 1, 0
+    G = to_bf16_bits((gen.standard_normal((40, K)) * 3).astype(np.float32))
+    U = to_bf16_bits((gen.standard_normal((40, K)) * 3).astype(np.float32))
+    at = gen.random((40, K)) < np.repeat(gen.random((40, K // 32)) < 0.5, 32, axis=1) * 0.2  # in half of the blocks
+    G[at], U[at] = gen.choice(edge, int(at.sum())), gen.choice(edge, int(at.sum()))
+    G[0], U[0] = 0x7E96, to_bf16_bits(np.linspace(-4e38, 4e38, K).clip(-3e38, 3e38).astype(np.float32))  # finite only, overflowing
+    Xq, Xs, Yn = osc.osc_swiglu_quantize_act(dev(G), dev(U), want_y=True)
+    y = Yn.cpu().numpy()
+    assert ((y[0] & 0x7FFF) == 0x7F80).any() and ((y & 0x7F80) != 0x7F80).any(), "the inputs miss what this test is about"
+    Uq, Us = osc.osc_quantize_act(Yn, None, osc.OSC_FMT_MXFP8)
+    assert torch.equal(osc.osc_unpack_act_scales(Us, 40, K), osc.osc_unpack_act_scales(Xs, 40, K))
+    assert torch.equal(Uq, Xq), "codes differ from the quantiser's"
+    codes = Xq.cpu().numpy()
+    assert not ((codes & 0x7F) == 0x7F).any(), "NaN codes"
+    inf = (y & 0x7FFF) == 0x7F80
+    assert np.array_equal(codes[inf], np.where(y[inf] >> 15, 0xFE, 0x7E)), "infinities do not saturate"
+    X8, xs, Y8 = osc.osc_swiglu_quantize_act_fp8(dev(G), dev(U), want_y=True)
+    U8, us = osc.osc_quantize_act(Y8, None, osc.OSC_FMT_FP8_E4M3_TOKEN)
+    assert torch.equal(Y8, Yn) and torch.equal(U8, X8) and torch.equal(us.view(torch.int32), xs.view(torch.int32))
