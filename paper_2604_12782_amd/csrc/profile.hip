@@ -389,10 +389,8 @@ int launch_profile_threshold(const double* abs_sum, int64_t count, float alpha, 
 }
 
 template <bool CALIBRATE>
-static int launch_hist(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int32_t G, const float* T, uint32_t* hist,
-                       const CalibrateTail& ct, hipStream_t st) {
-    int nseg, nslots;
-    profile_grid(S, H, &nseg, &nslots);
+static int launch_hist(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int nseg, int nslots, int32_t G, const float* T,
+                       uint32_t* hist, const CalibrateTail& ct, hipStream_t st) {
     auto kern = G == 16 ? profile_hist_kernel<16, CALIBRATE> : G == 32 ? profile_hist_kernel<32, CALIBRATE> : profile_hist_kernel<64, CALIBRATE>;
     hipLaunchKernelGGL(kern, dim3(nseg * nslots), dim3(PT), 0, st, X, S, (int)H, ldx, nseg, nslots, T, hist, ct);
     return check_launch("profile_hist_kernel");
@@ -400,7 +398,9 @@ static int launch_hist(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int
 
 int launch_profile_hist(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int32_t G, const float* T,
                         uint32_t* hist, hipStream_t st) {
-    return launch_hist<false>(X, S, H, ldx, G, T, hist, CalibrateTail{}, st);
+    int nseg, nslots;
+    profile_grid(S, H, &nseg, &nslots);
+    return launch_hist<false>(X, S, H, ldx, nseg, nslots, G, T, hist, CalibrateTail{}, st);
 }
 
 int launch_profile_table(const uint32_t* hist, int32_t Kg, int32_t G, int32_t R, int16_t* table,
@@ -422,7 +422,8 @@ int launch_profile_table(const uint32_t* hist, int32_t Kg, int32_t G, int32_t R,
 // launches and latency, so it is folded into three launches: 8192 x 4096 41.1 -> 31.9 us, 1024 x 4096
 // 24.2 -> 15.7 us against clear, sum, threshold, counts, table, mean and copy as kernels of their own.
 // Scratch layout (caller's workspace): float T at 0, arrival counters at 4, uint32 hist[H] at 256.  Until the
-// threshold is known the hist area holds the workgroups' partial sums (double, at most H / 2 of them).
+// threshold is known the hist area holds the workgroups' partial sums (double, at most H / 2 of them) or, for
+// many narrow rows, the one sum that they add to (cleared by a fourth launch).
 constexpr int CAL_SETS = 62;  // counters at 8 .. 255, the one for the sets at 4
 
 // Threshold from the partial sums (added in a fixed order), then counters and counts set to zero: workgroup 0
@@ -452,26 +453,50 @@ __global__ void __launch_bounds__(PT) profile_calibrate_mid_kernel(uint8_t* scra
 
 size_t profile_scratch_bytes(int64_t H) { return 256 + (size_t)H * 4; }
 
+// the one sum of narrow rows (below)
+__global__ void profile_calibrate_clear_kernel(uint32_t* words) { words[threadIdx.x] = 0u; }
+
 int launch_profile_calibrate(const uint16_t* X, int64_t S, int64_t H, int64_t ldx, int32_t G, float alpha, int32_t R,
                              int16_t* table, uint32_t* n_total, uint32_t* n_hit, float* density, float* cbar,
                              float* T_out, uint8_t* scratch, hipStream_t st) {
     uint32_t* hist = reinterpret_cast<uint32_t*>(scratch + 256);
     int nseg, nslots;
     profile_grid(S, H, &nseg, &nslots);
-    const int64_t room = H / 2 / nseg;  // partial sums fit the area of the counts
-    if (nslots > room) nslots = (int)room;
-    const int npart = nseg * nslots;
-    hipLaunchKernelGGL(profile_abs_sum_kernel<true>, dim3(npart), dim3(PT), 0, st, X, S, (int)H, ldx, nseg, nslots,
-                       reinterpret_cast<double*>(hist));
-    int rc = check_launch("profile_abs_sum_kernel");
-    if (rc) return rc;
+    // The partial sums have to fit the area of the counts, which for narrow rows (H < 1024, one strip) holds fewer
+    // of them than there are workgroups to keep the chip busy.  There the choice is between the sums of fewer
+    // workgroups and one sum that is cleared first and added to.  A wavefront takes 0.45 us a row (two rows in
+    // flight), an addition or an arrival at one address 9 ns a workgroup, the clearing launch 3 us; with
+    // additions, both passes do best at sqrt(0.45 us * S / 16 / 18 ns) workgroups as long as that is at most
+    // one per CU (more rows are a stream, which wants all of them).  us, seven launches / partial sums / this rule:
+    //   8192 x 32    23.2 / 28.3 / 18.4     65536 x 32   34 / 114 / 34     1048576 x 64   273 / 1050 / 270
+    //   8192 x 128   23.5 / 19.7 / 18.2     32768 x 128  28 / 31 / 27      131072 x 512   57.5 / 51.8 / 51.7
+    const int64_t room = H / 2 / nseg;
+    auto rows = [&](int64_t slots) { return (double)((S + PW * slots - 1) / (PW * slots)); };  // per wavefront
+    bool narrow = false;
+    if (nslots > room) {
+        const int best = (int)__builtin_sqrt(1.56 * (double)S), slots = best <= 256 && best < nslots ? best : nslots;
+        narrow = 0.45 * (rows(room) - rows(slots)) > 0.009 * (slots - (nslots - slots)) + 3.0;
+        if (narrow) nslots = slots;
+    }
+    int rc, npart = 1;
+    if (narrow) {
+        hipLaunchKernelGGL(profile_calibrate_clear_kernel, dim3(1), dim3(2), 0, st, hist);
+        if ((rc = check_launch("profile_calibrate_clear_kernel"))) return rc;
+        hipLaunchKernelGGL(profile_abs_sum_kernel<false>, dim3(nseg * nslots), dim3(PT), 0, st, X, S, (int)H, ldx, nseg, nslots,
+                           reinterpret_cast<double*>(hist));
+    } else {
+        npart = nseg * (int)(nslots < room ? nslots : room);
+        hipLaunchKernelGGL(profile_abs_sum_kernel<true>, dim3(npart), dim3(PT), 0, st, X, S, (int)H, ldx, nseg, npart / nseg,
+                           reinterpret_cast<double*>(hist));
+    }
+    if ((rc = check_launch("profile_abs_sum_kernel"))) return rc;
     const int64_t wgs = (H + 4 * PT - 1) / (4 * PT);
     hipLaunchKernelGGL(profile_calibrate_mid_kernel, dim3((unsigned)(wgs < 256 ? wgs : 256)), dim3(PT), 0, st, scratch, npart,
                        (double)(S * H), (double)alpha, H);
     if ((rc = check_launch("profile_calibrate_mid_kernel"))) return rc;
     const CalibrateTail ct{reinterpret_cast<uint32_t*>(scratch + 8), reinterpret_cast<uint32_t*>(scratch + 4),
                            nseg < CAL_SETS ? nseg : CAL_SETS, R, table, n_total, n_hit, density, cbar, T_out};
-    return launch_hist<true>(X, S, H, ldx, G, reinterpret_cast<const float*>(scratch), hist, ct, st);
+    return launch_hist<true>(X, S, H, ldx, nseg, nslots, G, reinterpret_cast<const float*>(scratch), hist, ct, st);
 }
 
 // ---- the same call for callers that cannot allocate -----------------------------------------------

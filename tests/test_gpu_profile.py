@@ -169,8 +169,10 @@ def test_calibrate_in_one_call(osc, S, H, G, R):
 
 
 # the one-call form at the edges of its scratch and of its arrival counters: fewer partial sums than
-# workgroups, more column strips than counters, every slot of a group asked for
-@pytest.mark.parametrize("S,H,G,R", [(700, 16, 16, 16), (3, 64, 64, 64), (40, 1040, 16, 2), (18, 65600, 32, 1), (2100, 2048, 64, 2)])
+# workgroups, more column strips than counters, every slot of a group asked for; narrow rows whose sum is added to
+# one address instead, by fewer workgroups than the chip holds and by all of them
+@pytest.mark.parametrize("S,H,G,R", [(700, 16, 16, 16), (3, 64, 64, 64), (40, 1040, 16, 2), (18, 65600, 32, 1), (2100, 2048, 64, 2),
+                                     (9001, 32, 32, 2), (70001, 16, 16, 1), (140001, 64, 64, 3)])
 def test_calibrate_scratch_edges(osc, S, H, G, R):
     X = wl.activations_diffuse(9600 + H, S, H, p=0.02)
     table, n_total, n_hit, density, cbar, T = osc.osc_profile_calibrate(bf(X), G, 5.0, R)
@@ -180,3 +182,24 @@ def test_calibrate_scratch_edges(osc, S, H, G, R):
     assert np.array_equal(table.cpu().numpy(), rt)
     assert np.array_equal(as_u32(n_total), rn.astype(np.uint32)) and np.array_equal(as_u32(n_hit), rh.astype(np.uint32))
     assert np.allclose(density.cpu().numpy(), rd, rtol=1e-6, atol=0) and abs(cbar.item() - rc) <= 1e-6
+
+
+def test_calibrate_narrow_rows_fill_the_chip(osc):
+    """Narrow rows, whose counts' area holds the partial sums of few workgroups only: the call must not wait for those
+    few.  2^26 values as 1048576 x 64 against 16384 x 4096, which reads them at the memory's rate: 270 against
+    50 us, and 1050 where 32 workgroups did all the summing; the bound lies between."""
+    def us(S, H):
+        X = torch.randn((S, H), device="cuda").to(torch.bfloat16)
+        ws = torch.empty(osc.osc_profile_workspace_bytes(H), dtype=torch.uint8, device="cuda")
+        best = float("inf")
+        for _ in range(6):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(4):
+                osc.osc_profile_calibrate(X, 32, 5.0, 1, workspace=ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 250)
+        return best
+    wide, narrow = us(16384, 4096), us(1048576, 64)
+    assert narrow <= 10 * wide, (narrow, wide)
