@@ -2213,16 +2213,25 @@ static int launch_skinny(KArgs a, hipStream_t st) {
 // v_mfma_f32_16x16x32_bf16: 8 elements (16 bytes).  Result register k: row 4q + k, column r.
 // An FP4 or bf16 line is two instructions, instruction i taking piece 2q + i for lane block q (its two scale
 // bytes are then one 16-bit word); an 8-bit line is one, pieces q and 4 + q.
-// GROUPED: blockIdx.y < E is the expert, of which the workgroup takes the first 16 MT rows (an expert without
-// rows leaves at once); the M / (16 MT) values after them number the further row blocks of all experts, and the
-// workgroup finds the expert of its own (most leave).  One workgroup taking an expert's blocks one after the
-// other made uneven routing expensive.  Both
-// expert GEMMs of the layer above, weights from HBM, us (64 x 128 tiles / an expert's blocks in turn / this):
-//   256 rows, all of one expert    27 / 70 / 21      evenly drawn (2 an expert)   137 / 83 / 83
-//   512 rows, all of one expert    27 / 131 / 29     evenly drawn (4)             145 / 92 / 94
-//   512 rows over eight experts    32 / 45 / 35
-//   1024 rows                                        evenly drawn (8)             145 / 96 / 102  RAGGED: rows need not be whole lines; pieces past the end of a row come from the block of
-// zeros in the packed weight.
+// GROUPED: the workgroup takes 16 MT rows of one expert.  The last E values of blockIdx.y are the experts' first
+// blocks (an expert without rows leaves at once); the values before them number the further blocks of all experts,
+// and the workgroup finds the expert of its own (most leave).  They come first because a busy expert's blocks
+// are what an uneven routing waits for; behind the first blocks they started when those were through.  Two
+// wavefronts a workgroup where rows are short and workgroups many.
+// Both expert GEMMs of 128 experts of 1536 x 2048 (dual) and 2048 x 768 (FP8), us: tiles of 64 x 128 / this with four
+// wavefronts and the further blocks last / this; the weights from HBM, and in the last-level cache as far as they fit:
+//   rows                            HBM                  cache
+//   256, two of every expert        96 / 76 / 72         80 / 74 / 70
+//   256, drawn                      85 / 66 / 63         69 / 62 / 59
+//   256, all of one expert          24 / 18 / 15         17 / 16 / 12
+//   256, of eight experts           26 / 24 / 19         17 / 19 / 14
+//   512, drawn                      95 / 78 / 75         78 / 75 / 72      (the launcher: tiles)
+//   512, of 16 experts              27 / 33 / 30         21 / 28 / 21      (tiles)
+//   512, of 30 experts              32 / 49 / 42         28 / 44 / 37      (tiles)
+//   1024, drawn                     96 / 88 / 85         81 / 86 / 83      (tiles)
+//   1024, of 16 experts             27 / 50 / 49         22 / 43 / 40      (tiles)
+// RAGGED: rows need not be whole lines; pieces past the end of a row come from the block of zeros in the packed weight
+// (not in MXFP8, whose rows are whole lines).
 // ------------------------------------------------------------------------------------------
 typedef float v4f __attribute__((ext_vector_type(4)));
 
@@ -2235,11 +2244,11 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(KArgs a) {
     int m_begin = blockIdx.y * (16 * MT), m_end = min(a.M, m_begin + 16 * MT);
     const uint8_t* wp = a.Wpack;
     if constexpr (GROUPED) {
-        int e = blockIdx.y, block = 0;
-        if (e >= a.E) {
+        const int nfurther = (a.M - 1) / (16 * MT);  // as many as one expert with all rows has
+        int e = (int)blockIdx.y - nfurther, block = 0;
+        if (e < 0) {
             // 64 experts at a time, one per lane: prefix sum of their further blocks (as in tile_at)
-            int j = e - a.E;
-            e = -1;
+            int j = blockIdx.y;
             for (int e0 = 0; e0 < a.E; e0 += 64) {
                 const int n = e0 + lane < a.E ? a.off[e0 + lane + 1] - a.off[e0 + lane] : 0;
                 const int more = n > 16 * MT ? (n - 1) / (16 * MT) : 0;
@@ -2443,8 +2452,8 @@ __global__ void __launch_bounds__(64 * NW) gemm_stream_kernel(KArgs a) {
 template <int MODE, int MT, int NT, int NW, bool GROUPED>
 static int launch_stream_cfg(const KArgs& a, bool ragged, hipStream_t st) {
     const unsigned gx = (unsigned)((a.N + 16 * NT - 1) / (16 * NT));
-    const unsigned gy = GROUPED ? (unsigned)(a.E + a.M / (16 * MT)) : (unsigned)((a.M + 16 * MT - 1) / (16 * MT));
-    if (gx == 0 || gy == 0) return OSC_OK;
+    if (a.M == 0 || gx == 0) return OSC_OK;
+    const unsigned gy = GROUPED ? (unsigned)(a.E + (a.M - 1) / (16 * MT)) : (unsigned)((a.M + 16 * MT - 1) / (16 * MT));
     auto kern = ragged ? gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, MODE != MODE_MX8> : gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, false>;
     hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(64 * NW), 0, st, a);
     return check_launch("gemm_stream_kernel");
@@ -2660,10 +2669,18 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     StreamTile stile = stream_tile(p.M, p.N, ncu_hint > 0 ? ncu_hint : 256);
     const bool stream_ok = !p.row_map && p.M >= 1 && (lines || MODE != MODE_MX8);
     if (stream_ok && !grouped && (p.M <= 32 || stile.cost <= (lines ? 3 : 8))) kind = 6;
-    // Experts of a few rows (at most eight on average: both GEMMs of 128 experts at 1024 rows 102 us against 145 on the
-    // tiles, 88 against 96 with half the weights in the last-level cache; at ten 96 against 96 there, beyond it the tiles are ahead)
+    // Experts of a few rows: at most eight on average, and even if the routing is as uneven as it can be, which the
+    // host cannot see, at most four workgroups (rows that are not whole lines: three) per CU for the row blocks
+    // after an expert's first.  Every such block reads its expert's weights again, where a tile of 64 rows reads
+    // them once: with more of them the tiles win on uneven routing (512 rows of 30 experts out of 128 of
+    // 1536 x 2048 and 2048 x 768: 28 us against 37) though they lose on even routing (95 against 75 from HBM,
+    // 78 against 72 from the last-level cache).  A row of tiles runs on one die, three resident per CU: where
+    // its columns need several rounds (N = 28672) the tiles are that much later.  The table beside the kernel
+    // holds both sides.
     const bool stream_grp = grouped && p.E > 0 && (lines || MODE != MODE_MX8) && p.E + p.M / 16 <= 65535;  // its grid's second extent
-    if (stream_grp && p.M <= 8 * (int64_t)p.E) kind = 6;
+    const int64_t ncu = ncu_hint > 0 ? ncu_hint : 256;
+    const int64_t further = (p.M - 1) / 16 * ((p.N + 31) / 32), die = 3 * ncu / 8 > 0 ? 3 * ncu / 8 : 1;
+    if (stream_grp && p.M >= 1 && p.M <= 8 * (int64_t)p.E && further <= (lines ? 4 : 3) * ncu * (((p.N + 127) / 128 + die - 1) / die)) kind = 6;
     if (const int t_tile = tuning(TUNE_GEMM_TILE), t_kern = tuning(TUNE_GEMM_KERNEL); t_tile >= 0 || t_kern >= 0) {
         // test and tuning overrides (osc_tuning.h); a kernel that cannot serve the shape is not forced
         if (t_tile >= 0) tm = (t_tile == 1 || t_tile == 2 || t_tile == 4) ? t_tile : 2;
@@ -2684,7 +2701,15 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         if ((t_kern == 4 || t_kern == 5) && ring_ok)
             return t_kern == 4 ? launch_ring<4, 2, 4, true>(a, st) : launch_ring<4, 2, 4, false>(a, st);
     }
-    if (kind == 6 && grouped) return launch_stream_cfg<MODE, 1, 2, 4, true>(a, !lines, st);
+    if (kind == 6 && grouped) {
+        // two wavefronts per workgroup where rows are short (two to six lines each) and there are workgroups enough to
+        // fill the CUs: less to sum and to start.  128 experts of 1536 x 2048 and 2048 x 768 with two rows each: 71.7 us
+        // against 75.8 with four wavefronts, eight experts 10.4 against 9.7; 16 experts of 8192 x 4096 54.4 against 52.9;
+        // with K = 2080 (not whole lines) 92 against 85
+        const int64_t nlines = (rowbytes + 127) / 128 + (MODE == MODE_DUAL ? (p.K_o * 2 + 127) / 128 : 0);
+        if (lines && nlines <= 12 && p.E * ((p.N + 31) / 32) >= 4 * ncu) return launch_stream_cfg<MODE, 1, 2, 2, true>(a, !lines, st);
+        return launch_stream_cfg<MODE, 1, 2, 4, true>(a, !lines, st);
+    }
     if (kind == 6) return launch_stream<MODE>(a, stile, !lines, st);
     if (kind == 3) return launch_skinny<MODE>(a, st);
     if (kind == 2 && p.N % (64 * tm) == 0 && p.M >= 64 * tm) {

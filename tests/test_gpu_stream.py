@@ -77,12 +77,13 @@ def test_8bit(osc, tuning, M, N, K):
         close(Y[:, c], ref, f"mxfp8 {M}x{N}x{K}")
 
 
-@pytest.mark.parametrize("K,r", [(512, 2), (256, 0), (1056, 1)])
-@pytest.mark.parametrize("sizes", [[0, 1, 15, 16, 17, 0, 33, 70, 2], [3], [0, 0, 5, 0], [0] * 62 + [17, 0, 33] + [1] * 64 + [48]],
-                         ids=["any", "one", "few", "past_64"])
+@pytest.mark.parametrize("K,r", [(512, 2), (256, 0), (1056, 1), (4096, 4)])
+@pytest.mark.parametrize("sizes", [[0, 1, 15, 16, 17, 0, 33, 70, 2], [3], [0, 0, 5, 0], [0] * 62 + [17, 0, 33] + [1] * 64 + [48],
+                                   [0] * 160 + [49]], ids=["any", "one", "few", "past_64", "all_of_one"])
 def test_experts(osc, tuning, sizes, K, r):
-    """Experts of no rows, of one tile, of several (whose further blocks are looked up 64 experts at a time); dual path
-    with a row map, FP8 and MXFP8."""
+    """Experts of no rows, of one tile, of several (whose further blocks are looked up 64 experts at a time), as many
+    further blocks as the grid holds; dual path with a row map, FP8 and MXFP8; two wavefronts a workgroup (short
+    rows of many experts) and four."""
     tuning.gemm("1,6")
     E, N, tokens = len(sizes), 200, 60
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
@@ -115,3 +116,37 @@ def test_experts(osc, tuning, sizes, K, r):
                               for e in range(E) if off[e + 1] > off[e]])
         Y = osc.osc_mxfp8_gemm(Xm, Xms, pack(osc.osc_pack_weight_mxfp8, osc.osc_packed_weight_mxfp8_bytes(N, K)), N, K, expert_offsets=dev(off))
         close(Y, ref, f"grouped mxfp8 {sizes} K={K}")
+
+
+@pytest.mark.parametrize("busy", [1, 8, 16, 25])
+def test_uneven_routing_is_no_slower_than_tiles(osc, tuning, busy):
+    """Few rows per expert on average, but all of them of `busy` experts out of 128, which the host cannot see: the
+    launcher's choice must not be far behind the tiled kernels, which read an expert's weights once.  (1024
+    rows of 16 experts: twice the time while the streaming kernel took them.)"""
+    E, N, K = 128, 1536, 2048
+    pack = osc.osc_packed_weight_bytes(N, K, 0)
+    W = torch.randint(0, 120, (E * pack,), dtype=torch.uint8, device="cuda")
+    for T in (256, 512, 1024):
+        sizes = torch.zeros(E, dtype=torch.int32)
+        for i in range(T):
+            sizes[i % busy * (E // busy)] += 1
+        off = torch.cat([torch.zeros(1, dtype=torch.int32), sizes.cumsum(0).to(torch.int32)]).cuda()
+        Xq = torch.randint(0, 255, (T, K // 2), dtype=torch.uint8, device="cuda")
+        Xs = torch.full((osc.osc_act_scale_bytes(T, K),), 127, dtype=torch.uint8, device="cuda")
+        Y = torch.empty((T, N), dtype=torch.bfloat16, device="cuda")
+
+        def us(cfg):
+            tuning.gemm(cfg)
+            best = float("inf")
+            for _ in range(8):
+                a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                a.record()
+                for _ in range(50):
+                    osc.osc_grouped_dual_gemm(Xq, Xs, None, None, off, T, W, N, K, 0, osc.OSC_DT_BF16, out=Y)
+                b.record()
+                b.synchronize()
+                best = min(best, a.elapsed_time(b) * 20)
+            return best
+
+        tiles, chosen = us("1,1"), us(None)
+        assert chosen <= 1.35 * tiles, (T, busy, chosen, tiles)
