@@ -28,9 +28,9 @@
 //   gemm_pipe2_kernel  the same data path, persistent workgroups, slot-pinned instruction order,
 //                      early buffer release; one problem (dual path, FP8 or MXFP8) of more than one whole
 //                      256x256 tile per CU (a ragged row tail goes to the DMA kernel);
-//   gemm_stream_kernel few rows: single problems of up to 32 (more where N is small), experts of up to eight on
-//                      average; 16-row instructions, any legal row length;
-//   gemm_skinny_kernel M <= 64 (decode) and other launches of at most 512 blocks of 32x32 outputs: one
+//   gemm_stream_kernel few rows: single problems of up to 16 (more where N is small), experts of up to eight on
+//                      average and a few hundred in all; 16-row instructions, any legal row length;
+//   gemm_skinny_kernel other launches of up to 64 rows or of at most 512 blocks of 32x32 outputs: one
 //                      workgroup per 32 output channels streams the weights once, its wavefronts split
 //                      the reduction axis;
 //   gemm_ring_kernel   a four-slot ring of half stages with two wavefront groups in anti-phase; never
@@ -2623,12 +2623,13 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         (p.M / 32 + 1) * ((p.K / 32 + 3) / 4) * 128 >= lim)
         return fail(OSC_ERR_UNSUPPORTED, "gemm: an operand of 4 GiB or more");
     const int64_t rows = grouped && p.E > 0 ? (p.M + p.E - 1) / p.E : p.M;  // rows per problem
-    // Kernel and tile choice.
-    //  - operand rows that are whole 128-byte lines: M <= 64 -> the skinny kernel; else 256x256 tiles
-    //    when they give every CU at least one tile (dual path, one problem: the persistent kernel;
-    //    otherwise the DMA kernel), else the DMA kernel with 128x128 tiles;
-    //  - everything else: the staged kernel, 64x128 or 128x128 tiles, with per-lane zero fill when
-    //    rows are not whole 64-byte steps.
+    // Kernel and tile choice, in the order in which a later rule overrides an earlier one:
+    //  - tiles: operand rows that are whole 128-byte lines go to the DMA kernel (one problem of more than one
+    //    256 x 256 tile per CU: the persistent kernel), others to the staged kernel, with per-lane zero fill when
+    //    rows are not whole 64-byte steps (not in MXFP8); 256-row tiles when they fill the chip, else 128 x 128,
+    //    else 64 x 128;
+    //  - few output blocks: the weight-streaming kernel (whole lines);
+    //  - few rows: the streaming kernel.
     const int64_t t256 = ((rows + 255) / 256) * ((p.N + 255) / 256) * (grouped ? p.E : 1);
     const bool lines = rowbytes > 0 && rowbytes % 128 == 0 &&
                        (MODE != MODE_DUAL || p.K_o == 0 || a.bpitch % 128 == 0);
@@ -2643,9 +2644,10 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     const int ncu_hint = cu_count();
     const bool second_round = !grouped && ncu_hint > 0 && t128 > 2 * (int64_t)ncu_hint;
     int tm = rows <= 64 ? 1 : (rows > 128 && (t256 >= 256 || second_round)) ? 4 : (t128 < t128_full ? 1 : 2);
-    if (MODE == MODE_MX8 && !lines)  // implemented in the DMA and skinny kernels only
+    if (MODE == MODE_MX8 && !lines)  // no kernel takes MXFP8 rows that are not whole lines
         return fail(OSC_ERR_UNSUPPORTED, "mxfp8 gemm: K must be a multiple of 128");
-    int kind = lines ? 1 : 0;  // 0 = staged kernel, 1 = DMA kernel, 2 = persistent pipelined kernel, 3 = skinny kernel
+    int kind = lines ? 1 : 0;  // 0 = staged kernel, 1 = DMA kernel, 2 = persistent pipelined kernel, 3 = skinny kernel,
+    // 6 = streaming kernel (4 and 5: the ring kernel, forced only)
     // persistent kernel: one dual-path problem, whole tiles along N, at least three stages; rows
     // past the last whole tile go to a second launch of the DMA kernel
     const bool pipe_ok = lines && !grouped && !p.row_map &&
@@ -2661,14 +2663,22 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     const int64_t skinny_wgs = ((p.N + 31) / 32) * ((p.M + 31) / 32);
     const bool skinny_ok = lines && !grouped && !p.row_map && p.M >= 1 && (p.M <= 64 || skinny_wgs <= 512);
     if (skinny_ok) kind = 3;
-    // The streaming kernel up to 32 rows at any N, and above that while its tile costs at most three 16-row
-    // panels per CU (64 x 1024 x 4096: 3.9 us against 5.0 on the weight-streaming kernel; at four panels,
-    // 64 x 4096 x 4096, 6.35 against 6.1).  Rows that are not whole lines have only the staged kernel otherwise,
-    // which eight panels still beat (64 x 4096 x 4128: 8.2 us against 26, 333 x 1000 x 2080: 7.5 against 12.7, 256 x 2048 x 8224:
-    // 17 against 43) and twelve no longer do (256 x 4096 x 1056: 11.1 against 8.8, 500 x 2048 x 4128: 20.4 against 18.6)
+    // The streaming kernel up to 16 rows at any N (per-token FP8: 32), and above that while its tile costs at most
+    // three 16-row panels per CU (MXFP8: two).  It is built for weights that come from HBM, as a decoding step's do;
+    // weight-streaming kernel above -> this one, us, from HBM and from the last-level cache:
+    //   16 x 12288 x 4096  FP8    13.8 -> 11.6   11.5 -> 11.1       16 x 4096 x 12288  MXFP8  16.6 -> 12.6   11.5 -> 12.4
+    //   32 x 4096 x 12288  dual   13.8 -> 11.3   10.2 -> 10.9       64 x 2048 x 4096   dual   6.0 -> 5.1     5.5 -> 4.8
+    //   32 x 12288 x 4096  FP8    15.1 -> 13.1   12.1 -> 12.4
+    // and beyond the line:
+    //   24 x 12288 x 4096  dual   9.9 -> 10.1    8.8 -> 9.8         32 x 24576 x 4096  MXFP8  23.5 -> 23.4   18.5 -> 22.9
+    //   17 x 4096 x 12288  MXFP8  16.6 -> 16.4   11.6 -> 15.8       64 x 4096 x 4096   dual   6.1 -> 6.35
+    // (Weights still in the second-level cache from the call before are up to a fifth slower than on that kernel.)
+    // Rows that are not whole lines have only the staged kernel otherwise, which 32 rows and eight panels still
+    // beat (64 x 4096 x 4128: 8.2 us against 26, 333 x 1000 x 2080: 7.5 against 12.7, 256 x 2048 x 8224: 17 against
+    // 43) and twelve panels no longer do (256 x 4096 x 1056: 11.1 against 8.8, 500 x 2048 x 4128: 20.4 against 18.6)
     StreamTile stile = stream_tile(p.M, p.N, ncu_hint > 0 ? ncu_hint : 256);
     const bool stream_ok = !p.row_map && p.M >= 1 && (lines || MODE != MODE_MX8);
-    if (stream_ok && !grouped && (p.M <= 32 || stile.cost <= (lines ? 3 : 8))) kind = 6;
+    if (stream_ok && !grouped && (p.M <= (lines && MODE != MODE_FP8 ? 16 : 32) || stile.cost <= (!lines ? 8 : MODE == MODE_MX8 ? 2 : 3))) kind = 6;
     // Experts of a few rows: at most eight on average, and even if the routing is as uneven as it can be, which the
     // host cannot see, at most four workgroups (rows that are not whole lines: three) per CU for the row blocks
     // after an expert's first.  Every such block reads its expert's weights again, where a tile of 64 rows reads
