@@ -33,16 +33,14 @@ class _Tuning:
         self.osc = osc
 
     def gemm(self, cfg):
-        """cfg = "<tile rows / 64>,<kernel id>" (0 staged, 1 DMA, 2 persistent, 3 skinny) or None."""
+        """cfg = "<tile rows / 64>,<kernel id>" (0 staged, 1 DMA, 2 persistent, 3 skinny, 4 and 5
+        ring, 6 streaming) or None.  A kernel that cannot serve a shape gives way to another."""
         tile, kern = (-1, -1) if cfg is None else map(int, cfg.split(","))
         self.osc.osc_tuning_set(self.osc.OSC_TUNE_GEMM_TILE, tile)
         self.osc.osc_tuning_set(self.osc.OSC_TUNE_GEMM_KERNEL, kern)
 
     def gemm_ksplit(self, on):
         self.osc.osc_tuning_set(self.osc.OSC_TUNE_GEMM_KSPLIT, -1 if on is None else int(on))
-
-    def swiglu_table(self, on):
-        self.osc.osc_tuning_set(self.osc.OSC_TUNE_SWIGLU_TABLE, -1 if on is None else int(on))
 
     def grouped_one_tile(self, on):
         self.osc.osc_tuning_set(self.osc.OSC_TUNE_GROUPED_ONE_TILE, -1 if on is None else int(on))

@@ -33,7 +33,7 @@ def close(Y, ref, what, bf16=False):
 
 # tile rows / 64, kernel id: 0 staged, 1 DMA (eight wavefronts at 256 rows), 2 persistent, 3 skinny,
 # 4 ring (wavefront groups in anti-phase), 5 ring (in phase)
-FORCED = ["4,1", "2,1", "1,1", "1,0", "2,0", "4,2", "2,2", "4,4", "4,5"]
+FORCED = ["4,1", "2,1", "1,1", "1,0", "2,0", "4,2", "2,2", "1,3", "4,4", "4,5"]  # (6, streaming: test_gpu_stream.py)
 
 
 @pytest.mark.parametrize("cfg", FORCED)
@@ -151,7 +151,49 @@ def test_fp8_persistent_pipeline(osc, tuning, M, N, K):
     assert float((Y1 - Y2).abs().max()) <= 1e-5 * float(Y1.abs().max())
 
 
-@pytest.mark.parametrize("cfg", ["4,1", "2,1", "1,1", "1,0", "2,0"])
+@pytest.mark.parametrize("cfg", ["1,0", "2,0"])
+@pytest.mark.parametrize("M,N,K,r", [(70, 1000, 96, 2), (300, 200, 2080, 1), (513, 520, 1056, 4), (64, 130, 32, 0)])
+def test_staged_rows_that_are_not_whole_lines(osc, tuning, cfg, M, N, K, r):
+    """The staged kernel with rows (codes, and with ldb = K_o rounded up to 8 the branch) that end inside a 64-byte step, whose
+    missing pieces come from the block of zeros: dual path, and per-token FP8 with K / 2 channels rounded to 16."""
+    tuning.gemm(cfg)
+    X, table = wl.activations_persistent(7700 + M, M, K, r) if r else (wl.activations_diffuse(7700 + M, M, K), None)
+    W = wl.weights(7710 + N, N, K)
+    oidx = oracle.table_to_index(table) if r else np.zeros(0, np.int32)
+    d_oidx = dev(oidx) if r else None
+    Wp = osc.osc_pack_weight(dev(W), d_oidx)
+    wq, ws, _ = oracle.quantize_mxfp4_osc(W)
+    for ldb in ((len(oidx) + 63) // 64 * 64, (len(oidx) + 7) // 8 * 8):
+        Xq, Xs, B = osc.osc_quantize_act(dev(X), d_oidx, ldb=ldb)
+        rq, rs, rb = oracle.quantize_mxfp4_osc(X, oidx, ldb=ldb)
+        ref = oracle.dual_gemm(rq, rs, rb if r else None, wq, ws, oracle.gather_wl(W, oidx))
+        for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
+            close(osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), ydt), ref, f"staged {cfg} {M}x{N}x{K} ldb={ldb} bf16={bf}", bf)
+    K8 = K // 2 // 16 * 16
+    X8 = wl.activations_diffuse(7720 + M, M, K8)
+    W8 = wl.weights(7730 + N, N, K8)
+    q8, s8 = osc.osc_quantize_act(dev(X8), None, osc.OSC_FMT_FP8_E4M3_TOKEN)
+    Y = osc.osc_fp8_gemm(q8, s8, osc.osc_pack_weight_fp8(dev(W8)), N, K8)
+    close(Y, oracle.fp8_gemm(*oracle.quantize_fp8_rows(X8), *oracle.quantize_fp8_rows(W8)), f"staged fp8 {cfg} {M}x{N}x{K8}")
+
+
+def test_long_prompt_with_ragged_rows(osc):
+    """500 x 2048 x 4128, where the launcher itself takes the staged kernel for rows that are not whole lines; sampled rows."""
+    M, N, K = 500, 2048, 4128
+    X, table = wl.activations_persistent(7740, M, K, 1)
+    W = wl.weights(7741, N, K)
+    oidx = oracle.table_to_index(table)
+    Xq, Xs, B = osc.osc_quantize_act(dev(X), dev(oidx))
+    Wp = osc.osc_pack_weight(dev(W), dev(oidx))
+    rows = np.array([0, 63, 64, 127, 128, 300, 447, 448, 499])
+    rq, rs, rb = oracle.quantize_mxfp4_osc(X[rows], oidx, ldb=B.shape[1])
+    wq, ws, _ = oracle.quantize_mxfp4_osc(W)
+    ref = oracle.dual_gemm(rq, rs, rb, wq, ws, oracle.gather_wl(W, oidx))
+    Y = osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), osc.OSC_DT_F32)
+    close(Y[torch.from_numpy(rows).cuda()], ref, "long ragged prompt")
+
+
+@pytest.mark.parametrize("cfg", ["4,1", "2,1", "1,1", "1,0", "2,0", "1,3"])
 def test_fp8_and_mxfp8_forced(osc, tuning, cfg):
     tuning.gemm(cfg)
     M, N, K = 300, 264, 768
@@ -161,7 +203,7 @@ def test_fp8_and_mxfp8_forced(osc, tuning, cfg):
     r8, rs = oracle.quantize_fp8_rows(X)
     w8, ws = oracle.quantize_fp8_rows(W)
     close(osc.osc_fp8_gemm(X8, xs, osc.osc_pack_weight_fp8(dev(W)), N, K), oracle.fp8_gemm(r8, rs, w8, ws), "fp8 " + cfg)
-    if cfg.endswith(",1"):  # the MXFP8 GEMM exists in the DMA (and skinny) kernels only
+    if not cfg.endswith(",0"):  # the MXFP8 GEMM has no staged form
         Xm, Xms = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_MXFP8)
         q, s = oracle.quantize_mxfp8(X)
         wq, wsc = oracle.quantize_mxfp8(W)
@@ -194,17 +236,17 @@ def test_output_into_wider_and_odd_buffers(osc, tuning, cfg):
             assert (rest == 7.0).all(), "wrote outside the output view"
 
 
-@pytest.mark.parametrize("cfg", ["4,1", "2,1", "1,1"])
-def test_grouped_with_skewed_experts(osc, tuning, cfg):
+@pytest.mark.parametrize("cfg,K,K2", [("4,1", 512, 384), ("2,1", 512, 384), ("1,1", 512, 384), ("1,0", 1056, 400), ("2,0", 1056, 400)])
+def test_grouped_with_skewed_experts(osc, tuning, cfg, K, K2):
     """Experts of 0, 1, 63 ... 700 rows, sizes on both sides of every tile border, through the
     256-row tiles with their 64-row remainder pass (4,1) and the smaller tiles: dual path with a row
-    map, per-token FP8 and MXFP8."""
+    map, per-token FP8 and MXFP8; staged (,0) with rows that are not whole lines."""
     tuning.gemm(cfg)
     sizes = [0, 1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 383, 384, 385, 700, 0, 130]
     E = len(sizes)
     off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
     T = int(off[-1])
-    tokens, K, N, r = 900, 512, 256, 2
+    tokens, N, r = 900, 256, 2
     X, table = wl.activations_persistent(7500, tokens, K, r)
     oidx = oracle.table_to_index(table)
     row_map = wl.rng(7501).integers(0, tokens, T).astype(np.int32)
@@ -222,13 +264,13 @@ def test_grouped_with_skewed_experts(osc, tuning, cfg):
     for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
         Y = osc.osc_grouped_dual_gemm(Xq, Xs, B, dev(row_map), dev(off), T, Wp, N, K, len(oidx), ydt)
         close(Y, ref, f"grouped dual {cfg} bf16={bf}", bf)
-    # 8-bit forms: rows in expert order (no row map in these entry points)
-    K2 = 384
+    # 8-bit forms: rows in expert order (no row map in these entry points); MXFP8 rows are whole lines
+    mx = K2 % 128 == 0
     X2 = wl.activations_diffuse(7502, T, K2)
     X8, xs = osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_FP8_E4M3_TOKEN)
-    Xm, Xms = osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_MXFP8)
+    Xm, Xms = osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_MXFP8) if mx else (None, None)
     r8, r8s = oracle.quantize_fp8_rows(X2)
-    m8, m8s = oracle.quantize_mxfp8(X2)
+    m8, m8s = oracle.quantize_mxfp8(X2) if mx else (None, None)
     s8, sm = osc.osc_packed_weight_fp8_bytes(N, K2), osc.osc_packed_weight_mxfp8_bytes(N, K2)
     Wp8 = torch.empty(E * s8, dtype=torch.uint8, device="cuda")
     Wpm = torch.empty(E * sm, dtype=torch.uint8, device="cuda")
@@ -237,14 +279,16 @@ def test_grouped_with_skewed_experts(osc, tuning, cfg):
     for e in range(E):
         W = wl.weights(7530 + e, N, K2)
         osc.osc_pack_weight_fp8(dev(W), out=Wp8[e * s8:(e + 1) * s8])
-        osc.osc_pack_weight_mxfp8(dev(W), out=Wpm[e * sm:(e + 1) * sm])
         a, b = oracle.quantize_fp8_rows(W)
         w8.append(a), w8s.append(b)
-        if off[e + 1] > off[e]:
+        if mx:
+            osc.osc_pack_weight_mxfp8(dev(W), out=Wpm[e * sm:(e + 1) * sm])
+        if mx and off[e + 1] > off[e]:
             refm[off[e]:off[e + 1]] = oracle.mxfp8_gemm(m8[off[e]:off[e + 1]], m8s[off[e]:off[e + 1]], *oracle.quantize_mxfp8(W))
     ref8 = oracle.grouped_fp8_gemm(r8, r8s, off, np.stack(w8), np.stack(w8s))
     close(osc.osc_fp8_gemm(X8, xs, Wp8, N, K2, expert_offsets=dev(off), y_dtype=osc.OSC_DT_BF16), ref8, "grouped fp8 " + cfg, True)
-    close(osc.osc_mxfp8_gemm(Xm, Xms, Wpm, N, K2, expert_offsets=dev(off), y_dtype=osc.OSC_DT_BF16), refm, "grouped mxfp8 " + cfg, True)
+    if mx:
+        close(osc.osc_mxfp8_gemm(Xm, Xms, Wpm, N, K2, expert_offsets=dev(off), y_dtype=osc.OSC_DT_BF16), refm, "grouped mxfp8 " + cfg, True)
 
 
 def test_wide_128x256_tiles_ragged(osc):

@@ -362,8 +362,10 @@ def test_quant_longest_rows(osc, r):
         osc.osc_quantize_act(dev(np.zeros((2, 65536 + 32), np.uint16)), None)
 
 
-def test_dual_gemm_long_k(osc):
-    """256 stages in one tile: M = 40 rows (the skinny kernel) and 200 rows (the DMA kernel)."""
+@pytest.mark.parametrize("cfg", [None, "1,3", "1,1"])
+def test_dual_gemm_long_k(osc, tuning, cfg):
+    """256 lines of codes along one row: the launcher's choice (the streaming kernel), the skinny and the DMA kernel."""
+    tuning.gemm(cfg)
     N, K = 96, 32768
     W = wl.weights(911, N, K)
     for M in (40, 200):

@@ -46,7 +46,7 @@ def test_static_scratch_equals_workspace_form_twice(osc):
         assert torch.cuda.memory_allocated() == before
         names = ("table", "n_total", "n_hit", "density", "cbar", "T")
         for n, a, b in zip(names, got, ref):
-            if n == "T":  # the sum behind it is added with floating-point atomics: last bits may differ
+            if n == "T":  # many narrow rows (not these) are summed with floating-point atomics, whose last bits may differ
                 assert abs(a.item() - b.item()) <= 1e-6 * abs(b.item()), n
             else:
                 assert torch.equal(a, b), f"{n} differs at S={S} H={H}"
