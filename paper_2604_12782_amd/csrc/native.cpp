@@ -56,12 +56,20 @@ int32_t count(PyObject* o) { return none(o) ? 0 : (int32_t)tensor(o).numel(); }
 int64_t pitch(PyObject* o) { return none(o) ? 0 : tensor(o).stride(0); }
 int64_t up64(int64_t n) { return (n + 63) / 64 * 64; }
 
-// an owned reference to a new tensor on t's device; like torch.empty, it asks torch whether the device may be
-// used first (in a process forked after the GPU was, torch refuses)
+// What torch.empty and torch.cuda.current_stream() do first: initialise the device, or raise torch's own error (no
+// GPU; a process forked after the GPU was used).  Torch's check takes 0.1 us, so it is made once, and
+// afterwards only whether this is such a forked process.
+void device_ready() {
+    static bool checked = false;  // under the interpreter lock
+    if (checked && !torch::utils::is_device_in_bad_fork(at::kCUDA)) return;
+    torch::utils::device_lazy_init(at::kCUDA);
+    checked = true;
+}
+
+// an owned reference to a new tensor on t's device
 PyObject* fresh(const at::Tensor& t, at::IntArrayRef size, at::ScalarType dtype) {
-    const at::TensorOptions options = t.options().dtype(dtype);
-    torch::utils::maybe_initialize_device(options);
-    PyObject* o = THPVariable_Wrap(at::empty(size, options));
+    if (t.is_cuda()) device_ready();
+    PyObject* o = THPVariable_Wrap(at::empty(size, t.options().dtype(dtype)));
     if (!o) throw PyFailed();
     return o;
 }
@@ -85,9 +93,8 @@ struct Ref {
     }
 };
 
-// torch's current stream, with the checks of torch.cuda.current_stream()
 void* stream() {
-    torch::utils::device_lazy_init(at::kCUDA);
+    device_ready();
     return c10::hip::getCurrentHIPStream().stream();
 }
 

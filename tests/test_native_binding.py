@@ -1,6 +1,7 @@
 """The native marshalling of the per-step calls: what it refuses, and that errors of the C ABI arrive as
 OscError with the library's code and text."""
 import os
+import signal
 import subprocess
 import sys
 
@@ -59,6 +60,30 @@ print("all refused")
     run = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))), capture_output=True,
                          text=True, timeout=300)
     assert run.returncode == 0 and "all refused" in run.stdout, run.stdout + run.stderr
+
+
+@pytest.mark.gpu
+def test_forked_process_is_refused():
+    """In a process forked after the GPU was used, torch's refusal arrives before anything touches the device."""
+    X = torch.zeros((4, 64), dtype=torch.bfloat16, device="cuda")
+    out = osc.osc_quantize_act(X)
+    torch.cuda.synchronize()
+    pid = os.fork()
+    if pid == 0:
+        status = 1
+        try:
+            signal.alarm(20)
+            refused = 0
+            for call in (lambda: osc.osc_quantize_act(X), lambda: osc.osc_quantize_act(X, out=out), osc.binding._stream):
+                try:
+                    call()
+                except RuntimeError as e:
+                    refused += "forked subprocess" in str(e)
+            status = 0 if refused == 3 else 2
+        finally:
+            os._exit(status)
+    assert os.waitpid(pid, 0)[1] == 0
+    assert torch.equal(osc.osc_quantize_act(X)[0], out[0])  # the parent goes on
 
 
 @pytest.mark.gpu
