@@ -9,8 +9,8 @@
  *     groups of 64: OSC_FMT_MXFP4_OSC_G64, osc_pack_weight_g).
  *   - Every tensor pointer is a DEVICE pointer owned by the caller unless marked
  *     "host".  The library never allocates, frees or keeps a pointer past the call
- *     (its only device memory of its own is one static 128 KB table, see
- *     osc_swiglu_quantize_act).
+ *     (its only device memory of its own is the static 64.25 KB scratch of
+ *     osc_profile_calibrate_static).
  *   - `stream` is a hipStream_t passed as void* (NULL = default stream).  Calls
  *     enqueue work and return; they never synchronise the device.
  *   - Return value: OSC_OK or a negative error; on error nothing was launched.

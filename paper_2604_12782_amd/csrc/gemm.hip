@@ -2454,7 +2454,8 @@ static int launch_stream_cfg(const KArgs& a, bool ragged, hipStream_t st) {
     const unsigned gx = (unsigned)((a.N + 16 * NT - 1) / (16 * NT));
     if (a.M == 0 || gx == 0) return OSC_OK;
     const unsigned gy = GROUPED ? (unsigned)(a.E + (a.M - 1) / (16 * MT)) : (unsigned)((a.M + 16 * MT - 1) / (16 * MT));
-    auto kern = ragged ? gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, MODE != MODE_MX8> : gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, false>;
+    constexpr bool ANY_ROWS = MODE != MODE_MX8 && !(GROUPED && NW == 2);  // the launcher has whole lines only for the others
+    auto kern = ragged ? gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, ANY_ROWS> : gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, false>;
     hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(64 * NW), 0, st, a);
     return check_launch("gemm_stream_kernel");
 }
@@ -2672,7 +2673,8 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     // and beyond the line:
     //   24 x 12288 x 4096  dual   9.9 -> 10.1    8.8 -> 9.8         32 x 24576 x 4096  MXFP8  23.5 -> 23.4   18.5 -> 22.9
     //   17 x 4096 x 12288  MXFP8  16.6 -> 16.4   11.6 -> 15.8       64 x 4096 x 4096   dual   6.1 -> 6.35
-    // (Weights still in the second-level cache from the call before are up to a fifth slower than on that kernel.)
+    // (From the last-level cache 17 to 32 rows of long weights are up to 1.37 times slower, 17 x 4096 x 12288 FP8 11.2 -> 14.5
+    // against 16.3 -> 15.2 from HBM; weights still in the second-level caches from the call before up to 1.25 times.)
     // Rows that are not whole lines have only the staged kernel otherwise, which 32 rows and eight panels still
     // beat (64 x 4096 x 4128: 8.2 us against 26, 333 x 1000 x 2080: 7.5 against 12.7, 256 x 2048 x 8224: 17 against
     // 43) and twelve panels no longer do (256 x 4096 x 1056: 11.1 against 8.8, 500 x 2048 x 4128: 20.4 against 18.6)
