@@ -160,3 +160,35 @@ def test_persistent_kernels_replay_equal_eager(osc, tuning):
             assert torch.equal(y, r), f"replay {i}"
         osc.osc_fp8_gemm(*f, W8, N, K, y_dtype=osc.OSC_DT_BF16)  # eager work of the same kernels in between
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("S,H", [(1536, 4096), (9001, 32)])
+def test_calibration_replays_equal_eager(osc, S, H):
+    """The one-call calibration under capture, in its three-launch form and in the four-launch form of narrow rows (whose sum
+    is cleared by a kernel of the call): replays on changing inputs, with eager calls on the same workspace in
+    between, equal eager runs (the threshold to its last bits: narrow rows are summed by floating-point atomics)."""
+    dev = torch.device("cuda:0")
+    inputs = [torch.from_numpy(wl.activations_persistent(4300 + i, S, H, 1, jitter=0.3)[0].view(np.int16)).to(dev).view(torch.bfloat16) for i in (0, 1)]
+    X = torch.empty((S, H), dtype=torch.bfloat16, device=dev)
+    ws = torch.empty(osc.osc_profile_workspace_bytes(H), dtype=torch.uint8, device=dev)
+
+    def eager(x):
+        X.copy_(x)
+        return [t.clone() for t in osc.osc_profile_calibrate(X, 32, 5.0, 2, workspace=ws)]
+
+    refs = [eager(x) for x in inputs]
+    out = osc.osc_profile_calibrate(X, 32, 5.0, 2, workspace=ws)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        osc.osc_profile_calibrate(X, 32, 5.0, 2, workspace=ws, out=out)
+    for i in range(4):
+        X.copy_(inputs[i & 1])
+        for t in out:
+            t.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        for n, a, b in zip(("table", "n_total", "n_hit", "density", "cbar"), out, refs[i & 1]):
+            assert torch.equal(a, b), f"{n}, replay {i}"
+        assert abs(out[5].item() - refs[i & 1][5].item()) <= 1e-6 * refs[i & 1][5].item()
+        eager(inputs[1 - (i & 1)])
