@@ -2196,7 +2196,7 @@ static int launch_skinny(KArgs a, hipStream_t st) {
 // wavefront loads the next line (eight lanes per row and line: 16-byte pieces of whole lines; loads in
 // matrix-core layout, where neighbouring lanes hold different rows, ran at a quarter of the rate) into one
 // of two register sets while it takes the current one through a strip of LDS of its own into
-// matrix-core layout: no barrier, and the waits are the compiler's counted ones.  Against the kernel below
+// matrix-core layout: no barrier, and the waits are the compiler's counted ones.  Against gemm_skinny_kernel
 // (32 channels and 32 rows per workgroup, operands by DMA through LDS rings), weights from HBM, us:
 //   M x N x K          dual path        FP8              MXFP8
 //   1 x 1024 x 4096    4.50 -> 3.71
@@ -2205,8 +2205,6 @@ static int launch_skinny(KArgs a, hipStream_t st) {
 //   16 x 24576 x 4096  14.9 -> 12.3
 //   16 x 4096 x 12288                   16.2 -> 11.4     16.5 -> 12.3     (50 MB: 4.5 TB/s with the launch)
 //   32 x 4096 x 4096   5.9 -> 5.3       K = 12288: 19.1 -> 14.4
-// and, grouped, 128 experts of 1536 x 2048 (dual) and 2048 x 768 (FP8) with two rows each on average against
-// tiles of 64 x 128: 50.5 -> 38.1 us and 42.1 -> 31.0 us (6 TB/s).
 // Layout of the 16-row instructions (lane = 16 q + r): v_mfma_scale_f32_16x16x128_f8f6f4 takes from lane
 // (q, r) of row r, FP4: the 32 elements (16 bytes) of scale block q and its scale byte; 8 bits: elements
 // 16q .. 16q+15 of each half of the 128 (registers 0-3, 4-7), and the scale of the 32-element block q.
