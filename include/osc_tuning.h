@@ -12,12 +12,13 @@ extern "C" {
 #endif
 
 enum {
-    OSC_TUNE_GEMM_TILE = 0,        /* tile rows / 64 of the GEMM kernels: 1, 2 or 4 */
-    OSC_TUNE_GEMM_KERNEL = 1,      /* 0 staged, 1 DMA, 2 persistent, 3 skinny, 4 and 5 ring, 6 streaming (ignored
+    OSC_TUNE_GEMM_TILE = 0,        /* tile rows / 64 of the GEMM kernels: 1, 2 or 4; with kernel 7 its tile: 0 128 x 256, 1 128 x 192,
+                                      2 128 x 128, 3 64 x 128 */
+    OSC_TUNE_GEMM_KERNEL = 1,      /* 0 staged, 1 DMA, 2 persistent, 3 skinny, 4 and 5 ring, 6 streaming, 7 flowing (ignored
                                       where a kernel cannot serve the shape) */
     OSC_TUNE_GROUPED_ONE_TILE = 2, /* 1: grouped 8-bit GEMMs keep one tile per workgroup */
     OSC_TUNE_SWIGLU_TABLE = 3,     /* accepted, no effect: the SwiGLU fusions have one kernel each */
-    OSC_TUNE_GEMM_KSPLIT = 4       /* 0 / 1: dual-path 64 x 128 tiles never / always split their K loop over two wavefront groups */
+    OSC_TUNE_GEMM_KSPLIT = 4       /* accepted, no effect: no kernel splits the K loop of a small tile any more */
 };
 
 /* Errors: OSC_ERR_UNSUPPORTED for an unknown knob.  Any negative value means "automatic". */

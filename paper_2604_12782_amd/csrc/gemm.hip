@@ -20,10 +20,12 @@
 // The kernels share these conventions; the host picks one per call (launch_gemm):
 //   gemm_kernel        register-staged (global -> VGPR -> LDS -> MFMA), 64-byte steps, any legal
 //                      shape (ragged rows through a block of zeros), grouped and row-mapped problems;
+//   gemm_flow_kernel   (gemm_flow.hip) one problem of more than a few rows: persistent workgroups, a ring of stages filled
+//                      several stages ahead; tiles from 64x128 to 128x256;
 //   gemm_dma2_kernel   global -> LDS by DMA in whole 128-byte lines, two LDS stages; dual path, FP8 and
 //                      MXFP8, grouped and row-mapped problems; needs 128-byte row pitches.  Tiles of
-//                      256x256 and 128x256 on eight wavefronts, 128x128 and 64x128 on four; a launch of
-//                      at most one 64x128 tile per CU splits every tile's K loop over two wavefront groups;
+//                      256x256 on eight wavefronts (one round of them also for one dual-path problem), 128x128 and
+//                      64x128 on four;
 //   gemm_dma2g_kernel  the same stages on persistent workgroups for grouped 8-bit problems;
 //   gemm_pipe2_kernel  the same data path, persistent workgroups, slot-pinned instruction order,
 //                      early buffer release; one problem (dual path, FP8 or MXFP8) of more than one whole
@@ -37,326 +39,10 @@
 //                      chosen by the launcher, reachable through the tuning override only.
 #include <cstdio>
 #include <cstdlib>
-#include <type_traits>
 
-#include "osc_internal.h"
-#include "lds_dma.h"
+#include "gemm_tile.h"
 
 namespace osc {
-
-typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-typedef float v2f __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
-constexpr int GT = 256;  // 4 wavefronts, arranged 2 x 2 over the workgroup tile
-enum { MODE_DUAL = 0, MODE_FP8 = 1, MODE_MX8 = 2 };  // MX8: E4M3 codes with E8M0 block scales on both operands
-
-struct KArgs {
-    const uint8_t* Xq;
-    const uint8_t* Xs;
-    const float* xs;
-    const uint8_t* B;
-    int64_t bpitch;  // bytes per row of B
-    const int32_t* row_map;
-    const int32_t* off;
-    int E;
-    const uint8_t* Wpack;
-    size_t pack_stride, off_q, off_s, off_l, off_z;
-    int64_t wlpitch;  // bytes per row of W_L^T
-    int M, N, K, K_o;
-    void* Y;
-    int y_bf16;
-    int64_t ldy;
-    int tiles_n;
-    // grouped problems, which rows of an expert this launch covers: 0 = all of them; 1 = its first
-    // (n + BM/2) / BM tiles (an expert whose last tile would be less than half full leaves those rows
-    // out); 2 = the rows that a mode-1 launch with tiles of grp_bm rows left out
-    int grp_mode, grp_bm;
-};
-
-
-
-struct TilePos {
-    int m0, n0, row_begin, row_end;
-    const uint8_t* wp;
-    bool valid;
-};
-
-// Workgroups are dealt round-robin to the 8 XCDs; renumber so that each XCD owns a contiguous
-// run of tiles and its L2 sees neighbouring tiles.  Single problem: tiles walk down bands of 8
-// m-tiles.  Grouped: m-tiles are numbered expert by expert (the grid is an upper bound).
-template <int BM, int BN>
-__device__ __forceinline__ TilePos tile_at(const KArgs& a, int tile);
-
-template <int BM, int BN>
-__device__ __forceinline__ TilePos locate_tile(const KArgs& a) {
-    int tile = blockIdx.x;
-    if (a.off) {
-        // grouped: XCD x takes m-tiles x, x+8, ... and walks the n-tiles of each in turn (they share
-        // the activation rows).  The surplus m-tiles at the end of the numbering (the grid is an
-        // upper bound, a multiple of 8 m-tiles) are then spread over all XCDs.
-        const int x = tile & 7, sidx = tile >> 3;
-        tile = ((sidx / a.tiles_n) * 8 + x) * a.tiles_n + sidx % a.tiles_n;
-    } else {
-        const int per = gridDim.x >> 3;
-        if (tile < (per << 3)) tile = (tile & 7) * per + (tile >> 3);
-    }
-    return tile_at<BM, BN>(a, tile);
-}
-
-// position of tile number `tile` (numbered so that neighbours share operand panels)
-template <int BM, int BN>
-__device__ __forceinline__ TilePos tile_at(const KArgs& a, int tile) {
-    TilePos p;
-    p.row_begin = 0;
-    p.row_end = a.M;
-    p.wp = a.Wpack;
-    p.valid = true;
-    int tm_idx, tn_idx;
-    if (a.off) {
-        // m-tiles are numbered expert by expert.  Every wavefront finds the expert of m-tile j by
-        // itself: 64 experts at a time, one per lane, prefix sum of their tile counts, first lane
-        // whose running total exceeds j.  (A serial walk over the offsets costs one dependent
-        // memory round trip per expert.)
-        tn_idx = tile % a.tiles_n;
-        const int j = tile / a.tiles_n;
-        const int lane = threadIdx.x & 63;
-        int before = 0, e_found = -1, j_in = 0;
-        for (int e0 = 0; e0 < a.E; e0 += 64) {
-            const int e = e0 + lane;
-            int b = e < a.E ? a.off[e] : 0;
-            int n = e < a.E ? a.off[e + 1] - b : 0;
-            if (a.grp_mode == 1) {
-                n = min(n, (n + BM / 2) / BM * BM);
-            } else if (a.grp_mode == 2) {
-                const int skip = min(n, (n + a.grp_bm / 2) / a.grp_bm * a.grp_bm);
-                b += skip;
-                n -= skip;
-            }
-            const int te = (n + BM - 1) / BM;
-            int ps = te;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int v = __shfl_up(ps, d);
-                if (lane >= d) ps += v;
-            }
-            const int total = __shfl(ps, 63);
-            if (j < before + total) {
-                const int l = __ffsll((unsigned long long)__ballot(before + ps > j)) - 1;
-                e_found = e0 + l;
-                j_in = j - (before + __shfl(ps, l) - __shfl(te, l));
-                p.row_begin = __shfl(b, l);
-                p.row_end = p.row_begin + __shfl(n, l);
-                break;
-            }
-            before += total;
-        }
-        e_found = __builtin_amdgcn_readfirstlane(e_found);
-        j_in = __builtin_amdgcn_readfirstlane(j_in);
-        p.row_begin = __builtin_amdgcn_readfirstlane(p.row_begin);
-        p.row_end = __builtin_amdgcn_readfirstlane(p.row_end);
-        if (e_found < 0) {  // surplus workgroup (the grid is an upper bound)
-            p.valid = false;
-            e_found = 0;
-        }
-        tm_idx = j_in;
-        p.wp += (size_t)e_found * a.pack_stride;
-    } else {
-        const int tiles_m = (a.M + BM - 1) / BM;
-        const int band = tile / (8 * a.tiles_n), within = tile - band * 8 * a.tiles_n;
-        const int rows = min(8, tiles_m - band * 8);
-        tm_idx = band * 8 + within % rows;
-        tn_idx = within / rows;
-    }
-    p.m0 = p.row_begin + tm_idx * BM;
-    p.n0 = tn_idx * BN;
-    return p;
-}
-
-// LDS_SCALES (FP8, tiles entirely inside Y): the row scales of the tile's BM rows and the column scales of
-// its BN columns are read from `tile_scales` in LDS (BM + BN floats) instead of global memory.
-template <int MODE, int TM, int TN, int WN = 2, bool LDS_SCALES = false>
-__device__ __forceinline__ void store_result(const KArgs& a, const TilePos& tp, v16f (&acc)[TM][TN],
-                                             const float* tile_scales = nullptr) {
-    constexpr int BM = 64 * TM, BN = 32 * TN * WN;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = wave / WN, wn = wave % WN, q = lane >> 5, r = lane & 31;
-    const int m0 = tp.m0, n0 = tp.n0, row_end = tp.row_end;
-    const uint8_t* wp = tp.wp;
-    // ---- epilogue ---------------------------------------------------------------------------
-    // Result register k of lane (q, r): row 8*(k/4) + 4*q + k%4, column r of its 32x32 tile.
-    // fp32: every register is one 128-byte row segment per half-wave.  bf16: neighbouring lanes
-    // swap one register of each pair so that every lane owns two adjacent columns of one row and
-    // writes them as one 32-bit word (even lanes row k, odd lanes row k+1).
-    const float* wsc = (MODE == MODE_FP8) ? reinterpret_cast<const float*>(wp + a.off_s) : nullptr;
-    const int odd = r & 1;
-    const int wu_m = __builtin_amdgcn_readfirstlane(wm), wu_n = __builtin_amdgcn_readfirstlane(wn);
-    // byte offset of this lane's four columns inside a 32x32 result tile: row 4q + r%4, columns 4(r/4) ..
-    const uint32_t yoff8 = 2u * (uint32_t)((4 * q + (r & 3)) * (int)a.ldy + (r & ~3));
-    const bool hi2 = (r & 2) != 0;
-    // 16-byte stores of eight bf16 columns need rows that keep 16-byte alignment
-    const bool wide16 = (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0;
-    // byte selector of step 2: even lanes [own.lo, other.lo], odd lanes [other.hi, own.hi]
-    const uint32_t sel12 = odd ? 0x03020706u : 0x05040100u;
-    auto store_tile = [&](auto kind_tag) __attribute__((always_inline)) {
-        // 2: tile entirely inside Y, no bounds tests; 1: all columns inside, rows tested (ragged
-        // last tile of a problem or an expert); 0: everything tested, 2-byte stores
-        constexpr int KIND = decltype(kind_tag)::value;
-        constexpr bool FULL = KIND == 2;
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-            const int rbase = m0 + wm * (TM * 32) + i * 32 + 4 * q;
-            float xr[16];
-            if (MODE == MODE_FP8) {
-#pragma unroll
-                for (int k = 0; k < 16; ++k) {
-                    const int row = rbase + 8 * (k >> 2) + (k & 3);
-                    if constexpr (LDS_SCALES) xr[k] = tile_scales[row - m0];
-                    else xr[k] = a.xs[FULL ? row : min(row, row_end - 1)];
-                }
-            }
-            if constexpr (KIND >= 1 && TN % 2 == 0) {
-                if (a.y_bf16 && wide16) {
-                    // 16-byte stores: the two exchange rounds described below, on two neighbouring tiles,
-                    // then a third between lanes l and l^4: lanes of even column groups complete eight
-                    // adjacent columns of the left tile, the others of the right tile, so one store
-                    // instruction writes eight rows of 128 contiguous bytes.
-                    const bool lo4 = (r & 4) != 0;
-                    const uint32_t yoff16 = 2u * (uint32_t)((4 * q + (r & 3)) * (int)a.ldy + (r & ~3) + (lo4 ? 28 : 0));
-#pragma unroll
-                    for (int jp = 0; jp < TN; jp += 2) {
-                        u32x2 o[2][4];
-#pragma unroll
-                        for (int s2 = 0; s2 < 2; ++s2) {
-                            const int j = jp + s2;
-                            float cs = 1.0f;
-                            if (MODE == MODE_FP8) cs = LDS_SCALES ? tile_scales[BM + wn * (TN * 32) + j * 32 + r] : wsc[n0 + wn * (TN * 32) + j * 32 + r];
-                            uint32_t P[8], W[8];
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) {
-                                const float v0 = (MODE == MODE_FP8) ? acc[i][j][2 * k] * (xr[2 * k] * cs) : acc[i][j][2 * k];
-                                const float v1 = (MODE == MODE_FP8) ? acc[i][j][2 * k + 1] * (xr[2 * k + 1] * cs)
-                                                                     : acc[i][j][2 * k + 1];
-                                const v2f pair = {v0, v1};
-                                P[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, v2bf));
-                            }
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) {
-                                const uint32_t Q = (uint32_t)__builtin_amdgcn_mov_dpp((int)P[k], 0xB1, 0xF, 0xF, true);
-                                W[k] = __builtin_amdgcn_perm(Q, P[k], sel12);
-                            }
-#pragma unroll
-                            for (int h = 0; h < 4; ++h) {
-                                const uint32_t ra = (uint32_t)__builtin_amdgcn_mov_dpp((int)W[2 * h], 0x4E, 0xF, 0xF, true);
-                                const uint32_t rb = (uint32_t)__builtin_amdgcn_mov_dpp((int)W[2 * h + 1], 0x4E, 0xF, 0xF, true);
-                                o[s2][h] = (u32x2){hi2 ? rb : W[2 * h], hi2 ? W[2 * h + 1] : ra};
-                            }
-                        }
-                        uint8_t* const ybase = reinterpret_cast<uint8_t*>(a.Y) +
-                            2 * ((int64_t)(m0 + wu_m * (TM * 32) + i * 32) * a.ldy + n0 + wu_n * (TN * 32) + jp * 32);
-#pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            // lane + 4 sends its left-tile words down, lane - 4 its right-tile words up
-                            const uint32_t dx = (uint32_t)__builtin_amdgcn_mov_dpp((int)o[0][h].x, 0x104, 0xF, 0xF, true);
-                            const uint32_t dy = (uint32_t)__builtin_amdgcn_mov_dpp((int)o[0][h].y, 0x104, 0xF, 0xF, true);
-                            const uint32_t ux = (uint32_t)__builtin_amdgcn_mov_dpp((int)o[1][h].x, 0x114, 0xF, 0xF, true);
-                            const uint32_t uy = (uint32_t)__builtin_amdgcn_mov_dpp((int)o[1][h].y, 0x114, 0xF, 0xF, true);
-                            const u32x4 out = {lo4 ? ux : o[0][h].x, lo4 ? uy : o[0][h].y, lo4 ? o[1][h].x : dx,
-                                               lo4 ? o[1][h].y : dy};
-                            uint8_t* const hbase = ybase + 2 * (int64_t)(8 * h) * a.ldy;
-                            if (FULL || rbase + 8 * h + (r & 3) < row_end)
-                                __builtin_nontemporal_store(out, reinterpret_cast<u32x4*>(hbase + yoff16));
-                        }
-                    }
-                    continue;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                const int col = n0 + wn * (TN * 32) + j * 32 + r;
-                float cs = 1.0f;
-                if (MODE == MODE_FP8) cs = LDS_SCALES ? tile_scales[BM + col - n0] : wsc[FULL ? col : min(col, a.N - 1)];
-                float v[16];
-#pragma unroll
-                for (int k = 0; k < 16; ++k)
-                    v[k] = (MODE == MODE_FP8) ? acc[i][j][k] * (xr[k] * cs) : acc[i][j][k];
-                if (a.y_bf16 && KIND >= 1) {
-                    // 8-byte stores: two rounds of exchanges inside each quad of lanes turn "one column,
-                    // sixteen rows per lane" into "four adjacent columns of one row per lane".
-                    //  1. pairs of result registers (rows R, R+1 of column c) are rounded to packed bf16;
-                    //  2. lanes c, c^1 swap halves: even lanes get row R, odd lanes row R+1, columns c&~1, +1;
-                    //  3. lanes l, l^2 swap words of register pairs (k, k+2): lanes 0,1 of a quad complete
-                    //     rows R, R+1, lanes 2,3 rows R+2, R+3, columns 4b .. 4b+3.
-                    // Each step runs over all registers of the tile before the next one starts, so the
-                    // single wavefront of a SIMD always has independent instructions to issue.
-                    uint8_t* const ybase = reinterpret_cast<uint8_t*>(a.Y) +
-                        2 * ((int64_t)(m0 + wu_m * (TM * 32) + i * 32) * a.ldy + n0 + wu_n * (TN * 32) + j * 32);
-                    uint32_t P[8], W[8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const v2f pair = {v[2 * k], v[2 * k + 1]};
-                        P[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, v2bf));
-                    }
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const uint32_t Q = (uint32_t)__builtin_amdgcn_mov_dpp((int)P[k], 0xB1, 0xF, 0xF, true);
-                        W[k] = __builtin_amdgcn_perm(Q, P[k], sel12);
-                    }
-#pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        // both words cross to lane l^2; each lane keeps one of its own and one of the other's
-                        // (every crossing has a single use, so it folds into the select that consumes it)
-                        const uint32_t ra = (uint32_t)__builtin_amdgcn_mov_dpp((int)W[2 * h], 0x4E, 0xF, 0xF, true);
-                        const uint32_t rb = (uint32_t)__builtin_amdgcn_mov_dpp((int)W[2 * h + 1], 0x4E, 0xF, 0xF, true);
-                        const u32x2 out = {hi2 ? rb : W[2 * h], hi2 ? W[2 * h + 1] : ra};
-                        uint8_t* const hbase = ybase + 2 * (int64_t)(8 * h) * a.ldy;
-                        if (FULL || rbase + 8 * h + (r & 3) < row_end)
-                            __builtin_nontemporal_store(out, reinterpret_cast<u32x2*>(hbase + yoff8));
-                    }
-                } else if (a.y_bf16) {
-                    uint16_t* Y = reinterpret_cast<uint16_t*>(a.Y);
-#pragma unroll
-                    for (int k = 0; k < 16; k += 2) {
-                        const float send = odd ? v[k] : v[k + 1];
-                        // neighbour lane's value: DPP quad_perm [1,0,3,2]
-                        const float recv = __builtin_bit_cast(
-                            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, false));
-                        const float lo = odd ? recv : v[k], hi = odd ? v[k + 1] : recv;
-                        const int row = rbase + 8 * (k >> 2) + (k & 3) + odd;
-                        const int c0 = col - odd;
-                        uint16_t* dst = Y + (int64_t)row * a.ldy + c0;
-                        const uint32_t word =
-                            (uint32_t)f32_to_bf16_rne(lo) | ((uint32_t)f32_to_bf16_rne(hi) << 16);
-                        if (row < row_end) {
-                            if (c0 < a.N) dst[0] = (uint16_t)word;
-                            if (c0 + 1 < a.N) dst[1] = (uint16_t)(word >> 16);
-                        }
-                    }
-                } else {
-                    float* Y = reinterpret_cast<float*>(a.Y);
-#pragma unroll
-                    for (int k = 0; k < 16; ++k) {
-                        const int row = rbase + 8 * (k >> 2) + (k & 3);
-                        if (FULL || (row < row_end && (KIND == 1 || col < a.N))) Y[(int64_t)row * a.ldy + col] = v[k];
-                    }
-                }
-            }
-        }
-    };
-    // 32-bit stores of bf16 pairs need an even leading dimension and a 4-byte aligned Y
-    const bool cols = (n0 + BN <= a.N) &&
-                      (!a.y_bf16 || (((a.ldy & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.Y) & 7) == 0)));
-    if (cols && m0 + BM <= row_end)
-        store_tile(std::integral_constant<int, 2>{});
-    else if (cols)
-        store_tile(std::integral_constant<int, 1>{});
-    else
-        store_tile(std::integral_constant<int, 0>{});
-}
 
 // ------------------------------------------------------------------------------------------
 // Ring kernel.  Per step every row contributes 64 contiguous bytes (FP4: 128 channels = four
@@ -690,14 +376,8 @@ __global__ void __launch_bounds__(GT) gemm_kernel(KArgs a) {
 
 constexpr int dma2_scale_bytes(int BM, int BN) { return ((BM + BN) / 32 * 256 + 1023) / 1024 * 1024; }
 
-template <int MODE, int TM, int TN, int WN, int KS = 1>
-__global__ void __launch_bounds__(128 * WN * KS) gemm_dma2_kernel(KArgs a) {
-    // KS = 2 (dual path and FP8, small tiles): two groups of 2 x WN wavefronts share a tile and split its reduction
-    // axis, group g taking stages g, g + 2, ... through LDS stages of its own; the partial sums meet in LDS
-    // at the end.  A launch of at most one small tile per CU leaves one wavefront on every SIMD, and a stage
-    // is then a chain of latencies (LDS read, eight MFMAs, barrier) with nothing to overlap it; the second
-    // group fills those gaps and halves the number of stages each wavefront walks through.
-    static_assert(KS == 1 || (KS == 2 && WN == 2 && (MODE == MODE_DUAL || MODE == MODE_FP8)), "K split: two groups, dual path or FP8");
+template <int MODE, int TM, int TN, int WN>
+__global__ void __launch_bounds__(128 * WN) gemm_dma2_kernel(KArgs a) {
     // 2 x WN wavefronts; WN = 4 puts two wavefronts on every SIMD: while one waits for its LDS
     // reads or sits between two dependent MFMAs the other keeps the matrix core busy
     constexpr int NWV = 2 * WN;                // wavefronts
@@ -711,12 +391,10 @@ __global__ void __launch_bounds__(128 * WN * KS) gemm_dma2_kernel(KArgs a) {
     // bytes of scale words per stage: [block][half step][32 rows][4], rounded up to whole 1 KB requests
     constexpr int SCL = dma2_scale_bytes(BM, BN);
     constexpr int NREQ = (NBLK + 3) / 4;       // 16-byte scale requests per stage (four blocks each)
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds_all[];
-    const int grp = KS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / (128 * WN)) : 0;
-    uint8_t* const lds = lds_all + grp * (2 * STG + 2 * SCL);  // this group's two stages and their scale words
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     uint8_t* const scl = lds + 2 * STG;        // scale words of the two stages
 
-    const int t = KS > 1 ? (int)threadIdx.x % (128 * WN) : (int)threadIdx.x, lane = t & 63, wave = t >> 6;
+    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm = wave / WN, wn = wave % WN, q = lane >> 5, r = lane & 31;
     const TilePos tp = locate_tile<BM, BN>(a);
     if (!tp.valid) return;
@@ -846,8 +524,8 @@ __global__ void __launch_bounds__(128 * WN * KS) gemm_dma2_kernel(KArgs a) {
     }
 
     // ---- prologue ---------------------------------------------------------------------------------
-    if ((MODE == MODE_DUAL || MODE == MODE_MX8) && grp < nTA) OSC_D2_SCALES(grp, 0)
-    OSC_D2_ANY(grp, 0, 0, LA, 0, LB)
+    if ((MODE == MODE_DUAL || MODE == MODE_MX8) && nTA > 0) OSC_D2_SCALES(0, 0)
+    OSC_D2_ANY(0, 0, 0, LA, 0, LB)
     wait_vmcnt<0>();
     __syncthreads();
     u32x4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
@@ -864,17 +542,17 @@ __global__ void __launch_bounds__(128 * WN * KS) gemm_dma2_kernel(KArgs a) {
         int sa[TM], sb[TN], ta[TM], tb[TN];                                                    \
         OSC_F2(buf, 2 * q, fa0, fb0)                                                           \
         OSC_D2_READ_SCALES(buf, 0, sa, sb)                                                     \
-        if ((T_) + KS < nTA) OSC_D2_SCALES((T_) + KS, buf ^ 1)                                   \
-        REFILL_((T_) + KS, buf ^ 1, 0, D2_R1A, 0, D2_R1B)                                       \
+        if ((T_) + 1 < nTA) OSC_D2_SCALES((T_) + 1, buf ^ 1)                                     \
+        REFILL_((T_) + 1, buf ^ 1, 0, D2_R1A, 0, D2_R1B)                                        \
         OSC_F2(buf, 2 * q + 1, fa1, fb1)                                                       \
         OSC_MFMA_FP4(0, fa0, fb0, sa, sb)                                                      \
         spread_hint<TM * TN, TM + TN, 0, NSB + D2_R1A + D2_R1B>();                             \
-        REFILL_((T_) + KS, buf ^ 1, D2_R1A, D2_R2A, D2_R1B, D2_R2B)                             \
+        REFILL_((T_) + 1, buf ^ 1, D2_R1A, D2_R2A, D2_R1B, D2_R2B)                              \
         OSC_F2(buf, 4 + 2 * q, fa0, fb0)                                                       \
         OSC_D2_READ_SCALES(buf, 1, ta, tb)                                                     \
         OSC_MFMA_FP4(1, fa1, fb1, sa, sb)                                                      \
         spread_hint<TM * TN, 2 * (TM + TN), 0, D2_R2A - D2_R1A + D2_R2B - D2_R1B>();           \
-        REFILL_((T_) + KS, buf ^ 1, D2_R2A, LA, D2_R2B, LB)                                     \
+        REFILL_((T_) + 1, buf ^ 1, D2_R2A, LA, D2_R2B, LB)                                      \
         OSC_F2(buf, 4 + 2 * q + 1, fa1, fb1)                                                   \
         OSC_MFMA_FP4(0, fa0, fb0, ta, tb)                                                      \
         spread_hint<TM * TN, TM + TN, 0, LA - D2_R2A + LB - D2_R2B>();                         \
@@ -888,11 +566,11 @@ __global__ void __launch_bounds__(128 * WN * KS) gemm_dma2_kernel(KArgs a) {
 #define OSC_D2_STAGE_BF16(T_)                                                                  \
     {                                                                                          \
         OSC_F2(buf, 2 * q, fa0, fb0)                                                           \
-        OSC_D2_BRANCH((T_) + KS, buf ^ 1, 0, LA / 2, 0, LB / 2)                                 \
+        OSC_D2_BRANCH((T_) + 1, buf ^ 1, 0, LA / 2, 0, LB / 2)                                  \
         OSC_F2(buf, 2 * q + 1, fa1, fb1)                                                       \
         OSC_MFMA_BF16(fa0, fb0)                                                                \
         spread_hint<TM * TN, TM + TN, 0, LA / 2 + LB / 2>();                                   \
-        OSC_D2_BRANCH((T_) + KS, buf ^ 1, LA / 2, LA, LB / 2, LB)                               \
+        OSC_D2_BRANCH((T_) + 1, buf ^ 1, LA / 2, LA, LB / 2, LB)                                \
         OSC_F2(buf, 4 + 2 * q, fa0, fb0)                                                       \
         OSC_MFMA_BF16(fa1, fb1)                                                                \
         spread_hint<TM * TN, TM + TN, 0, LA - LA / 2 + LB - LB / 2>();                         \
@@ -912,12 +590,12 @@ __global__ void __launch_bounds__(128 * WN * KS) gemm_dma2_kernel(KArgs a) {
         u32x4 ga0[TM], gb0[TN], ga1[TM], gb1[TN];                                              \
         OSC_F2(buf, 2 * q, fa0, fb0)                                                           \
         OSC_F2(buf, 2 * q + 1, ga0, gb0)                                                       \
-        if ((T_) + KS < nT) OSC_D2_MAIN((T_) + KS, buf ^ 1, 0, LA, 0, LB / 2)                    \
+        if ((T_) + 1 < nT) OSC_D2_MAIN((T_) + 1, buf ^ 1, 0, LA, 0, LB / 2)                      \
         OSC_F2(buf, 4 + 2 * q, fa1, fb1)                                                       \
         OSC_F2(buf, 4 + 2 * q + 1, ga1, gb1)                                                   \
         OSC_MFMA_FP8(0, TM * TN, fa0, ga0, fb0, gb0)                                           \
         spread_hint<TM * TN, 2 * (TM + TN), 0, LA + LB / 2>();                                 \
-        if ((T_) + KS < nT) OSC_D2_MAIN((T_) + KS, buf ^ 1, 0, 0, LB / 2, LB)                    \
+        if ((T_) + 1 < nT) OSC_D2_MAIN((T_) + 1, buf ^ 1, 0, 0, LB / 2, LB)                      \
         OSC_MFMA_FP8(0, TM * TN, fa1, ga1, fb1, gb1)                                           \
         spread_hint<TM * TN, 0, 0, LB - LB / 2>();                                             \
         __builtin_amdgcn_sched_barrier(0);                                                     \
@@ -1024,46 +702,17 @@ __global__ void __launch_bounds__(128 * WN * KS) gemm_dma2_kernel(KArgs a) {
         for (int T = 0; T < nT; ++T) OSC_D2_STAGE_FP8_LEAN(T)
     } else if (MODE == MODE_FP8) {
 #pragma unroll 1
-        for (int T = grp; T < nT; T += KS) OSC_D2_STAGE_FP8(T)
-        if constexpr (KS > 1) {
-            if (grp == 1 && (nT & 1)) __syncthreads();
-        }
+        for (int T = 0; T < nT; ++T) OSC_D2_STAGE_FP8(T)
     } else {
-        int T = grp;
+        int T = 0;
 #pragma unroll 1
-        for (; T + KS < nTA; T += KS) OSC_D2_STAGE_FP4(T, OSC_D2_MAIN)
+        for (; T + 1 < nTA; ++T) OSC_D2_STAGE_FP4(T, OSC_D2_MAIN)
         if (T < nTA) {
             OSC_D2_STAGE_FP4(T, OSC_D2_ANY)
-            T += KS;
+            ++T;
         }
 #pragma unroll 1
-        for (; T < nT; T += KS) OSC_D2_STAGE_BF16(T)
-        if constexpr (KS > 1) {
-            // every stage ends in a workgroup barrier: the group with one stage fewer keeps the count even
-            if (grp == 1 && (nT & 1)) __syncthreads();
-        }
-    }
-    if constexpr (KS > 1) {
-        // partial sums of group 1 -> LDS -> group 0 (every group has waited for its own last DMA request)
-        constexpr int GT_ = 128 * WN;
-        __syncthreads();
-        float* const red = reinterpret_cast<float*>(lds_all);
-        if (grp == 1) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-#pragma unroll
-                    for (int k2 = 0; k2 < 16; ++k2) red[((i * TN + j) * 16 + k2) * GT_ + t] = acc[i][j][k2];
-        }
-        __syncthreads();
-        if (grp != 0) return;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int k2 = 0; k2 < 16; ++k2) acc[i][j][k2] += red[((i * TN + j) * 16 + k2) * GT_ + t];
+        for (; T < nT; ++T) OSC_D2_STAGE_BF16(T)
     }
     store_result<MODE, TM, TN, WN>(a, tp, acc);
 }
@@ -2516,10 +2165,10 @@ static int launch_cfg(KArgs a, int64_t rows_total, bool grouped, hipStream_t st)
     return check_launch("gemm_kernel");
 }
 
-template <int MODE, int TM, int TN, int WN = 2, int KS = 1>
+template <int MODE, int TM, int TN, int WN = 2>
 static int launch_dma2(KArgs a, int64_t rows_total, bool grouped, hipStream_t st) {
     constexpr int BM = 64 * TM, BN = 32 * TN * WN;
-    const size_t smem = ((size_t)(BM + BN) * 128 * 2 + (size_t)dma2_scale_bytes(BM, BN) * 2) * KS;
+    const size_t smem = (size_t)(BM + BN) * 128 * 2 + (size_t)dma2_scale_bytes(BM, BN) * 2;
     a.tiles_n = (int)((a.N + BN - 1) / BN);
     int64_t tiles_m = (rows_total + BM - 1) / BM;
     if (grouped) {  // upper bounds, whole rounds of the 8 XCDs
@@ -2530,13 +2179,13 @@ static int launch_dma2(KArgs a, int64_t rows_total, bool grouped, hipStream_t st
     const int64_t grid = tiles_m * a.tiles_n;
     if (grid <= 0) return OSC_OK;
     if (grid > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "gemm: too many tiles");
-    auto kern = gemm_dma2_kernel<MODE, TM, TN, WN, KS>;
+    auto kern = gemm_dma2_kernel<MODE, TM, TN, WN>;
     if (smem > 64 * 1024) {
         static unsigned char lds_done[MAX_DEVICES];
         static size_t lds_reserved[MAX_DEVICES];
         if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc;
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN * KS), smem, st, a);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem, st, a);
     return check_launch("gemm_dma2_kernel");
 }
 
@@ -2623,45 +2272,79 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         return fail(OSC_ERR_UNSUPPORTED, "gemm: an operand of 4 GiB or more");
     const int64_t rows = grouped && p.E > 0 ? (p.M + p.E - 1) / p.E : p.M;  // rows per problem
     // Kernel and tile choice, in the order in which a later rule overrides an earlier one:
-    //  - tiles: operand rows that are whole 128-byte lines go to the DMA kernel (one problem of more than one
-    //    256 x 256 tile per CU: the persistent kernel), others to the staged kernel, with per-lane zero fill when
-    //    rows are not whole 64-byte steps (not in MXFP8); 256-row tiles when they fill the chip, else 128 x 128,
-    //    else 64 x 128;
+    //  - tiles: operand rows that are whole 128-byte lines go to the DMA kernel, others to the staged kernel, with
+    //    per-lane zero fill when rows are not whole 64-byte steps (not in MXFP8); 256-row tiles when they fill the chip,
+    //    else 128 x 128, else 64 x 128;
+    //  - one problem of whole lines and five stages or more: the flowing kernel, or where its model says so 256 x 256
+    //    tiles on the persistent kernel (more than one per CU) or the DMA kernel (dual path, at most one);
     //  - few output blocks: the weight-streaming kernel (whole lines);
     //  - few rows: the streaming kernel.
     const int64_t t256 = ((rows + 255) / 256) * ((p.N + 255) / 256) * (grouped ? p.E : 1);
     const bool lines = rowbytes > 0 && rowbytes % 128 == 0 &&
                        (MODE != MODE_DUAL || p.K_o == 0 || a.bpitch % 128 == 0);
     const bool ragged = rowbytes % 64 != 0 || (MODE == MODE_DUAL && p.K_o > 0 && a.bpitch % 64 != 0);
-    // 256-row tiles when they fill the chip, else 128x128, else (fewer than one tile per CU) 64x128
+    // DMA kernel: 256-row tiles when they fill the chip, else 128x128, else (fewer than one tile per CU) 64x128
     const int64_t t128 = ((rows + 127) / 128) * ((p.N + 127) / 128) * (grouped ? p.E : 1);
     const int64_t t128_full = MODE == MODE_DUAL ? 512 : 257;  // measured crossover: two (8-bit: one) 128x128 tiles per CU
-    // 256-row tiles also when they leave CUs idle but the 128 x 128 tiles would need a second round (two of
-    // them are resident per CU): 1024 x 12288 x 4096 takes 42.7 us on 192 tiles of 256 x 256 and 51 us on 768
-    // of 128 x 128, 768 x 12288 40 against 48 us; with one round of small tiles those are ahead (2048 x 4096:
-    // 28.6 against 39 us).  Measured for single problems; grouped ones keep the plain rule.
     const int ncu_hint = cu_count();
-    const bool second_round = !grouped && ncu_hint > 0 && t128 > 2 * (int64_t)ncu_hint;
+    const int64_t ncu = ncu_hint > 0 ? ncu_hint : 256;
+    // (one problem: 256-row tiles also when they leave CUs idle but the 128 x 128 tiles would need a second round, two of
+    // them being resident per CU: 1070 x 7424 x 512 takes 11.4 us on 145 tiles of 256 x 256 and 15.8 us on 522 small ones)
+    const bool second_round = !grouped && t128 > 2 * ncu;
     int tm = rows <= 64 ? 1 : (rows > 128 && (t256 >= 256 || second_round)) ? 4 : (t128 < t128_full ? 1 : 2);
     if (MODE == MODE_MX8 && !lines)  // no kernel takes MXFP8 rows that are not whole lines
         return fail(OSC_ERR_UNSUPPORTED, "mxfp8 gemm: K must be a multiple of 128");
     int kind = lines ? 1 : 0;  // 0 = staged kernel, 1 = DMA kernel, 2 = persistent pipelined kernel, 3 = skinny kernel,
-    // 6 = streaming kernel (4 and 5: the ring kernel, forced only)
-    // persistent kernel: one dual-path problem, whole tiles along N, at least three stages; rows
-    // past the last whole tile go to a second launch of the DMA kernel
-    const bool pipe_ok = lines && !grouped && !p.row_map &&
-                         (rowbytes / 128 + (MODE == MODE_DUAL ? (p.K_o * 2 + 127) / 128 : 0)) >= 3;
-    // (with at most one tile per CU there is no next tile to run ahead into, and the eight wavefronts of the
-    // DMA kernel are 6 % faster: 4096 x 4096 x 4096 in 46.5 against 49.4 us)
-    if (kind == 1 && pipe_ok && tm == 4 && t256 > 256) kind = 2;
-    // The weight-streaming kernel (one workgroup per 32 output channels and 32 rows) also wins for a few
-    // hundred rows as long as its grid is resident at once (two workgroups per CU): a tiled launch of so
-    // few tiles leaves most CUs idle (128 x 4096 x 4096: 11.8 us on 64 x 128 tiles, 6.8 us on 512 streaming
-    // workgroups).  Beyond 512 workgroups it needs a second round (1024 x 1024 x 4096, 1024 workgroups:
-    // 12.6 us) and the 64 x 128 tiles with their K loop split over two wavefront groups are ahead (9.9 us).
+    // 6 = streaming kernel, 7 = flowing kernel (4 and 5: the ring kernel, forced only)
+    const int stages = (int)(rowbytes / 128) + (MODE == MODE_DUAL ? (p.K_o * 2 + 127) / 128 : 0);
+    // persistent kernel: one problem, at least three stages; rows past the last whole tile go to a second launch
+    const bool pipe_ok = lines && !grouped && !p.row_map && stages >= 3;
+    if (pipe_ok && tm == 4 && t256 > 256) kind = 2;
+    int flow_tile = -1;
+    // (fewer than five stages: a tile is over before the ring has filled, 6493 x 640 x 512 FP8 10 us against 7.8 on the DMA
+    // kernel's tiles)
+    if (lines && !grouped && !p.row_map && p.M >= 1 && p.N >= 1 && stages >= 5) {
+        // One problem: the flowing kernel with the tile that its cost model prefers, or tiles of 256 x 256.  Those read
+        // LDS half as often per product, which is worth a higher clock, so they are ahead wherever their rounds are
+        // filled as well (8192 x 4096 x 4096: 85 us against 85 to 90, K = 12288 MXFP8 310 against 335) and behind where
+        // they are not (us, before -> flowing kernel):
+        //   dual  1000 x 24576 x 4096  94 -> 62 (three full rounds of 128 x 256 instead of 288 tiles of 256 x 256 and a
+        //         second launch), 3000 x 6144 x 4096  86 -> 58, 2048 x 12288 x 4096  76 -> 65, 512 x 12288 x 4096  24.5 -> 20.5
+        //   FP8   1000 x 4096 x 12288  60 -> 49, 2048 x 4096 x 4096  35.7 -> 30.1, 256 x 4096 x 12288  45 -> 29
+        //   MXFP8 512 x 4096 x 4096  25.7 -> 15.6, 1000 x 4096 x 12288  74 -> 52
+        // (weights from the last-level cache; from HBM the small tiles gain up to as much again, four stages of loads
+        // being in flight instead of one: dual 512 x 4096 x 4096  17.2 -> 12.9, MXFP8 256 x 4096 x 12288  95 -> 47).
+        // The 256 x 256 side costs, per round and in us, 3 + 0.83 a stage + 1.04 a stage and filled share of the CUs
+        // (dual path, DMA kernel for one round and persistent kernel for more), or 7 + 1.48 a stage (8 bits,
+        // persistent kernel), from the same measurements.
+        double flow_cost = 0.0;
+        flow_tile = flow_choose(MODE, p.M, p.N, stages, (int)ncu, &flow_cost);
+        if (flow_tile >= 0) {
+            kind = 7;
+            const bool more = t256 > ncu;  // more than one tile per CU
+            const int64_t tail = more ? p.M % 256 : 0;
+            if ((MODE == MODE_DUAL || more) && p.M > 128 && (!more || (p.N % 256 == 0 && p.M >= 256))) {
+                const int64_t tiles = more ? (p.M / 256) * (p.N / 256) : t256, rounds = (tiles + ncu - 1) / ncu;
+                double cost = MODE == MODE_DUAL ? (double)rounds * (3.0 + 0.83 * stages) + 1.04 * stages * (double)tiles / (double)ncu
+                                                : (double)rounds * (7.0 + 1.48 * stages);
+                double tail_cost = 0.0;
+                if (tail) flow_choose(MODE, tail, p.N, stages, (int)ncu, &tail_cost);
+                cost += tail ? 3.0 + tail_cost : 0.0;
+                if (cost <= 1.05 * flow_cost) {
+                    kind = more ? 2 : 1;
+                    tm = 4;
+                }
+            }
+        }
+    }
+    // The weight-streaming kernel (one workgroup per 32 output channels and 32 rows) wins for a few hundred rows as
+    // long as its grid is resident at once (two workgroups per CU): a tiled launch of so few tiles leaves most CUs idle
+    // (128 x 4096 x 4096: 11.8 us on 64 x 128 tiles, 6.8 us on 512 streaming workgroups), and for up to 64 rows until
+    // it needs a third round, from where the flowing kernel's 64 x 128 tiles are ahead (33 to 64 rows of 24576 x 4096:
+    // dual 23.4 -> 13.4 us, FP8 36 -> 18; of 12288 x 4096 equal or up to 1.1 times slower).
     const int64_t skinny_wgs = ((p.N + 31) / 32) * ((p.M + 31) / 32);
     const bool skinny_ok = lines && !grouped && !p.row_map && p.M >= 1 && (p.M <= 64 || skinny_wgs <= 512);
-    if (skinny_ok) kind = 3;
+    if (skinny_ok && (skinny_wgs <= 1024 || kind != 7)) kind = 3;
     // The streaming kernel up to 16 rows at any N (per-token FP8: 32), and above that while its tile costs at most
     // three 16-row panels per CU (MXFP8: two).  It is built for weights that come from HBM, as a decoding step's do;
     // weight-streaming kernel above -> this one, us, from HBM and from the last-level cache:
@@ -2688,14 +2371,17 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     // its columns need several rounds (N = 28672) the tiles are that much later.  The table beside the kernel
     // holds both sides.
     const bool stream_grp = grouped && p.E > 0 && (lines || MODE != MODE_MX8) && p.E + p.M / 16 <= 65535;  // its grid's second extent
-    const int64_t ncu = ncu_hint > 0 ? ncu_hint : 256;
     const int64_t further = (p.M - 1) / 16 * ((p.N + 31) / 32), die = 3 * ncu / 8 > 0 ? 3 * ncu / 8 : 1;
     if (stream_grp && p.M >= 1 && p.M <= 8 * (int64_t)p.E && further <= (lines ? 4 : 3) * ncu * (((p.N + 127) / 128 + die - 1) / die)) kind = 6;
     if (const int t_tile = tuning(TUNE_GEMM_TILE), t_kern = tuning(TUNE_GEMM_KERNEL); t_tile >= 0 || t_kern >= 0) {
         // test and tuning overrides (osc_tuning.h); a kernel that cannot serve the shape is not forced
         if (t_tile >= 0) tm = (t_tile == 1 || t_tile == 2 || t_tile == 4) ? t_tile : 2;
-        int k2 = ((t_kern >= 0 && t_kern <= 3) || t_kern == 6) ? t_kern : kind;  // ids 4 and 5 are handled before the launch below
-        if (t_tile >= 0 && t_kern < 0 && (k2 == 3 || k2 == 6)) k2 = lines ? 1 : 0;  // a forced tile means a tiled kernel
+        int k2 = ((t_kern >= 0 && t_kern <= 3) || t_kern == 6 || t_kern == 7) ? t_kern : kind;  // ids 4 and 5 are handled before the launch below
+        if (t_tile >= 0 && t_kern < 0 && (k2 == 3 || k2 == 6 || k2 == 7)) k2 = lines ? 1 : 0;  // a forced tile means a tiled kernel
+        if (k2 == 7) {  // the tile knob names one of the flowing kernel's own
+            if (t_tile >= 0) flow_tile = t_tile;
+            if (!lines || p.row_map || grouped || !flow_fits(MODE, flow_tile, stages, grouped, p.E)) k2 = lines ? 1 : 0;
+        }
         if (k2 == 6 && !(grouped ? stream_grp : stream_ok)) k2 = lines ? 1 : 0;
         if ((k2 == 1 || k2 == 2) && !lines) k2 = 0;
         if (k2 == 2 && (tm == 1 || (MODE != MODE_DUAL && tm != 4))) k2 = 1;
@@ -2722,6 +2408,7 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     }
     if (kind == 6) return launch_stream<MODE>(a, stile, !lines, st);
     if (kind == 3) return launch_skinny<MODE>(a, st);
+    if (kind == 7) return launch_flow(a, MODE, flow_tile, st);
     if (kind == 2 && p.N % (64 * tm) == 0 && p.M >= 64 * tm) {
         const int64_t m_full = p.M / (64 * tm) * (64 * tm);
         if (m_full < p.M) {  // ragged tail: rows m_full .. M-1 as a problem of their own
@@ -2767,29 +2454,7 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         // 256-row tiles run on eight wavefronts (2 x 4, 128x64 each): 6-8 % faster than four, the second
         // wavefront of a SIMD fills the issue gaps of the first
         if (tm == 4) return launch_dma2<MODE, 4, 2, 4>(a, p.M, grouped, st);
-        if constexpr (MODE == MODE_DUAL || MODE == MODE_FP8) {
-            // at most one 64 x 128 tile per CU: two groups of wavefronts per tile, each taking every second stage
-            // (2048 x 1024 x 4096: 12.7 -> 11.0 us, 128 x 12288 x 4096: 16.8 -> 13.2 us; with more tiles than CUs
-            // the doubled LDS footprint costs a round: 192 x 12288: 17.2 -> 23.9 us); the OSC_TUNE_GEMM_KSPLIT
-            // override switches it off (0) or on (1) where the shape allows it
-            const int ks = tuning(TUNE_GEMM_KSPLIT);
-            const int64_t t64 = ((p.M + 63) / 64) * ((p.N + 127) / 128);
-            const bool fits = !grouped && (rowbytes / 128 + (p.K_o * 2 + 127) / 128) >= 4;
-            if (tm == 1 && fits && (ks == 1 || (ks != 0 && ncu_hint > 0 && t64 <= ncu_hint)))
-                return launch_dma2<MODE, 1, 2, 2, 2>(a, p.M, grouped, st);
-            // more 64 x 128 tiles than CUs but at most one 128 x 128 tile per CU: those, split the same way
-            // (1024 x 4096 x 4096: 18.1 -> 16.5 us, 768 x 4096: 17.5 -> 14.5 us)
-            if (fits && rows > 64 && ((tm == 2 && ks == 1) || (tm == 1 && ks < 0 && ncu_hint > 0 && t128 <= ncu_hint)))
-                return launch_dma2<MODE, 2, 2, 2, 2>(a, p.M, grouped, st);
-        }
         if (tm == 1) return launch_dma2<MODE, 1, 2>(a, p.M, grouped, st);
-        // dual path, one problem: 128x256 tiles on eight wavefronts (64x64 each) beat two resident
-        // workgroups of 128x128 by 4 % when they still give every CU a tile (8192x1024x4096: 29.1
-        // against 30.3 us); the 8-bit modes gain nothing from them
-        if constexpr (MODE == MODE_DUAL) {
-            if (!grouped && ((p.M + 127) / 128) * ((p.N + 255) / 256) >= 256)
-                return launch_dma2<MODE, 2, 2, 4>(a, p.M, grouped, st);
-        }
         return launch_dma2<MODE, 2, 2>(a, p.M, grouped, st);
     }
     if constexpr (MODE == MODE_MX8) {

@@ -1,0 +1,107 @@
+"""The flowing GEMM kernel, every tile and mode, forced: ragged rows and columns, the fewest stages a tile takes, one tile per
+workgroup and several, odd output views.  Reference: the oracle on sampled rows, and the DMA kernel's result everywhere.  Both
+kernels add exact products in single precision; they differ in the order of at most 1 + K / 64 partial sums, so the
+whole results agree to a few 2^-24 of the largest output (1e-5 is used)."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-3
+TILES = {0: (128, 256, 3), 1: (128, 192, 3), 2: (128, 128, 4), 3: (64, 128, 4)}  # id: rows, columns, stages of lead
+
+
+@pytest.fixture(scope="module")
+def osc():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2604_12782_amd as m
+    m.lib()
+    return m
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def problem(osc, mode, M, N, K, r, seed):
+    """(call(y_dtype, out), reference(rows))"""
+    W = wl.weights(seed + 1, N, K)
+    if mode == "dual":
+        X, table = wl.activations_persistent(seed, M, K, r) if r else (wl.activations_diffuse(seed, M, K), None)
+        oidx = oracle.table_to_index(table) if r else np.zeros(0, np.int32)
+        d = dev(oidx) if r else None
+        q, Wp = osc.osc_quantize_act(dev(X), d), osc.osc_pack_weight(dev(W), d)
+
+        def ref(rows):
+            a = oracle.quantize_mxfp4_osc(X[rows], oidx, ldb=q[2].shape[1] if r else 0)
+            w = oracle.quantize_mxfp4_osc(W)
+            return oracle.dual_gemm(a[0], a[1], a[2] if r else None, w[0], w[1], oracle.gather_wl(W, oidx))
+        return lambda ydt, out=None: osc.osc_dual_gemm(*q, Wp, N, K, len(oidx), ydt, out=out), ref
+    X = wl.activations_diffuse(seed, M, K)
+    if mode == "fp8":
+        q, Wp = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_FP8_E4M3_TOKEN), osc.osc_pack_weight_fp8(dev(W))
+        return (lambda ydt, out=None: osc.osc_fp8_gemm(*q, Wp, N, K, y_dtype=ydt, out=out),
+                lambda rows: oracle.fp8_gemm(*oracle.quantize_fp8_rows(X[rows]), *oracle.quantize_fp8_rows(W)))
+    q, Wp = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_MXFP8), osc.osc_pack_weight_mxfp8(dev(W))
+    return (lambda ydt, out=None: osc.osc_mxfp8_gemm(*q, Wp, N, K, y_dtype=ydt, out=out),
+            lambda rows: oracle.mxfp8_gemm(*oracle.quantize_mxfp8(X[rows]), *oracle.quantize_mxfp8(W)))
+
+
+def check(osc, tuning, tile, mode, M, N, K, r, seed):
+    call, ref = problem(osc, mode, M, N, K, r, seed)
+    bm = TILES[tile][0]
+    rows = np.unique(np.clip(np.concatenate([np.arange(0, M, max(1, M // 5)), [bm - 1, bm, M - 1]]), 0, M - 1))
+    tuning.gemm(f"{tile},7")
+    Y, Yb = call(osc.OSC_DT_F32), call(osc.OSC_DT_BF16)
+    wide = torch.full((M, N + 24), 7.0, dtype=torch.bfloat16, device="cuda")  # rows that keep 16-byte alignment, and a view that does not
+    call(osc.OSC_DT_BF16, wide[:, 8:8 + N])
+    call(osc.OSC_DT_BF16, Yb)
+    odd = torch.full((M, N + 3), 7.0, dtype=torch.bfloat16, device="cuda")
+    call(osc.OSC_DT_BF16, odd[:, 1:1 + N])
+    tuning.gemm("1,1")
+    Y0 = call(osc.OSC_DT_F32)
+    want = ref(rows)
+    got = Y[torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64)
+    assert np.abs(got - want).max() <= TOL * np.abs(want).max()
+    assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max())
+    assert torch.equal(Yb, Y.to(torch.bfloat16))  # the same sums, rounded once
+    assert torch.equal(wide[:, 8:8 + N], Yb) and bool((wide[:, :8] == 7).all()) and bool((wide[:, 8 + N:] == 7).all())
+    assert torch.equal(odd[:, 1:1 + N], Yb) and bool((odd[:, :1] == 7).all()) and bool((odd[:, 1 + N:] == 7).all())
+
+
+@pytest.mark.parametrize("mode", ["dual", "fp8", "mx8"])
+@pytest.mark.parametrize("tile", sorted(TILES))
+def test_flow_edges(osc, tuning, tile, mode):
+    """One ragged tile with the fewest stages, one exact tile, a few ragged ones."""
+    bm, bn, lead = TILES[tile]
+    k1 = 256 if mode == "dual" else 128
+    check(osc, tuning, tile, mode, 1, 8, k1 * (lead + 1), 0, 7600 + tile)
+    check(osc, tuning, tile, mode, bm, bn, k1 * (lead + 2), 1 if mode == "dual" else 0, 7610 + tile)
+    check(osc, tuning, tile, mode, 2 * bm + 5, bn + 13, 2560, 4 if mode == "dual" else 0, 7620 + tile)
+
+
+@pytest.mark.parametrize("mode", ["dual", "fp8", "mx8"])
+@pytest.mark.parametrize("tile", sorted(TILES))
+def test_flow_several_tiles_per_workgroup(osc, tuning, tile, mode):
+    """More tiles than CUs, a number that the eight dies do not divide: the load cursor crosses into the next tile while the
+    current one is computed, both copies of the FP8 tile scales are used, and some workgroups have a tile more than others."""
+    bm, bn, lead = TILES[tile]
+    N = bn * 9 - 40
+    M = bm * 31 - 17  # 279 tiles
+    check(osc, tuning, tile, mode, M, N, 256 * (lead + 1) if mode == "dual" else 128 * (lead + 3), 2 if mode == "dual" else 0, 7700 + tile)
+
+
+def test_launcher_choice_agrees(osc, tuning):
+    """The launcher's own choice over shapes on both sides of its rules against the DMA kernel."""
+    for mode, M, N, K, r in [("dual", 1000, 1536, 4096, 1), ("dual", 130, 4096, 1280, 2), ("fp8", 300, 4104, 2048, 0), ("mx8", 700, 1000, 1536, 0),
+                             ("dual", 60, 33000, 1280, 0), ("fp8", 40, 33000, 640, 0), ("mx8", 2100, 2048, 640, 0), ("dual", 4200, 4096, 1536, 1)]:
+        call, _ = problem(osc, mode, M, N, K, r, 7800 + M)
+        tuning.gemm(None)
+        Y = call(osc.OSC_DT_F32)
+        tuning.gemm("1,1")
+        Y0 = call(osc.OSC_DT_F32)
+        assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max()), (mode, M, N, K, r)
