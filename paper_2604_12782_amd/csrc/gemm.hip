@@ -20,13 +20,12 @@
 // The kernels share these conventions; the host picks one per call (launch_gemm):
 //   gemm_kernel        register-staged (global -> VGPR -> LDS -> MFMA), 64-byte steps, any legal
 //                      shape (ragged rows through a block of zeros), grouped and row-mapped problems;
-//   gemm_flow_kernel   (gemm_flow.hip) one problem of more than a few rows: persistent workgroups, a ring of stages filled
+//   gemm_flow_kernel   (gemm_flow.hip) one problem or experts of more than a few rows: persistent workgroups, a ring of stages filled
 //                      several stages ahead; tiles from 64x128 to 128x256;
 //   gemm_dma2_kernel   global -> LDS by DMA in whole 128-byte lines, two LDS stages; dual path, FP8 and
 //                      MXFP8, grouped and row-mapped problems; needs 128-byte row pitches.  Tiles of
 //                      256x256 on eight wavefronts (one round of them also for one dual-path problem), 128x128 and
 //                      64x128 on four;
-//   gemm_dma2g_kernel  the same stages on persistent workgroups for grouped 8-bit problems;
 //   gemm_pipe2_kernel  the same data path, persistent workgroups, slot-pinned instruction order,
 //                      early buffer release; one problem (dual path, FP8 or MXFP8) of more than one whole
 //                      256x256 tile per CU (a ragged row tail goes to the DMA kernel);
@@ -718,184 +717,6 @@ __global__ void __launch_bounds__(128 * WN) gemm_dma2_kernel(KArgs a) {
 }
 
 // ------------------------------------------------------------------------------------------
-// The DMA kernel above for grouped 8-bit problems (FP8, MXFP8) with persistent workgroups.  An
-// expert's tile is a few stages long (K = 768: six), its weights are used by no other tile and come
-// from HBM, so a workgroup that handles one tile spends a third of its time before the first and
-// after the last MFMA.  Here a workgroup walks tiles v, v + grid, ... : the experts' row ranges and running tile
-// counts are put into LDS once, so finding a tile is a short binary search there; when the K
-// loop of a tile ends, both LDS stages are free and the first two stages of the next tile are
-// requested, then the results are stored, and the next K loop starts on operands that have
-// landed.  Measured on the MoE shape (T = 32768, 128 experts, 2048 x 768): FP8 109.6 -> 104 us,
-// MXFP8 102.5 -> 97.3 us; the dual path with its row map gained nothing from the same scheme
-// (131 us either way) and keeps one tile per workgroup.
-// ------------------------------------------------------------------------------------------
-template <int MODE, int TM, int TN, int WN>
-__global__ void __launch_bounds__(128 * WN) gemm_dma2g_kernel(KArgs a, int ntiles) {
-    static_assert(MODE != MODE_DUAL, "8-bit modes only (no row map, no bf16 branch)");
-    constexpr int NWV = 2 * WN;
-    constexpr int RPP = NWV * 8;
-    constexpr int BM = 64 * TM, BN = 32 * TN * WN;
-    constexpr int STG = (BM + BN) * 128;
-    constexpr int LA = BM / RPP, LB = BN / RPP;
-    constexpr int NBLK = (BM + BN) / 32;
-    constexpr int NSB = (NBLK + NWV - 1) / NWV;
-    static_assert(BM % RPP == 0 && BN % RPP == 0, "tile does not split over the wavefronts");
-    constexpr int SCL = NBLK * 256;
-    constexpr bool use16 = false;  // (the 16-byte scale requests of the DMA kernel are for single problems)
-    constexpr int NREQ = 0, wave_u = 0;
-    const uint8_t* const sc16_src = nullptr;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    uint8_t* const scl = lds + 2 * STG;
-    // per expert, behind the two stages and their scale words: first tile number, first row, rows
-    int* const cum_l = reinterpret_cast<int*>(scl + 2 * SCL);  // [E + 1]
-    int* const eb_l = cum_l + a.E + 1;                          // [E]
-    int* const en_l = eb_l + a.E;                               // [E]
-
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = wave / WN, wn = wave % WN, q = lane >> 5, r = lane & 31;
-    const int Kg4 = ((a.K >> 5) + 3) >> 2;
-    const int rowbytes = (MODE == MODE_DUAL) ? (a.K >> 1) : a.K;
-    const int nTA = rowbytes >> 7;
-    const int nTB = (MODE == MODE_DUAL) ? ((a.K_o * 2 + 127) >> 7) : 0;
-    const int nT = nTA + nTB;
-    const int c8 = (t & 7) ^ swz8(t >> 3);
-
-    // rows of every expert that this launch covers (see KArgs::grp_mode) and the running tile count
-    for (int e = t; e < a.E; e += 128 * WN) {
-        int b = a.off[e];
-        int n = a.off[e + 1] - b;
-        if (a.grp_mode == 1) {
-            n = min(n, (n + BM / 2) / BM * BM);
-        } else if (a.grp_mode == 2) {
-            const int skip = min(n, (n + a.grp_bm / 2) / a.grp_bm * a.grp_bm);
-            b += skip;
-            n -= skip;
-        }
-        eb_l[e] = b;
-        en_l[e] = n;
-    }
-    __syncthreads();
-    if (wave == 0) {
-        int before = 0;
-        for (int e0 = 0; e0 < a.E; e0 += 64) {
-            const int e = e0 + lane;
-            const int te = e < a.E ? (en_l[e] + BM - 1) / BM : 0;
-            int ps = te;
-#pragma unroll
-            for (int d = 1; d < 64; d <<= 1) {
-                const int u = __shfl_up(ps, d);
-                if (lane >= d) ps += u;
-            }
-            if (e < a.E) cum_l[e] = before + ps - te;
-            before += __shfl(ps, 63);
-        }
-        if (lane == 0) cum_l[a.E] = before;
-    }
-    __syncthreads();
-    // tile number v of the numbering of locate_tile() -> position: a binary search over the running
-    // tile counts (a few dependent LDS reads of uniform addresses, nothing kept in registers)
-    auto find_tile = [&](int v) -> TilePos {
-        TilePos p;
-        p.valid = false;
-        p.m0 = p.n0 = p.row_begin = p.row_end = 0;
-        p.wp = a.Wpack;
-        if (v >= ntiles) return p;
-        const int x = v & 7, sidx = v >> 3;
-        const int j = (sidx / a.tiles_n) * 8 + x;  // m-tile, counted over all experts
-        if (j >= cum_l[a.E]) return p;
-        // the last expert whose first tile number is <= j: experts without tiles share that number with
-        // their successor, so the last one is the one that owns tile j
-        int lo = 0, hi = a.E - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (cum_l[mid] <= j) lo = mid; else hi = mid - 1;
-        }
-        const int e = __builtin_amdgcn_readfirstlane(lo);
-        p.row_begin = __builtin_amdgcn_readfirstlane(eb_l[e]);
-        p.row_end = p.row_begin + __builtin_amdgcn_readfirstlane(en_l[e]);
-        p.m0 = p.row_begin + (j - __builtin_amdgcn_readfirstlane(cum_l[e])) * BM;
-        p.n0 = (sidx % a.tiles_n) * BN;
-        p.wp = a.Wpack + (size_t)e * a.pack_stride;
-        p.valid = true;
-        return p;
-    };
-
-    int v = blockIdx.x;
-    TilePos tp = find_tile(v);
-    if (!tp.valid) return;  // m-tiles are numbered in order: nothing valid follows an invalid one
-
-    uint32_t oa[LA], ob[LB], sco[NSB];
-    const uint8_t *wq, *wl, *wsb;
-    int m0, n0, row_end;
-    int buf = 0;
-    // the first two stages of tile TP_ into buffers buf and buf ^ 1
-#define D2G_START(TP_)                                                                                \
-    {                                                                                                 \
-        m0 = (TP_).m0;                                                                                \
-        n0 = (TP_).n0;                                                                                \
-        row_end = (TP_).row_end;                                                                      \
-        wq = (TP_).wp + a.off_q;                                                                      \
-        wl = (TP_).wp + a.off_l;                                                                      \
-        wsb = (TP_).wp + a.off_s;                                                                     \
-        _Pragma("unroll") for (int i = 0; i < LA; ++i) oa[i] = (uint32_t)min(m0 + (t >> 3) + RPP * i, row_end - 1); \
-        _Pragma("unroll") for (int i = 0; i < LB; ++i) ob[i] = (uint32_t)min(n0 + (t >> 3) + RPP * i, a.N - 1);     \
-        if (MODE == MODE_MX8) {                                                                       \
-            _Pragma("unroll") for (int k = 0; k < NSB; ++k) {                                         \
-                const int b = min(wave * NSB + k, NBLK - 1);                                          \
-                const int g = b < BM / 32 ? min(m0 + 32 * b + r, row_end - 1)                         \
-                                          : min(n0 + 32 * (b - BM / 32) + r, a.N - 1);                \
-                sco[k] = (uint32_t)(g >> 5) * (uint32_t)Kg4 * 128u + (g & 31) * 4;                    \
-            }                                                                                         \
-            OSC_D2_SCALES(0, buf)                                                                     \
-        }                                                                                             \
-        OSC_D2_ANY(0, buf, 0, LA, 0, LB)                                                              \
-        if (MODE == MODE_MX8 && 1 < nTA) OSC_D2_SCALES(1, buf ^ 1)                                    \
-        OSC_D2_ANY(1, buf ^ 1, 0, LA, 0, LB)                                                          \
-    }
-
-    D2G_START(tp)
-    wait_vmcnt<0>();
-    __syncthreads();
-
-    v16f acc[TM][TN];
-    u32x4 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-    const int ra0 = wm * (TM * 32) + r, rb0 = BM + wn * (TN * 32) + r;
-
-#pragma unroll 1
-    for (;;) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int k = 0; k < 16; ++k) acc[i][j][k] = 0.0f;
-        const TilePos nxt = find_tile(v + (int)gridDim.x);
-        // stage 0: its operands and those of stage 1 are in LDS; stage number nT switches every request off
-        if (MODE == MODE_MX8) {
-            OSC_D2_STAGE_MX8_LEAN(nT)
-#pragma unroll 1
-            for (int T = 1; T < nT; ++T) OSC_D2_STAGE_MX8_LEAN(T)
-        } else {
-            OSC_D2_STAGE_FP8_LEAN(nT)
-#pragma unroll 1
-            for (int T = 1; T < nT; ++T) OSC_D2_STAGE_FP8_LEAN(T)
-        }
-        const TilePos ctp = tp;
-        if (nxt.valid) D2G_START(nxt)
-        __builtin_amdgcn_sched_barrier(0);
-        store_result<MODE, TM, TN, WN>(a, ctp, acc);
-        if (!nxt.valid) break;
-        tp = nxt;
-        v += (int)gridDim.x;
-        wait_vmcnt<0>();
-        __syncthreads();
-    }
-#undef D2G_START
-}
-
-
-
-// ------------------------------------------------------------------------------------------
 // Persistent pipelined kernel for one problem made of whole tiles (M % BM == 0,
 // N % BN == 0, no row map).  Same operands and LDS image as the DMA kernel above, but
 //  (1) the order of every instruction of a stage is pinned: a stage is a row of slots, one MFMA per
@@ -1395,8 +1216,7 @@ static int launch_pipe2(KArgs a, int64_t rows_total, bool grouped, hipStream_t s
     a.tiles_n = (int)((a.N + BN - 1) / BN);
     int64_t tiles_m = (rows_total + BM - 1) / BM;
     if (grouped) {  // upper bounds, whole rounds of the 8 XCDs
-        if (a.grp_mode == 2) tiles_m = (int64_t)a.E * ((a.grp_bm / 2 + BM - 1) / BM);  // less than half a main tile each
-        else tiles_m += a.E;                                                          // one ragged tile each
+        tiles_m += a.E;  // one ragged tile each
         tiles_m = (tiles_m + 7) / 8 * 8;
     }
     const int64_t ntiles = tiles_m * a.tiles_n;
@@ -2148,8 +1968,7 @@ static int launch_cfg(KArgs a, int64_t rows_total, bool grouped, hipStream_t st)
     a.tiles_n = (int)((a.N + BN - 1) / BN);
     int64_t tiles_m = (rows_total + BM - 1) / BM;
     if (grouped) {  // upper bounds, whole rounds of the 8 XCDs
-        if (a.grp_mode == 2) tiles_m = (int64_t)a.E * ((a.grp_bm / 2 + BM - 1) / BM);  // less than half a main tile each
-        else tiles_m += a.E;                                                          // one ragged tile each
+        tiles_m += a.E;  // one ragged tile each
         tiles_m = (tiles_m + 7) / 8 * 8;
     }
     const int64_t grid = tiles_m * a.tiles_n;
@@ -2172,8 +1991,7 @@ static int launch_dma2(KArgs a, int64_t rows_total, bool grouped, hipStream_t st
     a.tiles_n = (int)((a.N + BN - 1) / BN);
     int64_t tiles_m = (rows_total + BM - 1) / BM;
     if (grouped) {  // upper bounds, whole rounds of the 8 XCDs
-        if (a.grp_mode == 2) tiles_m = (int64_t)a.E * ((a.grp_bm / 2 + BM - 1) / BM);  // less than half a main tile each
-        else tiles_m += a.E;                                                          // one ragged tile each
+        tiles_m += a.E;  // one ragged tile each
         tiles_m = (tiles_m + 7) / 8 * 8;
     }
     const int64_t grid = tiles_m * a.tiles_n;
@@ -2187,34 +2005,6 @@ static int launch_dma2(KArgs a, int64_t rows_total, bool grouped, hipStream_t st
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem, st, a);
     return check_launch("gemm_dma2_kernel");
-}
-
-// persistent form of the DMA kernel for grouped problems (at most 1024 experts, at least two stages)
-template <int MODE, int TM, int TN, int WN>
-static int launch_dma2g(KArgs a, int64_t rows_total, hipStream_t st) {
-    constexpr int BM = 64 * TM, BN = 32 * TN * WN;
-    const size_t smem = (size_t)(BM + BN) * 128 * 2 + (size_t)(BM + BN) / 32 * 256 * 2;
-    a.tiles_n = (int)((a.N + BN - 1) / BN);
-    int64_t tiles_m = (rows_total + BM - 1) / BM;
-    if (a.grp_mode == 2) tiles_m = (int64_t)a.E * ((a.grp_bm / 2 + BM - 1) / BM);
-    else tiles_m += a.E;
-    tiles_m = (tiles_m + 7) / 8 * 8;
-    const int64_t ntiles = tiles_m * a.tiles_n;
-    if (ntiles <= 0) return OSC_OK;
-    if (ntiles > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "gemm: too many tiles");
-    const int ncu = cu_count();
-    if (ncu <= 0) return fail(OSC_ERR_HIP, "gemm: cannot read the number of compute units");
-    const int64_t cap = (int64_t)ncu / 8 * 8;  // whole rounds of the 8 XCDs
-    const int64_t grid = ntiles < cap ? ntiles : cap;
-    const size_t smem_all = smem + (size_t)(3 * a.E + 1) * 4;  // + the per-expert table
-    auto kern = gemm_dma2g_kernel<MODE, TM, TN, WN>;
-    {
-        static unsigned char lds_done[MAX_DEVICES];
-        static size_t lds_reserved[MAX_DEVICES];
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem_all, lds_done, lds_reserved)) return rc;
-    }
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem_all, st, a, (int)ntiles);
-    return check_launch("gemm_dma2g_kernel");
 }
 
 template <int MODE>
@@ -2260,8 +2050,6 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     a.y_bf16 = p.y_dtype == OSC_DT_BF16;
     a.ldy = p.ldy;
     a.tiles_n = 0;
-    a.grp_mode = 0;
-    a.grp_bm = 0;
     const bool grouped = p.expert_offsets != nullptr;
     const int64_t rowbytes = (MODE == MODE_DUAL) ? p.K / 2 : p.K;
     // the kernel addresses operand rows through 32-bit byte offsets (with a row_map the caller
@@ -2337,6 +2125,22 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
             }
         }
     }
+    // Experts: 128 x 256 tiles of the flowing kernel, which take an expert's rows in one launch, run its row tiles of a
+    // column strip side by side on one die (they share its weights) and skip the products of a last tile's empty half.
+    // Against 256-row tiles with a second launch for what overran them, or 64 x 128 tiles (us, 128 experts of 1536 x 2048
+    // and 2048 x 768, MXFP8): 256 rows an expert 117 -> 103 and 94 -> 79, 128 rows 85 -> 74 and 67 -> 56, 64 rows
+    // 64 -> 48 and 52 -> 39, 20 rows 43 -> 42 and 36.5 -> 34.  Few rows of few experts leave CUs without a tile or with
+    // two, where the 64 x 128 tiles, three to a CU, are up to 15 % ahead (64 experts of 1280 x 2048, 12 rows each: 19.6
+    // against 23.5; 85 rows each at four stages: 10.1 against 10.8), and so they are with few rows on one of many experts
+    // (1024 rows of one: 10.1 and 8.5 us against 13.4 and 10.0; from 2048 rows on, 12.0 and 11.2 against 13.8 and 10.5, only
+    // the first GEMM of a single expert is; 4096 rows of one 18.2 and 17.0 against 14.7 and 12.3).
+    if (lines && grouped && p.E > 0 && p.M >= 1 && flow_fits(MODE, 0, stages, true, p.E)) {
+        const int64_t least = p.E * ((p.N + 255) / 256);  // tiles if no expert has more than 128 rows
+        if (rows > 112 || (rows > 56 && stages >= 6) || (rows >= 12 && 2 * least >= 5 * ncu)) {
+            kind = 7;
+            flow_tile = 0;
+        }
+    }
     // The weight-streaming kernel (one workgroup per 32 output channels and 32 rows) wins for a few hundred rows as
     // long as its grid is resident at once (two workgroups per CU): a tiled launch of so few tiles leaves most CUs idle
     // (128 x 4096 x 4096: 11.8 us on 64 x 128 tiles, 6.8 us on 512 streaming workgroups), and for up to 64 rows until
@@ -2380,7 +2184,8 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         if (t_tile >= 0 && t_kern < 0 && (k2 == 3 || k2 == 6 || k2 == 7)) k2 = lines ? 1 : 0;  // a forced tile means a tiled kernel
         if (k2 == 7) {  // the tile knob names one of the flowing kernel's own
             if (t_tile >= 0) flow_tile = t_tile;
-            if (!lines || p.row_map || grouped || !flow_fits(MODE, flow_tile, stages, grouped, p.E)) k2 = lines ? 1 : 0;
+            if (grouped) flow_tile = 0;
+            if (!lines || (p.row_map && !grouped) || !flow_fits(MODE, flow_tile, stages, grouped, p.E)) k2 = lines ? 1 : 0;
         }
         if (k2 == 6 && !(grouped ? stream_grp : stream_ok)) k2 = lines ? 1 : 0;
         if ((k2 == 1 || k2 == 2) && !lines) k2 = 0;
@@ -2431,25 +2236,6 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         }
     }
 
-    if (kind >= 1 && grouped && tm == 4) {
-        // experts in 256-row tiles, and what is left of an expert whose last tile would be less than
-        // half full in 64-row tiles (an expert of 270 rows: one big tile and one small one, not two
-        // big ones)
-        a.grp_mode = 1;
-        int rc;
-        if constexpr (MODE != MODE_DUAL) {
-            // 8-bit modes: persistent workgroups (the OSC_TUNE_GROUPED_ONE_TILE override keeps one tile each)
-            const bool persistent = p.E >= 1 && p.E <= 1024 && !p.row_map && rowbytes / 128 >= 2 &&
-                                    tuning(TUNE_GROUPED_ONE_TILE) != 1;
-            rc = persistent ? launch_dma2g<MODE, 4, 2, 4>(a, p.M, st) : launch_dma2<MODE, 4, 2, 4>(a, p.M, grouped, st);
-        } else {
-            rc = launch_dma2<MODE, 4, 2, 4>(a, p.M, grouped, st);
-        }
-        if (rc != OSC_OK) return rc;
-        a.grp_mode = 2;
-        a.grp_bm = 256;
-        return launch_dma2<MODE, 1, 2>(a, p.M, grouped, st);
-    }
     if (kind >= 1) {
         // 256-row tiles run on eight wavefronts (2 x 4, 128x64 each): 6-8 % faster than four, the second
         // wavefront of a SIMD fills the issue gaps of the first

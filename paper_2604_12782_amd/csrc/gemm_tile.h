@@ -35,10 +35,6 @@ struct KArgs {
     int y_bf16;
     int64_t ldy;
     int tiles_n;
-    // grouped problems, which rows of an expert this launch covers: 0 = all of them; 1 = its first
-    // (n + BM/2) / BM tiles (an expert whose last tile would be less than half full leaves those rows
-    // out); 2 = the rows that a mode-1 launch with tiles of grp_bm rows left out
-    int grp_mode, grp_bm;
 };
 
 
@@ -91,15 +87,8 @@ __device__ __forceinline__ TilePos tile_at(const KArgs& a, int tile) {
         int before = 0, e_found = -1, j_in = 0;
         for (int e0 = 0; e0 < a.E; e0 += 64) {
             const int e = e0 + lane;
-            int b = e < a.E ? a.off[e] : 0;
-            int n = e < a.E ? a.off[e + 1] - b : 0;
-            if (a.grp_mode == 1) {
-                n = min(n, (n + BM / 2) / BM * BM);
-            } else if (a.grp_mode == 2) {
-                const int skip = min(n, (n + a.grp_bm / 2) / a.grp_bm * a.grp_bm);
-                b += skip;
-                n -= skip;
-            }
+            const int b = e < a.E ? a.off[e] : 0;
+            const int n = e < a.E ? a.off[e + 1] - b : 0;
             const int te = (n + BM - 1) / BM;
             int ps = te;
 #pragma unroll

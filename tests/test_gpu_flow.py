@@ -105,3 +105,51 @@ def test_launcher_choice_agrees(osc, tuning):
         tuning.gemm("1,1")
         Y0 = call(osc.OSC_DT_F32)
         assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max()), (mode, M, N, K, r)
+
+
+SIZES = [0, 1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 256, 257, 385, 700, 0, 130, 0]
+
+
+@pytest.mark.parametrize("N", [264, 5000])
+def test_flow_experts(osc, tuning, N):
+    """Experts of every size around the tile's borders and the half tile that is skipped, empty ones at the ends: fewer tiles than CUs
+    against the oracle; several per workgroup against the DMA kernel.  Rows beyond the offsets stay untouched."""
+    E, K, K2, r, tokens = len(SIZES), 1024, 512, 2, 700
+    off = np.concatenate([[0], np.cumsum(SIZES)]).astype(np.int32)
+    T = int(off[-1])
+    X, table = wl.activations_persistent(7900, tokens, K, r)
+    oidx = oracle.table_to_index(table)
+    row_map = wl.rng(7901).integers(0, tokens, T).astype(np.int32)
+    X2 = wl.activations_diffuse(7902, T, K2)
+    q = osc.osc_quantize_act(dev(X), dev(oidx))
+    q8, qm = osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_FP8_E4M3_TOKEN), osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_MXFP8)
+    W, W2 = [wl.weights(7910 + e, N, K) for e in range(E)], [wl.weights(7950 + e, N, K2) for e in range(E)]
+    Wp = torch.cat([osc.osc_pack_weight(dev(w), dev(oidx)) for w in W])
+    Wp8, Wpm = torch.cat([osc.osc_pack_weight_fp8(dev(w)) for w in W2]), torch.cat([osc.osc_pack_weight_mxfp8(dev(w)) for w in W2])
+    d_off = dev(off)
+    calls = {"dual": lambda ydt, out=None: osc.osc_grouped_dual_gemm(*q, dev(row_map), d_off, T, Wp, N, K, len(oidx), ydt, out=out),
+             "fp8": lambda ydt, out=None: osc.osc_fp8_gemm(*q8, Wp8, N, K2, expert_offsets=d_off, y_dtype=ydt, out=out),
+             "mx8": lambda ydt, out=None: osc.osc_mxfp8_gemm(*qm, Wpm, N, K2, expert_offsets=d_off, y_dtype=ydt, out=out)}
+    refs = {}
+    if N < 1000:
+        a = oracle.quantize_mxfp4_osc(X, oidx, ldb=q[2].shape[1])
+        w = [oracle.quantize_mxfp4_osc(x)[:2] for x in W]
+        refs["dual"] = oracle.grouped_dual_gemm(a[0], a[1], a[2], row_map, off, np.stack([x[0] for x in w]), np.stack([x[1] for x in w]),
+                                                np.stack([oracle.gather_wl(x, oidx) for x in W]))
+        w = [oracle.quantize_fp8_rows(x) for x in W2]
+        refs["fp8"] = oracle.grouped_fp8_gemm(*oracle.quantize_fp8_rows(X2), off, np.stack([x[0] for x in w]), np.stack([x[1] for x in w]))
+    for name, call in calls.items():
+        tuning.gemm("0,7")
+        Y, Yb = call(osc.OSC_DT_F32), call(osc.OSC_DT_BF16)
+        tuning.gemm("1,1")
+        Y0 = call(osc.OSC_DT_F32)
+        assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max()), name
+        assert torch.equal(Yb, Y.to(torch.bfloat16)), name
+        if name in refs:
+            assert np.abs(Y.cpu().numpy().astype(np.float64) - refs[name]).max() <= TOL * np.abs(refs[name]).max(), name
+    # offsets that end before the output does
+    tuning.gemm("0,7")
+    short = torch.from_numpy(np.minimum(off, 500)).cuda()
+    out = torch.full((T, N), 7.0, dtype=torch.bfloat16, device="cuda")
+    osc.osc_fp8_gemm(*q8, Wp8, N, K2, expert_offsets=short, y_dtype=osc.OSC_DT_BF16, out=out)
+    assert bool((out[500:] == 7).all()) and not bool((out[:500] == 7).all())
