@@ -18,9 +18,11 @@ namespace osc {
 
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int QT16 = 256;
 
@@ -157,24 +159,7 @@ int launch_quant_fp4_g16(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, c
     return check_launch("quant_fp4_g16_kernel");
 }
 
-// ------------------------------------------------------------------------------------------
-// Streaming GEMM.  One workgroup per 32 output channels and 32 rows of X; its wavefronts take the
-// 128-byte lines of the reduction axis in turn (256 four-bit channels = 16 scale blocks per row and
-// line, then the bf16 lines of the branch) and never synchronise until the end.  A wavefront moves
-// a line global -> LDS by DMA into a strip of its own (codes in whole 128-byte lines, the 16 scale
-// bytes of every row beside them), expands it in registers and multiplies.
-// K order inside a line: the bf16 matrix core pairs lane half q of one operand with lane half q of
-// the other, nothing else, so a lane takes the 16 contiguous bytes [32j + 16q, +16) of its row for
-// the four MFMAs 4j .. 4j+3 (dword t feeds MFMA 4j+t); those 32 channels are scale blocks 4j+2q and
-// 4j+2q+1, applied during the expansion.
-// ------------------------------------------------------------------------------------------
-template <int FMT>
-__device__ __forceinline__ float scale16_f32(uint32_t byte) {
-    if (FMT == 0) return __builtin_bit_cast(float, byte ? byte << 23 : 0x00400000u);  // 2^(byte - 127)
-    return __builtin_amdgcn_cvt_f32_fp8((int)byte, 0);
-}
-// Expansion of 16 bytes of codes (32 channels, scale blocks s0 | s1) into four operand registers
-// sets of 8 values each, the block scale folded in.
+// A dword of codes (8 channels of one scale block) as a matrix-core operand, the block scale folded in.
 //   format 0: the conversion instruction multiplies by a power of two (it takes only the exponent of
 //             its scale operand, which is all an E8M0 scale has): E2M1 x 2^e, exact in bf16.
 //   format 1: an E4M3 scale has a mantissa, so the codes become fp16 (exact) and are multiplied by the
@@ -184,35 +169,38 @@ __device__ __forceinline__ float scale16_f32(uint32_t byte) {
 typedef _Float16 v2h __attribute__((ext_vector_type(2)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 template <int FMT>
-struct Operand;
+struct Scales16;
 template <>
-struct Operand<0> {
-    typedef v8bf type;
-};
-template <>
-struct Operand<1> {
-    typedef v8h type;
-};
-template <int FMT>
-__device__ __forceinline__ void expand32(const u32x4 c, uint32_t sbytes, typename Operand<FMT>::type (&out)[4]) {
-    const float s0 = scale16_f32<FMT>(sbytes & 0xffu), s1 = scale16_f32<FMT>((sbytes >> 8) & 0xffu);
-    const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+struct Scales16<0> {
+    typedef v8bf operand;
+    float s[4];
+    // the four scale bytes of a lane; a zero byte is 2^-127
+    __device__ __forceinline__ explicit Scales16(uint32_t w) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        const float s = t < 2 ? s0 : s1;
-        if constexpr (FMT == 0) {
-            const v2bf p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[t], s, 0), p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[t], s, 1),
-                       p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[t], s, 2), p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w[t], s, 3);
-            out[t] = (v8bf){p0.x, p0.y, p1.x, p1.y, p2.x, p2.y, p3.x, p3.y};
-        } else {
-            const _Float16 sh = (_Float16)s;  // exact: every E4M3 value is an fp16 value
-            const v2h ss = {sh, sh};
-            const v2h p0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w[t], 1.0f, 0) * ss, p1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w[t], 1.0f, 1) * ss,
-                      p2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w[t], 1.0f, 2) * ss, p3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w[t], 1.0f, 3) * ss;
-            out[t] = (v8h){p0.x, p0.y, p1.x, p1.y, p2.x, p2.y, p3.x, p3.y};
-        }
+        for (int b = 0; b < 4; ++b) s[b] = __builtin_bit_cast(float, max(((w >> (8 * b)) & 0xffu) << 23, 0x00400000u));
     }
-}
+    __device__ __forceinline__ operand expand(uint32_t w, int b) const {
+        const v2bf p0 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, s[b], 0), p1 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, s[b], 1),
+                   p2 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, s[b], 2), p3 = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(w, s[b], 3);
+        return (v8bf){p0.x, p0.y, p1.x, p1.y, p2.x, p2.y, p3.x, p3.y};
+    }
+};
+template <>
+struct Scales16<1> {
+    typedef v8h operand;
+    v2h s[2];  // exact: every E4M3 value is an fp16 value
+    __device__ __forceinline__ explicit Scales16(uint32_t w) {
+        s[0] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w, 1.0f, false);
+        s[1] = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(w, 1.0f, true);
+    }
+    __device__ __forceinline__ operand expand(uint32_t w, int b) const {
+        const _Float16 sh = s[b >> 1][b & 1];
+        const v2h ss = {sh, sh};
+        const v2h p0 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 0) * ss, p1 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 1) * ss,
+                  p2 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 2) * ss, p3 = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(w, 1.0f, 3) * ss;
+        return (v8h){p0.x, p0.y, p1.x, p1.y, p2.x, p2.y, p3.x, p3.y};
+    }
+};
 
 struct G16Args {
     const uint8_t* Xq;
@@ -230,8 +218,248 @@ struct G16Args {
     int64_t ldy;
 };
 
-template <int FMT, int NW>
+// ------------------------------------------------------------------------------------------
+// Streaming GEMM, up to 16 rows (32 where that leaves CUs idle).  A workgroup owns 16 rows of X and 16 NT output
+// channels; its NW wavefronts take the 128-byte lines of the reduction axis (256 four-bit channels = 16 scale blocks
+// per row and line, then the bf16 lines of the branch) in turn and never synchronise until the end.  A wavefront loads
+// the next line (eight lanes per row) into one of two register sets while it takes the current one through a strip of
+// LDS of its own into matrix-core layout, expands it in registers and multiplies.
+// Layout of v_mfma_f32_16x16x32_{f16,bf16} (lane = 16 q + r): row r, eight elements of block q; which elements is free
+// as long as both operands agree.  A lane takes pieces 2q and 2q + 1 of its row's line, 64 codes in eight dwords: dword
+// m feeds instruction m, and its scale block is 4q + m / 2, byte m / 2 of the word that the lane loads for its row.
+// What bounds it: the vector work of the expansion, a conversion per two values and in NVFP4 a product per two as well,
+// 32 (64) instructions per 16 rows or channels and line.  32 rows of X per 32 channels, 16 of them copies at up to 16
+// tokens, made that twice what it has to be, on 384 workgroups for 256 CUs; 16 rows and 48 channels are half of it and
+// one workgroup per CU at N = 12288.  16 tokens, weights from HBM, us, wide kernel below -> this one:
+//   12288 x 4096  NVFP4 13.1 -> 8.8, E8M0 11.4 -> 8.5      4096 x 12288  15.2 -> 9.9, 13.9 -> 9.7      4096 x 4096  6.9 -> 4.9, 6.1 -> 4.8
+// and 32 tokens: 4096 x 4096  7.4 -> 6.1, 6.7 -> 5.9; but 12288 x 4096 from the last-level cache 11.8 -> 12.5 and 9.9 -> 11.8,
+// and 33 to 128 tokens in tiles of 32 or 64 rows 1.0 to 1.3 times slower: these stay on the wide kernel.
+// ------------------------------------------------------------------------------------------
+template <int FMT, int NT, int NW>
 __global__ void __launch_bounds__(64 * NW) gemm_g16_kernel(G16Args a) {
+    constexpr int MT = 1;  // 16-row tiles of X
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int q = lane >> 4, r = lane & 15;
+    const int n0 = blockIdx.x * (16 * NT), m0 = blockIdx.y * (16 * MT);
+    const uint32_t rowbytes = (uint32_t)a.K >> 1, srow = (uint32_t)a.K >> 4;
+    const int nL = (int)(rowbytes >> 7);
+    const int nLT = nL + ((a.K_o * 2 + 127) >> 7);
+    // instruction h of a 16-row tile loads rows 8h .. 8h+7, eight lanes per line
+    const int lrow = lane >> 3;
+    const uint32_t p0 = (uint32_t)(lane & 7) * 16u;
+    uint32_t ow[NT][2], owb[NT][2], osw[NT], ox[MT][2], oxb[MT][2], osx[MT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t n = (uint32_t)min(n0 + 16 * j + 8 * h + lrow, a.N - 1);
+            ow[j][h] = n * rowbytes + p0;
+            owb[j][h] = n * (uint32_t)a.wlpitch + p0;
+        }
+        osw[j] = (uint32_t)min(n0 + 16 * j + r, a.N - 1) * srow + 4u * q;
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t g = (uint32_t)min(m0 + 16 * i + 8 * h + lrow, a.M - 1);
+            ox[i][h] = g * rowbytes + p0;
+            oxb[i][h] = g * (uint32_t)a.bpitch + p0;
+        }
+        osx[i] = (uint32_t)min(m0 + 16 * i + r, a.M - 1) * srow + 4u * q;
+    }
+    // one line of the workgroup's rows per wavefront (weights, then X); later the partial sums
+    constexpr int STRIP = 16 * (NT + MT) * 128;
+    __shared__ __attribute__((aligned(16))) uint8_t lds_s[NW * (STRIP > MT * NT * 1024 ? STRIP : MT * NT * 1024)];
+    uint8_t* const strip = lds_s + wave * STRIP;
+    float* const red = reinterpret_cast<float*>(lds_s);
+    uint32_t wpos[2], rpos[2];  // places in a 16-row tile: written (instruction h), read (piece 2q + h)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        wpos[h] = (uint32_t)st128_off(8 * h + lrow, lane & 7);
+        rpos[h] = (uint32_t)st128_off(r, 2 * q + h);
+    }
+    struct Line {
+        u32x4 w[NT][2], x[MT][2];
+        uint32_t sw[NT], sx[MT];
+    };
+    v4f acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] = (v4f){0.0f, 0.0f, 0.0f, 0.0f};
+    bool scaled = FMT == 0;  // the tensor scales go on once, before the first branch line
+
+    // line L into S (a branch line fetches the last scale words again, unused)
+    auto load = [&](int L, Line& S) __attribute__((always_inline)) {
+        const bool main = L < nL;
+        const uint32_t lo = (uint32_t)(main ? L : L - nL) * 128u, ls = (uint32_t)min(L, nL - 1) * 16u;
+        const uint8_t *const wb = (main ? a.Wq : a.WL) + lo, *const xb = (main ? a.Xq : a.B) + lo;
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                S.w[j][h] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(wb + (main ? ow[j][h] : owb[j][h])));
+            S.sw[j] = *reinterpret_cast<const uint32_t*>(a.Ws + (osw[j] + ls));
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) S.x[i][h] = *reinterpret_cast<const u32x4*>(xb + (main ? ox[i][h] : oxb[i][h]));
+            S.sx[i] = *reinterpret_cast<const uint32_t*>(a.Xs + (osx[i] + ls));
+        }
+    };
+    auto compute = [&](int L, const Line& S) __attribute__((always_inline)) {
+        // through the wavefront's strip into matrix-core layout (LDS runs a wavefront's operations in order)
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int j = 0; j < NT; ++j) *reinterpret_cast<u32x4*>(strip + j * 2048 + wpos[h]) = S.w[j][h];
+#pragma unroll
+            for (int i = 0; i < MT; ++i) *reinterpret_cast<u32x4*>(strip + (NT + i) * 2048 + wpos[h]) = S.x[i][h];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (L < nL) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                u32x4 cw[NT], cx[MT];
+#pragma unroll
+                for (int j = 0; j < NT; ++j) cw[j] = *reinterpret_cast<const u32x4*>(strip + j * 2048 + rpos[h]);
+#pragma unroll
+                for (int i = 0; i < MT; ++i) cx[i] = *reinterpret_cast<const u32x4*>(strip + (NT + i) * 2048 + rpos[h]);
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    typename Scales16<FMT>::operand fx[MT];
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) fx[i] = Scales16<FMT>(S.sx[i]).expand(cx[i][m], 2 * h + m / 2);
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) {
+                        const typename Scales16<FMT>::operand fw = Scales16<FMT>(S.sw[j]).expand(cw[j][m], 2 * h + m / 2);
+#pragma unroll
+                        for (int i = 0; i < MT; ++i) {
+                            if constexpr (FMT == 0) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fx[i], fw, acc[i][j], 0, 0, 0);
+                            else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fx[i], fw, acc[i][j], 0, 0, 0);
+                        }
+                    }
+                }
+            }
+        } else {
+            if (!scaled) {
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) acc[i][j] *= a.ts;
+                scaled = true;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    const u32x4 fw = *reinterpret_cast<const u32x4*>(strip + j * 2048 + rpos[h]);
+#pragma unroll
+                    for (int i = 0; i < MT; ++i) {
+                        const u32x4 fx = *reinterpret_cast<const u32x4*>(strip + (NT + i) * 2048 + rpos[h]);
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, fx), __builtin_bit_cast(v8bf, fw), acc[i][j], 0, 0, 0);
+                    }
+                }
+        }
+    };
+    if (wave < nLT) {
+        // two sets written out in turn: a copy from one to the other would wait for the loads in flight
+        Line sa, sb;
+        int L = wave;
+        load(L, sa);
+#pragma unroll 1
+        for (; L + 2 * NW < nLT; L += 2 * NW) {
+            load(L + NW, sb);
+            compute(L, sa);
+            load(L + 2 * NW, sa);
+            compute(L + NW, sb);
+        }
+        if (L + NW < nLT) {
+            load(L + NW, sb);
+            compute(L, sa);
+            compute(L + NW, sb);
+        } else {
+            compute(L, sa);
+        }
+    }
+    if (!scaled) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] *= a.ts;
+    }
+    // ---- sum the NW partial results in a fixed order, store ----
+    __syncthreads();  // every wavefront is done with its strip
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) red[((wave * MT * NT + i * NT + j) * 4 + k) * 64 + lane] = acc[i][j][k];
+    __syncthreads();
+    for (int u = t; u < MT * NT * 256; u += 64 * NW) {
+        const int l = u & 63, k = (u >> 6) & 3, ij = u >> 8;
+        const int row = m0 + 16 * (ij / NT) + 4 * (l >> 4) + k, col = n0 + 16 * (ij % NT) + (l & 15);
+        if (row >= a.M || col >= a.N) continue;
+        float v = red[u];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += red[w * MT * NT * 256 + u];
+        if (a.y_bf16) reinterpret_cast<uint16_t*>(a.Y)[(int64_t)row * a.ldy + col] = f32_to_bf16_rne(v);
+        else reinterpret_cast<float*>(a.Y)[(int64_t)row * a.ldy + col] = v;
+    }
+}
+
+template <int FMT, int NT, int NW>
+static int launch_g16(const G16Args& a, hipStream_t st) {
+    const dim3 grid((unsigned)((a.N + 16 * NT - 1) / (16 * NT)), (unsigned)((a.M + 15) / 16));
+    hipLaunchKernelGGL((gemm_g16_kernel<FMT, NT, NW>), grid, dim3(64 * NW), 0, st, a);
+    return check_launch("gemm_g16_kernel");
+}
+
+// Channels / 16 of a workgroup: the smallest ceil(workgroups / CUs) x (1 + NT), the smaller one among equals (a launch
+// lasts as long as the CU with the most workgroups, a workgroup as long as its expansion takes).  0: more than 16 rows
+// that would give a CU more than one workgroup, where the wide kernel is ahead.
+static int g16_rows16_tile(int64_t M, int64_t N, int ncu) {
+    int best = 1;
+    int64_t best_cost = INT64_MAX, best_per = 0;
+    for (int nt = 1; nt <= 4; ++nt) {
+        const int64_t wgs = (N + 16 * nt - 1) / (16 * nt) * ((M + 15) / 16), per = (wgs + ncu - 1) / ncu, cost = per * (1 + nt);
+        if (cost < best_cost) {
+            best_cost = cost;
+            best_per = per;
+            best = nt;
+        }
+    }
+    return M <= 16 || (M <= 32 && best_per == 1) ? best : 0;
+}
+
+template <int FMT>
+static int launch_g16_rows16(const G16Args& a, int nt, hipStream_t st) {
+    switch (nt) {
+        case 1: return launch_g16<FMT, 1, 8>(a, st);
+        case 2: return launch_g16<FMT, 2, 8>(a, st);
+        case 3: return launch_g16<FMT, 3, 8>(a, st);
+        default: return launch_g16<FMT, 4, 8>(a, st);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// Wide form, more rows: one workgroup per 32 output channels and 32 rows of X; its wavefronts take the
+// 128-byte lines in turn.  A wavefront moves a line global -> LDS by DMA into a strip of its own (codes in whole
+// 128-byte lines, the 16 scale bytes of every row beside them), expands it in registers and multiplies.
+// K order inside a line: the bf16 matrix core pairs lane half q of one operand with lane half q of
+// the other, nothing else, so a lane takes the 16 contiguous bytes [32j + 16q, +16) of its row for
+// the four MFMAs 4j .. 4j+3 (dword t feeds MFMA 4j+t); those 32 channels are scale blocks 4j+2q and
+// 4j+2q+1, applied during the expansion.
+// ------------------------------------------------------------------------------------------
+template <int FMT, int NW>
+__global__ void __launch_bounds__(64 * NW) gemm_g16_wide_kernel(G16Args a) {
     constexpr int IMG = 64 * 128 + 64 * 16;  // codes of 32 weight rows and 32 X rows, then their scale bytes
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -291,13 +519,12 @@ __global__ void __launch_bounds__(64 * NW) gemm_g16_kernel(G16Args a) {
             for (int j = 0; j < 4; ++j) {
                 const u32x4 cw = *reinterpret_cast<const u32x4*>(src + st128_off(r, 2 * j + q));
                 const u32x4 cx = *reinterpret_cast<const u32x4*>(src + st128_off(32 + r, 2 * j + q));
-                typename Operand<FMT>::type fw[4], fx[4];
-                expand32<FMT>(cw, swv[j] >> (16 * q), fw);
-                expand32<FMT>(cx, sxv[j] >> (16 * q), fx);
+                const Scales16<FMT> bw(swv[j] >> (16 * q)), bx(sxv[j] >> (16 * q));
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    if constexpr (FMT == 0) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[k], fw[k], acc, 0, 0, 0);
-                    else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fx[k], fw[k], acc, 0, 0, 0);
+                    const typename Scales16<FMT>::operand fx = bx.expand(cx[k], k >> 1), fw = bw.expand(cw[k], k >> 1);
+                    if constexpr (FMT == 0) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx, fw, acc, 0, 0, 0);
+                    else acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(fx, fw, acc, 0, 0, 0);
                 }
             }
         } else {
@@ -366,16 +593,17 @@ int launch_dual_gemm_g16(const uint8_t* Xq, const uint8_t* Xs, float xts, const 
     const int64_t lim = (int64_t)1 << 32;
     if (M * (K / 2) >= lim || N * (K / 2) >= lim || M * a.bpitch >= lim || N * a.wlpitch >= lim)
         return fail(OSC_ERR_UNSUPPORTED, "gemm: an operand of 4 GiB or more");
-    const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((M + 31) / 32));
     const int ncu = cu_count();
     if (ncu <= 0) return fail(OSC_ERR_HIP, "gemm: cannot read the number of compute units");
+    if (const int nt = g16_rows16_tile(M, N, ncu)) return fmt == 0 ? launch_g16_rows16<0>(a, nt, st) : launch_g16_rows16<1>(a, nt, st);
+    const dim3 grid((unsigned)((N + 31) / 32), (unsigned)((M + 31) / 32));
     constexpr int IMG = 64 * 128 + 64 * 16;
     // eight wavefronts when the grid leaves CUs idle, four otherwise (two workgroups per CU)
     const bool wide = (int64_t)grid.x * grid.y <= ncu;
     const size_t smem = (size_t)(wide ? 8 : 4) * 2 * IMG;
 #define G16_LAUNCH(F_, NW_)                                                                               \
     {                                                                                                     \
-        auto kern = gemm_g16_kernel<F_, NW_>;                                                             \
+        auto kern = gemm_g16_wide_kernel<F_, NW_>;                                                             \
         static unsigned char lds_done[MAX_DEVICES];                                                       \
         static size_t lds_reserved[MAX_DEVICES];                                                          \
         if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc; \
@@ -387,7 +615,7 @@ int launch_dual_gemm_g16(const uint8_t* Xq, const uint8_t* Xs, float xts, const 
         if (wide) G16_LAUNCH(1, 8) else G16_LAUNCH(1, 4)
     }
 #undef G16_LAUNCH
-    return check_launch("gemm_g16_kernel");
+    return check_launch("gemm_g16_wide_kernel");
 }
 
 }  // namespace osc

@@ -768,7 +768,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
                   SCL = BLKSC ? NBLK * 256 : (BM + BN) * 4;
     static_assert(BLKSC || (BM + BN) % (64 * NWV) == 0, "tile scales do not split over the wavefronts");
     static_assert(BM % RPP == 0 && BN % RPP == 0 && NBLK % NWV == 0, "tile does not split over the wavefronts");
-    constexpr int NT = TM * TN, NSLOT = 4 * NT, NRD = 2 * (TM + TN), NLD = NSB + LA + LB;
+    constexpr int NT = TM * TN, NSLOT = 4 * NT, NLD = NSB + LA + LB;
     // Three register sets: X holds piece 2q, then 4+2q, then piece 2q of the next stage; Y holds piece
     // 2q+1; Z holds piece 4+2q+1.  Reads: Z in group 0, X again in group 1 (after group 0 consumed
     // it), and X, Y of the next stage in group 3.
