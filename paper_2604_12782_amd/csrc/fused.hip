@@ -45,6 +45,30 @@ __device__ __forceinline__ void sq_add(double& acc, uint32_t fbits) {
     asm volatile("v_fma_f64 %0, %1, %1, %0" : "+v"(acc) : "v"(x));
 }
 
+// Scale code and E2M1 codes of chunk c (eight normalised channels, y: pairs of bf16) of a row; four neighbouring lanes hold
+// a 32-channel group, sixteen the four scale bytes of one word.
+__device__ __forceinline__ void quant_chunk(const uint32_t (&y)[4], int lane, int c, bool valid, uint32_t* __restrict__ dst,
+                                            uint8_t* __restrict__ sdst) {
+    const uint32_t a2 = max_pair(max_pair(y[0] & 0x7fff7fffu, y[1] & 0x7fff7fffu),
+                                 max_pair(y[2] & 0x7fff7fffu, y[3] & 0x7fff7fffu));
+    uint32_t a = max(a2 & 0xffffu, a2 >> 16);
+    a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0xB1, 0xF, 0xF, true));
+    a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x4E, 0xF, 0xF, true));
+    const uint32_t code = (uint32_t)max((int)(a >> 7) - 2, 0);
+    uint32_t word = code;
+    word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x104, 0xF, 0xF, true) << 8;
+    word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x108, 0xF, 0xF, true) << 16;
+    word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x10C, 0xF, 0xF, true) << 24;
+    if ((lane & 15) == 0 && valid) *reinterpret_cast<uint32_t*>(sdst + (c >> 4) * 128) = word;
+    const float scale = __builtin_bit_cast(float, code << 23);
+    uint32_t out = 0;
+    out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, y[0]), scale, 0);
+    out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, y[1]), scale, 1);
+    out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, y[2]), scale, 2);
+    out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, y[3]), scale, 3);
+    if (valid) __builtin_nontemporal_store(out, dst + c);
+}
+
 // A wavefront owns a whole row: lane l holds the 16-byte chunks l, l + 64, ... (NCI of them), so
 // the two row-wide reductions (largest exponent, sum of squares) are register work plus DPP.
 // The sum of squares is an integer in fixed point relative to the row's largest exponent: exact
@@ -129,24 +153,7 @@ __global__ void __launch_bounds__(FT) rmsnorm_quant_mxfp4_kernel(
                     y[0] &= kp.x, y[1] &= kp.y, y[2] &= kp.z, y[3] &= kp.w;  // zero (step 3)
                 }
             }
-            const uint32_t a2 = max_pair(max_pair(y[0] & 0x7fff7fffu, y[1] & 0x7fff7fffu),
-                                         max_pair(y[2] & 0x7fff7fffu, y[3] & 0x7fff7fffu));
-            uint32_t a = max(a2 & 0xffffu, a2 >> 16);
-            a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0xB1, 0xF, 0xF, true));
-            a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x4E, 0xF, 0xF, true));
-            const uint32_t code = (uint32_t)max((int)(a >> 7) - 2, 0);
-            uint32_t word = code;
-            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x104, 0xF, 0xF, true) << 8;
-            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x108, 0xF, 0xF, true) << 16;
-            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x10C, 0xF, 0xF, true) << 24;
-            if ((lane & 15) == 0 && (FULL || c < nchunk)) *reinterpret_cast<uint32_t*>(sdst + (c >> 4) * 128) = word;
-            const float scale = __builtin_bit_cast(float, code << 23);
-            uint32_t out = 0;
-            out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, y[0]), scale, 0);
-            out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, y[1]), scale, 1);
-            out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, y[2]), scale, 2);
-            out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, y[3]), scale, 3);
-            if ((FULL || c < nchunk)) __builtin_nontemporal_store(out, dst + c);
+            quant_chunk(y, lane, c, FULL || c < nchunk, dst, sdst);
         }
         if (B) {
             uint16_t* brow = B + (int64_t)m * ldb;
@@ -165,11 +172,126 @@ __global__ void __launch_bounds__(FT) rmsnorm_quant_mxfp4_kernel(
     }
 }
 
+// The same for few rows: a workgroup of four wavefronts owns a row, thread t the chunks t, t + 256, ... (NCH of them).  One
+// wavefront per row leaves most SIMDs empty below a few thousand rows and is then a chain of 1100 vector instructions;
+// here it is 300, with three more barriers (largest exponent, sum, the row for the gather).  The sum of squares is an
+// integer that does not depend on how it is split, so the results are the same bits.  us, a
+// wavefront per row -> a workgroup per row (calls in a row; 4.3 is the host's rate):
+//   K = 4096   16 rows 5.7 -> 4.5   100: 6.0 -> 4.4   500: 6.7 -> 5.1   1000: 7.1 -> 6.5   2000: 9.0 -> 9.6   8192: 22 -> 27
+//   K = 12288  16 rows 13.3 -> 7.2  100: 14.1 -> 8.5  500: 14.9 -> 10.5 1000: 16.4 -> 19.7
+template <int NCH>
+__global__ void __launch_bounds__(FT) rmsnorm_quant_mxfp4_row_kernel(
+    const uint16_t* __restrict__ X, const uint16_t* __restrict__ gamma, double eps, int K, int64_t ldx,
+    const int32_t* __restrict__ oidx, int K_o, uint8_t* __restrict__ Xq, uint8_t* __restrict__ Xs,
+    uint16_t* __restrict__ B, int64_t ldb, uint16_t* __restrict__ Xn) {
+    extern __shared__ uint32_t smem[];
+    __shared__ uint32_t top[4];
+    __shared__ uint64_t sums[4];
+    const int Kg4 = ((K >> 5) + 3) >> 2, nchunk = K >> 3, m = blockIdx.x;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    u32x4* const strip = reinterpret_cast<u32x4*>(smem);  // the normalised row
+    uint32_t* const keep = smem + NCH * 256 * 4;
+    const u32x4* const src = reinterpret_cast<const u32x4*>(X + (int64_t)m * ldx);
+    u32x4 v[NCH], g[NCH];
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int c = t + 256 * i;
+        v[i] = g[i] = (u32x4){0u, 0u, 0u, 0u};
+        if (c < nchunk) {
+            v[i] = __builtin_nontemporal_load(src + c);
+            g[i] = reinterpret_cast<const u32x4*>(gamma)[c];
+        }
+    }
+    int och = t < K_o ? oidx[t] : -1;
+    if (K_o > 0) {
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) *reinterpret_cast<u32x4*>(keep + 4 * (t + 256 * i)) = (u32x4){~0u, ~0u, ~0u, ~0u};
+    }
+    uint32_t am2 = 0;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const u32x4 ab = v[i] & 0x7fff7fffu;
+        am2 = max_pair(am2, max_pair(max_pair(ab.x, ab.y), max_pair(ab.z, ab.w)));
+    }
+    const uint32_t wtop = wave_max_u32(max(am2 & 0xffffu, am2 >> 16));
+    if (lane == 0) top[wave] = wtop;
+    __syncthreads();
+    for (int o = t; o < K_o; o += FT) {
+        if (o != t) och = oidx[o];
+        if (och >= 0 && och < K) atomicAnd(&keep[och >> 1], (och & 1) ? 0x0000ffffu : 0xffff0000u);
+    }
+    const int e = max(1, (int)(max(max(top[0], top[1]), max(top[2], top[3])) >> 7));
+    const double base = __builtin_bit_cast(double, (uint64_t)(1023 + 52 + 2 * e - 296) << 52);
+    double s0 = base, s1 = base;
+    f64_round_mode<F64_ROUND_TOWARD_ZERO>(s0, s1);
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            sq_add(s0, w[k] << 16);
+            sq_add(s1, w[k] & 0xffff0000u);
+        }
+    }
+    f64_round_mode<F64_ROUND_NEAREST>(s0, s1);
+    const double units = ((s0 - base) + (s1 - base)) * __builtin_bit_cast(double, (uint64_t)(1023 + 296 - 2 * e) << 52);
+    const uint64_t wsum = wave_sum_u64((uint64_t)units);
+    if (lane == 0) sums[wave] = wsum;
+    __syncthreads();  // sums and keep masks
+    const uint64_t S = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+    const double mean = ldexp((double)S, 2 * e - 296) / (double)K;
+    const float r = (float)(1.0 / sqrt(mean + eps));
+
+    uint32_t* const dst = reinterpret_cast<uint32_t*>(Xq + (int64_t)m * (K >> 1));
+    uint8_t* const sdst = Xs + (int64_t)(m >> 5) * Kg4 * 128 + (m & 31) * 4;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int c = t + 256 * i;
+        uint32_t y[4] = {mul_pair(scale_pair(v[i].x, r), g[i].x), mul_pair(scale_pair(v[i].y, r), g[i].y),
+                         mul_pair(scale_pair(v[i].z, r), g[i].z), mul_pair(scale_pair(v[i].w, r), g[i].w)};
+        const u32x4 yv = {y[0], y[1], y[2], y[3]};
+        if (Xn && c < nchunk) __builtin_nontemporal_store(yv, reinterpret_cast<u32x4*>(Xn + (int64_t)m * K) + c);
+        if (K_o > 0) {
+            strip[c] = yv;
+            const u32x4 kp = *reinterpret_cast<const u32x4*>(keep + 4 * c);
+            y[0] &= kp.x, y[1] &= kp.y, y[2] &= kp.z, y[3] &= kp.w;
+        }
+        quant_chunk(y, lane, c, c < nchunk, dst, sdst);
+    }
+    if (B) {
+        uint16_t* const brow = B + (int64_t)m * ldb;
+        if (K_o > 0) {
+            __syncthreads();
+            const uint16_t* const raw = reinterpret_cast<const uint16_t*>(strip);
+            for (int o = t; o < K_o; o += FT) {
+                const int c = oidx[o];
+                brow[o] = c >= 0 && c < K ? raw[c] : 0;
+            }
+        }
+        for (int o = K_o + t; o < (int)ldb; o += FT) brow[o] = 0;  // padding columns: +0
+    }
+}
+
+template <int NCH>
+static int launch_row(const uint16_t* X, const uint16_t* gamma, double eps, int64_t M, int64_t K, int64_t ldx, const int32_t* oidx,
+                      int32_t K_o, uint8_t* Xq, uint8_t* Xs, uint16_t* B, int64_t ldb, uint16_t* Xn, hipStream_t st) {
+    const size_t smem = (size_t)NCH * 256 * 32;  // the row and its keep masks, at most 48 KB
+    hipLaunchKernelGGL(rmsnorm_quant_mxfp4_row_kernel<NCH>, dim3((unsigned)M), dim3(FT), smem, st, X, gamma, eps, (int)K, ldx, oidx,
+                       (int)K_o, Xq, Xs, B, ldb, Xn);
+    return check_launch("rmsnorm_quant_mxfp4_row_kernel");
+}
+
+// LDS of the kernel with a row per wavefront; its limit on K_o holds for both kernels
+static size_t rmsnorm_lds(int64_t nci, int64_t K, int32_t K_o) {
+    const int64_t chunks = nci <= 4 ? 4 : nci <= 8 ? 8 : nci <= 16 ? 16 : 24;
+    return (size_t)4 * chunks * 64 * 16 + (size_t)(K / 2) * 4 + (size_t)K * 2 + (size_t)K_o * 2 + 16;
+}
+
 template <int NCI>
 static int launch_fused_nci(const uint16_t* X, const uint16_t* gamma, double eps, int64_t M, int64_t K, int64_t ldx,
                             const int32_t* oidx, int32_t K_o, uint8_t* Xq, uint8_t* Xs, uint16_t* B, int64_t ldb,
                             uint16_t* Xn, hipStream_t st) {
-    const size_t smem = (size_t)4 * NCI * 64 * 16 + (size_t)(K / 2) * 4 + (size_t)K * 2 + (size_t)K_o * 2 + 16;
+    const size_t smem = rmsnorm_lds(NCI, K, K_o);
     if (smem > 160 * 1024)
         return fail(OSC_ERR_UNSUPPORTED, "rmsnorm+quantize: K=%lld with K_o=%d needs %zu bytes of LDS", (long long)K,
                     (int)K_o, smem);
@@ -198,6 +320,14 @@ int launch_rmsnorm_quant_mxfp4(const uint16_t* X, const uint16_t* gamma, float e
                                uint16_t* Xn, hipStream_t st) {
     const int64_t nci = (K / 8 + 63) / 64;
     const double e = (double)eps;
+    // up to four rows per CU (wide rows: two) the workgroup per row is ahead: figures at the kernel
+    const int ncu = cu_count();
+    if (M >= 1 && M <= (int64_t)(nci > 8 ? 2 : 4) * (ncu > 0 ? ncu : 256) && nci <= 24 && rmsnorm_lds(nci, K, K_o) <= 160 * 1024) {
+        if (nci <= 4) return launch_row<1>(X, gamma, e, M, K, ldx, oidx, K_o, Xq, Xs, B, ldb, Xn, st);
+        if (nci <= 8) return launch_row<2>(X, gamma, e, M, K, ldx, oidx, K_o, Xq, Xs, B, ldb, Xn, st);
+        if (nci <= 16) return launch_row<4>(X, gamma, e, M, K, ldx, oidx, K_o, Xq, Xs, B, ldb, Xn, st);
+        return launch_row<6>(X, gamma, e, M, K, ldx, oidx, K_o, Xq, Xs, B, ldb, Xn, st);
+    }
     if (nci <= 4) return launch_fused_nci<4>(X, gamma, e, M, K, ldx, oidx, K_o, Xq, Xs, B, ldb, Xn, st);
     if (nci <= 8) return launch_fused_nci<8>(X, gamma, e, M, K, ldx, oidx, K_o, Xq, Xs, B, ldb, Xn, st);
     if (nci <= 16) return launch_fused_nci<16>(X, gamma, e, M, K, ldx, oidx, K_o, Xq, Xs, B, ldb, Xn, st);

@@ -201,3 +201,24 @@ def test_swiglu_saturates_beyond_bf16(osc, K):
     X8, xs, Y8 = osc.osc_swiglu_quantize_act_fp8(dev(G), dev(U), want_y=True)
     U8, us = osc.osc_quantize_act(Y8, None, osc.OSC_FMT_FP8_E4M3_TOKEN)
     assert torch.equal(Y8, Yn) and torch.equal(U8, X8) and torch.equal(us.view(torch.int32), xs.view(torch.int32))
+
+
+@pytest.mark.parametrize("K,r", [(32, 1), (1056, 2), (2048, 32), (4096, 0), (4096, 2), (8192, 4), (12288, 1)])
+def test_fused_row_forms(osc, K, r):
+    """A workgroup per row (few rows) and a wavefront per row (many) give the same bits: one call on many rows against
+    calls on pieces of them, rows of very different magnitude, more protected channels than a workgroup has threads."""
+    gen = wl.rng(1300 + K + r)
+    M = 1100
+    x = gen.standard_normal((M, K)).astype(np.float32) * np.exp2(gen.integers(-40, 40, (M, 1))).astype(np.float32)
+    x[7] = 0.0
+    X, gamma = dev(to_bf16_bits(x)), dev(to_bf16_bits((1.0 + 0.3 * gen.standard_normal(K)).astype(np.float32)))
+    oidx = None
+    if r:
+        table = np.stack([np.sort(gen.permutation(32)[:r]) for _ in range(K // 32)]).astype(np.int16)
+        oidx = dev(osc.osc_table_to_index(table))
+    Xq, Xs, B, Xn = osc.osc_rmsnorm_quantize_act(X, gamma, 1e-6, oidx, want_norm=True)
+    Xs = osc.osc_unpack_act_scales(Xs, M, K)
+    for a, b in ((0, 32), (32, 33), (64, 500), (512, 1012)):
+        q, s, bb, xn = osc.osc_rmsnorm_quantize_act(X[a:b], gamma, 1e-6, oidx, want_norm=True)
+        assert torch.equal(q, Xq[a:b]) and torch.equal(xn, Xn[a:b]) and torch.equal(osc.osc_unpack_act_scales(s, b - a, K), Xs[a:b])
+        assert not r or torch.equal(bb, B[a:b])
