@@ -1921,7 +1921,7 @@ static int launch_stream_cfg(const KArgs& a, bool ragged, hipStream_t st) {
     const unsigned gx = (unsigned)((a.N + 16 * NT - 1) / (16 * NT));
     if (a.M == 0 || gx == 0) return OSC_OK;
     const unsigned gy = GROUPED ? (unsigned)(a.E + (a.M - 1) / (16 * MT)) : (unsigned)((a.M + 16 * MT - 1) / (16 * MT));
-    constexpr bool ANY_ROWS = MODE != MODE_MX8 && !(GROUPED && NW == 2);  // the launcher has whole lines only for the others
+    constexpr bool ANY_ROWS = MODE != MODE_MX8 && !(GROUPED && NW == 2) && NW != 16;  // the launcher has whole lines only for the others
     auto kern = ragged ? gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, ANY_ROWS> : gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, false>;
     hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(64 * NW), 0, st, a);
     return check_launch("gemm_stream_kernel");
@@ -1930,11 +1930,14 @@ static int launch_stream_cfg(const KArgs& a, bool ragged, hipStream_t st) {
 // Tile of the streaming kernel for one problem.  A workgroup reads (MT + NT) x 16 rows of the reduction axis
 // and the launch lasts as long as the CU with the most workgroups: take the tile with the smallest
 // ceil(workgroups / CUs) x (MT + NT), the smaller one among equals (it predicts the measured order at
-// N = 1024 .. 24576, M = 16 .. 64).  Eight wavefronts as long as all workgroups of a CU are resident, else four.
+// N = 1024 .. 24576, M = 16 .. 64).  Eight wavefronts as long as all workgroups of a CU are resident, else four; sixteen where a
+// CU has one workgroup of few channels and a wavefront of eight would take four lines or more, two of them in flight
+// (16 rows, weights from HBM, us: FP8 8192 x 8192 17.2 -> 15.1, 4096 x 4096 6.2 -> 5.7, 4096 x 12288 11.5 -> 11.0; MXFP8
+// 17.7 -> 16.3, 6.5 -> 6.2, 12.5 -> 12.0; dual path 8192 x 8192 10.8 -> 9.7).
 struct StreamTile {
     int mt, nt, nw, cost;
 };
-static StreamTile stream_tile(int64_t M, int64_t N, int ncu) {
+static StreamTile stream_tile(int64_t M, int64_t N, int64_t nlines, bool ragged, int ncu) {
     static const int shapes[5][2] = {{1, 1}, {1, 2}, {1, 4}, {2, 2}, {2, 4}};
     StreamTile best{0, 0, 0, 0x7fffffff};
     for (const auto& sh : shapes) {
@@ -1942,12 +1945,14 @@ static StreamTile stream_tile(int64_t M, int64_t N, int ncu) {
         const int64_t wgs = ((N + 16 * sh[1] - 1) / (16 * sh[1])) * ((M + 16 * sh[0] - 1) / (16 * sh[0]));
         const int64_t per = (wgs + ncu - 1) / ncu, cost = per * (sh[0] + sh[1]);
         if (cost >= best.cost) continue;
-        best = StreamTile{sh[0], sh[1], per <= 4 && per * 8 * (sh[0] + sh[1]) * 2048 <= 160 * 1024 ? 8 : 4, (int)cost};
+        const bool wide = per == 1 && sh[0] == 1 && sh[1] <= 2 && nlines >= 32 && !ragged;
+        best = StreamTile{sh[0], sh[1], wide ? 16 : per <= 4 && per * 8 * (sh[0] + sh[1]) * 2048 <= 160 * 1024 ? 8 : 4, (int)cost};
     }
     return best;
 }
 template <int MODE>
 static int launch_stream(const KArgs& a, const StreamTile& tile, bool ragged, hipStream_t st) {
+    if (tile.nw == 16) return tile.nt == 1 ? launch_stream_cfg<MODE, 1, 1, 16, false>(a, false, st) : launch_stream_cfg<MODE, 1, 2, 16, false>(a, false, st);
 #define STREAM_CASE(MT_, NT_)                                                                          \
     if (tile.mt == MT_ && tile.nt == NT_)                                                              \
         return tile.nw == 8 ? launch_stream_cfg<MODE, MT_, NT_, 8, false>(a, ragged, st)               \
@@ -2163,7 +2168,7 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     // Rows that are not whole lines have only the staged kernel otherwise, which 32 rows and eight panels still
     // beat (64 x 4096 x 4128: 8.2 us against 26, 333 x 1000 x 2080: 7.5 against 12.7, 256 x 2048 x 8224: 17 against
     // 43) and twelve panels no longer do (256 x 4096 x 1056: 11.1 against 8.8, 500 x 2048 x 4128: 20.4 against 18.6)
-    StreamTile stile = stream_tile(p.M, p.N, ncu_hint > 0 ? ncu_hint : 256);
+    StreamTile stile = stream_tile(p.M, p.N, (rowbytes + 127) / 128, !lines, (int)ncu);
     const bool stream_ok = !p.row_map && p.M >= 1 && (lines || MODE != MODE_MX8);
     if (stream_ok && !grouped && (p.M <= (lines && MODE != MODE_FP8 ? 16 : 32) || stile.cost <= (!lines ? 8 : MODE == MODE_MX8 ? 2 : 3))) kind = 6;
     // Experts of a few rows: at most eight on average, and even if the routing is as uneven as it can be, which the

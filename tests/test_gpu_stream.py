@@ -176,3 +176,24 @@ def test_chosen_kernel_for_few_rows_is_not_far_behind(osc, tuning, M, N, K):
 
     other, chosen = us("1,3"), us(None)
     assert chosen <= 1.2 * other, (chosen, other)
+
+
+@pytest.mark.parametrize("mode,M,N,K", [("fp8", 1, 16, 4096), ("fp8", 16, 4090, 4224), ("mx8", 7, 8190, 4096), ("dual", 16, 4096, 8192), ("dual", 3, 5000, 16640)])
+def test_sixteen_wavefronts(osc, tuning, mode, M, N, K):
+    """Few channels a workgroup and 32 lines or more: sixteen wavefronts, line counts that they divide and do not, one and two channel
+    tiles; against the skinny kernel, which adds the same exact products in another order."""
+    X, W = dev(wl.activations_diffuse(9100 + N, M, K)), dev(wl.weights(9101 + N, N, K))
+    if mode == "dual":
+        oidx = torch.arange(0, K, 32, dtype=torch.int32, device="cuda")
+        q, Wp = osc.osc_quantize_act(X, oidx), osc.osc_pack_weight(W, oidx)
+        call = lambda: osc.osc_dual_gemm(*q, Wp, N, K, K // 32, osc.OSC_DT_F32)  # noqa: E731
+    elif mode == "fp8":
+        q, Wp = osc.osc_quantize_act(X, None, osc.OSC_FMT_FP8_E4M3_TOKEN), osc.osc_pack_weight_fp8(W)
+        call = lambda: osc.osc_fp8_gemm(*q, Wp, N, K, y_dtype=osc.OSC_DT_F32)  # noqa: E731
+    else:
+        q, Wp = osc.osc_quantize_act(X, None, osc.OSC_FMT_MXFP8), osc.osc_pack_weight_mxfp8(W)
+        call = lambda: osc.osc_mxfp8_gemm(*q, Wp, N, K, y_dtype=osc.OSC_DT_F32)  # noqa: E731
+    Y = call()
+    tuning.gemm("1,3")
+    Y0 = call()
+    assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max())
