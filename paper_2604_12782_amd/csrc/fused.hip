@@ -368,6 +368,25 @@ __device__ __forceinline__ uint32_t max_mag4(const uint32_t (&w)[4]) {  // two 1
 }
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
+// Chunk c (eight channels) of a row: activation, scale code and E4M3 codes; four neighbouring lanes hold a 32-channel block,
+// sixteen the four scale bytes of one word.
+__device__ __forceinline__ void swiglu_mxfp8_chunk(const u32x4 gv, const u32x4 uv, int lane, int c, bool ok, u32x4* yrow, u32x2* dst, uint8_t* sdst) {
+    const uint32_t ww[4] = {swiglu_pair(gv.x, uv.x), swiglu_pair(gv.y, uv.y), swiglu_pair(gv.z, uv.z), swiglu_pair(gv.w, uv.w)};
+    if (yrow && ok) __builtin_nontemporal_store((u32x4){ww[0], ww[1], ww[2], ww[3]}, yrow + c);
+    const uint32_t a2 = max_mag4(ww);
+    uint32_t a = max(a2 & 0xffffu, a2 >> 16);
+    a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0xB1, 0xF, 0xF, true));  // lane ^ 1
+    a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x4E, 0xF, 0xF, true));  // lane ^ 2
+    const uint32_t code = (uint32_t)max((int)(a >> 7) - 8, 0);  // E8M0 code = max(E - 8, 0)
+    uint32_t word = code;
+    word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x104, 0xF, 0xF, true) << 8;
+    word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x108, 0xF, 0xF, true) << 16;
+    word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x10C, 0xF, 0xF, true) << 24;
+    if ((lane & 15) == 0 && ok) *reinterpret_cast<uint32_t*>(sdst + (c >> 4) * 128) = word;
+    const u32x2 out = mxfp8_codes(ww, code);
+    if (ok) __builtin_nontemporal_store(out, dst + c);
+}
+
 // 4 B read and 1 B written per element.  One (row, 1024-channel segment) per wavefront and trip as in
 // the quantisers; a lane's four 16-byte loads per trip on up to eight wavefronts per SIMD keep enough
 // bytes in flight.  8192 x 12288: 98.9 -> 79.0 us (6.4 TB/s), 1000 x 12288: 16.9 -> 12.9 us, table launch
@@ -399,25 +418,44 @@ __global__ void __launch_bounds__(FT) swiglu_quant_mxfp8_kernel(const uint16_t* 
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int c = c0 + 64 * i;
-            const uint32_t ww[4] = {swiglu_pair(gv[i].x, uv[i].x), swiglu_pair(gv[i].y, uv[i].y),
-                                    swiglu_pair(gv[i].z, uv[i].z), swiglu_pair(gv[i].w, uv[i].w)};
-            if (Yn && c < nchunk)
-                __builtin_nontemporal_store((u32x4){ww[0], ww[1], ww[2], ww[3]},
-                                            reinterpret_cast<u32x4*>(Yn + (int64_t)m * K) + c);
-            const uint32_t a2 = max_mag4(ww);
-            uint32_t a = max(a2 & 0xffffu, a2 >> 16);
-            a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0xB1, 0xF, 0xF, true));  // lane ^ 1
-            a = max(a, (uint32_t)__builtin_amdgcn_mov_dpp((int)a, 0x4E, 0xF, 0xF, true));  // lane ^ 2
-            const uint32_t code = (uint32_t)max((int)(a >> 7) - 8, 0);  // E8M0 code = max(E - 8, 0)
-            uint32_t word = code;
-            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x104, 0xF, 0xF, true) << 8;
-            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x108, 0xF, 0xF, true) << 16;
-            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x10C, 0xF, 0xF, true) << 24;
-            if ((lane & 15) == 0 && c < nchunk) *reinterpret_cast<uint32_t*>(sdst + (c >> 4) * 128) = word;
-            const u32x2 out = mxfp8_codes(ww, code);
-            if (c < nchunk) __builtin_nontemporal_store(out, dst + c);
+            swiglu_mxfp8_chunk(gv[i], uv[i], lane, c, c < nchunk, Yn ? reinterpret_cast<u32x4*>(Yn + (int64_t)m * K) : nullptr, dst, sdst);
         }
     }
+}
+
+// Rows of whole 128-channel words but not of whole segments: the chunks of all rows in one line, 128 per wavefront, so that no
+// lane is idle (a segment per row leaves a quarter of them idle at 768 channels and half at 512).  Every die takes a run of
+// rows of its own: the four-byte scale words of a 32-row block meet in one L2.  A kernel of its own: with rows by lane instead of by
+// wavefront whole segments are 3 to 6 % slower.
+__global__ void __launch_bounds__(FT) swiglu_quant_mxfp8_flat_kernel(const uint16_t* __restrict__ G, const uint16_t* __restrict__ U, int M, int K,
+                                                                     int64_t ldg, int64_t ldu, uint8_t* __restrict__ Xq,
+                                                                     uint8_t* __restrict__ Xs, uint16_t* __restrict__ Yn) {
+    const int Kg4 = ((K >> 5) + 3) >> 2, nchunk = K >> 3;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int first = (((int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + (int)(blockIdx.x >> 3)) * 4 + wave) * SEG_CHUNKS;  // gridDim.x: a multiple of 8
+    const int row = first / nchunk, col = first - row * nchunk;
+    if (row >= M) return;  // uniform over the wavefront
+    int m[2], c[2];
+    u32x4 gv[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}}, uv[2] = {{0u, 0u, 0u, 0u}, {0u, 0u, 0u, 0u}};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        m[i] = row;
+        c[i] = col + lane + 64 * i;
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {  // nchunk >= 64, c < nchunk + 128
+            const bool over = c[i] >= nchunk;
+            c[i] -= over ? nchunk : 0;
+            m[i] += over ? 1 : 0;
+        }
+        if (m[i] < M) {
+            gv[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(G + (int64_t)m[i] * ldg) + c[i]);
+            uv[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(U + (int64_t)m[i] * ldu) + c[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        swiglu_mxfp8_chunk(gv[i], uv[i], lane, c[i], m[i] < M, Yn ? reinterpret_cast<u32x4*>(Yn + (int64_t)m[i] * K) : nullptr,
+                           reinterpret_cast<u32x2*>(Xq + (int64_t)m[i] * K), Xs + (int64_t)(m[i] >> 5) * Kg4 * 128 + (m[i] & 31) * 4);
 }
 
 int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, int64_t K, int64_t ldg, int64_t ldu,
@@ -429,7 +467,16 @@ int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, i
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "swiglu+quantize: M=%lld too large", (long long)M);
     // One trip per workgroup: the hardware hands out new workgroups as old ones drain, which beats walking a
     // fixed grid at every size of whole segments (8192 x 12288: 79 us, a grid of 8192 86 us, of 2048 92 us).
-    // Rows of less than a segment leave lanes idle and are the exception (32768 x 768: 26.4 us against 24.7).
+    // Rows of less than a segment are the exception.
+    const int64_t flat_wg = (M * nchunk + 4 * SEG_CHUNKS - 1) / (4 * SEG_CHUNKS) + 7;
+    // All rows' chunks in one line where segments would leave a fifth of the lanes or more idle (us: 32768 x 512 22.3 -> 16.9,
+    // x 640 23.6 -> 20.8, x 768 25.8 -> 23.7, 8192 x 1152 13.4 -> 11.6, 4096 x 3200 14.8 -> 14.3; beyond: 2000 x 1920 5.7 -> 6.1,
+    // 4096 x 11136 39 -> 44)
+    if (K % 128 == 0 && K >= 512 && 4 * nseg * SEG_CHUNKS >= 5 * nchunk && M * nchunk < ((int64_t)1 << 30) && flat_wg <= MAX_GRID) {
+        const unsigned wgs = (unsigned)(flat_wg / 8 * 8);
+        hipLaunchKernelGGL(swiglu_quant_mxfp8_flat_kernel, dim3(wgs), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, Xq, Xs, Yn);
+        return check_launch("swiglu_quant_mxfp8_flat_kernel");
+    }
     const int64_t cap = K >= SEG_CH ? MAX_GRID : 4096;
     const int grid = (int)(total_wg < cap ? total_wg : cap);
     hipLaunchKernelGGL(swiglu_quant_mxfp8_kernel, dim3(grid), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, Xq,

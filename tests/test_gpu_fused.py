@@ -222,3 +222,18 @@ def test_fused_row_forms(osc, K, r):
         q, s, bb, xn = osc.osc_rmsnorm_quantize_act(X[a:b], gamma, 1e-6, oidx, want_norm=True)
         assert torch.equal(q, Xq[a:b]) and torch.equal(xn, Xn[a:b]) and torch.equal(osc.osc_unpack_act_scales(s, b - a, K), Xs[a:b])
         assert not r or torch.equal(bb, B[a:b])
+
+
+@pytest.mark.parametrize("M,K", [(1, 512), (33, 640), (37, 768), (130, 1152), (65, 2304), (5, 3200), (1030, 768)])
+def test_swiglu_mxfp8_rows_in_one_line(osc, M, K):
+    """Rows of whole 128-channel words that segments of 1024 would leave lanes idle on: wavefronts that cover one, two and three
+    rows, a last one that ends past the last row, against the oracle's fixed sequence and quantiser, from the halves of one buffer."""
+    gen = wl.rng(1400 + M + K)
+    H = to_bf16_bits((gen.standard_normal((M, 2 * K)) * 2).astype(np.float32))
+    d = dev(H).view(torch.bfloat16) if dev(H).dtype != torch.bfloat16 else dev(H)
+    Xq, Xs, Yn = osc.osc_swiglu_quantize_act(d[:, :K], d[:, K:], want_y=True)
+    y = oracle.swiglu(np.ascontiguousarray(H[:, :K]), np.ascontiguousarray(H[:, K:]))
+    q, s = oracle.quantize_mxfp8(y)
+    assert np.array_equal(Yn.view(torch.int16).cpu().numpy().view(np.uint16), y.view(np.uint16))
+    assert np.array_equal(osc.osc_unpack_act_scales(Xs, M, K).cpu().numpy(), s)
+    assert np.array_equal(Xq.cpu().numpy(), q)
