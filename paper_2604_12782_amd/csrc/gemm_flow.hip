@@ -160,6 +160,8 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
     static_assert(FP8 || (GROUPED ? (DUAL ? NBA : (NBA + 1) / 2) + (NBB + BPR - 1) / BPR : (NBLK + BPR - 1) / BPR) <= NW, "scale requests");
 
     auto request_map = [&](const TilePos& p) __attribute__((always_inline)) {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the entries that these replace have been read
         const int idx = lane < 32 ? wave * 8 + (lane & 7) + RPP * min(lane >> 3, LA - 1) : min(wave, NBA - 1) * 32 + r;
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(a.row_map + min(p.m0 + idx, p.row_end - 1)),
                                          (__attribute__((address_space(3))) void*)(map_l + wave * 64), 4, 0, 0);
