@@ -2094,9 +2094,15 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     const bool pipe_ok = lines && !grouped && !p.row_map && stages >= 3;
     if (pipe_ok && tm == 4 && t256 > 256) kind = 2;
     int flow_tile = -1;
+    // launches that the rules for few rows further down take: no tile is looked for (a call's host time is what bounds them)
+    const int64_t skinny_wgs = ((p.N + 31) / 32) * ((p.M + 31) / 32);
+    const StreamTile stile = stream_tile(p.M, p.N, (rowbytes + 127) / 128, !lines, (int)ncu);
+    const bool stream_ok = !p.row_map && p.M >= 1 && (lines || MODE != MODE_MX8);
+    const bool few_rows = stream_ok && !grouped && (p.M <= (lines && MODE != MODE_FP8 ? 16 : 32) || stile.cost <= (!lines ? 8 : MODE == MODE_MX8 ? 2 : 3));
+    const bool few_blocks = skinny_wgs <= 512 || (p.M <= 64 && skinny_wgs <= 1024);
     // (fewer than five stages: a tile is over before the ring has filled, 6493 x 640 x 512 FP8 10 us against 7.8 on the DMA
     // kernel's tiles)
-    if (lines && !grouped && !p.row_map && p.M >= 1 && p.N >= 1 && stages >= 5) {
+    if (lines && !grouped && !p.row_map && p.M >= 1 && p.N >= 1 && stages >= 5 && !few_rows && !few_blocks) {
         // One problem: the flowing kernel with the tile that its cost model prefers, or tiles of 256 x 256.  Those read
         // LDS half as often per product, which is worth a higher clock, so they are ahead wherever their rounds are
         // filled as well (8192 x 4096 x 4096: 85 us against 85 to 90, K = 12288 MXFP8 310 against 335) and behind where
@@ -2151,9 +2157,8 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     // (128 x 4096 x 4096: 11.8 us on 64 x 128 tiles, 6.8 us on 512 streaming workgroups), and for up to 64 rows until
     // it needs a third round, from where the flowing kernel's 64 x 128 tiles are ahead (33 to 64 rows of 24576 x 4096:
     // dual 23.4 -> 13.4 us, FP8 36 -> 18; of 12288 x 4096 equal or up to 1.1 times slower).
-    const int64_t skinny_wgs = ((p.N + 31) / 32) * ((p.M + 31) / 32);
     const bool skinny_ok = lines && !grouped && !p.row_map && p.M >= 1 && (p.M <= 64 || skinny_wgs <= 512);
-    if (skinny_ok && (skinny_wgs <= 1024 || kind != 7)) kind = 3;
+    if (skinny_ok && (few_blocks || kind != 7)) kind = 3;
     // The streaming kernel up to 16 rows at any N (per-token FP8: 32), and above that while its tile costs at most
     // three 16-row panels per CU (MXFP8: two).  It is built for weights that come from HBM, as a decoding step's do;
     // weight-streaming kernel above -> this one, us, from HBM and from the last-level cache:
@@ -2168,9 +2173,7 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     // Rows that are not whole lines have only the staged kernel otherwise, which 32 rows and eight panels still
     // beat (64 x 4096 x 4128: 8.2 us against 26, 333 x 1000 x 2080: 7.5 against 12.7, 256 x 2048 x 8224: 17 against
     // 43) and twelve panels no longer do (256 x 4096 x 1056: 11.1 against 8.8, 500 x 2048 x 4128: 20.4 against 18.6)
-    StreamTile stile = stream_tile(p.M, p.N, (rowbytes + 127) / 128, !lines, (int)ncu);
-    const bool stream_ok = !p.row_map && p.M >= 1 && (lines || MODE != MODE_MX8);
-    if (stream_ok && !grouped && (p.M <= (lines && MODE != MODE_FP8 ? 16 : 32) || stile.cost <= (!lines ? 8 : MODE == MODE_MX8 ? 2 : 3))) kind = 6;
+    if (few_rows) kind = 6;
     // Experts of a few rows: at most eight on average, and even if the routing is as uneven as it can be, which the
     // host cannot see, at most four workgroups (rows that are not whole lines: three) per CU for the row blocks
     // after an expert's first.  Every such block reads its expert's weights again, where a tile of 64 rows reads
