@@ -298,9 +298,8 @@ static int launch_fused_nci(const uint16_t* X, const uint16_t* gamma, double eps
     // FULL: every lane holds NCI whole chunks, so the per-chunk bounds tests (and the branches they cost) drop out
     auto kern = K == (int64_t)NCI * 512 ? rmsnorm_quant_mxfp4_kernel<NCI, true> : rmsnorm_quant_mxfp4_kernel<NCI, false>;
     if (smem > 48 * 1024) {
-        static unsigned char lds_done[MAX_DEVICES];
-        static size_t lds_reserved[MAX_DEVICES];
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc;
+        static LdsReserved lds_reserved;
+        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     const int64_t want = (M + 3) / 4;
     // as many workgroups as the chip holds at once (LDS decides how many per CU), each wavefront then

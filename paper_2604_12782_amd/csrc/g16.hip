@@ -146,9 +146,8 @@ int launch_quant_fp4_g16(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, c
         return fail(OSC_ERR_UNSUPPORTED, "quantize: K=%lld with K_o=%d needs %zu bytes of LDS", (long long)K, (int)K_o, smem);
     auto kern = fmt == 0 ? quant_fp4_g16_kernel<0> : quant_fp4_g16_kernel<1>;
     if (smem > 48 * 1024) {
-        static unsigned char lds_done[2][MAX_DEVICES];
-        static size_t lds_reserved[2][MAX_DEVICES];
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done[fmt], lds_reserved[fmt])) return rc;
+        static LdsReserved lds_reserved[2];
+        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved[fmt])) return rc;
     }
     const int64_t blocks = (M + 31) / 32;
     const int64_t total_wg = (blocks + 7) / 8 * 8 * (8 * nseg);
@@ -604,9 +603,8 @@ int launch_dual_gemm_g16(const uint8_t* Xq, const uint8_t* Xs, float xts, const 
 #define G16_LAUNCH(F_, NW_)                                                                               \
     {                                                                                                     \
         auto kern = gemm_g16_wide_kernel<F_, NW_>;                                                             \
-        static unsigned char lds_done[MAX_DEVICES];                                                       \
-        static size_t lds_reserved[MAX_DEVICES];                                                          \
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc; \
+        static LdsReserved lds_reserved;                                                                  \
+        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc; \
         hipLaunchKernelGGL(kern, grid, dim3(64 * NW_), smem, st, a);                                      \
     }
     if (fmt == 0) {

@@ -1228,9 +1228,8 @@ static int launch_pipe2(KArgs a, int64_t rows_total, bool grouped, hipStream_t s
     const int64_t grid = ntiles < (int64_t)ncu * per_cu ? ntiles : (int64_t)ncu * per_cu;
     auto kern = gemm_pipe2_kernel<MODE, TM, TN, WN>;
     if (smem > 64 * 1024) {
-        static unsigned char lds_done[MAX_DEVICES];
-        static size_t lds_reserved[MAX_DEVICES];
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc;
+        static LdsReserved lds_reserved;
+        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem, st, a, (int)ntiles);
     return check_launch("gemm_pipe2_kernel");
@@ -1412,9 +1411,8 @@ static int launch_ring(KArgs a, hipStream_t st) {
     if (grid <= 0) return OSC_OK;
     if (grid > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "gemm: too many tiles");
     auto kern = gemm_ring_kernel<TM, TN, WN, PINGPONG>;
-    static unsigned char lds_done[MAX_DEVICES];
-    static size_t lds_reserved[MAX_DEVICES];
-    if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc;
+    static LdsReserved lds_reserved;
+    if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem, st, a);
     return check_launch("gemm_ring_kernel");
 }
@@ -1628,9 +1626,8 @@ static int launch_skinny_cfg(KArgs a, unsigned grid, unsigned mtiles, hipStream_
     constexpr size_t smem = (size_t)NW * DEPTH * IMG;
     auto kern = gemm_skinny_kernel<MODE, 1, NW, DEPTH>;
     if (smem > 48 * 1024) {
-        static unsigned char lds_done[MAX_DEVICES];
-        static size_t lds_reserved[MAX_DEVICES];
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc;
+        static LdsReserved lds_reserved;
+        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     hipLaunchKernelGGL(kern, dim3(grid, mtiles), dim3(64 * NW), smem, st, a);
     return check_launch("gemm_skinny_kernel");
@@ -1981,9 +1978,8 @@ static int launch_cfg(KArgs a, int64_t rows_total, bool grouped, hipStream_t st)
     if (grid > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "gemm: too many tiles");
     auto kern = gemm_kernel<MODE, TM, TN, RAGGED>;
     if (smem > 64 * 1024) {
-        static unsigned char lds_done[MAX_DEVICES];
-        static size_t lds_reserved[MAX_DEVICES];
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc;
+        static LdsReserved lds_reserved;
+        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(GT), smem, st, a);
     return check_launch("gemm_kernel");
@@ -2004,9 +2000,8 @@ static int launch_dma2(KArgs a, int64_t rows_total, bool grouped, hipStream_t st
     if (grid > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "gemm: too many tiles");
     auto kern = gemm_dma2_kernel<MODE, TM, TN, WN>;
     if (smem > 64 * 1024) {
-        static unsigned char lds_done[MAX_DEVICES];
-        static size_t lds_reserved[MAX_DEVICES];
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc;
+        static LdsReserved lds_reserved;
+        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem, st, a);
     return check_launch("gemm_dma2_kernel");

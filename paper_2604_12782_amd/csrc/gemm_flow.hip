@@ -441,9 +441,8 @@ static int launch_cfg(KArgs a, hipStream_t st) {
     const size_t smem = flow_lds(MODE, BM, BN, NSTG, GROUPED, a.E);
     const int64_t grid = ntiles < ncu ? ntiles : ncu;  // one workgroup per CU, each walks its list of tiles
     auto kern = gemm_flow_kernel<MODE, WM, WN, TM, TN, NSTG, LAG, GROUPED>;
-    static unsigned char lds_done[MAX_DEVICES];
-    static size_t lds_reserved[MAX_DEVICES];
-    if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_done, lds_reserved)) return rc;
+    static LdsReserved lds_reserved;
+    if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), smem, st, a, (int)ntiles);
     return check_launch("gemm_flow_kernel");
 }

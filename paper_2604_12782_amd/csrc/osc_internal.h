@@ -4,6 +4,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/osc.h"
 
 namespace osc {
@@ -16,10 +18,13 @@ enum { TUNE_GEMM_TILE = 0, TUNE_GEMM_KERNEL = 1, TUNE_GROUPED_ONE_TILE = 2, TUNE
 int tuning(int knob);
 // number of compute units of the current device (cached per device); <= 0 on error
 int cu_count();
-// hipFuncAttributeMaxDynamicSharedMemorySize, issued once per (kernel, device); `done` is the
-// caller's per-kernel flag array, one entry per device
+// hipFuncAttributeMaxDynamicSharedMemorySize of a kernel, issued only where a launch needs more than any before it on
+// that device; `r` is the caller's static per-kernel record (zero: nothing reserved yet)
 constexpr int MAX_DEVICES = 64;
-int reserve_lds(const void* kernel, size_t bytes, unsigned char (&done)[MAX_DEVICES], size_t (&reserved)[MAX_DEVICES]);
+struct LdsReserved {
+    std::atomic<size_t> bytes[MAX_DEVICES];
+};
+int reserve_lds(const void* kernel, size_t bytes, LdsReserved& r);
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }

@@ -1,6 +1,7 @@
 // Process-wide kernel-choice overrides (include/osc_tuning.h) and small per-device caches that keep
 // repeated host work (device queries, function attributes) off the launch path.
 #include <atomic>
+#include <mutex>
 
 #include "osc_internal.h"
 #include "../../include/osc_tuning.h"
@@ -22,18 +23,22 @@ int cu_count() {
     return n;
 }
 
-int reserve_lds(const void* kernel, size_t bytes, unsigned char (&done)[MAX_DEVICES], size_t (&reserved)[MAX_DEVICES]) {
+int reserve_lds(const void* kernel, size_t bytes, LdsReserved& r) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= MAX_DEVICES)
         return fail(OSC_ERR_HIP, "cannot read the current device");
-    // racing first calls from two threads both set the attribute to the value they need; harmless
-    if (done[dev] && reserved[dev] >= bytes) return OSC_OK;
+    std::atomic<size_t>& reserved = r.bytes[dev];
+    if (reserved.load(std::memory_order_acquire) >= bytes) return OSC_OK;
+    // The amount depends on the call (experts, channels), and setting the attribute lowers it as well as raises it: threads
+    // that need different amounts take turns, so that the attribute only grows and the record never exceeds it.
+    static std::mutex mu;
+    const std::lock_guard<std::mutex> lock(mu);
+    if (reserved.load(std::memory_order_relaxed) >= bytes) return OSC_OK;
     if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) {
         (void)hipGetLastError();
         return fail(OSC_ERR_HIP, "cannot reserve %zu bytes of LDS", bytes);
     }
-    reserved[dev] = bytes;
-    done[dev] = 1;
+    reserved.store(bytes, std::memory_order_release);
     return OSC_OK;
 }
 

@@ -1,0 +1,78 @@
+"""How much LDS a kernel may be launched with is an attribute of the kernel that every call sets to what it needs; the amount
+depends on the call (number of experts, of channels).  CPU only: csrc/tuning.hip is compiled with the HIP calls it makes
+replaced by the ones below."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <chrono>
+#include <condition_variable>
+#include <cstdio>
+#include <thread>
+#include "tuning.hip"
+
+static std::mutex g_mu;
+static std::condition_variable g_cv;
+static size_t g_attribute = 0;  // what the "driver" allows
+static int g_set = 0;           // calls that have set it
+
+extern "C" hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+extern "C" hipError_t hipGetLastError() { return hipSuccess; }
+extern "C" hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+// the first caller sets the attribute and then stays inside until another one has set it too (or half a second has passed:
+// nobody else may come in while it is there)
+extern "C" hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int bytes) {
+    std::unique_lock<std::mutex> l(g_mu);
+    g_attribute = (size_t)bytes;
+    if (++g_set == 1) g_cv.wait_for(l, std::chrono::milliseconds(500), [] { return g_set > 1; });
+    else {
+        g_cv.notify_all();
+        l.unlock();
+        std::this_thread::sleep_for(std::chrono::milliseconds(50));  // the first caller records its amount before or after
+    }
+    return hipSuccess;
+}
+namespace osc {
+int fail(int code, const char*, ...) { return code; }
+}
+
+int main() {
+    static osc::LdsReserved r;
+    const size_t large = 150000, small = 100000;
+    int bad = 0;
+    std::thread a([&] { bad |= osc::reserve_lds(nullptr, large, r) != OSC_OK; });
+    std::thread b([&] {
+        for (;;) {  // until the first caller has set its amount
+            std::this_thread::sleep_for(std::chrono::milliseconds(1));
+            std::lock_guard<std::mutex> l(g_mu);
+            if (g_set) break;
+        }
+        bad |= osc::reserve_lds(nullptr, small, r) != OSC_OK;
+    });
+    a.join();
+    b.join();
+    std::printf("after both: %zu\n", g_attribute);
+    if (bad || g_attribute < large) return 1;  // the larger call's own launch would be refused
+    if (osc::reserve_lds(nullptr, large, r) != OSC_OK || g_attribute < large) return 2;
+    if (osc::reserve_lds(nullptr, large + 1, r) != OSC_OK || g_attribute != large + 1) return 3;  // still grows
+    const int calls = g_set;
+    if (osc::reserve_lds(nullptr, small, r) != OSC_OK || g_set != calls) return 4;  // and is not asked for again
+    return 0;
+}
+"""
+
+
+def test_racing_calls_never_lower_it(tmp_path):
+    if not shutil.which("g++") or not os.path.exists("/opt/rocm/include/hip/hip_runtime.h"):
+        pytest.skip("no host compiler or HIP headers")
+    src, exe = tmp_path / "race.cpp", tmp_path / "race"
+    src.write_text(PROGRAM)
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-D__HIP_PLATFORM_AMD__", "-w", "-isystem", "/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_2604_12782_amd", "csrc"), str(src), "-o", str(exe), "-pthread"], check=True, timeout=300)
+    p = subprocess.run([str(exe)], capture_output=True, text=True, timeout=60)
+    assert p.returncode == 0, (p.returncode, p.stdout)
