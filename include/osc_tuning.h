@@ -25,6 +25,13 @@ enum {
 int osc_tuning_set(int knob, int value);
 /* The current setting (-1 = automatic, also for an unknown knob). */
 int osc_tuning_get(int knob);
+/*
+ * What served the calling thread's last GEMM call that launched anything (-1 before the first): kernel id | detail << 8.
+ * Ids as above, and 8 the 16-row kernel and 9 the wide kernel of the formats with a scale per 16 channels.  Detail: tile
+ * rows / 64 of kernels 0, 1 and 2; wavefronts of a workgroup of kernels 3, 6 and 9; the tile of kernel 7; channels / 16 of a
+ * workgroup of kernel 8.  For tests: a forced kernel gives way silently where it cannot serve a shape.
+ */
+int osc_tuning_last_gemm(void);
 
 #ifdef __cplusplus
 }

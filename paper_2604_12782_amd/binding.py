@@ -46,6 +46,7 @@ _SIGS = {
     "osc_quantize_act_dynamic": (C.c_int, [vp, i64, i64, i64, vp, vp, vp, i64, vp, vp]),
     "osc_tuning_set": (C.c_int, [C.c_int, C.c_int]),
     "osc_tuning_get": (C.c_int, [C.c_int]),
+    "osc_tuning_last_gemm": (C.c_int, []),
     "osc_profile_abs_sum": (C.c_int, [vp, i64, i64, i64, vp, vp]),
     "osc_profile_threshold": (C.c_int, [vp, i64, C.c_float, vp, vp]),
     "osc_profile_hist": (C.c_int, [vp, i64, i64, i64, i32, vp, vp, vp]),
@@ -396,6 +397,12 @@ def osc_tuning_set(knob, value):
 
 def osc_tuning_get(knob):
     return lib().osc_tuning_get(knob)
+
+
+def osc_tuning_last_gemm():
+    """(kernel id, detail) of this thread's last GEMM launch, None before the first (include/osc_tuning.h); for tests."""
+    v = lib().osc_tuning_last_gemm()
+    return None if v < 0 else (v & 0xff, v >> 8)
 
 
 def osc_swiglu_quantize_act(G, U, want_y=False, out=None):

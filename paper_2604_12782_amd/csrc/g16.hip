@@ -418,6 +418,7 @@ template <int FMT, int NT, int NW>
 static int launch_g16(const G16Args& a, hipStream_t st) {
     const dim3 grid((unsigned)((a.N + 16 * NT - 1) / (16 * NT)), (unsigned)((a.M + 15) / 16));
     hipLaunchKernelGGL((gemm_g16_kernel<FMT, NT, NW>), grid, dim3(64 * NW), 0, st, a);
+    note_gemm(GEMM_G16_ROWS16, NT);
     return check_launch("gemm_g16_kernel");
 }
 
@@ -613,6 +614,7 @@ int launch_dual_gemm_g16(const uint8_t* Xq, const uint8_t* Xs, float xts, const 
         if (wide) G16_LAUNCH(1, 8) else G16_LAUNCH(1, 4)
     }
 #undef G16_LAUNCH
+    note_gemm(GEMM_G16_WIDE, wide ? 8 : 4);
     return check_launch("gemm_g16_wide_kernel");
 }
 

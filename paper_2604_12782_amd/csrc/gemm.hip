@@ -1232,6 +1232,7 @@ static int launch_pipe2(KArgs a, int64_t rows_total, bool grouped, hipStream_t s
         if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem, st, a, (int)ntiles);
+    note_gemm(GEMM_PERSISTENT, TM);
     return check_launch("gemm_pipe2_kernel");
 }
 
@@ -1414,6 +1415,7 @@ static int launch_ring(KArgs a, hipStream_t st) {
     static LdsReserved lds_reserved;
     if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem, st, a);
+    note_gemm(GEMM_RING, TM);
     return check_launch("gemm_ring_kernel");
 }
 
@@ -1630,6 +1632,7 @@ static int launch_skinny_cfg(KArgs a, unsigned grid, unsigned mtiles, hipStream_
         if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     hipLaunchKernelGGL(kern, dim3(grid, mtiles), dim3(64 * NW), smem, st, a);
+    note_gemm(GEMM_SKINNY, NW);
     return check_launch("gemm_skinny_kernel");
 }
 
@@ -1921,6 +1924,7 @@ static int launch_stream_cfg(const KArgs& a, bool ragged, hipStream_t st) {
     constexpr bool ANY_ROWS = MODE != MODE_MX8 && !(GROUPED && NW == 2) && NW != 16;  // the launcher has whole lines only for the others
     auto kern = ragged ? gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, ANY_ROWS> : gemm_stream_kernel<MODE, MT, NT, NW, GROUPED, false>;
     hipLaunchKernelGGL(kern, dim3(gx, gy), dim3(64 * NW), 0, st, a);
+    note_gemm(GEMM_STREAM, NW);
     return check_launch("gemm_stream_kernel");
 }
 
@@ -1982,6 +1986,7 @@ static int launch_cfg(KArgs a, int64_t rows_total, bool grouped, hipStream_t st)
         if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(GT), smem, st, a);
+    note_gemm(GEMM_STAGED, TM);
     return check_launch("gemm_kernel");
 }
 
@@ -2004,6 +2009,7 @@ static int launch_dma2(KArgs a, int64_t rows_total, bool grouped, hipStream_t st
         if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     }
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(128 * WN), smem, st, a);
+    note_gemm(GEMM_DMA, TM);
     return check_launch("gemm_dma2_kernel");
 }
 

@@ -498,6 +498,7 @@ static int launch_mode(const KArgs& a, int tile, hipStream_t st) {
 }
 
 int launch_flow(const KArgs& a, int mode, int tile, hipStream_t st) {
+    note_gemm(GEMM_FLOW, tile);
     if (mode == MODE_DUAL) return launch_mode<MODE_DUAL>(a, tile, st);
     if (mode == MODE_FP8) return launch_mode<MODE_FP8>(a, tile, st);
     return launch_mode<MODE_MX8>(a, tile, st);

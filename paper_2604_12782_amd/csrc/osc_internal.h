@@ -16,6 +16,9 @@ int check_launch(const char* what);        // hipGetLastError -> OSC_OK / OSC_ER
 // Kernel-choice overrides (osc_tuning.h): process-wide, -1 = automatic.  Read with relaxed loads.
 enum { TUNE_GEMM_TILE = 0, TUNE_GEMM_KERNEL = 1, TUNE_GROUPED_ONE_TILE = 2, TUNE_SWIGLU_TABLE = 3, TUNE_GEMM_KSPLIT = 4, TUNE_COUNT = 5 };
 int tuning(int knob);
+// what osc_tuning_last_gemm reports for this thread
+enum { GEMM_STAGED = 0, GEMM_DMA = 1, GEMM_PERSISTENT = 2, GEMM_SKINNY = 3, GEMM_RING = 4, GEMM_STREAM = 6, GEMM_FLOW = 7, GEMM_G16_ROWS16 = 8, GEMM_G16_WIDE = 9 };
+void note_gemm(int kernel, int detail);
 // number of compute units of the current device (cached per device); <= 0 on error
 int cu_count();
 // hipFuncAttributeMaxDynamicSharedMemorySize of a kernel, issued only where a launch needs more than any before it on

@@ -10,6 +10,9 @@ namespace osc {
 
 static std::atomic<int> g_knob[TUNE_COUNT] = {{-1}, {-1}, {-1}, {-1}, {-1}};
 
+static thread_local int g_last_gemm = -1;
+void note_gemm(int kernel, int detail) { g_last_gemm = kernel | detail << 8; }
+
 int tuning(int knob) { return g_knob[knob].load(std::memory_order_relaxed); }
 
 int cu_count() {
@@ -54,3 +57,5 @@ extern "C" int osc_tuning_get(int knob) {
     if (knob < 0 || knob >= osc::TUNE_COUNT) return -1;
     return osc::tuning(knob);
 }
+
+extern "C" int osc_tuning_last_gemm(void) { return osc::g_last_gemm; }

@@ -62,8 +62,10 @@ def check(osc, tuning, tile, mode, M, N, K, r, seed):
     call(osc.OSC_DT_BF16, Yb)
     odd = torch.full((M, N + 3), 7.0, dtype=torch.bfloat16, device="cuda")
     call(osc.OSC_DT_BF16, odd[:, 1:1 + N])
+    assert osc.osc_tuning_last_gemm() == (7, tile)
     tuning.gemm("1,1")
     Y0 = call(osc.OSC_DT_F32)
+    assert osc.osc_tuning_last_gemm() == (1, 1)
     want = ref(rows)
     got = Y[torch.from_numpy(rows).cuda()].cpu().numpy().astype(np.float64)
     assert np.abs(got - want).max() <= TOL * np.abs(want).max()
@@ -96,12 +98,14 @@ def test_flow_several_tiles_per_workgroup(osc, tuning, tile, mode):
 
 
 def test_launcher_choice_agrees(osc, tuning):
-    """The launcher's own choice over shapes on both sides of its rules against the DMA kernel."""
-    for mode, M, N, K, r in [("dual", 1000, 1536, 4096, 1), ("dual", 130, 4096, 1280, 2), ("fp8", 300, 4104, 2048, 0), ("mx8", 700, 1000, 1536, 0),
-                             ("dual", 60, 33000, 1280, 0), ("fp8", 40, 33000, 640, 0), ("mx8", 2100, 2048, 640, 0), ("dual", 4200, 4096, 1536, 1)]:
+    """The launcher's own choice (kernel, tile) over shapes on both sides of its rules, and its result against the DMA kernel."""
+    for mode, M, N, K, r, chosen in [("dual", 1000, 1536, 4096, 1, (7, 3)), ("dual", 130, 4096, 1280, 2, (7, 3)), ("fp8", 300, 4104, 2048, 0, (7, 3)),
+                                     ("mx8", 700, 1000, 1536, 0, (7, 3)), ("dual", 60, 33000, 1280, 0, (7, 3)), ("fp8", 40, 33000, 640, 0, (7, 3)),
+                                     ("mx8", 2100, 2048, 640, 0, (7, 0)), ("dual", 4200, 4096, 1536, 1, (2, 4))]:
         call, _ = problem(osc, mode, M, N, K, r, 7800 + M)
         tuning.gemm(None)
         Y = call(osc.OSC_DT_F32)
+        assert osc.osc_tuning_last_gemm() == chosen, (mode, M, N, K, r)
         tuning.gemm("1,1")
         Y0 = call(osc.OSC_DT_F32)
         assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max()), (mode, M, N, K, r)
@@ -141,8 +145,10 @@ def test_flow_experts(osc, tuning, N):
     for name, call in calls.items():
         tuning.gemm("0,7")
         Y, Yb = call(osc.OSC_DT_F32), call(osc.OSC_DT_BF16)
+        assert osc.osc_tuning_last_gemm() == (7, 0), name
         tuning.gemm("1,1")
         Y0 = call(osc.OSC_DT_F32)
+        assert osc.osc_tuning_last_gemm() == (1, 1), name
         assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max()), name
         assert torch.equal(Yb, Y.to(torch.bfloat16)), name
         if name in refs:

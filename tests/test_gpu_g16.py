@@ -97,9 +97,10 @@ def test_decode_shape_of_the_density_sweep(osc, fmt, xts, wts):
 
 
 @pytest.mark.parametrize("fmt", [0, 1])
-@pytest.mark.parametrize("M,N,K,r", [(1, 16, 256, 0), (16, 48, 512, 1), (15, 12280, 256, 2), (16, 4100, 2304, 1), (7, 8200, 512, 4), (17, 4096, 768, 1),
-                                     (32, 2049, 4352, 2), (33, 100, 512, 1)])
-def test_gemm_g16_tiles_of_16_rows(osc, fmt, M, N, K, r):
+@pytest.mark.parametrize("M,N,K,r,kernel", [(1, 16, 256, 0, (8, 1)), (16, 48, 512, 1, (8, 1)), (15, 12280, 256, 2, (8, 3)), (16, 4100, 2304, 1, (8, 2)),
+                                            (7, 8200, 512, 4, (8, 3)), (5, 16380, 256, 1, (8, 4)), (17, 4096, 768, 1, (8, 2)),
+                                            (32, 2049, 4352, 2, (8, 2)), (33, 100, 512, 1, (9, 8))])
+def test_gemm_g16_tiles_of_16_rows(osc, fmt, M, N, K, r, kernel):
     """Every channel count of the 16-row kernel's workgroups (16 to 64: N picks it), one and two blocks of rows, ragged rows
     and channels, fewer lines than wavefronts and odd numbers of them, branch lines of zero to two; the first size past it."""
     X, table = wl.activations_persistent(8800 + M, M, K, r) if r else (wl.activations_diffuse(8800 + M, M, K), None)
@@ -114,5 +115,6 @@ def test_gemm_g16_tiles_of_16_rows(osc, fmt, M, N, K, r):
     ref = oracle.dual_gemm_g16(a[0], a[1], a[2] if r else None, w[0], w[1], oracle.gather_wl(W, oidx), fmt=fmt, x_tensor_scale=xts, w_tensor_scale=wts)
     for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
         Y = osc.osc_dual_gemm_g16(*q, Wp, N, K, len(oidx), fmt, xts, wts, ydt).float().cpu().numpy().astype(np.float64)
+        assert osc.osc_tuning_last_gemm() == kernel
         slack = 1e-3 * np.abs(ref).max() + (2.0 ** -8 * np.abs(ref) if bf else 0.0)
         assert (np.abs(Y - ref) <= slack).all(), (fmt, M, N, K, r, bf)

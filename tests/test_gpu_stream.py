@@ -56,6 +56,7 @@ def test_dual(osc, tuning, M, N, K, r):
         ref = oracle.dual_gemm(rq, rs, rb if r else None, wq, ws, oracle.gather_wl(W[c], oidx))
         for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
             close(osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), ydt)[:, c], ref, f"{M}x{N}x{K} r={r} ldb={ldb} bf16={bf}", bf)
+            assert osc.osc_tuning_last_gemm()[0] == 6
 
 
 @pytest.mark.parametrize("M,N,K", [(1, 40, 128), (16, 12288, 256), (33, 260, 4352), (64, 4096, 384), (32, 12288, 128), (9, 100, 16),
@@ -70,6 +71,7 @@ def test_8bit(osc, tuning, M, N, K):
     Wp = osc.osc_pack_weight_fp8(dev(W))
     for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
         close(osc.osc_fp8_gemm(X8, xs, Wp, N, K, y_dtype=ydt)[:, c], ref, f"fp8 {M}x{N}x{K} bf16={bf}", bf)
+        assert osc.osc_tuning_last_gemm()[0] == 6
     if K % 128 == 0:
         Xm, Xms = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_MXFP8)
         ref = oracle.mxfp8_gemm(*oracle.quantize_mxfp8(X), *oracle.quantize_mxfp8(W[c]))
@@ -194,6 +196,8 @@ def test_sixteen_wavefronts(osc, tuning, mode, M, N, K):
         q, Wp = osc.osc_quantize_act(X, None, osc.OSC_FMT_MXFP8), osc.osc_pack_weight_mxfp8(W)
         call = lambda: osc.osc_mxfp8_gemm(*q, Wp, N, K, y_dtype=osc.OSC_DT_F32)  # noqa: E731
     Y = call()
+    assert osc.osc_tuning_last_gemm() == (6, 16)
     tuning.gemm("1,3")
     Y0 = call()
+    assert osc.osc_tuning_last_gemm()[0] == 3
     assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max())
