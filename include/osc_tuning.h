@@ -16,7 +16,7 @@ enum {
                                       2 128 x 128, 3 64 x 128 */
     OSC_TUNE_GEMM_KERNEL = 1,      /* 0 staged, 1 DMA, 2 persistent, 3 skinny, 4 and 5 ring, 6 streaming, 7 flowing (ignored
                                       where a kernel cannot serve the shape) */
-    OSC_TUNE_GROUPED_ONE_TILE = 2, /* accepted, no effect: experts in large tiles always run on persistent workgroups */
+    OSC_TUNE_GROUPED_ONE_TILE = 2, /* accepted, no effect */
     OSC_TUNE_SWIGLU_TABLE = 3,     /* accepted, no effect: the SwiGLU fusions have one kernel each */
     OSC_TUNE_GEMM_KSPLIT = 4       /* accepted, no effect: no kernel splits the K loop of a small tile any more */
 };

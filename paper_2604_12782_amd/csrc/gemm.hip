@@ -2069,7 +2069,7 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     //  - tiles: operand rows that are whole 128-byte lines go to the DMA kernel, others to the staged kernel, with
     //    per-lane zero fill when rows are not whole 64-byte steps (not in MXFP8); 256-row tiles when they fill the chip,
     //    else 128 x 128, else 64 x 128;
-    //  - one problem of whole lines and five stages or more: the flowing kernel, or where its model says so 256 x 256
+    //  - one problem of whole lines and five stages or more (in one case four): the flowing kernel, or where its model says so 256 x 256
     //    tiles on the persistent kernel (more than one per CU) or the DMA kernel (dual path, at most one);
     //  - few output blocks: the weight-streaming kernel (whole lines);
     //  - few rows: the streaming kernel.
@@ -2103,7 +2103,15 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     const bool few_blocks = skinny_wgs <= 512 || (p.M <= 64 && skinny_wgs <= 1024);
     // (fewer than five stages: a tile is over before the ring has filled, 6493 x 640 x 512 FP8 10 us against 7.8 on the DMA
     // kernel's tiles)
-    if (lines && !grouped && !p.row_map && p.M >= 1 && p.N >= 1 && stages >= 5 && !few_rows && !few_blocks) {
+    const bool one_problem = lines && !grouped && !p.row_map && p.M >= 1 && p.N >= 1 && !few_rows && !few_blocks;
+    // (dual path, four stages, at most one tile of 64 x 128 per CU: all of them are asked for before the first product; against
+    // the DMA kernel's tiles of that size 512 x 4096 x 768 with a branch 6.2 -> 5.7 us, 768 x 2048 5.8 -> 5.6, 128 x 12288
+    // 6.0 -> 5.8, K = 1024 without a branch 6.0 -> 5.7, 5.6 -> 5.6 and 5.8 -> 5.8; FP8 5.4 -> 5.4, 5.1 -> 5.3, 5.2 -> 5.4)
+    if (MODE == MODE_DUAL && one_problem && stages == 4 && ((p.M + 63) / 64) * ((p.N + 127) / 128) <= ncu) {
+        kind = 7;
+        flow_tile = 3;
+    }
+    if (one_problem && stages >= 5) {
         // One problem: the flowing kernel with the tile that its cost model prefers, or tiles of 256 x 256.  Those read
         // LDS half as often per product, which is worth a higher clock, so they are ahead wherever their rounds are
         // filled as well (8192 x 4096 x 4096: 85 us against 85 to 90, K = 12288 MXFP8 310 against 335) and behind where
@@ -2146,9 +2154,16 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     // against 23.5; 85 rows each at four stages: 10.1 against 10.8), and so they are with few rows on one of many experts
     // (1024 rows of one: 10.1 and 8.5 us against 13.4 and 10.0; from 2048 rows on, 12.0 and 11.2 against 13.8 and 10.5, only
     // the first GEMM of a single expert is; 4096 rows of one 18.2 and 17.0 against 14.7 and 12.3).
+    // One to three stages a tile, against 256 x 256 tiles (more than one per CU; the ratio of the times depends on how full an
+    // expert's last tile is).  8 bits, two stages or more: from 160 rows an expert on (128 experts, us, those tiles -> here: 270 rows
+    // of 2048 x 384 FP8 101 -> 62, MXFP8 94 -> 61, 500 rows 122 -> 100 and 111 -> 98; below, 64 experts of 130 rows MXFP8 24.1 and
+    // 24.7).  Dual path, or one stage: where experts have a few rows more than whole tiles, on average or by the routing's spread
+    // (270 rows of 1536 x 512 with a branch, all alike 80 -> 57, drawn 69 -> 57, of 1024 x 128 FP8 40 -> 24; elsewhere a tile of 256
+    // rows is level or ahead by up to a quarter: 512 experts of 132 rows, dual 1536 x 512, 147 against 169).
     if (lines && grouped && p.E > 0 && p.M >= 1 && flow_fits(MODE, 0, stages, true, p.E)) {
         const int64_t least = p.E * ((p.N + 255) / 256);  // tiles if no expert has more than 128 rows
-        if (rows > 112 || (rows > 56 && stages >= 6) || (rows >= 12 && 2 * least >= 5 * ncu)) {
+        if (stages < 4 ? tm == 4 && t256 > ncu && rows > 160 && ((MODE != MODE_DUAL && stages > 1) || (rows + 8) % 256 < (stages == 1 ? 88 : 112))
+                       : rows > 112 || (rows > 56 && stages >= 6) || (rows >= 12 && 2 * least >= 5 * ncu)) {
             kind = 7;
             flow_tile = 0;
         }

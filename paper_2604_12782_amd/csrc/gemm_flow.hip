@@ -6,7 +6,7 @@ namespace osc {
 
 // ------------------------------------------------------------------------------------------
 // One persistent workgroup of eight wavefronts (two per SIMD) per CU walks a list of tiles.  A stage is 128 bytes of
-// every operand row, as in the DMA kernel; a ring of NSTG stages in LDS is filled by global->LDS DMA three to five
+// every operand row, as in the DMA kernel; a ring of NSTG stages in LDS is filled by global->LDS DMA three or four
 // stages ahead of the products, across tile borders, and a stage costs one barrier:
 //
 //   first half:   products on X (first half of stage T, registers)   | fragments of the second half -> Yf
@@ -34,8 +34,13 @@ namespace osc {
 // 8192 x 1024 x 4096: nothing covers a wavefront that waits for its request to be taken); results kept as bf16 and stored
 // during the next tile's stages (no change, though without any stores the kernel is 10 to 20 % faster); raised wave
 // priority around the products (4 to 7 % slower); fragments read in the first one or two slots (no change).
-// Figures against the kernels that had these calls stand beside the launcher's rule.
+// Figures against the kernels that had these calls stand beside the launcher's rule.  With LEAD stages a tile or fewer the load
+// cursor crosses several tiles: the FP8 tile scales then have more copies, and with one stage the row map is waited for.
 // ------------------------------------------------------------------------------------------
+
+// FP8: copies of the tile scales.  The load cursor fetches those of the tile that its next stage belongs to, LEAD + 1 stages
+// ahead of the products: the next tile, or with no more than LEAD stages a tile (FEW) up to the fourth from here.
+constexpr int tile_scale_copies(bool few) { return few ? 5 : 2; }
 
 // LDS of one ring slot: the operand rows of a stage, 128 bytes each, then its scale words in whole 1 KB requests
 template <int MODE, int BM, int BN>
@@ -48,7 +53,8 @@ struct FlowSlot {
     static constexpr int BYTES = ROWS + (SCL > SCL1 ? SCL : SCL1);
 };
 
-template <int MODE, int WM, int WN, int TM, int TN, int NSTG, bool LAG, bool GROUPED>
+// FEW: LEAD stages a tile or fewer.  A form of its own because the others run up to half a percent slower with its bookkeeping.
+template <int MODE, int WM, int WN, int TM, int TN, int NSTG, bool LAG, bool GROUPED, bool FEW>
 __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int ntiles) {
     constexpr bool DUAL = MODE == MODE_DUAL, FP8 = MODE == MODE_FP8, MX = MODE == MODE_MX8;
     constexpr int NW = WM * WN, RPP = 8 * NW, BM = 32 * TM * WM, BN = 32 * TN * WN;
@@ -60,20 +66,20 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
     constexpr int LEAD = LAG ? NSTG - 1 : NSTG;  // stages between the compute cursor and the load cursor
     static_assert(BM % RPP == 0 && BN % RPP == 0, "tile does not split over the wavefronts");
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
-    // behind the ring: FP8, the row and column scales of two tiles in turn; grouped, the experts' running tile
-    // counts and first rows; mapped rows, 64 entries per wavefront
-    float* const tsc = reinterpret_cast<float*>(lds + NSTG * Slot::BYTES);
-    int* const cum_l = reinterpret_cast<int*>(lds + NSTG * Slot::BYTES + (FP8 ? 2 * (BM + BN) * 4 : 0));  // [E + 1]
-    int* const off_l = cum_l + a.E + 1;                                                                   // [E + 1]
-    int* const map_l = off_l + a.E + 1;                                                                   // [NW][64]
-
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave / WN, wn = wave % WN, q = lane >> 5, r = lane & 31;
     const int Kg4 = ((a.K >> 5) + 3) >> 2;
     const uint32_t rowbytes = DUAL ? (uint32_t)a.K >> 1 : (uint32_t)a.K;
     const int nTA = (int)(rowbytes >> 7);
     const int nTB = DUAL ? (a.K_o * 2 + 127) >> 7 : 0;
-    const int nT = nTA + nTB;  // > LEAD (checked on the host)
+    const int nT = nTA + nTB;  // without FEW more than LEAD (the host sees to it)
+    // behind the ring: FP8, the row and column scales of NTSC tiles in turn; grouped, the experts' running tile
+    // counts and first rows; mapped rows, 64 entries per wavefront
+    constexpr int NTSC = tile_scale_copies(FEW);
+    float* const tsc = reinterpret_cast<float*>(lds + NSTG * Slot::BYTES);
+    int* const cum_l = reinterpret_cast<int*>(lds + NSTG * Slot::BYTES + (FP8 ? NTSC * (BM + BN) * 4 : 0));  // [E + 1]
+    int* const off_l = cum_l + a.E + 1;                                                                   // [E + 1]
+    int* const map_l = off_l + a.E + 1;                                                                   // [NW][64]
     const bool mapped = GROUPED && DUAL && a.row_map != nullptr;
     const int tiles_m = (a.M + BM - 1) / BM;
 
@@ -112,6 +118,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
     const int last = ltile + per + (xcd < extra ? 1 : 0);
     ltile += blockIdx.x >> 3;
     if (ltile >= last) return;
+    int left = FEW ? (last - ltile + step - 1) / step * nT : 0;  // stages from the compute cursor on
 
     auto find_tile = [&](int v) __attribute__((always_inline)) -> TilePos {
         TilePos p;
@@ -244,9 +251,10 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
             for (int i = 0; i < LB; ++i) vob[i] = gb[i] * (uint32_t)a.wlpitch + c8;
         }
         if (lT == nT && ltile + step < last) {
+            if (FEW && mapped && nT == 1) wait_vmcnt<0>();  // the map entries have been asked for since the last barrier
             ltile += step;
             ld = find_tile(ltile);
-            lpar ^= 1;
+            lpar = lpar + 1 == NTSC ? 0 : lpar + 1;
             enter_tile();
             if (mapped && ltile + step < last) request_map(find_tile(ltile + step));
         }
@@ -346,6 +354,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
     };
 
     // ---- prologue ----------------------------------------------------------------------------------------
+    int ctile = ltile, cpar = 0;  // (with LEAD stages or fewer the load cursor leaves the first tile here)
     if (mapped) {
         request_map(ld);
         wait_vmcnt<0>();
@@ -353,21 +362,23 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
     enter_tile();
     if (mapped && ltile + step < last) request_map(find_tile(ltile + step));
 #pragma unroll 1
-    for (int s = 0; s < LEAD; ++s) {
+    for (int s = 0; s < (FEW ? min(LEAD, left) : LEAD); ++s) {
 #pragma unroll
         for (int l = 0; l < NLD; ++l) load_one(l);
+        if (FEW && mapped && lT + 1 == nT) wait_vmcnt<0>();  // the next tile is entered before the loop's waits have covered its map entries
         finish_stage();
     }
-    wait_vmcnt<(LEAD - 1) * NLD>();
+    if (!FEW || left >= LEAD) wait_vmcnt<(LEAD - 1) * NLD>();
+    else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     read_first();
-    int ctile = ltile, cpar = 0;
 
 #pragma unroll 1
     for (;;) {
         const bool more = ctile + step < last;
-        const int L = more ? nT : nT - LEAD;  // stages during which there is still something to load
+        const int L = FEW ? min(nT, max(left - LEAD, 0)) : more ? nT : nT - LEAD;  // stages during which there is still something to load
+        if constexpr (FEW) left -= nT;
         int T = 0;
         if (!GROUPED || cur.m0 + wm * (TM * 32) < cur.row_end) {
 #pragma unroll
@@ -413,22 +424,23 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
             read_first();
         }
         if (!more) break;
-        cur = ld;
         ctile += step;
-        cpar ^= 1;
+        if constexpr (FEW) cur = find_tile(ctile);
+        else cur = ld;
+        cpar = cpar + 1 == NTSC ? 0 : cpar + 1;
     }
 }
 
 // ---- host ------------------------------------------------------------------------------------------
 
-static size_t flow_lds(int mode, int bm, int bn, int slots, bool grouped, int E) {
+static size_t flow_lds(int mode, int bm, int bn, int slots, bool few, bool grouped, int E) {
     const size_t scl = mode == MODE_FP8 ? 0 : mode == MODE_DUAL ? 256 : 128;
     const size_t together = align_up((bm + bn) / 32 * scl, 1024), apart = bm / 32 * scl + align_up(bn / 32 * scl, 1024);
-    return slots * ((size_t)(bm + bn) * 128 + (apart > together ? apart : together)) + (mode == MODE_FP8 ? (size_t)2 * (bm + bn) * 4 : 0) +
+    return slots * ((size_t)(bm + bn) * 128 + (apart > together ? apart : together)) + (mode == MODE_FP8 ? (size_t)tile_scale_copies(few) * (bm + bn) * 4 : 0) +
            (grouped ? (size_t)(2 * E + 2) * 4 + (mode == MODE_DUAL ? 8 * 256 : 0) : 0);
 }
 
-template <int MODE, int WM, int WN, int TM, int TN, int NSTG, bool LAG, bool GROUPED>
+template <int MODE, int WM, int WN, int TM, int TN, int NSTG, bool LAG, bool GROUPED, bool FEW>
 static int launch_cfg(KArgs a, hipStream_t st) {
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN, NW = WM * WN;
     static_assert(NW == 8, "two wavefronts per SIMD");
@@ -438,9 +450,9 @@ static int launch_cfg(KArgs a, hipStream_t st) {
     if (ntiles > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "gemm: too many tiles");
     const int ncu = cu_count();
     if (ncu <= 0) return fail(OSC_ERR_HIP, "gemm: cannot read the number of compute units");
-    const size_t smem = flow_lds(MODE, BM, BN, NSTG, GROUPED, a.E);
+    const size_t smem = flow_lds(MODE, BM, BN, NSTG, FEW, GROUPED, a.E);
     const int64_t grid = ntiles < ncu ? ntiles : ncu;  // one workgroup per CU, each walks its list of tiles
-    auto kern = gemm_flow_kernel<MODE, WM, WN, TM, TN, NSTG, LAG, GROUPED>;
+    auto kern = gemm_flow_kernel<MODE, WM, WN, TM, TN, NSTG, LAG, GROUPED, FEW>;
     static LdsReserved lds_reserved;
     if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved)) return rc;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * NW), smem, st, a, (int)ntiles);
@@ -466,7 +478,9 @@ constexpr int FLOW_COUNT = sizeof(FLOW_TILES) / sizeof(FLOW_TILES[0]);
 bool flow_fits(int mode, int tile, int stages, bool grouped, int E) {
     if (tile < 0 || tile >= FLOW_COUNT || (grouped && tile != 0)) return false;
     const FlowTile& f = FLOW_TILES[tile];
-    return stages > f.lead && flow_lds(mode, f.bm, f.bn, f.slots, grouped, E) <= 160 * 1024;
+    const bool few = stages <= f.lead;  // built for experts, and for the dual path on 64 x 128 tiles (two stages or more)
+    if (few && !(grouped ? stages >= 1 : mode == MODE_DUAL && tile == 3 && stages >= 2)) return false;
+    return flow_lds(mode, f.bm, f.bn, f.slots, few, grouped, E) <= 160 * 1024;
 }
 
 int flow_choose(int mode, int64_t M, int64_t N, int stages, int ncu, double* cost) {
@@ -488,12 +502,17 @@ int flow_choose(int mode, int64_t M, int64_t N, int stages, int ncu, double* cos
 
 template <int MODE>
 static int launch_mode(const KArgs& a, int tile, hipStream_t st) {
-    if (a.off) return launch_cfg<MODE, 2, 4, 2, 2, 3, false, true>(a, st);
+    const int stages = (MODE == MODE_DUAL ? a.K / 2 : a.K) / 128 + (MODE == MODE_DUAL ? (a.K_o * 2 + 127) / 128 : 0);
+    const bool few = stages <= FLOW_TILES[tile].lead;
+    if (a.off && few) return launch_cfg<MODE, 2, 4, 2, 2, 3, false, true, true>(a, st);
+    if (a.off) return launch_cfg<MODE, 2, 4, 2, 2, 3, false, true, false>(a, st);
+    if constexpr (MODE == MODE_DUAL)
+        if (few) return launch_cfg<MODE, 2, 4, 1, 1, 5, true, false, true>(a, st);
     switch (tile) {
-        case 0: return launch_cfg<MODE, 2, 4, 2, 2, 3, false, false>(a, st);
-        case 1: return launch_cfg<MODE, 4, 2, 1, 3, 3, false, false>(a, st);
-        case 2: return launch_cfg<MODE, 2, 4, 2, 1, 4, false, false>(a, st);
-        default: return launch_cfg<MODE, 2, 4, 1, 1, 5, true, false>(a, st);
+        case 0: return launch_cfg<MODE, 2, 4, 2, 2, 3, false, false, false>(a, st);
+        case 1: return launch_cfg<MODE, 4, 2, 1, 3, 3, false, false, false>(a, st);
+        case 2: return launch_cfg<MODE, 2, 4, 2, 1, 4, false, false, false>(a, st);
+        default: return launch_cfg<MODE, 2, 4, 1, 1, 5, true, false, false>(a, st);
     }
 }
 

@@ -97,11 +97,24 @@ def test_flow_several_tiles_per_workgroup(osc, tuning, tile, mode):
     check(osc, tuning, tile, mode, M, N, 256 * (lead + 1) if mode == "dual" else 128 * (lead + 3), 2 if mode == "dual" else 0, 7700 + tile)
 
 
+@pytest.mark.parametrize("stages,r", [(2, 0), (2, 1), (3, 4), (4, 0), (4, 2)])
+def test_flow_no_more_stages_than_the_lead(osc, tuning, stages, r):
+    """Dual path on 64 x 128 tiles, where the load cursor is up to three tiles ahead of the products: one tile, two, and six or seven
+    a workgroup.  (Experts of few stages: below.)"""
+    tile = 3
+    bm, bn, _ = TILES[tile]
+    K = 256 * (stages - (1 if r else 0))  # a branch of up to 64 channels is one stage
+    check(osc, tuning, tile, "dual", bm - 3, bn, K, r, 8000 + tile)
+    check(osc, tuning, tile, "dual", bm * 31, bn * 16 + 8, K, r, 8010 + tile)
+    check(osc, tuning, tile, "dual", bm * 180 - 17, bn * 9 - 40, K, r, 8020 + tile)
+
+
 def test_launcher_choice_agrees(osc, tuning):
     """The launcher's own choice (kernel, tile) over shapes on both sides of its rules, and its result against the DMA kernel."""
     for mode, M, N, K, r, chosen in [("dual", 1000, 1536, 4096, 1, (7, 3)), ("dual", 130, 4096, 1280, 2, (7, 3)), ("fp8", 300, 4104, 2048, 0, (7, 3)),
                                      ("mx8", 700, 1000, 1536, 0, (7, 3)), ("dual", 60, 33000, 1280, 0, (7, 3)), ("fp8", 40, 33000, 640, 0, (7, 3)),
-                                     ("mx8", 2100, 2048, 640, 0, (7, 0)), ("dual", 4200, 4096, 1536, 1, (2, 4))]:
+                                     ("mx8", 2100, 2048, 640, 0, (7, 0)), ("dual", 4200, 4096, 1536, 1, (2, 4)),
+                                     ("dual", 500, 4096, 768, 2, (7, 3)), ("dual", 1500, 1300, 768, 2, (1, 1)), ("dual", 300, 4096, 768, 0, (1, 1))]:
         call, _ = problem(osc, mode, M, N, K, r, 7800 + M)
         tuning.gemm(None)
         Y = call(osc.OSC_DT_F32)
@@ -114,21 +127,24 @@ def test_launcher_choice_agrees(osc, tuning):
 SIZES = [0, 1, 63, 64, 65, 127, 128, 129, 191, 192, 193, 256, 257, 385, 700, 0, 130, 0]
 
 
-@pytest.mark.parametrize("N", [264, 5000])
-def test_flow_experts(osc, tuning, N):
+@pytest.mark.parametrize("N,K,K2,r", [(264, 1024, 512, 2), (5000, 1024, 512, 2), (264, 256, 128, 0), (13000, 256, 128, 0), (264, 256, 256, 2), (9000, 512, 256, 0),
+                                      (264, 512, 384, 2), (9000, 512, 384, 2)])
+def test_flow_experts(osc, tuning, N, K, K2, r):
     """Experts of every size around the tile's borders and the half tile that is skipped, empty ones at the ends: fewer tiles than CUs
-    against the oracle; several per workgroup against the DMA kernel.  Rows beyond the offsets stay untouched."""
-    E, K, K2, r, tokens = len(SIZES), 1024, 512, 2, 700
+    against the oracle; several per workgroup against the DMA kernel; one stage a tile (the row map's entries are needed as soon as
+    they have been asked for), two, three and more than the lead.  Rows beyond the offsets stay untouched."""
+    E, tokens = len(SIZES), 700
     off = np.concatenate([[0], np.cumsum(SIZES)]).astype(np.int32)
     T = int(off[-1])
-    X, table = wl.activations_persistent(7900, tokens, K, r)
-    oidx = oracle.table_to_index(table)
+    X, table = wl.activations_persistent(7900, tokens, K, r) if r else (wl.activations_diffuse(7900, tokens, K), None)
+    oidx = oracle.table_to_index(table) if r else np.zeros(0, np.int32)
+    d_oidx = dev(oidx) if r else None
     row_map = wl.rng(7901).integers(0, tokens, T).astype(np.int32)
     X2 = wl.activations_diffuse(7902, T, K2)
-    q = osc.osc_quantize_act(dev(X), dev(oidx))
+    q = osc.osc_quantize_act(dev(X), d_oidx)
     q8, qm = osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_FP8_E4M3_TOKEN), osc.osc_quantize_act(dev(X2), None, osc.OSC_FMT_MXFP8)
     W, W2 = [wl.weights(7910 + e, N, K) for e in range(E)], [wl.weights(7950 + e, N, K2) for e in range(E)]
-    Wp = torch.cat([osc.osc_pack_weight(dev(w), dev(oidx)) for w in W])
+    Wp = torch.cat([osc.osc_pack_weight(dev(w), d_oidx) for w in W])
     Wp8, Wpm = torch.cat([osc.osc_pack_weight_fp8(dev(w)) for w in W2]), torch.cat([osc.osc_pack_weight_mxfp8(dev(w)) for w in W2])
     d_off = dev(off)
     calls = {"dual": lambda ydt, out=None: osc.osc_grouped_dual_gemm(*q, dev(row_map), d_off, T, Wp, N, K, len(oidx), ydt, out=out),
@@ -136,9 +152,9 @@ def test_flow_experts(osc, tuning, N):
              "mx8": lambda ydt, out=None: osc.osc_mxfp8_gemm(*qm, Wpm, N, K2, expert_offsets=d_off, y_dtype=ydt, out=out)}
     refs = {}
     if N < 1000:
-        a = oracle.quantize_mxfp4_osc(X, oidx, ldb=q[2].shape[1])
+        a = oracle.quantize_mxfp4_osc(X, oidx, ldb=q[2].shape[1] if r else 0)
         w = [oracle.quantize_mxfp4_osc(x)[:2] for x in W]
-        refs["dual"] = oracle.grouped_dual_gemm(a[0], a[1], a[2], row_map, off, np.stack([x[0] for x in w]), np.stack([x[1] for x in w]),
+        refs["dual"] = oracle.grouped_dual_gemm(a[0], a[1], a[2] if r else None, row_map, off, np.stack([x[0] for x in w]), np.stack([x[1] for x in w]),
                                                 np.stack([oracle.gather_wl(x, oidx) for x in W]))
         w = [oracle.quantize_fp8_rows(x) for x in W2]
         refs["fp8"] = oracle.grouped_fp8_gemm(*oracle.quantize_fp8_rows(X2), off, np.stack([x[0] for x in w]), np.stack([x[1] for x in w]))
@@ -159,3 +175,33 @@ def test_flow_experts(osc, tuning, N):
     out = torch.full((T, N), 7.0, dtype=torch.bfloat16, device="cuda")
     osc.osc_fp8_gemm(*q8, Wp8, N, K2, expert_offsets=short, y_dtype=osc.OSC_DT_BF16, out=out)
     assert bool((out[500:] == 7).all()) and not bool((out[:500] == 7).all())
+
+
+@pytest.mark.parametrize("mode,E,rows,N,K,chosen", [("dual", 128, 270, 1536, 512, (7, 0)), ("fp8", 128, 270, 2048, 384, (7, 0)), ("mx8", 128, 270, 1024, 256, (7, 0)),
+                                                    ("fp8", 128, 270, 1024, 128, (7, 0)), ("mx8", 128, 500, 2048, 384, (7, 0)), ("dual", 128, 150, 1536, 512, (1, 4)),
+                                                    ("mx8", 64, 130, 2048, 384, (1, 4)), ("dual", 32, 270, 1536, 1024, (7, 0))])
+def test_launcher_choice_for_experts(osc, tuning, mode, E, rows, N, K, chosen):
+    """Experts of one to four stages: 256-row tiles where those are ahead, the flowing kernel where they would start a few last rows
+    of every expert on a tile of their own; same numbers as the DMA kernel's small tiles."""
+    g = torch.Generator(device="cuda").manual_seed(8100 + rows)
+    draw = lambda hi, *shape: torch.randint(0, hi, shape, dtype=torch.uint8, device="cuda", generator=g)  # noqa: E731
+    sizes = torch.bincount(torch.randint(0, E, (E * rows,), device="cuda", generator=g), minlength=E)
+    off = torch.cat([torch.zeros(1, dtype=torch.int64, device="cuda"), sizes.cumsum(0)]).to(torch.int32)
+    T = E * rows
+    if mode == "dual":
+        Xq, W = draw(256, T, K // 2), draw(120, E * osc.osc_packed_weight_bytes(N, K, 0))
+        Xs = torch.full((osc.osc_act_scale_bytes(T, K),), 127, dtype=torch.uint8, device="cuda")
+        call = lambda: osc.osc_grouped_dual_gemm(Xq, Xs, None, None, off, T, W, N, K, 0, osc.OSC_DT_F32)  # noqa: E731
+    elif mode == "fp8":
+        Xq, Xs, W = draw(120, T, K), torch.ones(T, device="cuda"), draw(60, E * osc.osc_packed_weight_fp8_bytes(N, K))
+        call = lambda: osc.osc_fp8_gemm(Xq, Xs, W, N, K, expert_offsets=off, y_dtype=osc.OSC_DT_F32)  # noqa: E731
+    else:
+        Xq, Xs, W = draw(120, T, K), torch.full((osc.osc_act_scale_bytes(T, K),), 127, dtype=torch.uint8, device="cuda"), draw(120, E * osc.osc_packed_weight_mxfp8_bytes(N, K))
+        call = lambda: osc.osc_mxfp8_gemm(Xq, Xs, W, N, K, expert_offsets=off, y_dtype=osc.OSC_DT_F32)  # noqa: E731
+    Y = call()
+    assert osc.osc_tuning_last_gemm() == chosen
+    tuning.gemm("1,1")
+    Y0 = call()
+    assert osc.osc_tuning_last_gemm() == (1, 1)
+    rows_max = Y0.abs().amax(dim=1, keepdim=True)  # scale bytes drawn freely differ by many powers of two from channel to channel
+    assert bool(torch.isfinite(Y).all()) and bool(((Y - Y0).abs() <= 1e-5 * rows_max).all())
