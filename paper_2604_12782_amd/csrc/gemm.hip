@@ -445,7 +445,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_dma2_kernel(KArgs a) {
     // one 16-byte request (a request costs the memory pipeline the same whatever its width: three or four
     // per stage and workgroup instead of one per block and lane half).  Blocks past the last valid row or
     // channel repeat the last valid one; their rows are never stored.
-    const bool use16 = MODE == MODE_DUAL && !a.off && !a.row_map;
+    const bool use16 = MODE == MODE_DUAL && !a.off && !a.row_map && (reinterpret_cast<uintptr_t>(a.Xs) & 15) == 0;
     const int wave_u = __builtin_amdgcn_readfirstlane(wave);
     const uint8_t* sc16_src = nullptr;
     if (use16) {
@@ -2091,8 +2091,11 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     int kind = lines ? 1 : 0;  // 0 = staged kernel, 1 = DMA kernel, 2 = persistent pipelined kernel, 3 = skinny kernel,
     // 6 = streaming kernel, 7 = flowing kernel (4 and 5: the ring kernel, forced only)
     const int stages = (int)(rowbytes / 128) + (MODE == MODE_DUAL ? (p.K_o * 2 + 127) / 128 : 0);
+    // activation scales at any 4-byte address are legal: kernels that fetch them 16 bytes a lane (one problem on the persistent,
+    // flowing or ring kernel) are for 16-byte addresses, the DMA kernel takes the others word by word
+    const bool xs16 = MODE == MODE_FP8 || aligned(p.Xs, 16);
     // persistent kernel: one problem, at least three stages; rows past the last whole tile go to a second launch
-    const bool pipe_ok = lines && !grouped && !p.row_map && stages >= 3;
+    const bool pipe_ok = lines && !grouped && !p.row_map && stages >= 3 && xs16;
     if (pipe_ok && tm == 4 && t256 > 256) kind = 2;
     int flow_tile = -1;
     // launches that the rules for few rows further down take: no tile is looked for (a call's host time is what bounds them)
@@ -2103,7 +2106,7 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     const bool few_blocks = skinny_wgs <= 512 || (p.M <= 64 && skinny_wgs <= 1024);
     // (fewer than five stages: a tile is over before the ring has filled, 6493 x 640 x 512 FP8 10 us against 7.8 on the DMA
     // kernel's tiles)
-    const bool one_problem = lines && !grouped && !p.row_map && p.M >= 1 && p.N >= 1 && !few_rows && !few_blocks;
+    const bool one_problem = lines && !grouped && !p.row_map && p.M >= 1 && p.N >= 1 && xs16 && !few_rows && !few_blocks;
     // (dual path, four stages, at most one tile of 64 x 128 per CU: all of them are asked for before the first product; against
     // the DMA kernel's tiles of that size 512 x 4096 x 768 with a branch 6.2 -> 5.7 us, 768 x 2048 5.8 -> 5.6, 128 x 12288
     // 6.0 -> 5.8, K = 1024 without a branch 6.0 -> 5.7, 5.6 -> 5.6 and 5.8 -> 5.8; FP8 5.4 -> 5.4, 5.1 -> 5.3, 5.2 -> 5.4)
@@ -2209,7 +2212,7 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         if (k2 == 7) {  // the tile knob names one of the flowing kernel's own
             if (t_tile >= 0) flow_tile = t_tile;
             if (grouped) flow_tile = 0;
-            if (!lines || (p.row_map && !grouped) || !flow_fits(MODE, flow_tile, stages, grouped, p.E)) k2 = lines ? 1 : 0;
+            if (!lines || (p.row_map && !grouped) || (!grouped && !xs16) || !flow_fits(MODE, flow_tile, stages, grouped, p.E)) k2 = lines ? 1 : 0;
         }
         if (k2 == 6 && !(grouped ? stream_grp : stream_ok)) k2 = lines ? 1 : 0;
         if ((k2 == 1 || k2 == 2) && !lines) k2 = 0;
@@ -2221,7 +2224,7 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     if constexpr (MODE == MODE_DUAL) {
         // ring kernel (ids 4 and 5: with and without the two wavefront groups in anti-phase)
         const int t_kern = tuning(TUNE_GEMM_KERNEL);
-        const bool ring_ok = lines && !grouped && !p.row_map && (rowbytes / 64 + (p.K_o * 2 + 63) / 64) >= 3 &&
+        const bool ring_ok = lines && !grouped && !p.row_map && xs16 && (rowbytes / 64 + (p.K_o * 2 + 63) / 64) >= 3 &&
                              (p.K_o == 0 || a.bpitch % 64 == 0) && p.M >= 1;
         if ((t_kern == 4 || t_kern == 5) && ring_ok)
             return t_kern == 4 ? launch_ring<4, 2, 4, true>(a, st) : launch_ring<4, 2, 4, false>(a, st);

@@ -308,3 +308,31 @@ def test_wide_128x256_tiles_ragged(osc):
     for ydt, bf in ((osc.OSC_DT_BF16, True), (osc.OSC_DT_F32, False)):
         Y = osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), ydt)
         close(Y[sel], ref, f"128x256 tiles bf16={bf}", bf)
+
+
+# a shape for each: one round of 256 x 256 tiles and more on the persistent kernel, the flowing kernel, few rows, few blocks
+@pytest.mark.parametrize("cfg,M,N,K", [(None, 400, 4096, 1280), (None, 4400, 4096, 512), (None, 4096, 4096, 1536), (None, 16, 512, 1024), (None, 200, 600, 768),
+                                       ("4,2", 600, 520, 1024), ("0,7", 600, 520, 1024), ("3,7", 600, 520, 1024), ("4,4", 600, 520, 1024),
+                                       ("1,1", 600, 520, 1024), ("2,1", 600, 520, 1024), ("4,1", 600, 520, 1024)])
+def test_activation_scales_at_any_word(osc, tuning, cfg, M, N, K):
+    """Activation scales may start at any 4-byte address: same numbers (up to the order of the sums, where another kernel takes the
+    call) as from a 16-byte address, and no kernel that fetches them 16 bytes at a time."""
+    X, table = wl.activations_persistent(7800, M, K, 1)
+    d_oidx = dev(oracle.table_to_index(table))
+    W = dev(wl.weights(7801, N, K))
+    q, Wp = osc.osc_quantize_act(dev(X), d_oidx), osc.osc_pack_weight(W, d_oidx)
+    qm, Wm = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_MXFP8), osc.osc_pack_weight_mxfp8(W)
+    calls = {"dual": (q[1], lambda s: osc.osc_dual_gemm(q[0], s, q[2], Wp, N, K, K // 32, osc.OSC_DT_F32)),
+             "mxfp8": (qm[1], lambda s: osc.osc_mxfp8_gemm(qm[0], s, Wm, N, K, y_dtype=osc.OSC_DT_F32))}
+    for name, (scales, call) in calls.items():
+        tuning.gemm("1,1")
+        Y0 = call(scales)
+        tuning.gemm(cfg)
+        for words in (1, 2, 3):
+            buf = torch.full((scales.numel() + 16,), 0xff, dtype=torch.uint8, device="cuda")
+            view = buf[4 * words:4 * words + scales.numel()]
+            view.copy_(scales)
+            assert view.data_ptr() % 16 == 4 * words
+            Y = call(view)
+            assert osc.osc_tuning_last_gemm()[0] not in (2, 4, 7), (name, osc.osc_tuning_last_gemm())
+            assert float((Y - Y0).abs().max()) <= 1e-5 * float(Y0.abs().max()), (name, words)
