@@ -33,17 +33,12 @@ class _Tuning:
         self.osc = osc
 
     def gemm(self, cfg):
-        """cfg = "<tile rows / 64>,<kernel id>" (0 staged, 1 DMA, 2 persistent, 3 skinny, 4 and 5
-        ring, 6 streaming) or None.  A kernel that cannot serve a shape gives way to another."""
+        """cfg = "<tile>,<kernel id>" (0 staged, 1 DMA, 2 persistent, 3 skinny, 4 and 5 ring, 6 streaming, 7 flowing) or None;
+        the tile is rows / 64, of kernel 7 one of its own.  A kernel that cannot serve a shape gives way to another:
+        osc_tuning_last_gemm() tells."""
         tile, kern = (-1, -1) if cfg is None else map(int, cfg.split(","))
         self.osc.osc_tuning_set(self.osc.OSC_TUNE_GEMM_TILE, tile)
         self.osc.osc_tuning_set(self.osc.OSC_TUNE_GEMM_KERNEL, kern)
-
-    def gemm_ksplit(self, on):
-        self.osc.osc_tuning_set(self.osc.OSC_TUNE_GEMM_KSPLIT, -1 if on is None else int(on))
-
-    def grouped_one_tile(self, on):
-        self.osc.osc_tuning_set(self.osc.OSC_TUNE_GROUPED_ONE_TILE, -1 if on is None else int(on))
 
     def reset(self):
         for k in range(5):

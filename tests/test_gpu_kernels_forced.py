@@ -57,12 +57,10 @@ def test_dual_forced(osc, tuning, cfg, M, N, K, r):
 @pytest.mark.parametrize("M,N,K,r", [(300, 200, 1024, 2), (200, 300, 1280, 2), (64, 128, 2048, 1), (130, 260, 4096, 4),
                                      (513, 520, 1024, 0), (1, 40, 2304, 3), (2048, 1024, 4096, 2)])
 @pytest.mark.parametrize("tile", ["1,1", "2,1"])
-def test_dual_small_tiles_with_k_split(osc, tuning, tile, M, N, K, r):
-    """64 x 128 and 128 x 128 tiles with the reduction axis split over two groups of wavefronts (forced on:
-    the launcher itself takes it only when the launch has at most one tile per CU): even and odd numbers
-    of stages, a branch of one to eight stages, ragged tiles in both directions."""
+def test_dual_small_tiles(osc, tuning, tile, M, N, K, r):
+    """64 x 128 and 128 x 128 tiles of the DMA kernel: even and odd numbers of stages, a branch of one to eight stages, ragged
+    tiles in both directions."""
     tuning.gemm(tile)
-    tuning.gemm_ksplit(1)
     X, table = wl.activations_persistent(7060 + M, M, K, r) if r else (wl.activations_diffuse(7060 + M, M, K), None)
     W = wl.weights(7160 + N, N, K)
     oidx = oracle.table_to_index(table) if r else np.zeros(0, np.int32)
@@ -76,21 +74,15 @@ def test_dual_small_tiles_with_k_split(osc, tuning, tile, M, N, K, r):
     sel = torch.from_numpy(rows).cuda()
     for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
         Y = osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), ydt)
-        close(Y[sel], ref, f"k split {M}x{N}x{K} r={r} bf16={bf}", bf)
-    # the same launch without the split gives the same numbers up to the order of two partial sums
-    tuning.gemm_ksplit(0)
-    Y0 = osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), osc.OSC_DT_F32)
-    tuning.gemm_ksplit(1)
-    Y1 = osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), osc.OSC_DT_F32)
-    assert float((Y0 - Y1).abs().max()) <= 1e-5 * float(Y0.abs().max())
+        assert osc.osc_tuning_last_gemm() == (1, int(tile[0]))
+        close(Y[sel], ref, f"{tile} {M}x{N}x{K} r={r} bf16={bf}", bf)
 
 
 @pytest.mark.parametrize("M,N,K", [(300, 200, 1024), (200, 300, 640), (64, 128, 2048), (513, 520, 896), (2048, 1024, 4096)])
 @pytest.mark.parametrize("tile", ["1,1", "2,1"])
-def test_fp8_small_tiles_with_k_split(osc, tuning, tile, M, N, K):
-    """The per-token FP8 GEMM on 64 x 128 and 128 x 128 tiles with the K split forced on: even and odd stage counts."""
+def test_fp8_small_tiles(osc, tuning, tile, M, N, K):
+    """The per-token FP8 GEMM on 64 x 128 and 128 x 128 tiles of the DMA kernel: even and odd stage counts."""
     tuning.gemm(tile)
-    tuning.gemm_ksplit(1)
     X = wl.activations_diffuse(7250 + M, M, K)
     W = wl.weights(7251 + N, N, K)
     X8, xs = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_FP8_E4M3_TOKEN)
@@ -100,7 +92,30 @@ def test_fp8_small_tiles_with_k_split(osc, tuning, tile, M, N, K):
     sel = torch.from_numpy(rows).cuda()
     for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
         Y = osc.osc_fp8_gemm(X8, xs, osc.osc_pack_weight_fp8(dev(W)), N, K, y_dtype=ydt)
-        close(Y[sel], oracle.fp8_gemm(r8, rs, w8, ws), f"fp8 k split {M}x{N}x{K} bf16={bf}", bf)
+        assert osc.osc_tuning_last_gemm() == (1, int(tile[0]))
+        close(Y[sel], oracle.fp8_gemm(r8, rs, w8, ws), f"fp8 {tile} {M}x{N}x{K} bf16={bf}", bf)
+
+
+def test_knobs_without_effect(osc, tuning):
+    """The knobs that are accepted for kernels that are gone leave the choice and every bit of the results alone."""
+    M, N, K = 300, 264, 1024
+    X, W = dev(wl.activations_diffuse(7260, M, K)), dev(wl.weights(7261, N, K))
+    d_oidx = torch.arange(0, K, 32, dtype=torch.int32, device="cuda")
+    off = torch.tensor([0, 130, 130, M], dtype=torch.int32, device="cuda")
+    rows = torch.arange(M, dtype=torch.int32, device="cuda")
+    q, Wp = osc.osc_quantize_act(X, d_oidx), osc.osc_pack_weight(W, d_oidx)
+    q8, W8 = osc.osc_quantize_act(X, None, osc.OSC_FMT_FP8_E4M3_TOKEN), osc.osc_pack_weight_fp8(W)
+    calls = [lambda: osc.osc_dual_gemm(*q, Wp, N, K, K // 32), lambda: osc.osc_fp8_gemm(*q8, W8, N, K),
+             lambda: osc.osc_grouped_dual_gemm(*q, rows, off, M, Wp.repeat(3), N, K, K // 32),
+             lambda: osc.osc_fp8_gemm(*q8, W8.repeat(3), N, K, expert_offsets=off),
+             lambda: osc.osc_swiglu_quantize_act(X, X)[0], lambda: osc.osc_swiglu_quantize_act_fp8(X, X)[0]]
+    for call in calls:
+        want, kernel = call(), osc.osc_tuning_last_gemm()
+        for knob in (osc.OSC_TUNE_GROUPED_ONE_TILE, osc.OSC_TUNE_SWIGLU_TABLE, osc.OSC_TUNE_GEMM_KSPLIT):
+            for value in (0, 1):
+                osc.osc_tuning_set(knob, value)
+                assert torch.equal(call(), want) and osc.osc_tuning_last_gemm() == kernel
+            osc.osc_tuning_set(knob, -1)
 
 
 @pytest.mark.parametrize("M,N,K", [(256, 512, 768), (300, 256, 384), (4392, 4096, 384), (2560, 7168, 640)])
@@ -238,9 +253,9 @@ def test_output_into_wider_and_odd_buffers(osc, tuning, cfg):
 
 @pytest.mark.parametrize("cfg,K,K2", [("4,1", 512, 384), ("2,1", 512, 384), ("1,1", 512, 384), ("1,0", 1056, 400), ("2,0", 1056, 400)])
 def test_grouped_with_skewed_experts(osc, tuning, cfg, K, K2):
-    """Experts of 0, 1, 63 ... 700 rows, sizes on both sides of every tile border, through the
-    256-row tiles with their 64-row remainder pass (4,1) and the smaller tiles: dual path with a row
-    map, per-token FP8 and MXFP8; staged (,0) with rows that are not whole lines."""
+    """Experts of 0, 1, 63 ... 700 rows, sizes on both sides of every tile border, through the DMA
+    kernel's 256-row tiles (4,1) and the smaller ones: dual path with a row map, per-token FP8 and
+    MXFP8; staged (,0) with rows that are not whole lines."""
     tuning.gemm(cfg)
     sizes = [0, 1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 383, 384, 385, 700, 0, 130]
     E = len(sizes)
@@ -263,6 +278,7 @@ def test_grouped_with_skewed_experts(osc, tuning, cfg, K, K2):
     ref = oracle.grouped_dual_gemm(rq, rs, rb, row_map, off, np.stack(wq), np.stack(wsc), np.stack(wlr))
     for ydt, bf in ((osc.OSC_DT_F32, False), (osc.OSC_DT_BF16, True)):
         Y = osc.osc_grouped_dual_gemm(Xq, Xs, B, dev(row_map), dev(off), T, Wp, N, K, len(oidx), ydt)
+        assert osc.osc_tuning_last_gemm() == (int(cfg[2]), int(cfg[0]))
         close(Y, ref, f"grouped dual {cfg} bf16={bf}", bf)
     # 8-bit forms: rows in expert order (no row map in these entry points); MXFP8 rows are whole lines
     mx = K2 % 128 == 0
@@ -291,9 +307,9 @@ def test_grouped_with_skewed_experts(osc, tuning, cfg, K, K2):
         close(osc.osc_mxfp8_gemm(Xm, Xms, Wpm, N, K2, expert_offsets=dev(off), y_dtype=osc.OSC_DT_BF16), refm, "grouped mxfp8 " + cfg, True)
 
 
-def test_wide_128x256_tiles_ragged(osc):
-    """4100 x 2000: the launcher's own choice here is 128x256 tiles on eight wavefronts, with a ragged
-    last tile in both directions; a row of every fourth m-tile and the borders against the oracle."""
+def test_launcher_takes_256_row_dma_tiles_for_few_stages(osc):
+    """4100 x 2000 at three stages: the launcher's own choice is 256 x 256 tiles of the DMA kernel on eight wavefronts, with a ragged
+    last tile in both directions; a row of every fourth 128 and the borders against the oracle."""
     M, N, K, r = 4100, 2000, 512, 2
     X, table = wl.activations_persistent(7600, M, K, r)
     W = wl.weights(7601, N, K)
@@ -307,7 +323,8 @@ def test_wide_128x256_tiles_ragged(osc):
     sel = torch.from_numpy(rows).cuda()
     for ydt, bf in ((osc.OSC_DT_BF16, True), (osc.OSC_DT_F32, False)):
         Y = osc.osc_dual_gemm(Xq, Xs, B, Wp, N, K, len(oidx), ydt)
-        close(Y[sel], ref, f"128x256 tiles bf16={bf}", bf)
+        assert osc.osc_tuning_last_gemm() == (1, 4)
+        close(Y[sel], ref, f"256-row tiles bf16={bf}", bf)
 
 
 # a shape for each: one round of 256 x 256 tiles and more on the persistent kernel, the flowing kernel, few rows, few blocks
