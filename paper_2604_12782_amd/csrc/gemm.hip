@@ -28,7 +28,7 @@
 //                      64x128 on four;
 //   gemm_pipe2_kernel  the same data path, persistent workgroups, slot-pinned instruction order,
 //                      early buffer release; one problem (dual path, FP8 or MXFP8) of more than one whole
-//                      256x256 tile per CU (a ragged row tail goes to the DMA kernel);
+//                      256x256 tile per CU (a ragged row tail is a launch of its own, its kernel chosen like any other's);
 //   gemm_stream_kernel few rows: single problems of up to 16 (more where N is small), experts of up to eight on
 //                      average and a few hundred in all; 16-row instructions, any legal row length;
 //   gemm_skinny_kernel other launches of up to 64 rows or of at most 512 blocks of 32x32 outputs: one
@@ -1210,16 +1210,11 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
 }
 
 template <int MODE, int TM, int TN, int WN = 2>
-static int launch_pipe2(KArgs a, int64_t rows_total, bool grouped, hipStream_t st) {
+static int launch_pipe2(KArgs a, hipStream_t st) {
     constexpr int BM = 64 * TM, BN = 32 * TN * WN;
     const size_t smem = (size_t)(BM + BN) * 128 * 2 + (MODE != MODE_FP8 ? (size_t)(BM + BN) / 32 * 256 * 2 : (size_t)(BM + BN) * 4 * 2);
     a.tiles_n = (int)((a.N + BN - 1) / BN);
-    int64_t tiles_m = (rows_total + BM - 1) / BM;
-    if (grouped) {  // upper bounds, whole rounds of the 8 XCDs
-        tiles_m += a.E;  // one ragged tile each
-        tiles_m = (tiles_m + 7) / 8 * 8;
-    }
-    const int64_t ntiles = tiles_m * a.tiles_n;
+    const int64_t ntiles = (int64_t)((a.M + BM - 1) / BM) * a.tiles_n;
     if (ntiles <= 0) return OSC_OK;
     if (ntiles > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "gemm: too many tiles");
     const int ncu = cu_count();
@@ -2256,10 +2251,10 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         }
         a.M = (int)m_full;
         if constexpr (MODE == MODE_DUAL) {
-            if (tm == 4) return launch_pipe2<MODE_DUAL, 4, 4>(a, m_full, grouped, st);
-            return launch_pipe2<MODE_DUAL, 2, 2>(a, m_full, grouped, st);
+            if (tm == 4) return launch_pipe2<MODE_DUAL, 4, 4>(a, st);
+            return launch_pipe2<MODE_DUAL, 2, 2>(a, st);
         } else {
-            return launch_pipe2<MODE, 4, 4>(a, m_full, grouped, st);
+            return launch_pipe2<MODE, 4, 4>(a, st);
         }
     }
 

@@ -129,8 +129,8 @@ __device__ __forceinline__ TilePos tile_at(const KArgs& a, int tile) {
     return p;
 }
 
-// LDS_SCALES (FP8, tiles entirely inside Y): the row scales of the tile's BM rows and the column scales of
-// its BN columns are read from `tile_scales` in LDS (BM + BN floats) instead of global memory.
+// LDS_SCALES (FP8): the row scales of the tile's BM rows and the column scales of its BN columns are read from
+// `tile_scales` in LDS (all BM + BN floats, past the end of Y any values) instead of global memory.
 // WM x WN wavefronts of TM x TN blocks of 32 x 32.
 template <int MODE, int TM, int TN, int WN = 2, bool LDS_SCALES = false, int WM = 2>
 __device__ __forceinline__ void store_result(const KArgs& a, const TilePos& tp, v16f (&acc)[TM][TN],
