@@ -3,6 +3,7 @@ and rejects bad arguments on the host before anything is launched (no GPU needed
 import ctypes as C
 import os
 import re
+import sys
 
 import numpy as np
 import pytest
@@ -234,3 +235,25 @@ def test_g16_arguments(lib):
     assert g(FAKE, FAKE, 1.0, FAKE, 40, FAKE, 1.0, 4, 64, 256, 16, 0, FAKE, 0, 64, None) == -4  # ldb % 64
     assert lib.osc_packed_weight_g16_bytes(64, 256, 16) > 64 * 128 + 64 * 16 + 64 * 64 * 2
     assert lib.osc_packed_weight_g16_bytes(64, 100, 0) == 0
+
+
+def test_bench_line_stays_short():
+    """A caller that keeps the last 2000 characters of the benchmark's output gets its line whole."""
+    import json
+    sys.path.insert(0, ROOT)
+    import bench
+    f = 123456.7891
+    roof = {"bound": "mfma", "achieved": f, "peak": f, "unit": "TFLOP/s", "frac": 0.1234}
+    out = {"metric": "OSC linear TFLOP/s & % MXFP4 MFMA peak vs FP8 W8A8, Qwen3-8B shapes", "value": f, "unit": "TFLOP/s", "n_gpus": 1,
+           "steps": 1000, "warmup": 100, "ms_per_step": f, "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
+           "dtype": "mxfp4 x mxfp4 + bf16 x bf16, f32 accumulate, bf16 out", "data": "synthetic",
+           "config": {"workload": "x" * 160, "tokens": 8192, "K": 4096, "K_o": 256},
+           "roofline": {**roof, "traffic": 123456789.0, "kernel": "dual-path GEMM M=8192 N=4096 K=4096 K_o=256", "avg_ms": f,
+                        "avg_ms_single_launch_events_in_step": f},
+           "frac_mxfp4_peak_whole_step": 0.1234, "quant_roofline": roof, "shapes": {"row": "x" * 50000},
+           "fp8_w8a8": {"ms_per_step": f, "tflops": f, "speedup_osc_over_fp8": 1.234, "alternating_ms": {"osc": f, "fp8": f},
+                        "model_speedup_compute_bound": 1.6},
+           "cpu_baseline": {"value": 0.0038595088197528, "unit": "TFLOP/s", "cores": 16, "kind": "oracle", "sample": "x" * 270}}
+    line = bench.headline(out)
+    got = json.loads(line)
+    assert len(line) < 2000 and "shapes" not in got and got["value"] == f and set(got["config"]) == {"workload", "tokens", "K", "K_o"}
