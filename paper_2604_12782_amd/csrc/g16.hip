@@ -218,7 +218,7 @@ struct G16Args {
 };
 
 // ------------------------------------------------------------------------------------------
-// Streaming GEMM, up to 16 rows (32 where that leaves CUs idle).  A workgroup owns 16 rows of X and 16 NT output
+// Streaming GEMM, up to 16 rows (32 where that leaves CUs idle: rule below).  A workgroup owns 16 rows of X and 16 NT output
 // channels; its NW wavefronts take the 128-byte lines of the reduction axis (256 four-bit channels = 16 scale blocks
 // per row and line, then the bf16 lines of the branch) in turn and never synchronise until the end.  A wavefront loads
 // the next line (eight lanes per row) into one of two register sets while it takes the current one through a strip of
@@ -231,7 +231,7 @@ struct G16Args {
 // tokens, made that twice what it has to be, on 384 workgroups for 256 CUs; 16 rows and 48 channels are half of it and
 // one workgroup per CU at N = 12288.  16 tokens, weights from HBM, us, wide kernel below -> this one:
 //   12288 x 4096  NVFP4 13.1 -> 8.8, E8M0 11.4 -> 8.5      4096 x 12288  15.2 -> 9.9, 13.9 -> 9.7      4096 x 4096  6.9 -> 4.9, 6.1 -> 4.8
-// and 32 tokens: 4096 x 4096  7.4 -> 6.1, 6.7 -> 5.9; but 12288 x 4096 from the last-level cache 11.8 -> 12.5 and 9.9 -> 11.8,
+// and 32 tokens: 4096 x 4096  8.5 -> 7.0, 7.9 -> 6.8; but 12288 x 4096 from the last-level cache 11.8 -> 12.5 and 9.9 -> 11.8,
 // and 33 to 128 tokens in tiles of 32 or 64 rows 1.0 to 1.3 times slower: these stay on the wide kernel.
 // ------------------------------------------------------------------------------------------
 template <int FMT, int NT, int NW>
@@ -239,7 +239,11 @@ __global__ void __launch_bounds__(64 * NW) gemm_g16_kernel(G16Args a) {
     constexpr int MT = 1;  // 16-row tiles of X
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int q = lane >> 4, r = lane & 15;
-    const int n0 = blockIdx.x * (16 * NT), m0 = blockIdx.y * (16 * MT);
+    // two blocks of rows: workgroups b and b + 8, which run on the same die, share the weights of a strip
+    const bool two = a.M > 16 * MT;
+    const int strip_n = two ? (int)(blockIdx.x >> 4) * 8 + (int)(blockIdx.x & 7) : (int)blockIdx.x;
+    const int n0 = strip_n * (16 * NT), m0 = two ? (int)(blockIdx.x >> 3 & 1) * (16 * MT) : 0;
+    if (n0 >= a.N) return;  // (the grid is whole groups of eight strips)
     const uint32_t rowbytes = (uint32_t)a.K >> 1, srow = (uint32_t)a.K >> 4;
     const int nL = (int)(rowbytes >> 7);
     const int nLT = nL + ((a.K_o * 2 + 127) >> 7);
@@ -416,15 +420,18 @@ __global__ void __launch_bounds__(64 * NW) gemm_g16_kernel(G16Args a) {
 
 template <int FMT, int NT, int NW>
 static int launch_g16(const G16Args& a, hipStream_t st) {
-    const dim3 grid((unsigned)((a.N + 16 * NT - 1) / (16 * NT)), (unsigned)((a.M + 15) / 16));
-    hipLaunchKernelGGL((gemm_g16_kernel<FMT, NT, NW>), grid, dim3(64 * NW), 0, st, a);
+    const unsigned strips = (unsigned)((a.N + 16 * NT - 1) / (16 * NT)), grid = a.M > 16 ? (strips + 7) / 8 * 16 : strips;  // M <= 32
+    hipLaunchKernelGGL((gemm_g16_kernel<FMT, NT, NW>), dim3(grid), dim3(64 * NW), 0, st, a);
     note_gemm(GEMM_G16_ROWS16, NT);
     return check_launch("gemm_g16_kernel");
 }
 
 // Channels / 16 of a workgroup: the smallest ceil(workgroups / CUs) x (1 + NT), the smaller one among equals (a launch
-// lasts as long as the CU with the most workgroups, a workgroup as long as its expansion takes).  0: more than 16 rows
-// that would give a CU more than one workgroup, where the wide kernel is ahead.
+// lasts as long as the CU with the most workgroups, a workgroup as long as its expansion takes).  0: the wide kernel, which
+// expands as many rows for 32 of X as two row blocks here and the weights once: more than 16 rows, where a CU would get more
+// than one workgroup or one of more than 32 channels (32 rows, wide -> here, us, weights cached and from HBM: E8M0 2048 x 4096
+// 5.9 -> 4.0 and 6.3 -> 5.0, 4096 x 4096 6.1 -> 5.9 and 7.9 -> 6.8; 6144 x 8192 9.3 and 11.7, 13.4 and 14.1; 8192 x 4096 6.9 and 8.8,
+// 8.7 and 10.5; NVFP4 8.1 and 9.5, 9.6 and 11.0; very long rows of E8M0 gain from HBM only: 4096 x 12288 12.0 and 12.5, 17.4 -> 15.1).
 static int g16_rows16_tile(int64_t M, int64_t N, int ncu) {
     int best = 1;
     int64_t best_cost = INT64_MAX, best_per = 0;
@@ -436,7 +443,7 @@ static int g16_rows16_tile(int64_t M, int64_t N, int ncu) {
             best = nt;
         }
     }
-    return M <= 16 || (M <= 32 && best_per == 1) ? best : 0;
+    return M <= 16 || (M <= 32 && best_per == 1 && best <= 2) ? best : 0;
 }
 
 template <int FMT>

@@ -99,10 +99,13 @@ def test_decode_shape_of_the_density_sweep(osc, fmt, xts, wts):
 @pytest.mark.parametrize("fmt", [0, 1])
 @pytest.mark.parametrize("M,N,K,r,kernel", [(1, 16, 256, 0, (8, 1)), (16, 48, 512, 1, (8, 1)), (15, 12280, 256, 2, (8, 3)), (16, 4100, 2304, 1, (8, 2)),
                                             (7, 8200, 512, 4, (8, 3)), (5, 16380, 256, 1, (8, 4)), (17, 4096, 768, 1, (8, 2)),
-                                            (32, 2049, 4352, 2, (8, 2)), (33, 100, 512, 1, (9, 8))])
+                                            (32, 2049, 4352, 2, (8, 2)), (33, 100, 512, 1, (9, 8)),
+                                            (17, 16 * 9 + 3, 1280, 1, (8, 1)), (32, 40, 512, 2, (8, 1)), (32, 6144, 512, 1, (9, 8)), (17, 8192, 512, 1, (9, 8)),
+                                            (32, 3001, 2048, 1, (8, 2))])
 def test_gemm_g16_tiles_of_16_rows(osc, fmt, M, N, K, r, kernel):
-    """Every channel count of the 16-row kernel's workgroups (16 to 64: N picks it), one and two blocks of rows, ragged rows
-    and channels, fewer lines than wavefronts and odd numbers of them, branch lines of zero to two; the first size past it."""
+    """Every channel count of the 16-row kernel's workgroups (16 to 64: N picks it), one and two blocks of rows (in strips that eight
+    does and does not divide), ragged rows and channels, fewer lines than wavefronts and odd numbers of them, branch lines of zero
+    to two; the first size past it, and two blocks of rows that would take workgroups of more than 32 channels."""
     X, table = wl.activations_persistent(8800 + M, M, K, r) if r else (wl.activations_diffuse(8800 + M, M, K), None)
     W = wl.weights(8801 + N, N, K)
     oidx = oracle.table_to_index(table) if r else np.zeros(0, np.int32)
