@@ -468,10 +468,11 @@ int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, i
     // fixed grid at every size of whole segments (8192 x 12288: 79 us, a grid of 8192 86 us, of 2048 92 us).
     // Rows of less than a segment are the exception.
     const int64_t flat_wg = (M * nchunk + 4 * SEG_CHUNKS - 1) / (4 * SEG_CHUNKS) + 7;
-    // All rows' chunks in one line where segments would leave a fifth of the lanes or more idle (us: 32768 x 512 22.3 -> 16.9,
-    // x 640 23.6 -> 20.8, x 768 25.8 -> 23.7, 8192 x 1152 13.4 -> 11.6, 4096 x 3200 14.8 -> 14.3; beyond: 2000 x 1920 5.7 -> 6.1,
-    // 4096 x 11136 39 -> 44)
-    if (K % 128 == 0 && K >= 512 && 4 * nseg * SEG_CHUNKS >= 5 * nchunk && M * nchunk < ((int64_t)1 << 30) && flat_wg <= MAX_GRID) {
+    // All rows' chunks in one line where segments would leave a fifth of the lanes or more idle, and lanes for a thousand segments
+    // in all (us: 32768 x 512 22.3 -> 16.9, x 640 23.6 -> 20.8, x 768 25.8 -> 23.7, 8192 x 1152 13.4 -> 11.6, 4096 x 3200
+    // 14.8 -> 14.3, 2000 x 512 3.5 -> 3.2; beyond: 2000 x 1920 5.7 -> 6.1, 4096 x 11136 39 -> 44; with fewer rows idle lanes cost
+    // nothing and the division per wavefront does: 32 x 512 2.65 -> 2.86, 512 x 768 3.0 -> 3.3, 1000 x 2304 4.4 -> 4.5)
+    if (K % 128 == 0 && K >= 512 && 4 * nseg * SEG_CHUNKS >= 5 * nchunk && M * (nseg * SEG_CHUNKS - nchunk) >= 1000 * SEG_CHUNKS && M * nchunk < ((int64_t)1 << 30) && flat_wg <= MAX_GRID) {
         const unsigned wgs = (unsigned)(flat_wg / 8 * 8);
         hipLaunchKernelGGL(swiglu_quant_mxfp8_flat_kernel, dim3(wgs), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, Xq, Xs, Yn);
         return check_launch("swiglu_quant_mxfp8_flat_kernel");

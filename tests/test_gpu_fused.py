@@ -224,10 +224,12 @@ def test_fused_row_forms(osc, K, r):
         assert not r or torch.equal(bb, B[a:b])
 
 
-@pytest.mark.parametrize("M,K", [(1, 512), (33, 640), (37, 768), (130, 1152), (65, 2304), (5, 3200), (1030, 768)])
+@pytest.mark.parametrize("M,K", [(1, 512), (33, 640), (37, 768), (130, 1152), (65, 2304), (5, 3200), (1030, 768), (1999, 512), (2000, 512), (2001, 512), (2675, 640),
+                                 (4001, 768), (1150, 1152), (1337, 2304), (1147, 3200)])
 def test_swiglu_mxfp8_rows_in_one_line(osc, M, K):
-    """Rows of whole 128-channel words that segments of 1024 would leave lanes idle on: wavefronts that cover one, two and three
-    rows, a last one that ends past the last row, against the oracle's fixed sequence and quantiser, from the halves of one buffer."""
+    """Rows of whole 128-channel words that segments of 1024 would leave lanes idle on, few of them (in segments) and many (in one
+    line, from 2000 rows of 512 channels on): wavefronts that cover one, two and three rows, a last one that ends
+    past the last row, against the oracle's fixed sequence and quantiser, from the halves of one buffer."""
     gen = wl.rng(1400 + M + K)
     H = to_bf16_bits((gen.standard_normal((M, 2 * K)) * 2).astype(np.float32))
     d = dev(H).view(torch.bfloat16) if dev(H).dtype != torch.bfloat16 else dev(H)
