@@ -2148,10 +2148,14 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     // Against 256-row tiles with a second launch for what overran them, or 64 x 128 tiles (us, 128 experts of 1536 x 2048
     // and 2048 x 768, MXFP8): 256 rows an expert 117 -> 103 and 94 -> 79, 128 rows 85 -> 74 and 67 -> 56, 64 rows
     // 64 -> 48 and 52 -> 39, 20 rows 43 -> 42 and 36.5 -> 34.  Few rows of few experts leave CUs without a tile or with
-    // two, where the 64 x 128 tiles, three to a CU, are up to 15 % ahead (64 experts of 1280 x 2048, 12 rows each: 19.6
-    // against 23.5; 85 rows each at four stages: 10.1 against 10.8), and so they are with few rows on one of many experts
+    // two, where the DMA kernel's small tiles, two or three to a CU, are ahead (64 experts of 1280 x 2048, 12 rows each: 19.6
+    // against 23.5), and so they are with few rows on one of many experts
     // (1024 rows of one: 10.1 and 8.5 us against 13.4 and 10.0; from 2048 rows on, 12.0 and 11.2 against 13.8 and 10.5, only
-    // the first GEMM of a single expert is; 4096 rows of one 18.2 and 17.0 against 14.7 and 12.3).
+    // the first GEMM of a single expert is; 4096 rows of one 18.2 and 17.0 against 14.7 and 12.3).  Where the lines lie (us, flowing
+    // kernel / 64 x 128 / 128 x 128 tiles): 0.55 flowing tiles per CU, 0.45 from six stages on (eight experts of 1024 x 1024, six
+    // stages: 160 rows, 0.25, 10.5 / 7.4 / 8.3; 330 rows, 0.38, 10.6 / 10.9 / 8.5; 16 of 200 rows, 0.5, 10.7 / 12.6 / 9.4, of 330 rows,
+    // 0.75, 11.0 / 17.0 / 12.6); up to 112 rows, where a tile is half empty, and short of eight stages one tile per CU (64 experts of
+    // 80 rows 15.3 / 22.7 / 13.5, of 160 rows 21.4 / 32.0 / 26.5).  Of the small tiles 64 x 128 as long as they are about one to a CU.
     // One to three stages a tile, against 256 x 256 tiles (more than one per CU; the ratio of the times depends on how full an
     // expert's last tile is).  8 bits, two stages or more: from 160 rows an expert on (128 experts, us, those tiles -> here: 270 rows
     // of 2048 x 384 FP8 101 -> 62, MXFP8 94 -> 61, 500 rows 122 -> 100 and 111 -> 98; below, 64 experts of 130 rows MXFP8 24.1 and
@@ -2159,9 +2163,20 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
     // (270 rows of 1536 x 512 with a branch, all alike 80 -> 57, drawn 69 -> 57, of 1024 x 128 FP8 40 -> 24; elsewhere a tile of 256
     // rows is level or ahead by up to a quarter: 512 experts of 132 rows, dual 1536 x 512, 147 against 169).
     if (lines && grouped && p.E > 0 && p.M >= 1 && flow_fits(MODE, 0, stages, true, p.E)) {
-        const int64_t least = p.E * ((p.N + 255) / 256);  // tiles if no expert has more than 128 rows
-        if (stages < 4 ? tm == 4 && t256 > ncu && rows > 160 && ((MODE != MODE_DUAL && stages > 1) || (rows + 8) % 256 < (stages == 1 ? 88 : 112))
-                       : rows > 112 || (rows > 56 && stages >= 6) || (rows >= 12 && 2 * least >= 5 * ncu)) {
+        const int64_t strips = p.E * ((p.N + 255) / 256);  // tiles if no expert has more than 128 rows
+        bool flow;
+        if (stages < 4) {
+            flow = tm == 4 && t256 > ncu && rows > 160 && ((MODE != MODE_DUAL && stages > 1) || (rows + 8) % 256 < (stages == 1 ? 88 : 112));
+        } else {
+            flow = rows > 112 || (rows > 56 && stages >= 6) || (rows >= 12 && 2 * strips >= 5 * ncu);
+            const int64_t tiles = strips * ((rows + 127) / 128);
+            const bool few = stages > 7 || rows > 112 ? 20 * tiles < (stages >= 6 ? 9 : 11) * ncu : 20 * tiles <= 21 * ncu;
+            if (flow && few) {
+                flow = false;
+                tm = stages >= 5 && 5 * p.E * ((rows + 71) / 64) * ((p.N + 127) / 128) > 6 * ncu ? 2 : 1;
+            }
+        }
+        if (flow) {
             kind = 7;
             flow_tile = 0;
         }

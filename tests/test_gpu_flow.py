@@ -179,10 +179,12 @@ def test_flow_experts(osc, tuning, N, K, K2, r):
 
 @pytest.mark.parametrize("mode,E,rows,N,K,chosen", [("dual", 128, 270, 1536, 512, (7, 0)), ("fp8", 128, 270, 2048, 384, (7, 0)), ("mx8", 128, 270, 1024, 256, (7, 0)),
                                                     ("fp8", 128, 270, 1024, 128, (7, 0)), ("mx8", 128, 500, 2048, 384, (7, 0)), ("dual", 128, 150, 1536, 512, (1, 4)),
-                                                    ("mx8", 64, 130, 2048, 384, (1, 4)), ("dual", 32, 270, 1536, 1024, (7, 0))])
+                                                    ("mx8", 64, 130, 2048, 384, (1, 4)), ("dual", 32, 270, 1536, 1024, (7, 0)), ("dual", 8, 160, 1024, 1024, (1, 1)),
+                                                    ("mx8", 64, 80, 1024, 768, (1, 2)), ("fp8", 8, 330, 1024, 768, (1, 2)), ("fp8", 64, 160, 1024, 768, (7, 0))])
 def test_launcher_choice_for_experts(osc, tuning, mode, E, rows, N, K, chosen):
-    """Experts of one to four stages: 256-row tiles where those are ahead, the flowing kernel where they would start a few last rows
-    of every expert on a tile of their own; same numbers as the DMA kernel's small tiles."""
+    """Experts of one to three stages: 256-row tiles where those are ahead, the flowing kernel where they would start a few last rows
+    of every expert on a tile of their own.  More stages: small tiles where those of the flowing kernel would leave CUs without
+    one.  Same numbers as the DMA kernel's small tiles."""
     g = torch.Generator(device="cuda").manual_seed(8100 + rows)
     draw = lambda hi, *shape: torch.randint(0, hi, shape, dtype=torch.uint8, device="cuda", generator=g)  # noqa: E731
     sizes = torch.bincount(torch.randint(0, E, (E * rows,), device="cuda", generator=g), minlength=E)
