@@ -18,7 +18,7 @@ PROGRAM = r"""
 
 static std::mutex g_mu;
 static std::condition_variable g_cv;
-static size_t g_attribute = 0;  // what the "driver" allows
+static size_t g_attribute = 0;  // what a launch may ask for
 static int g_set = 0;           // calls that have set it
 
 extern "C" hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
