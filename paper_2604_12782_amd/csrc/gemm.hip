@@ -120,7 +120,7 @@ __global__ void __launch_bounds__(GT) gemm_kernel(KArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < LB; ++i) {
-        const int n = min(n0 + (t >> 2) + 64 * i, a.N - 1);
+        const int n = min(n0 + pair_col<TN>((t >> 2) + 64 * i), a.N - 1);
         ob[i] = (uint32_t)n * (uint32_t)rowbytes + c4 * 16;
         ob2[i] = (uint32_t)n * (uint32_t)a.wlpitch + c4 * 16;
     }
@@ -129,7 +129,9 @@ __global__ void __launch_bounds__(GT) gemm_kernel(KArgs a) {
     const uint8_t* zeros = wp + a.off_z;  // 256 bytes of zeros at the end of every packed weight
 
     // ---- scale words: one per (row, step) -----------------------------------------------------
-    uint32_t so_a[TM], so_b[TN];
+    // (weights: a lane's rows of a pair of blocks are neighbours, so are their words)
+    static_assert(TN == 2, "one pair of weight blocks");
+    uint32_t so_a[TM], so_b = 0;
     if (MODE == MODE_DUAL) {
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
@@ -137,11 +139,8 @@ __global__ void __launch_bounds__(GT) gemm_kernel(KArgs a) {
             if (a.row_map) g = a.row_map[g];
             so_a[i] = (uint32_t)(g >> 5) * (uint32_t)Kg4 * 128u + (g & 31) * 4;
         }
-#pragma unroll
-        for (int i = 0; i < TN; ++i) {
-            const int n = min(n0 + wn * (TN * 32) + i * 32 + r, a.N - 1);
-            so_b[i] = (uint32_t)(n >> 5) * (uint32_t)Kg4 * 128u + (n & 31) * 4;
-        }
+        const int n = min(n0 + pair_col<TN>(wn * (TN * 32) + r), (a.N - 1) & ~1);
+        so_b = (uint32_t)(n >> 5) * (uint32_t)Kg4 * 128u + (n & 31) * 4;
     }
     const uint8_t* wsb = wp + a.off_s;
 
@@ -214,8 +213,9 @@ __global__ void __launch_bounds__(GT) gemm_kernel(KArgs a) {
         const uint32_t o__ = (uint32_t)min((T_), Kg4 - 1) * 128u;                                     \
         _Pragma("unroll") for (int i = 0; i < TM; ++i) SA_[i] =                                       \
             *reinterpret_cast<const int*>(a.Xs + o__ + so_a[i]);                                      \
-        _Pragma("unroll") for (int i = 0; i < TN; ++i) SB_[i] =                                       \
-            *reinterpret_cast<const int*>(wsb + o__ + so_b[i]);                                       \
+        const u32x2 pair__ = *reinterpret_cast<const u32x2*>(wsb + o__ + so_b);                       \
+        SB_[0] = (int)pair__.x;                                                                       \
+        SB_[1] = (int)pair__.y;                                                                       \
     }
 #define OSC_MFMA_FP4(I_, FA_, FB_, SA_, SB_)                                                          \
     {                                                                                                 \
@@ -359,7 +359,7 @@ __global__ void __launch_bounds__(GT) gemm_kernel(KArgs a) {
         }
         if (s < nS) OSC_STEP_BF16(s, ra0s, rb0s, ra1s, rb1s)
     }
-    store_result<MODE, TM, TN>(a, tp, acc);
+    store_pairs<MODE, TM, TN, 2, 2>(a, tp, acc);
 }
 
 
@@ -386,7 +386,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_dma2_kernel(KArgs a) {
     constexpr int LA = BM / RPP, LB = BN / RPP;  // DMA loads per thread and stage
     constexpr int NBLK = (BM + BN) / 32;      // 32-row blocks of a stage
     constexpr int NSB = (NBLK + NWV - 1) / NWV;  // scale DMA loads per wave and stage (one block each)
-    static_assert(BM % RPP == 0 && BN % RPP == 0, "tile does not split over the wavefronts");
+    static_assert(BM % RPP == 0 && BN % RPP == 0 && TN % 2 == 0, "tile does not split over the wavefronts");
     // bytes of scale words per stage: [block][half step][32 rows][4], rounded up to whole 1 KB requests
     constexpr int SCL = dma2_scale_bytes(BM, BN);
     constexpr int NREQ = (NBLK + 3) / 4;       // 16-byte scale requests per stage (four blocks each)
@@ -416,7 +416,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_dma2_kernel(KArgs a) {
         oa[i] = (uint32_t)g;
     }
 #pragma unroll
-    for (int i = 0; i < LB; ++i) ob[i] = (uint32_t)min(n0 + (t >> 3) + RPP * i, a.N - 1);
+    for (int i = 0; i < LB; ++i) ob[i] = (uint32_t)min(n0 + pair_col<TN>((t >> 3) + RPP * i), a.N - 1);
     const uint8_t* wq = wp + a.off_q;
     const uint8_t* wl = wp + a.off_l;
     // Scale words travel through LDS as well (a register load in the loop would make the compiler
@@ -440,6 +440,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_dma2_kernel(KArgs a) {
         }
     }
     const uint8_t* wsb = wp + a.off_s;
+    const uint32_t so_b = pair_scale(r, 256);
     // Dual path, one problem, rows not mapped: a stage's scale words are whole 256-byte blocks of the
     // row-block-major layout, and lane l of wavefront w < NREQ fetches piece l % 16 of block 4w + l / 16 with
     // one 16-byte request (a request costs the memory pipeline the same whatever its width: three or four
@@ -515,11 +516,11 @@ __global__ void __launch_bounds__(128 * WN) gemm_dma2_kernel(KArgs a) {
     // this lane's scale words of half step H_ of buffer BUF_, byte I = scale of piece 2q+I
 #define OSC_D2_READ_SCALES(BUF_, H_, SA_, SB_)                                                        \
     {                                                                                                 \
-        const uint8_t* sc__ = scl + (BUF_)*SCL + (H_)*128 + r * 4;                                    \
+        const uint8_t* sc__ = scl + (BUF_)*SCL + (H_)*128;                                            \
         _Pragma("unroll") for (int i = 0; i < TM; ++i) SA_[i] =                                       \
-            *reinterpret_cast<const uint32_t*>(sc__ + (wm * TM + i) * 256) >> ((MODE == MODE_MX8 ? 8 : 16) * q); \
-        _Pragma("unroll") for (int j = 0; j < TN; ++j) SB_[j] =                                       \
-            *reinterpret_cast<const uint32_t*>(sc__ + (BM / 32 + wn * TN + j) * 256) >> ((MODE == MODE_MX8 ? 8 : 16) * q); \
+            *reinterpret_cast<const uint32_t*>(sc__ + (wm * TM + i) * 256 + r * 4) >> ((MODE == MODE_MX8 ? 8 : 16) * q); \
+        _Pragma("unroll") for (int j = 0; j < TN; ++j) SB_[j] =  /* a pair's words lie in the order of the rows */ \
+            *reinterpret_cast<const uint32_t*>(sc__ + (BM / 32 + wn * TN + (j & ~1)) * 256 + (j & 1) * 4 + so_b) >> ((MODE == MODE_MX8 ? 8 : 16) * q); \
     }
 
     // ---- prologue ---------------------------------------------------------------------------------
@@ -713,7 +714,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_dma2_kernel(KArgs a) {
 #pragma unroll 1
         for (; T < nT; ++T) OSC_D2_STAGE_BF16(T)
     }
-    store_result<MODE, TM, TN, WN>(a, tp, acc);
+    store_pairs<MODE, TM, TN, WN, 2>(a, tp, acc);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -827,9 +828,13 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
 
     // per-thread parts of the addresses: row (t >> 3) of a block of RPP rows, 16-byte piece c8
     const uint32_t c8 = (uint32_t)((t & 7) ^ swz8(t >> 3)) * 16u;
-    const uint32_t vo_main = (uint32_t)(t >> 3) * (uint32_t)rowbytes + c8;       // FP4 phase, both operands
+    // weight rows: the blocks of 32 are paired (pair_col), so block i of a pass holds rows 64 (i / 2) + i % 2 + 4, 2, ...
+    static_assert(RPP == 32 && TN % 2 == 0, "a pass is one block of weight rows");
+    const uint32_t brow = (uint32_t)pair_col<TN>(t >> 3);
+    const uint32_t vo_a = (uint32_t)(t >> 3) * (uint32_t)rowbytes + c8;          // FP4 phase, X rows
+    const uint32_t vo_w = brow * (uint32_t)rowbytes + c8;                        // FP4 phase, W rows
     const uint32_t vo_ba = (uint32_t)(t >> 3) * (uint32_t)a.bpitch + c8;         // branch phase, B rows
-    const uint32_t vo_bw = (uint32_t)(t >> 3) * (uint32_t)a.wlpitch + c8;        // branch phase, W_L rows
+    const uint32_t vo_bw = brow * (uint32_t)a.wlpitch + c8;                      // branch phase, W_L rows
     const uint32_t vo_s = (uint32_t)(r * 4 + (DUAL ? q * 128 : 0));               // scale word of row r (dual path: of half step q)
     // 16-byte form: lane l fetches piece l % 16 of the 256 bytes (two half steps x 32 rows x 4) of block l / 16
     const uint32_t vo_s16 = (uint32_t)(lane >> 4) * ((uint32_t)Kg4 * 128u) + (uint32_t)(lane & 15) * 16u;
@@ -844,7 +849,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
     int nm0 = 0, nn0 = 0;      // position of this workgroup's tile after the one under the load cursor
     bool hasnext;
     const uint8_t *pa, *pb, *psa = nullptr, *psb = nullptr;  // A rows, B rows, A scale block, B scale block at this stage
-    uint32_t sa32, sb32;                 // bytes between consecutive blocks of RPP rows
+    uint32_t sa32, sb1;                  // bytes between consecutive blocks of RPP X rows, and between weight rows
     uint32_t voa, vob;                   // per-thread offsets in use
 #define PIPE2_TILE_POS(TILE_, M0_, N0_)                                                              \
     {                                                                                                \
@@ -862,11 +867,11 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
         const uint32_t pitcha__ = fp4__ ? (uint32_t)rowbytes : (uint32_t)a.bpitch;                   \
         const uint32_t pitchb__ = fp4__ ? (uint32_t)rowbytes : (uint32_t)a.wlpitch;                  \
         sa32 = (uint32_t)RPP * pitcha__;                                                                       \
-        sb32 = (uint32_t)RPP * pitchb__;                                                                       \
+        sb1 = pitchb__;                                                                              \
         pa = (fp4__ ? a.Xq : a.B) + ((size_t)lm0 * pitcha__ + ko__);                                 \
         pb = (fp4__ ? wq : wl) + ((size_t)ln0 * pitchb__ + ko__);                                    \
-        voa = fp4__ ? vo_main : vo_ba;                                                               \
-        vob = fp4__ ? vo_main : vo_bw;                                                               \
+        voa = fp4__ ? vo_a : vo_ba;                                                                  \
+        vob = fp4__ ? vo_w : vo_bw;                                                                  \
         if (BLKSC) {                                                                                 \
             const uint32_t so__ = (uint32_t)(DUAL ? min(2 * lT, Kg4 - 2) : min(lT, Kg4 - 1)) * 128u; \
             psa = a.Xs + ((size_t)(lm0 >> 5) * (uint32_t)Kg4 * 128u + so__);                         \
@@ -911,7 +916,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
             load_to_lds16(pa + (size_t)i__ * sa32 + voa, lds + (BUF_)*STG + wave * 1024 + i__ * (RPP * 128)); \
         } else {                                                                                     \
             const int i__ = (L_)-NSB - LA;                                                           \
-            load_to_lds16(pb + (size_t)i__ * sb32 + vob,                                             \
+            load_to_lds16(pb + (size_t)((i__ & ~1) * 32 + (i__ & 1)) * sb1 + vob,                                             \
                           lds + (BUF_)*STG + wave * 1024 + BM * 128 + i__ * (RPP * 128));                   \
         }                                                                                            \
     }
@@ -920,19 +925,20 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
 #define PIPE_READ_SCALE(R_, BUF_, H_, SA_, SB_)                                                         \
     {                                                                                                   \
         /* a 16-bit read at byte 2q of the word: byte I of the register = scale of piece 2q+I, no shift */ \
-        const uint8_t* sc__ = scl + (BUF_)*SCL + (H_)*128 + r * 4 + 2 * q;                              \
+        const uint8_t* sc__ = scl + (BUF_)*SCL + (H_)*128 + 2 * q;                                      \
         if ((R_) < TM)                                                                                  \
-            SA_[(R_) < TM ? (R_) : 0] = *reinterpret_cast<const uint16_t*>(sc__ + (wm * TM + (R_)) * 256); \
+            SA_[(R_) < TM ? (R_) : 0] = *reinterpret_cast<const uint16_t*>(sc__ + r * 4 + (wm * TM + (R_)) * 256); \
         else                                                                                            \
             SB_[(R_) >= TM ? (R_)-TM : 0] =                                                             \
-                *reinterpret_cast<const uint16_t*>(sc__ + (BM / 32 + wn * TN + (R_)-TM) * 256);         \
+                *reinterpret_cast<const uint16_t*>(sc__ + so_b + (BM / 32 + wn * TN + (((R_)-TM) & ~1)) * 256 + (((R_)-TM) & 1) * 4); \
     }
-#define PIPE_MFMA_FP4(N_, FA_, FB_, SA_, SB_, SEL_)                                                     \
+    // NEW_: the first product of a tile, which starts from zero (clearing 256 accumulators takes 1024 cycles)
+#define PIPE_MFMA_FP4(N_, FA_, FB_, SA_, SB_, SEL_, NEW_)                                               \
     {                                                                                                   \
         const int i__ = (N_) / TN, j__ = (N_) % TN;                                                     \
         const v8i av__ = {(int)FA_[i__].x, (int)FA_[i__].y, (int)FA_[i__].z, (int)FA_[i__].w, 0, 0, 0, 0}; \
         const v8i bv__ = {(int)FB_[j__].x, (int)FB_[j__].y, (int)FB_[j__].z, (int)FB_[j__].w, 0, 0, 0, 0}; \
-        acc[i__][j__] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av__, bv__, acc[i__][j__], 4, 4, SEL_, \
+        acc[i__][j__] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av__, bv__, (NEW_) ? zero : acc[i__][j__], 4, 4, SEL_, \
                                                                         SA_[i__], SEL_, SB_[j__]);      \
     }
 #define PIPE_MFMA_BF16(N_, FA_, FB_)                                                                    \
@@ -951,6 +957,8 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
         if ((R_) < TM) SA_[(R_) < TM ? (R_) : 0] = v__;                                                \
         else SB_[(R_) >= TM ? (R_)-TM : 0] = v__;                                                      \
     }
+    // scale words of a pair of weight blocks lie in the order of the rows: this lane's in the pair's 64
+    const uint32_t so_b = pair_scale(r, 256);
     u32x4 Xa[TM], Xb[TN], Ya[TM], Yb[TN], Za[TM], Zb[TN];
     int s0a[TM], s0b[TN], s1a[TM], s1b[TN];
     // 8-bit modes: a lane's fragment of a 64-channel MFMA step is two pieces (32 bytes).  One set for the A
@@ -962,6 +970,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
     int m8a[TM], m8b[TN];
     uint32_t m8an[TM], m8bn[TN];
     v16f acc[TM][TN];
+    const v16f zero = {};
     // half H_ (0, 1) of the fragment of 32-row block I_ / J_ for MFMA step KS_ (0, 1) of buffer BUF_
     // (per-token FP8: lane half q supplies bytes 32q .. 32q+31 of the step, pieces 2q and 2q+1; MXFP8: elements
     // 16q .. 16q+15 of each of the step's two scale blocks, pieces q and 2+q, see the DMA kernel)
@@ -973,16 +982,17 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
     // scale word number R_ (0..TM+TN-1) of the stage in buffer BUF_
 #define PIPE8_READ_SCALE(R_, BUF_)                                                                      \
     {                                                                                                   \
-        const uint8_t* sc__ = scl + (BUF_)*SCL + r * 4;                                                 \
-        if ((R_) < TM) m8an[(R_) < TM ? (R_) : 0] = *reinterpret_cast<const uint32_t*>(sc__ + (wm * TM + (R_)) * 256); \
-        else m8bn[(R_) >= TM ? (R_)-TM : 0] = *reinterpret_cast<const uint32_t*>(sc__ + (BM / 32 + wn * TN + (R_)-TM) * 256); \
+        const uint8_t* sc__ = scl + (BUF_)*SCL;                                                         \
+        if ((R_) < TM) m8an[(R_) < TM ? (R_) : 0] = *reinterpret_cast<const uint32_t*>(sc__ + r * 4 + (wm * TM + (R_)) * 256); \
+        else m8bn[(R_) >= TM ? (R_)-TM : 0] =                                                           \
+            *reinterpret_cast<const uint32_t*>(sc__ + so_b + (BM / 32 + wn * TN + (((R_)-TM) & ~1)) * 256 + (((R_)-TM) & 1) * 4); \
     }
 #define PIPE8_TAKE_SCALES                                                                               \
     {                                                                                                   \
         _Pragma("unroll") for (int i = 0; i < TM; ++i) m8a[i] = (int)(m8an[i] >> (8 * q));              \
         _Pragma("unroll") for (int j = 0; j < TN; ++j) m8b[j] = (int)(m8bn[j] >> (8 * q));              \
     }
-#define PIPE8_MFMA(N_, BS_, KS_)                                                                        \
+#define PIPE8_MFMA(N_, BS_, KS_, NEW_)                                                                  \
     {                                                                                                   \
         const int i__ = (N_) / TN, j__ = (N_) % TN;                                                     \
         const bool x__ = (KS_) == 1 && i__ == TM - 1;                                                   \
@@ -992,10 +1002,10 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
         const v8i bv__ = {(int)BS_[j__][0].x, (int)BS_[j__][0].y, (int)BS_[j__][0].z, (int)BS_[j__][0].w, \
                           (int)BS_[j__][1].x, (int)BS_[j__][1].y, (int)BS_[j__][1].z, (int)BS_[j__][1].w}; \
         if (MX)                                                                                         \
-            acc[i__][j__] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av__, bv__, acc[i__][j__], 0, 0, 2 * (KS_), \
+            acc[i__][j__] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av__, bv__, (NEW_) ? zero : acc[i__][j__], 0, 0, 2 * (KS_), \
                                                                             m8a[i__], 2 * (KS_), m8b[j__]); \
         else                                                                                            \
-            acc[i__][j__] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av__, bv__, acc[i__][j__], 0, 0, 0, \
+            acc[i__][j__] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av__, bv__, (NEW_) ? zero : acc[i__][j__], 0, 0, 0, \
                                                                             0x7f7f7f7f, 0, 0x7f7f7f7f); \
     }
 
@@ -1023,16 +1033,16 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
     int cpar = 0;  // FP8: which copy of the tile scales the tile under the compute cursor reads
 
 #define PIPE2_FENCE __builtin_amdgcn_sched_barrier(0);
-#define PIPE2_GROUP(G_, FP4_)                                                                          \
+#define PIPE2_GROUP(G_, FP4_, NEW_)                                                                    \
     {                                                                                                  \
         _Pragma("unroll") for (int n__ = 0; n__ < NT; ++n__) {                                         \
             constexpr int g__ = (G_);                                                                  \
             const int k = g__ * NT + n__;                                                              \
             if (FP4_) {                                                                                \
-                if (g__ == 0) PIPE_MFMA_FP4(n__, Xa, Xb, s0a, s0b, 0)                                  \
-                else if (g__ == 1) PIPE_MFMA_FP4(n__, Ya, Yb, s0a, s0b, 1)                             \
-                else if (g__ == 2) PIPE_MFMA_FP4(n__, Xa, Xb, s1a, s1b, 0)                             \
-                else PIPE_MFMA_FP4(n__, Za, Zb, s1a, s1b, 1)                                           \
+                if (g__ == 0) PIPE_MFMA_FP4(n__, Xa, Xb, s0a, s0b, 0, NEW_)                            \
+                else if (g__ == 1) PIPE_MFMA_FP4(n__, Ya, Yb, s0a, s0b, 1, 0)                             \
+                else if (g__ == 2) PIPE_MFMA_FP4(n__, Xa, Xb, s1a, s1b, 0, 0)                             \
+                else PIPE_MFMA_FP4(n__, Za, Zb, s1a, s1b, 1, 0)                                           \
             } else {                                                                                   \
                 if (g__ == 0) PIPE_MFMA_BF16(n__, Xa, Xb)                                              \
                 else if (g__ == 1) PIPE_MFMA_BF16(n__, Ya, Yb)                                         \
@@ -1079,9 +1089,9 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
             PIPE2_FENCE                                                                                \
         }                                                                                              \
     }
-#define PIPE2_STAGE(FP4_)                                                                              \
+#define PIPE2_STAGE(FP4_, NEW_)                                                                        \
     {                                                                                                  \
-        PIPE2_GROUP(0, FP4_) PIPE2_GROUP(1, FP4_) PIPE2_GROUP(2, FP4_) PIPE2_GROUP(3, FP4_)            \
+        PIPE2_GROUP(0, FP4_, NEW_) PIPE2_GROUP(1, FP4_, 0) PIPE2_GROUP(2, FP4_, 0) PIPE2_GROUP(3, FP4_, 0) \
         PIPE2_ADVANCE                                                                                  \
         buf ^= 1;                                                                                      \
     }
@@ -1097,10 +1107,10 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
     //   behind it:             Bp and A <- step 0 of stage T+1: block TM-1 first (free since slot NT-1), then
     //                          blocks 0 .. TM-2 (block i is free after slot NT + i TN + TN-1 and is read in
     //                          slots F8_B_AT + 3 + 2i, + 4 + 2i)
-#define PIPE8_STAGE                                                                                    \
+#define PIPE8_STAGE(NEW_)                                                                              \
     {                                                                                                  \
         _Pragma("unroll") for (int n__ = 0; n__ < NT; ++n__) {                                         \
-            PIPE8_MFMA(n__, Bp, 0)                                                                     \
+            PIPE8_MFMA(n__, Bp, 0, NEW_)                                                               \
             if (n__ == NT - 6 || n__ == NT - 5)                                                        \
                 A8x[n__ - (NT - 6)] = *reinterpret_cast<const u32x4*>(                                 \
                     lds + buf * STG + st128_off(ra0 + 32 * (TM - 1), PIPE8_PIECE(1, n__ - (NT - 6)))); \
@@ -1110,7 +1120,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
         }                                                                                              \
         _Pragma("unroll") for (int n__ = 0; n__ < NT; ++n__) {                                         \
             const int k = NT + n__;                                                                    \
-            PIPE8_MFMA(n__, Bq, 1)                                                                     \
+            PIPE8_MFMA(n__, Bq, 1, 0)                                                                  \
             if (k == F8_A_AT) {                                                                        \
                 PIPE2_FENCE                                                                            \
                 __builtin_amdgcn_s_waitcnt(0xC07F); /* lgkmcnt(0) */                                   \
@@ -1147,12 +1157,6 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
 
 #pragma unroll 1
     for (;;) {
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int j = 0; j < TN; ++j)
-#pragma unroll
-                for (int k = 0; k < 16; ++k) acc[i][j][k] = 0.0f;
         // the load cursor is at stage 2 of this tile; it will cross into the next one (if any)
         hasnext = ctile + step < last;
         if (hasnext) PIPE2_TILE_POS(ctile + step, nm0, nn0)
@@ -1171,13 +1175,15 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
             }
         }
         if constexpr (DUAL) {
+            PIPE2_STAGE(1, 1)
 #pragma unroll 1
-            for (int T = 0; T < nTA; ++T) PIPE2_STAGE(1)
+            for (int T = 1; T < nTA; ++T) PIPE2_STAGE(1, 0)
 #pragma unroll 1
-            for (int T = nTA; T < nT; ++T) PIPE2_STAGE(0)
+            for (int T = nTA; T < nT; ++T) PIPE2_STAGE(0, 0)
         } else {
+            PIPE8_STAGE(1)
 #pragma unroll 1
-            for (int T = 0; T < nTA; ++T) PIPE8_STAGE
+            for (int T = 1; T < nTA; ++T) PIPE8_STAGE(0)
         }
         const bool done = !hasnext;
         if (done) wait_vmcnt<0>();  // the idle re-fetches of the last stage still target LDS
@@ -1188,9 +1194,9 @@ __global__ void __launch_bounds__(128 * WN) gemm_pipe2_kernel(KArgs a, int ntile
         ctp.wp = a.Wpack;
         ctp.valid = true;
         if constexpr (BLKSC) {
-            store_result<MODE, TM, TN, WN>(a, ctp, acc);
+            store_pairs<MODE, TM, TN, WN, 2, false, true, (TM * TN >= 16)>(a, ctp, acc);
         } else {
-            store_result<MODE, TM, TN, WN, true>(a, ctp, acc, reinterpret_cast<const float*>(scl + cpar * SCL));
+            store_pairs<MODE, TM, TN, WN, 2, true, true, (TM * TN >= 16)>(a, ctp, acc, reinterpret_cast<const float*>(scl + cpar * SCL));
             cpar ^= 1;
         }
         if (done) break;
@@ -1279,14 +1285,14 @@ __global__ void __launch_bounds__(128 * WN) gemm_ring_kernel(KArgs a) {
     for (int i = 0; i < LPT; ++i) {
         const int chunk = (i < LPA ? 0 : BM / 16) + wave + NWV * (i < LPA ? i : i - LPA);
         const int lrow = 16 * chunk + (lane >> 2) - (i < LPA ? 0 : BM);
-        grow[i] = i < LPA ? (uint32_t)min(m0 + lrow, row_end - 1) : (uint32_t)min(n0 + lrow, a.N - 1);
+        grow[i] = i < LPA ? (uint32_t)min(m0 + lrow, row_end - 1) : (uint32_t)min(n0 + pair_col<TN>(lrow), a.N - 1);
     }
     // the piece stored at position p of stage row R is piece p ^ ((R >> 2) & 3) (ring_off)
     const uint32_t piece16 = (uint32_t)(((lane & 3) ^ ((lane >> 4) & 3)) << 4);
     uint32_t sco;                                    // scale word of this lane's row in its block, first half stage
     {
         const int b = 2 * wave + q;                  // block of this lane half
-        const int g = b < BM / 32 ? min(m0 + 32 * b + r, row_end - 1) : min(n0 + 32 * (b - BM / 32) + r, a.N - 1);
+        const int g = b < BM / 32 ? min(m0 + 32 * b + r, row_end - 1) : min(n0 + pair_col<TN>(32 * (b - BM / 32) + r), a.N - 1);
         sco = (uint32_t)(g >> 5) * (uint32_t)Kg4 * 128u + (uint32_t)(g & 31) * 4u;
     }
     const bool sc_is_a = 2 * wave < BM / 32;         // both blocks of a wavefront lie on the same operand (BM/32 even)
@@ -1395,7 +1401,7 @@ __global__ void __launch_bounds__(128 * WN) gemm_ring_kernel(KArgs a) {
 #undef RING_ITER
 #undef RING_READ
 #undef RING_LOAD
-    store_result<MODE_DUAL, TM, TN, WN>(a, tp, acc);
+    store_pairs<MODE_DUAL, TM, TN, WN, 2>(a, tp, acc);
 }
 
 template <int TM, int TN, int WN, bool PINGPONG>

@@ -177,7 +177,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
 #pragma unroll
         for (int i = 0; i < LA; ++i) ga[i] = (uint32_t)min(ld.m0 + (t >> 3) + RPP * i, ld.row_end - 1);
 #pragma unroll
-        for (int i = 0; i < LB; ++i) gb[i] = (uint32_t)min(ld.n0 + (t >> 3) + RPP * i, a.N - 1);
+        for (int i = 0; i < LB; ++i) gb[i] = (uint32_t)min(ld.n0 + pair_col<TN>((t >> 3) + RPP * i), a.N - 1);
         int gs = min(ld.m0 + wave * 32 + r, ld.row_end - 1);
         if (mapped) {
 #pragma unroll
@@ -274,8 +274,11 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
                                                     st128_off(blk < TM ? ra0 + 32 * blk : rb0 + 32 * (blk - TM), piece));
     };
     auto read_scale = [&](int (&S)[HR], int b, int H, int s) __attribute__((always_inline)) {
-        const int blk = b < TM ? wm * TM + b : NBA + wn * TN + (b - TM);
-        const uint8_t* const sc = lds + s * Slot::BYTES + Slot::ROWS + blk * SBB + r * 4;
+        // X: row r of block b.  Weights: the row that pair_col() gives to lane r; a block's words lie in the order of the rows
+        const int j = b - TM;
+        const bool single = TN % 2 && j == TN - 1;
+        const uint8_t* const blk = lds + s * Slot::BYTES + Slot::ROWS + (b < TM ? wm * TM + b : NBA + wn * TN + (j & ~1)) * SBB;
+        const uint8_t* const sc = blk + (b < TM ? r * 4 : single ? (2 * (r & 15) + (r >> 4)) * 4 : pair_scale(r, SBB) + (j & 1) * 4);
         if constexpr (DUAL) S[b] = *reinterpret_cast<const uint16_t*>(sc + H * 128 + 2 * q);
         else S[b] = sc[2 * H + q];
     };
@@ -404,7 +407,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
 #pragma unroll 1
                 for (; T < nT; ++T) stage(yes, no);
             }
-            store_result<MODE, TM, TN, WN, FP8, WM>(a, cur, acc, tsc + cpar * (BM + BN));
+            store_pairs<MODE, TM, TN, WN, WM, FP8>(a, cur, acc, tsc + cpar * (BM + BN));
         } else {
             // an expert's last tile, no rows for this wavefront: it loads for the others and keeps their barriers
 #pragma unroll 1
@@ -511,7 +514,7 @@ static int launch_mode(const KArgs& a, int tile, hipStream_t st) {
     switch (tile) {
         case 0: return launch_cfg<MODE, 2, 4, 2, 2, 3, false, false, false>(a, st);
         case 1: return launch_cfg<MODE, 4, 2, 1, 3, 3, false, false, false>(a, st);
-        case 2: return launch_cfg<MODE, 2, 4, 2, 1, 4, false, false, false>(a, st);
+        case 2: return launch_cfg<MODE, 4, 2, 1, 2, 4, false, false, false>(a, st);  // (a wavefront's 64 columns: whole lines of bf16 results)
         default: return launch_cfg<MODE, 2, 4, 1, 1, 5, true, false, false>(a, st);
     }
 }

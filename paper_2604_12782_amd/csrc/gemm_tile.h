@@ -129,188 +129,169 @@ __device__ __forceinline__ TilePos tile_at(const KArgs& a, int tile) {
     return p;
 }
 
-// LDS_SCALES (FP8): the row scales of the tile's BM rows and the column scales of its BN columns are read from
-// `tile_scales` in LDS (all BM + BN floats, past the end of Y any values) instead of global memory.
-// WM x WN wavefronts of TM x TN blocks of 32 x 32.
-template <int MODE, int TM, int TN, int WN = 2, bool LDS_SCALES = false, int WM = 2>
-__device__ __forceinline__ void store_result(const KArgs& a, const TilePos& tp, v16f (&acc)[TM][TN],
-                                             const float* tile_scales = nullptr) {
+// Output column, relative to its wavefront's first, that lane r = p % 32 of block p / 32 (of TN) holds with store_pairs below:
+// the kernel places that weight row of the tile on LDS row p.  Blocks 2b and 2b + 1 share 64 columns: a lane's two results of
+// one row are neighbours, and lanes r and r ^ 16 hold four columns in a row.  In the last block of an odd TN those lanes
+// hold neighbours.
+template <int TN>
+__device__ __forceinline__ int pair_col(int p) {
+    const int w = TN % 2 ? p / (32 * TN) * (32 * TN) : p & ~63, o = p - w;  // the wavefront's first, or the pair's
+    const int c = o & 15, h = (o >> 4) & 1, j = o >> 5;
+    if (TN % 2 && j == TN - 1) return w + 32 * j + 2 * c + h;
+    return w + 64 * (j >> 1) + 4 * c + 2 * h + (j & 1);
+}
+
+// Where lane r finds its row's scale word of a pair of weight blocks' first block: a block's words lie in the order of the rows, four
+// bytes each, `block` bytes from block to block; the second block's is the word behind it.
+__device__ __forceinline__ uint32_t pair_scale(int r, uint32_t block) {
+    return ((uint32_t)(r >> 3) & 1) * block + (4 * ((uint32_t)r & 7) + 2 * ((uint32_t)r >> 4)) * 4;
+}
+
+// Epilogue: WM x WN wavefronts of TM x TN blocks of 32 x 32, columns dealt to the lanes as pair_col() says.  Result register k of
+// lane (q, r) is row 8 (k / 4) + 4 q + k % 4 of its block.  Turning "one column, sixteen rows a lane" into rows takes one
+// conversion per two results and one exchange of lanes r and r ^ 16 per four (per two in the last block of an odd TN), and 16
+// lanes store 128 (64) bytes of a row.  With the columns in order it took three rounds of lane exchanges, seven instructions per
+// two results, for 16-byte stores: 8192 x 8192 x 512 dual path 53 us then, 48 now; 300 x 4096 x 2048 8.2 and 7.3;
+// 8192 x 24576 x 4096 482 and 456 (with the first products of a tile starting from zero, see the persistent kernel).
+// LDS_SCALES (FP8): the tile's BM row scales and BN column scales are read from `tile_scales` in LDS (past the end of Y any
+// values), not from memory.  WHOLE: the tile lies inside Y.  ACC_REGS: the accumulators fill the accumulation registers, and
+// every result is read from there by itself (left to the compiler, whole blocks are copied and spilled at the head of the
+// epilogue: 82 registers in the MXFP8 form of the persistent kernel).
+template <int MODE, int TM, int TN, int WN, int WM, bool LDS_SCALES = false, bool WHOLE = false, bool ACC_REGS = false>
+__device__ __forceinline__ void store_pairs(const KArgs& a, const TilePos& tp, v16f (&acc)[TM][TN],
+                                            const float* tile_scales = nullptr) {
     constexpr int BM = 32 * TM * WM, BN = 32 * TN * WN;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    typedef float v2f4 __attribute__((ext_vector_type(2), aligned(4)));  // (wide stores need 4-byte alignment only)
+    typedef unsigned int u32x4_4 __attribute__((ext_vector_type(4), aligned(4)));
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wm = wave / WN, wn = wave % WN, q = lane >> 5, r = lane & 31;
-    const int m0 = tp.m0, n0 = tp.n0, row_end = tp.row_end;
-    const uint8_t* wp = tp.wp;
-    // ---- epilogue ---------------------------------------------------------------------------
-    // Result register k of lane (q, r): row 8*(k/4) + 4*q + k%4, column r of its 32x32 tile.
-    // fp32: every register is one 128-byte row segment per half-wave.  bf16: neighbouring lanes
-    // swap one register of each pair so that every lane owns two adjacent columns of one row and
-    // writes them as one 32-bit word (even lanes row k, odd lanes row k+1).
-    const float* wsc = (MODE == MODE_FP8) ? reinterpret_cast<const float*>(wp + a.off_s) : nullptr;
-    const int odd = r & 1;
-    const int wu_m = __builtin_amdgcn_readfirstlane(wm), wu_n = __builtin_amdgcn_readfirstlane(wn);
-    // byte offset of this lane's four columns inside a 32x32 result tile: row 4q + r%4, columns 4(r/4) ..
-    const uint32_t yoff8 = 2u * (uint32_t)((4 * q + (r & 3)) * (int)a.ldy + (r & ~3));
-    const bool hi2 = (r & 2) != 0;
-    // 16-byte stores of eight bf16 columns need rows that keep 16-byte alignment
-    const bool wide16 = (a.ldy & 7) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 15) == 0;
-    // byte selector of step 2: even lanes [own.lo, other.lo], odd lanes [other.hi, own.hi]
-    const uint32_t sel12 = odd ? 0x03020706u : 0x05040100u;
-    auto store_tile = [&](auto kind_tag) __attribute__((always_inline)) {
-        // 2: tile entirely inside Y, no bounds tests; 1: all columns inside, rows tested (ragged
-        // last tile of a problem or an expert); 0: everything tested, 2-byte stores
+    int64_t ldy = a.ldy;
+    if constexpr (ACC_REGS) {  // the asm reads below are not known to the compiler as reads of a matrix instruction's result
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_nop 15\n\ts_nop 15");
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    asm volatile("" : "+s"(ldy));  // the row addresses are worked out here: hoisted out of the tile loop they spill
+    // KIND 2: tile inside Y; 1: columns inside, rows tested; 0: everything tested, bf16 element by element
+    auto store = [&](auto kind_tag, auto bf16_tag) __attribute__((always_inline)) {
         constexpr int KIND = decltype(kind_tag)::value;
-        constexpr bool FULL = KIND == 2;
+        constexpr bool BF16 = decltype(bf16_tag)::value;
+        constexpr int SZ = BF16 ? 2 : 4;
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
-            const int rbase = m0 + wm * (TM * 32) + i * 32 + 4 * q;
+            const int row0 = tp.m0 + wm * (TM * 32) + i * 32, rl = 4 * q;  // uniform, this lane's
             float xr[16];
-            if (MODE == MODE_FP8) {
+            if constexpr (MODE == MODE_FP8) {
 #pragma unroll
                 for (int k = 0; k < 16; ++k) {
-                    const int row = rbase + 8 * (k >> 2) + (k & 3);
-                    if constexpr (LDS_SCALES) xr[k] = tile_scales[row - m0];
-                    else xr[k] = a.xs[FULL ? row : min(row, row_end - 1)];
+                    const int row = row0 + rl + 8 * (k >> 2) + (k & 3);
+                    if constexpr (LDS_SCALES) xr[k] = tile_scales[row - tp.m0];
+                    else xr[k] = a.xs[KIND == 2 ? row : min(row, tp.row_end - 1)];
                 }
             }
-            int j0 = 0;
-            if constexpr (KIND >= 1 && TN >= 2) {
-                if (a.y_bf16 && wide16) {
-                    // 16-byte stores: the two exchange rounds described below, on two neighbouring tiles,
-                    // then a third between lanes l and l^4: lanes of even column groups complete eight
-                    // adjacent columns of the left tile, the others of the right tile, so one store
-                    // instruction writes eight rows of 128 contiguous bytes.
-                    const bool lo4 = (r & 4) != 0;
-                    const uint32_t yoff16 = 2u * (uint32_t)((4 * q + (r & 3)) * (int)a.ldy + (r & ~3) + (lo4 ? 28 : 0));
-#pragma unroll
-                    for (int jp = 0; jp + 1 < TN; jp += 2) {
-                        u32x2 o[2][4];
-#pragma unroll
-                        for (int s2 = 0; s2 < 2; ++s2) {
-                            const int j = jp + s2;
-                            float cs = 1.0f;
-                            if (MODE == MODE_FP8) cs = LDS_SCALES ? tile_scales[BM + wn * (TN * 32) + j * 32 + r] : wsc[n0 + wn * (TN * 32) + j * 32 + r];
-                            uint32_t P[8], W[8];
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) {
-                                const float v0 = (MODE == MODE_FP8) ? acc[i][j][2 * k] * (xr[2 * k] * cs) : acc[i][j][2 * k];
-                                const float v1 = (MODE == MODE_FP8) ? acc[i][j][2 * k + 1] * (xr[2 * k + 1] * cs)
-                                                                     : acc[i][j][2 * k + 1];
-                                const v2f pair = {v0, v1};
-                                P[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, v2bf));
-                            }
-#pragma unroll
-                            for (int k = 0; k < 8; ++k) {
-                                const uint32_t Q = (uint32_t)__builtin_amdgcn_mov_dpp((int)P[k], 0xB1, 0xF, 0xF, true);
-                                W[k] = __builtin_amdgcn_perm(Q, P[k], sel12);
-                            }
-#pragma unroll
-                            for (int h = 0; h < 4; ++h) {
-                                const uint32_t ra = (uint32_t)__builtin_amdgcn_mov_dpp((int)W[2 * h], 0x4E, 0xF, 0xF, true);
-                                const uint32_t rb = (uint32_t)__builtin_amdgcn_mov_dpp((int)W[2 * h + 1], 0x4E, 0xF, 0xF, true);
-                                o[s2][h] = (u32x2){hi2 ? rb : W[2 * h], hi2 ? W[2 * h + 1] : ra};
-                            }
-                        }
-                        uint8_t* const ybase = reinterpret_cast<uint8_t*>(a.Y) +
-                            2 * ((int64_t)(m0 + wu_m * (TM * 32) + i * 32) * a.ldy + n0 + wu_n * (TN * 32) + jp * 32);
-#pragma unroll
-                        for (int h = 0; h < 4; ++h) {
-                            // lane + 4 sends its left-tile words down, lane - 4 its right-tile words up
-                            const uint32_t dx = (uint32_t)__builtin_amdgcn_mov_dpp((int)o[0][h].x, 0x104, 0xF, 0xF, true);
-                            const uint32_t dy = (uint32_t)__builtin_amdgcn_mov_dpp((int)o[0][h].y, 0x104, 0xF, 0xF, true);
-                            const uint32_t ux = (uint32_t)__builtin_amdgcn_mov_dpp((int)o[1][h].x, 0x114, 0xF, 0xF, true);
-                            const uint32_t uy = (uint32_t)__builtin_amdgcn_mov_dpp((int)o[1][h].y, 0x114, 0xF, 0xF, true);
-                            const u32x4 out = {lo4 ? ux : o[0][h].x, lo4 ? uy : o[0][h].y, lo4 ? o[1][h].x : dx,
-                                               lo4 ? o[1][h].y : dy};
-                            uint8_t* const hbase = ybase + 2 * (int64_t)(8 * h) * a.ldy;
-                            if (FULL || rbase + 8 * h + (r & 3) < row_end)
-                                __builtin_nontemporal_store(out, reinterpret_cast<u32x4*>(hbase + yoff16));
-                        }
-                    }
-                    j0 = TN & ~1;
-                }
-            }
-#pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                if (j < j0) continue;  // stored in pairs above
-                const int col = n0 + wn * (TN * 32) + j * 32 + r;
-                float cs = 1.0f;
-                if (MODE == MODE_FP8) cs = LDS_SCALES ? tile_scales[BM + col - n0] : wsc[FULL ? col : min(col, a.N - 1)];
-                float v[16];
-#pragma unroll
-                for (int k = 0; k < 16; ++k)
-                    v[k] = (MODE == MODE_FP8) ? acc[i][j][k] * (xr[k] * cs) : acc[i][j][k];
-                if (a.y_bf16 && KIND >= 1) {
-                    // 8-byte stores: two rounds of exchanges inside each quad of lanes turn "one column,
-                    // sixteen rows per lane" into "four adjacent columns of one row per lane".
-                    //  1. pairs of result registers (rows R, R+1 of column c) are rounded to packed bf16;
-                    //  2. lanes c, c^1 swap halves: even lanes get row R, odd lanes row R+1, columns c&~1, +1;
-                    //  3. lanes l, l^2 swap words of register pairs (k, k+2): lanes 0,1 of a quad complete
-                    //     rows R, R+1, lanes 2,3 rows R+2, R+3, columns 4b .. 4b+3.
-                    // Each step runs over all registers of the tile before the next one starts, so the
-                    // single wavefront of a SIMD always has independent instructions to issue.
-                    uint8_t* const ybase = reinterpret_cast<uint8_t*>(a.Y) +
-                        2 * ((int64_t)(m0 + wu_m * (TM * 32) + i * 32) * a.ldy + n0 + wu_n * (TN * 32) + j * 32);
-                    uint32_t P[8], W[8];
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const v2f pair = {v[2 * k], v[2 * k + 1]};
-                        P[k] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, v2bf));
-                    }
-#pragma unroll
-                    for (int k = 0; k < 8; ++k) {
-                        const uint32_t Q = (uint32_t)__builtin_amdgcn_mov_dpp((int)P[k], 0xB1, 0xF, 0xF, true);
-                        W[k] = __builtin_amdgcn_perm(Q, P[k], sel12);
-                    }
-#pragma unroll
-                    for (int h = 0; h < 4; ++h) {
-                        // both words cross to lane l^2; each lane keeps one of its own and one of the other's
-                        // (every crossing has a single use, so it folds into the select that consumes it)
-                        const uint32_t ra = (uint32_t)__builtin_amdgcn_mov_dpp((int)W[2 * h], 0x4E, 0xF, 0xF, true);
-                        const uint32_t rb = (uint32_t)__builtin_amdgcn_mov_dpp((int)W[2 * h + 1], 0x4E, 0xF, 0xF, true);
-                        const u32x2 out = {hi2 ? rb : W[2 * h], hi2 ? W[2 * h + 1] : ra};
-                        uint8_t* const hbase = ybase + 2 * (int64_t)(8 * h) * a.ldy;
-                        if (FULL || rbase + 8 * h + (r & 3) < row_end)
-                            __builtin_nontemporal_store(out, reinterpret_cast<u32x2*>(hbase + yoff8));
-                    }
-                } else if (a.y_bf16) {
-                    uint16_t* Y = reinterpret_cast<uint16_t*>(a.Y);
-#pragma unroll
-                    for (int k = 0; k < 16; k += 2) {
-                        const float send = odd ? v[k] : v[k + 1];
-                        // neighbour lane's value: DPP quad_perm [1,0,3,2]
-                        const float recv = __builtin_bit_cast(
-                            float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, false));
-                        const float lo = odd ? recv : v[k], hi = odd ? v[k + 1] : recv;
-                        const int row = rbase + 8 * (k >> 2) + (k & 3) + odd;
-                        const int c0 = col - odd;
-                        uint16_t* dst = Y + (int64_t)row * a.ldy + c0;
-                        const uint32_t word =
-                            (uint32_t)f32_to_bf16_rne(lo) | ((uint32_t)f32_to_bf16_rne(hi) << 16);
-                        if (row < row_end) {
-                            if (c0 < a.N) dst[0] = (uint16_t)word;
-                            if (c0 + 1 < a.N) dst[1] = (uint16_t)(word >> 16);
-                        }
+            auto column_scale = [&](int col) __attribute__((always_inline)) -> float {
+                if constexpr (MODE != MODE_FP8) return 1.0f;
+                else if constexpr (LDS_SCALES) return tile_scales[BM + col - tp.n0];
+                else return reinterpret_cast<const float*>(tp.wp + a.off_s)[KIND >= 1 ? col : min(col, a.N - 1)];
+            };
+            auto result = [&](int j, int k, float scale) __attribute__((always_inline)) -> float {
+                float v = acc[i][j][k];
+                if constexpr (ACC_REGS) asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v) : "a"(acc[i][j][k]));
+                if constexpr (MODE == MODE_FP8) return v * (xr[k] * scale);
+                else return v;
+            };
+            // two neighbouring columns of a row, at p
+            auto store2 = [&](uint8_t* p, int row, int col, v2f v) __attribute__((always_inline)) {
+                if (KIND < 2 && !WHOLE && row >= tp.row_end) return;
+                if constexpr (BF16) {
+                    const uint32_t word = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, v2bf));
+                    if constexpr (KIND >= 1) {
+                        __builtin_nontemporal_store(word, reinterpret_cast<uint32_t*>(p));
+                    } else {
+                        uint16_t* const dst = reinterpret_cast<uint16_t*>(p);
+                        if (WHOLE || col < a.N) dst[0] = (uint16_t)word;
+                        if (WHOLE || col + 1 < a.N) dst[1] = (uint16_t)(word >> 16);
                     }
                 } else {
-                    float* Y = reinterpret_cast<float*>(a.Y);
+                    float* const dst = reinterpret_cast<float*>(p);
+                    if (KIND >= 1 || WHOLE || col + 1 < a.N) *reinterpret_cast<v2f4*>(dst) = v;
+                    else if (col < a.N) dst[0] = v.x;
+                }
+            };
+#pragma unroll
+            for (int j = 0; j < TN; j += 2) {
+                const int col0 = tp.n0 + wn * (TN * 32) + j * 32;
+                uint8_t* p = reinterpret_cast<uint8_t*>(a.Y) + SZ * ((int64_t)row0 * ldy + col0);
+                if constexpr (TN % 2 == 1)
+                    if (j + 1 == TN) {
+                        const int held = 2 * (r & 15) + (r >> 4);
+                        const float cs = column_scale(col0 + held);
+                        p += SZ * ((rl + (r >> 4)) * ldy + 2 * (r & 15));
+#pragma unroll
+                        for (int k = 0; k < 16; k += 2) {
+                            const u32x2 o = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, result(j, k, cs)),
+                                                                             __builtin_bit_cast(uint32_t, result(j, k + 1, cs)), false, false);
+                            const uint32_t o0 = o.x, o1 = o.y;
+                            store2(p, row0 + rl + (r >> 4) + 8 * (k >> 2) + (k & 2), col0 + 2 * (r & 15),
+                                   (v2f){__builtin_bit_cast(float, o0), __builtin_bit_cast(float, o1)});
+                            p += (k & 2 ? 6 : 2) * SZ * ldy;
+                        }
+                        break;
+                    }
+                const int jr = j + 1 < TN ? j + 1 : j;
+                const int lc = 4 * (r & 15) + 2 * (r >> 4);  // this lane's columns lc, lc + 1 of the pair's 64
+                const float c0 = column_scale(col0 + lc), c1 = column_scale(col0 + lc + 1);
+                auto both = [&](int k) __attribute__((always_inline)) -> v2f { return (v2f){result(j, k, c0), result(jr, k, c1)}; };
+                if constexpr (BF16 && KIND >= 1) {
+                    const uint32_t off = 2u * (uint32_t)((rl + (r >> 4)) * (int)ldy + 4 * (r & 15));
+#pragma unroll
+                    for (int k = 0; k < 16; k += 2) {
+                        // lanes 0..15 of a half keep row k of both lanes of an exchange, lanes 16..31 row k + 1
+                        const u32x2 out = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, __builtin_convertvector(both(k), v2bf)),
+                                                                           __builtin_bit_cast(uint32_t, __builtin_convertvector(both(k + 1), v2bf)),
+                                                                           false, false);
+                        if (KIND == 2 || row0 + rl + (r >> 4) + 8 * (k >> 2) + (k & 2) < tp.row_end)
+                            __builtin_nontemporal_store(out, reinterpret_cast<u32x2*>(p + off));
+                        p += (k & 2 ? 6 : 2) * SZ * ldy;
+                    }
+                } else if constexpr (KIND >= 1) {
+                    p += SZ * ((rl + (r >> 4)) * ldy + 4 * (r & 15));
+#pragma unroll
+                    for (int k = 0; k < 16; k += 2) {
+                        const v2f a0 = both(k), a1 = both(k + 1);
+                        const float x0 = a0.x, y0 = a0.y, x1 = a1.x, y1 = a1.y;
+                        const u32x2 x = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, x0), __builtin_bit_cast(uint32_t, x1), false, false);
+                        const u32x2 y = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, y0), __builtin_bit_cast(uint32_t, y1), false, false);
+                        if (KIND == 2 || row0 + rl + (r >> 4) + 8 * (k >> 2) + (k & 2) < tp.row_end)
+                            *reinterpret_cast<u32x4_4*>(p) = (u32x4_4){x.x, y.x, x.y, y.y};
+                        p += (k & 2 ? 6 : 2) * SZ * ldy;
+                    }
+                } else {
+                    p += SZ * (rl * ldy + lc);
 #pragma unroll
                     for (int k = 0; k < 16; ++k) {
-                        const int row = rbase + 8 * (k >> 2) + (k & 3);
-                        if (FULL || (row < row_end && (KIND == 1 || col < a.N))) Y[(int64_t)row * a.ldy + col] = v[k];
+                        store2(p, row0 + rl + 8 * (k >> 2) + (k & 3), col0 + lc, both(k));
+                        p += ((k & 3) == 3 ? 5 : 1) * SZ * ldy;
                     }
                 }
             }
         }
     };
-    // 32-bit stores of bf16 pairs need an even leading dimension and a 4-byte aligned Y
-    const bool cols = (n0 + BN <= a.N) &&
-                      (!a.y_bf16 || (((a.ldy & 3) == 0) && ((reinterpret_cast<uintptr_t>(a.Y) & 7) == 0)));
-    if (cols && m0 + BM <= row_end)
-        store_tile(std::integral_constant<int, 2>{});
-    else if (cols)
-        store_tile(std::integral_constant<int, 1>{});
-    else
-        store_tile(std::integral_constant<int, 0>{});
+    const std::integral_constant<int, 0> any{};
+    const std::integral_constant<int, 1> rows{};
+    const std::integral_constant<int, 2> inside{};
+    // bf16: 8-byte stores of four columns
+    const bool wide = !a.y_bf16 || ((ldy & 3) == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 7) == 0);
+    if (wide && (WHOLE || (tp.n0 + BN <= a.N && tp.m0 + BM <= tp.row_end))) {
+        if (a.y_bf16) store(inside, std::true_type{});
+        else store(inside, std::false_type{});
+    } else if (!WHOLE && wide && tp.n0 + BN <= a.N) {
+        if (a.y_bf16) store(rows, std::true_type{});
+        else store(rows, std::false_type{});
+    } else {
+        if (a.y_bf16) store(any, std::true_type{});
+        else if (!WHOLE) store(any, std::false_type{});
+    }
 }
 
 // Flowing kernel (gemm_flow.hip).  flow_choose: the tile that should be fastest for one problem (-1: too few stages for

@@ -97,6 +97,28 @@ def test_flow_several_tiles_per_workgroup(osc, tuning, tile, mode):
     check(osc, tuning, tile, mode, M, N, 256 * (lead + 1) if mode == "dual" else 128 * (lead + 3), 2 if mode == "dual" else 0, 7700 + tile)
 
 
+@pytest.mark.parametrize("mode", ["dual", "fp8", "mx8"])
+@pytest.mark.parametrize("cfg", ["0,7", "1,7", "2,7", "3,7", "4,2", "4,1", "2,1", "1,1"])
+def test_output_views(osc, tuning, cfg, mode):
+    """The epilogue that all tiled kernels share, into views whose rows start at every residue of its store widths (16 bytes fp32, 8 bytes
+    bf16): the same values as in a buffer of their own, the rest of the view's buffer untouched; columns up to a
+    tile's last one, and rows past it.  The values themselves: the tests of each kernel."""
+    tuning.gemm(cfg)
+    for M, N in ((256, 512), (131, 395), (70, 1)) if cfg != "4,2" else ((256, 512),):
+        call, _ = problem(osc, mode, M, N, 1280, 1 if mode == "dual" else 0, 8100 + M)
+        for dt, ydt in ((torch.float32, osc.OSC_DT_F32), (torch.bfloat16, osc.OSC_DT_BF16)):
+            Y = call(ydt)
+            assert osc.osc_tuning_last_gemm() == tuple(int(x) for x in reversed(cfg.split(",")))
+            for pad, col0 in ((4, 0), (4, 2), (8, 4), (2, 2), (3, 1), (1, 0)):
+                wide = torch.full((M, N + pad), 7.0, dtype=dt, device="cuda")
+                call(ydt, wide[:, col0:col0 + N])
+                assert torch.equal(wide[:, col0:col0 + N], Y), (cfg, mode, M, N, dt, pad, col0)
+                assert bool((wide[:, :col0] == 7).all()) and bool((wide[:, col0 + N:] == 7).all())
+            if dt == torch.float32:
+                Y32 = Y
+        assert torch.equal(Y, Y32.to(torch.bfloat16))
+
+
 @pytest.mark.parametrize("stages,r", [(2, 0), (2, 1), (3, 4), (4, 0), (4, 2)])
 def test_flow_no_more_stages_than_the_lead(osc, tuning, stages, r):
     """Dual path on 64 x 128 tiles, where the load cursor is up to three tiles ahead of the products: one tile, two, and six or seven
