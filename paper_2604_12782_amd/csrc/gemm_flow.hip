@@ -282,13 +282,16 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
         if constexpr (DUAL) S[b] = *reinterpret_cast<const uint16_t*>(sc + H * 128 + 2 * q);
         else S[b] = sc[2 * H + q];
     };
-    auto mfma = [&](auto fp4, const u32x4 (&F)[HR][2], const int (&S)[HR], int n) __attribute__((always_inline)) {
+    const v16f zero = {};
+    // fresh: the tile's first products start from zero (clearing the accumulators takes two wavefronts 512 cycles a tile: 1 to 2 %
+    // of experts' tiles, 1 % of others; FEW, whose first stage may be the last, clears them)
+    auto mfma = [&](auto fp4, auto fresh, const u32x4 (&F)[HR][2], const int (&S)[HR], int n) __attribute__((always_inline)) {
         if constexpr (DUAL) {
             const int p = n / (TM * TN), i = n % (TM * TN) / TN, j = n % TN;
             if constexpr (decltype(fp4)::value) {
                 const v8i av = {(int)F[i][p].x, (int)F[i][p].y, (int)F[i][p].z, (int)F[i][p].w, 0, 0, 0, 0};
                 const v8i bv = {(int)F[TM + j][p].x, (int)F[TM + j][p].y, (int)F[TM + j][p].z, (int)F[TM + j][p].w, 0, 0, 0, 0};
-                if (p == 0) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[i][j], 4, 4, 0, S[i], 0, S[TM + j]);
+                if (p == 0) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, decltype(fresh)::value ? zero : acc[i][j], 4, 4, 0, S[i], 0, S[TM + j]);
                 else acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[i][j], 4, 4, 1, S[i], 1, S[TM + j]);
             } else {
                 acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, F[i][p]), __builtin_bit_cast(v8bf, F[TM + j][p]),
@@ -300,19 +303,19 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
                             (int)F[i][1].x, (int)F[i][1].y, (int)F[i][1].z, (int)F[i][1].w};
             const v8i bv = {(int)F[TM + j][0].x, (int)F[TM + j][0].y, (int)F[TM + j][0].z, (int)F[TM + j][0].w,
                             (int)F[TM + j][1].x, (int)F[TM + j][1].y, (int)F[TM + j][1].z, (int)F[TM + j][1].w};
-            if constexpr (MX) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[i][j], 0, 0, 0, S[i], 0, S[TM + j]);
-            else acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, acc[i][j], 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
+            if constexpr (MX) acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, decltype(fresh)::value ? zero : acc[i][j], 0, 0, 0, S[i], 0, S[TM + j]);
+            else acc[i][j] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, decltype(fresh)::value ? zero : acc[i][j], 0, 0, 0, 0x7f7f7f7f, 0, 0x7f7f7f7f);
         }
     };
     constexpr int NSLOT = (DUAL ? 2 : 1) * TM * TN;              // MFMAs of a half stage
     constexpr int RSL = NSLOT * 5 / 8 > 0 ? NSLOT * 5 / 8 : 1;   // slots that carry fragment reads
     constexpr int RPS = (2 * HR + RSL - 1) / RSL;
     constexpr int SPS = (HR + RSL - 1) / RSL;
-    auto half = [&](auto fp4, auto load, const u32x4 (&F)[HR][2], const int (&S)[HR], u32x4 (&G)[HR][2], int (&R)[HR], int H,
+    auto half = [&](auto fp4, auto fresh, auto load, const u32x4 (&F)[HR][2], const int (&S)[HR], u32x4 (&G)[HR][2], int (&R)[HR], int H,
                     int s) __attribute__((always_inline)) {
 #pragma unroll
         for (int n = 0; n < NSLOT; ++n) {
-            mfma(fp4, F, S, n);
+            mfma(fp4, fresh, F, S, n);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int u = 0; u < SPS; ++u)
@@ -328,15 +331,15 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto stage = [&](auto fp4, auto load) __attribute__((always_inline)) {
+    auto stage = [&](auto fp4, auto fresh, auto load) __attribute__((always_inline)) {
         constexpr bool LOAD = decltype(load)::value;
-        half(fp4, std::false_type{}, X, sX, Yf, sY, 1, cslot);
+        half(fp4, fresh, std::false_type{}, X, sX, Yf, sY, 1, cslot);
         if constexpr (!LAG) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront has read the whole stage
         wait_vmcnt<LOAD ? (LEAD - 2) * NLD : 0>();
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         cslot = cslot + 1 == NSTG ? 0 : cslot + 1;
-        half(fp4, load, Yf, sY, X, sX, 0, cslot);
+        half(fp4, std::false_type{}, load, Yf, sY, X, sX, 0, cslot);
         // the branches of finish_stage() end the basic block: without a use of the results here the compiler sinks
         // every MFMA of the stage below them
 #pragma unroll
@@ -384,28 +387,31 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
         if constexpr (FEW) left -= nT;
         int T = 0;
         if (!GROUPED || cur.m0 + wm * (TM * 32) < cur.row_end) {
+            if constexpr (FEW) {
 #pragma unroll
-            for (int i = 0; i < TM; ++i)
+                for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int j = 0; j < TN; ++j)
+                    for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int k = 0; k < 16; ++k) acc[i][j][k] = 0.0f;
+                        for (int k = 0; k < 16; ++k) acc[i][j][k] = 0.0f;
+            }
             const std::true_type yes{};
             const std::false_type no{};
+            if constexpr (!FEW) stage(yes, yes, yes), ++T;
             if constexpr (DUAL) {
 #pragma unroll 1
-                for (; T < min(nTA, L); ++T) stage(yes, yes);
+                for (; T < min(nTA, L); ++T) stage(yes, no, yes);
 #pragma unroll 1
-                for (; T < L; ++T) stage(no, yes);
+                for (; T < L; ++T) stage(no, no, yes);
 #pragma unroll 1
-                for (; T < nTA; ++T) stage(yes, no);
+                for (; T < nTA; ++T) stage(yes, no, no);
 #pragma unroll 1
-                for (; T < nT; ++T) stage(no, no);
+                for (; T < nT; ++T) stage(no, no, no);
             } else {
 #pragma unroll 1
-                for (; T < L; ++T) stage(yes, yes);
+                for (; T < L; ++T) stage(yes, no, yes);
 #pragma unroll 1
-                for (; T < nT; ++T) stage(yes, no);
+                for (; T < nT; ++T) stage(yes, no, no);
             }
             store_pairs<MODE, TM, TN, WN, WM, FP8>(a, cur, acc, tsc + cpar * (BM + BN));
         } else {
