@@ -9,9 +9,10 @@ namespace osc {
 // every operand row, as in the DMA kernel; a ring of NSTG stages in LDS is filled by global->LDS DMA three or four
 // stages ahead of the products, across tile borders, and a stage costs one barrier:
 //
-//   first half:   products on X (first half of stage T, registers)   | fragments of the second half -> Yf
+//   first half:   products on X (first half of stage T, registers)   | fragments of the second half -> Yf;
+//                                                                      SPLIT: rest of the requests for stage T + LEAD - 1
 //   barrier:      this wavefront's requests for stage T + 1 have landed; all have read stage T
-//   second half:  products on Yf                                     | requests for stage T + LEAD into the slot of T;
+//   second half:  products on Yf                                     | (first) requests for stage T + LEAD into the slot of T;
 //                                                                      first half of stage T + 1 -> X
 //
 // so fragments are read half a stage before the products that need them, and no wait in the loop is for a request
@@ -311,7 +312,17 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
     constexpr int RSL = NSLOT * 5 / 8 > 0 ? NSLOT * 5 / 8 : 1;   // slots that carry fragment reads
     constexpr int RPS = (2 * HR + RSL - 1) / RSL;
     constexpr int SPS = (HR + RSL - 1) / RSL;
-    auto half = [&](auto fp4, auto fresh, auto load, const u32x4 (&F)[HR][2], const int (&S)[HR], u32x4 (&G)[HR][2], int (&R)[HR], int H,
+    // SPLIT: NL1 of a stage's requests go out behind the barrier, the others before the next one.  A CU takes a request of
+    // 1 KB in 16 cycles, so the 24 to 48 of a stage are more than half a stage of FP4 products covers.  Experts of 256 rows 122 ->
+    // 119.5 us (dual), 92.8 -> 91.4 (MXFP8); 64 x 128 tiles 11.3 -> 11.0, 7.2 -> 6.9.  The larger tiles of one problem are level or, with
+    // operands in the second-level caches, up to 2 % slower (8192 x 1024 x 4096), as is 512 x 4096 x 768 in the form FEW (3 %).
+    constexpr bool SPLIT = (LAG || GROUPED) && !FEW;
+    constexpr int NL1 = SPLIT ? (NLD + 1) / 2 : NLD;
+    const std::integral_constant<int, 0> none{};
+    const std::integral_constant<int, NL1> part1{};
+    const std::integral_constant<int, NLD - NL1> part2{};
+    // requests first, first + 1, ... (count of them) are spread over the half's products
+    auto half = [&](auto fp4, auto fresh, auto first, auto count, const u32x4 (&F)[HR][2], const int (&S)[HR], u32x4 (&G)[HR][2], int (&R)[HR], int H,
                     int s) __attribute__((always_inline)) {
 #pragma unroll
         for (int n = 0; n < NSLOT; ++n) {
@@ -323,30 +334,47 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
 #pragma unroll
             for (int u = 0; u < RPS; ++u)
                 if (n * RPS + u < 2 * HR) read_frag(G, n * RPS + u, H, s);
-            if constexpr (decltype(load)::value) {
+            constexpr int FIRST = decltype(first)::value, COUNT = decltype(count)::value;
 #pragma unroll
-                for (int l = 0; l < NLD; ++l)
-                    if (l * NSLOT / NLD == n) load_one(l);
-            }
+            for (int l = 0; l < COUNT; ++l)
+                if (l * NSLOT / (COUNT > 0 ? COUNT : 1) == n) load_one(FIRST + l);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
-    auto stage = [&](auto fp4, auto fresh, auto load) __attribute__((always_inline)) {
-        constexpr bool LOAD = decltype(load)::value;
-        half(fp4, fresh, std::false_type{}, X, sX, Yf, sY, 1, cslot);
-        if constexpr (!LAG) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront has read the whole stage
-        wait_vmcnt<LOAD ? (LEAD - 2) * NLD : 0>();
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        cslot = cslot + 1 == NSTG ? 0 : cslot + 1;
-        half(fp4, std::false_type{}, load, Yf, sY, X, sX, 0, cslot);
-        // the branches of finish_stage() end the basic block: without a use of the results here the compiler sinks
-        // every MFMA of the stage below them
+    // the branches of finish_stage() end the basic block: without a use of the results there the compiler sinks
+    // every MFMA of the stage below them
+    auto keep_products = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
             for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(acc[i][j]));
-        if constexpr (LOAD) finish_stage();
+    };
+    auto load_rest = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int l = NL1; l < NLD; ++l) load_one(l);
+        finish_stage();
+    };
+    // load: there is a stage to ask for behind the barrier; rest: the one before it still has requests to come
+    auto stage = [&](auto fp4, auto fresh, auto load, bool rest) __attribute__((always_inline)) {
+        constexpr bool LOAD = decltype(load)::value;
+        if constexpr (SPLIT && LOAD) {
+            half(fp4, fresh, part1, part2, X, sX, Yf, sY, 1, cslot);
+            keep_products();
+            finish_stage();
+        } else {
+            if (SPLIT && rest) load_rest();
+            half(fp4, fresh, none, none, X, sX, Yf, sY, 1, cslot);
+        }
+        if constexpr (!LAG) __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wavefront has read the whole stage
+        if (LOAD || (SPLIT && rest)) wait_vmcnt<(LEAD - 2) * NLD>();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        cslot = cslot + 1 == NSTG ? 0 : cslot + 1;
+        if constexpr (LOAD) half(fp4, std::false_type{}, none, part1, Yf, sY, X, sX, 0, cslot);
+        else half(fp4, std::false_type{}, none, none, Yf, sY, X, sX, 0, cslot);
+        keep_products();
+        if constexpr (!SPLIT && LOAD) finish_stage();
     };
 
     // first half of the stage under the compute cursor
@@ -370,11 +398,14 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
 #pragma unroll 1
     for (int s = 0; s < (FEW ? min(LEAD, left) : LEAD); ++s) {
 #pragma unroll
-        for (int l = 0; l < NLD; ++l) load_one(l);
+        for (int l = 0; l < NL1; ++l) load_one(l);
+        if (SPLIT && s + 1 == LEAD) break;  // the first stage asks for the rest
+#pragma unroll
+        for (int l = NL1; l < NLD; ++l) load_one(l);
         if (FEW && mapped && lT + 1 == nT) wait_vmcnt<0>();  // the next tile is entered before the loop's waits have covered its map entries
         finish_stage();
     }
-    if (!FEW || left >= LEAD) wait_vmcnt<(LEAD - 1) * NLD>();
+    if (!FEW || left >= LEAD) wait_vmcnt<(LEAD - 2) * NLD + NL1>();
     else wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
@@ -383,7 +414,9 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
 #pragma unroll 1
     for (;;) {
         const bool more = ctile + step < last;
-        const int L = FEW ? min(nT, max(left - LEAD, 0)) : more ? nT : nT - LEAD;  // stages during which there is still something to load
+        // stages behind whose barrier there is still something to load, and those that have a rest to ask for (SPLIT)
+        const int L = FEW ? min(nT, max(left - LEAD, 0)) : more ? nT : nT - LEAD;
+        const int LR = more ? nT : nT - LEAD + 1;
         if constexpr (FEW) left -= nT;
         int T = 0;
         if (!GROUPED || cur.m0 + wm * (TM * 32) < cur.row_end) {
@@ -397,37 +430,38 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
             }
             const std::true_type yes{};
             const std::false_type no{};
-            if constexpr (!FEW) stage(yes, yes, yes), ++T;
+            if constexpr (!FEW) stage(yes, yes, yes, true), ++T;
             if constexpr (DUAL) {
 #pragma unroll 1
-                for (; T < min(nTA, L); ++T) stage(yes, no, yes);
+                for (; T < min(nTA, L); ++T) stage(yes, no, yes, true);
 #pragma unroll 1
-                for (; T < L; ++T) stage(no, no, yes);
+                for (; T < L; ++T) stage(no, no, yes, true);
 #pragma unroll 1
-                for (; T < nTA; ++T) stage(yes, no, no);
+                for (; T < nTA; ++T) stage(yes, no, no, T < LR);
 #pragma unroll 1
-                for (; T < nT; ++T) stage(no, no, no);
+                for (; T < nT; ++T) stage(no, no, no, T < LR);
             } else {
 #pragma unroll 1
-                for (; T < L; ++T) stage(yes, no, yes);
+                for (; T < L; ++T) stage(yes, no, yes, true);
 #pragma unroll 1
-                for (; T < nT; ++T) stage(yes, no, no);
+                for (; T < nT; ++T) stage(yes, no, no, T < LR);
             }
             store_pairs<MODE, TM, TN, WN, WM, FP8>(a, cur, acc, tsc + cpar * (BM + BN));
         } else {
             // an expert's last tile, no rows for this wavefront: it loads for the others and keeps their barriers
 #pragma unroll 1
             for (; T < nT; ++T) {
+                if (SPLIT && T < LR) load_rest();
                 __builtin_amdgcn_s_waitcnt(0xC07F);
-                if (T < L) wait_vmcnt<(LEAD - 2) * NLD>();
+                if (T < (SPLIT ? LR : L)) wait_vmcnt<(LEAD - 2) * NLD>();
                 else wait_vmcnt<0>();
                 __builtin_amdgcn_s_barrier();
                 __builtin_amdgcn_sched_barrier(0);
                 cslot = cslot + 1 == NSTG ? 0 : cslot + 1;
                 if (T < L) {
 #pragma unroll
-                    for (int l = 0; l < NLD; ++l) load_one(l);
-                    finish_stage();
+                    for (int l = 0; l < NL1; ++l) load_one(l);
+                    if constexpr (!SPLIT) finish_stage();
                 }
             }
             read_first();
