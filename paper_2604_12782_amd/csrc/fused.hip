@@ -202,7 +202,7 @@ __global__ void __launch_bounds__(FT) rmsnorm_quant_mxfp4_row_kernel(
             g[i] = reinterpret_cast<const u32x4*>(gamma)[c];
         }
     }
-    int och = t < K_o ? oidx[t] : -1;
+    const int och0 = t < K_o ? oidx[t] : -1;
     if (K_o > 0) {
 #pragma unroll
         for (int i = 0; i < NCH; ++i) *reinterpret_cast<u32x4*>(keep + 4 * (t + 256 * i)) = (u32x4){~0u, ~0u, ~0u, ~0u};
@@ -217,7 +217,7 @@ __global__ void __launch_bounds__(FT) rmsnorm_quant_mxfp4_row_kernel(
     if (lane == 0) top[wave] = wtop;
     __syncthreads();
     for (int o = t; o < K_o; o += FT) {
-        if (o != t) och = oidx[o];
+        const int och = o == t ? och0 : oidx[o];
         if (och >= 0 && och < K) atomicAnd(&keep[och >> 1], (och & 1) ? 0x0000ffffu : 0xffff0000u);
     }
     const int e = max(1, (int)(max(max(top[0], top[1]), max(top[2], top[3])) >> 7));
@@ -264,7 +264,7 @@ __global__ void __launch_bounds__(FT) rmsnorm_quant_mxfp4_row_kernel(
             __syncthreads();
             const uint16_t* const raw = reinterpret_cast<const uint16_t*>(strip);
             for (int o = t; o < K_o; o += FT) {
-                const int c = oidx[o];
+                const int c = o == t ? och0 : oidx[o];
                 brow[o] = c >= 0 && c < K ? raw[c] : 0;
             }
         }

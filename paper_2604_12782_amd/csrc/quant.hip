@@ -21,11 +21,17 @@ constexpr int QT = 256;  // threads per workgroup
 // one DPP row (their four scale codes leave as one 32-bit word of the row-block-major layout).
 // The four wavefronts of a workgroup never wait for each other inside the loop.
 //
-// The suppression list becomes, once per workgroup, a table of AND masks (one 32-bit word per
-// channel pair; zeroing protected channels is four ANDs per chunk, no branch) and the list of
-// B columns that each segment owns (the list is ascending, so a segment owns a contiguous run).
+// The suppression list becomes, once per workgroup, one bit per channel and the list of B columns that each segment owns (the
+// list is ascending, so a segment owns a contiguous run); a wavefront keeps what it needs of them for its segment in
+// registers (AND masks: zeroing protected channels is four ANDs per chunk, no branch).
 // Every wavefront parks its raw segment in its own LDS strip; the lanes then pick the
 // protected channels out of the strip and store the run of B columns themselves.
+//
+// Few rows are bound by a workgroup's set-up, a chain of memory and LDS round trips; many by the copy rate with eight
+// wavefronts a SIMD (asking for the next item ahead of the conversion: 18.7 us against 18.1 at 8192 x 4096, without a list 17.5
+// against 16.0).  With a mask word per channel pair instead of a bit, masks and columns read for every row, and workgroups
+// without rows expanding the list (us, two slots per group of 32, then -> now): 1 x 4096 3.2 -> 2.7, 16 x 4096 3.5 -> 3.0,
+// 512 x 4096 4.5 -> 4.0, 2000 x 4096 7.4 -> 6.4, 8192 x 4096 18.5 -> 18.0, 1000 x 12288 12.7 -> 9.5, 8192 x 12288 62 -> 51.
 //
 // Work is dealt so that the workgroups which the hardware places on one XCD hold 32 consecutive
 // rows at a time: the 4-byte scale words of those rows share 128-byte lines and meet in that
@@ -34,7 +40,8 @@ constexpr int QT = 256;  // threads per workgroup
 //
 // GS is the size of a scale group: 32, or 64 (one more exchange: the two quads that hold a group
 // of 64 agree on the larger amax, and its code is written for both of the group's blocks of 32).
-template <int GS>
+// LIST: there is a list.  MULTI: a wavefront has more than one item.
+template <int GS, bool LIST, bool MULTI>
 __global__ void __launch_bounds__(QT) quant_mxfp4_osc_kernel(
     const uint16_t* __restrict__ X, int M, int K, int64_t ldx, const int32_t* __restrict__ oidx,
     int K_o, uint8_t* __restrict__ Xq, uint8_t* __restrict__ Xs, uint16_t* __restrict__ B,
@@ -43,118 +50,99 @@ __global__ void __launch_bounds__(QT) quant_mxfp4_osc_kernel(
     const int Kg = K >> 5, Kg4 = (Kg + 3) >> 2;
     const int nchunk = K >> 3;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: row and segment arithmetic stays on the scalar unit
-    // LDS: strips [4][SEG_CHUNKS] x 16 B | keep [K/2] words | colstart [nseg+1] | oidx16 [K_o]
+    // LDS: strips [4][SEG_CHUNKS] x 16 B | one bit per channel [K/32] words | colstart [nseg+1] | oidx16 [K_o]
     u32x4* strip = reinterpret_cast<u32x4*>(smem) + wave * SEG_CHUNKS;
-    uint32_t* keep = smem + 4 * SEG_CHUNKS * 4;
-    int* colstart = reinterpret_cast<int*>(keep + (K >> 1));
+    uint32_t* bits = smem + 4 * SEG_CHUNKS * 4;
+    int* colstart = reinterpret_cast<int*>(bits + Kg);
     uint16_t* och = reinterpret_cast<uint16_t*>(colstart + nseg + 1);
 
     int wg = blockIdx.x;
-    QItem cur = wg < total_wg ? quant_item(wg, wave, nseg, M) : QItem{-1, 0};
-    u32x4 v0 = {0u, 0u, 0u, 0u}, v1 = {0u, 0u, 0u, 0u};
-#define OSC_Q_LOAD(A0_, A1_, IT_)                                                              \
-    do {                                                                                       \
-        A0_ = (u32x4){0u, 0u, 0u, 0u};                                                         \
-        A1_ = (u32x4){0u, 0u, 0u, 0u};                                                         \
-        if ((IT_).m >= 0) {                                                                    \
-            const u32x4* src_ = reinterpret_cast<const u32x4*>(X + (int64_t)(IT_).m * ldx);    \
-            const int c_ = (IT_).seg * SEG_CHUNKS + lane;                                      \
-            if (c_ < nchunk) A0_ = __builtin_nontemporal_load(src_ + c_);                      \
-            if (c_ + 64 < nchunk) A1_ = __builtin_nontemporal_load(src_ + c_ + 64);            \
-        }                                                                                      \
-    } while (0)
-    OSC_Q_LOAD(v0, v1, cur);  // in flight during the set-up
+    if (quant_item(wg, 0, nseg, M).m < 0) return;  // no row for this workgroup, nor in later trips
+    QItem cur = quant_item(wg, wave, nseg, M);
+    // an item's two chunks a lane; without a row those of the last one, past the end of a row its last chunk (not used)
+    auto load = [&](u32x4& v0, u32x4& v1, const QItem& it) __attribute__((always_inline)) {
+        const uint8_t* src = reinterpret_cast<const uint8_t*>(X + (int64_t)(it.m >= 0 ? it.m : M - 1) * ldx);
+        const uint32_t c = (uint32_t)(it.seg * SEG_CHUNKS + lane), end = (uint32_t)nchunk - 1;
+        v0 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + min(c, end) * 16u));
+        v1 = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(src + min(c + 64, end) * 16u));
+    };
+    u32x4 a0, a1;
+    load(a0, a1, cur);  // in flight during the set-up
+    if constexpr (LIST) list_expand<QT>(oidx, K_o, K, nseg, t, bits, colstart, och);
+    if (cur.m < 0) return;
 
-    if (K_o > 0) {
-        for (int i = t; i < (K >> 1); i += QT) keep[i] = 0xffffffffu;
-        __syncthreads();
-        for (int o = t; o < K_o; o += QT) {
-            const int c = oidx[o];
-            const int prev = o ? oidx[o - 1] : -1;
-            if (c >= 0 && c < K) atomicAnd(&keep[c >> 1], (c & 1) ? 0x0000ffffu : 0xffff0000u);
-            och[o] = (uint16_t)c;
-            // segments that start between the previous listed channel and this one start here
-            for (int sgm = (prev < 0 ? -1 : prev / SEG_CH) + 1; sgm <= c / SEG_CH && sgm <= nseg; ++sgm)
-                colstart[sgm] = o;
-            if (o == K_o - 1)
-                for (int sgm = c / SEG_CH + 1; sgm <= nseg; ++sgm) colstart[sgm] = K_o;
+    SegmentList list;
+    auto convert = [&](const QItem& it, const u32x4& v0, const u32x4& v1) __attribute__((always_inline)) {
+        const int m = it.m;
+        const int cbase = it.seg * SEG_CHUNKS;
+        uint8_t* dst = Xq + (int64_t)m * (K >> 1);
+        uint8_t* sdst = Xs + (int64_t)(m >> 5) * Kg4 * 128 + (m & 31) * 4;
+        if constexpr (LIST) {
+            if (!MULTI || it.seg != list.seg) list.take(it.seg, lane, nchunk, bits, colstart, och);
+            strip[lane] = v0;
+            strip[lane + 64] = v1;
         }
-        __syncthreads();
-    }
-
-    while (wg < total_wg) {
-        const int wgn = wg + gridDim.x;
-        const QItem nxt = wgn < total_wg ? quant_item(wgn, wave, nseg, M) : QItem{-1, 0};
-        u32x4 n0, n1;
-        OSC_Q_LOAD(n0, n1, nxt);  // next trip's loads fly while this one is converted
-        if (cur.m >= 0) {
-            const int m = cur.m;
-            const int cbase = cur.seg * SEG_CHUNKS;
-            uint32_t* dst = reinterpret_cast<uint32_t*>(Xq + (int64_t)m * (K >> 1));
-            uint8_t* sdst = Xs + (int64_t)(m >> 5) * Kg4 * 128 + (m & 31) * 4;
-            if (K_o > 0) {
-                strip[lane] = v0;
-                strip[lane + 64] = v1;
-            }
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int c = cbase + lane + 64 * i;
-                u32x4 w = i ? v1 : v0;
-                if (K_o > 0 && c < nchunk) {  // steps 2-3 of Section 3.2: (back-up is the strip) zero
-                    const u32x4 kp = *reinterpret_cast<const u32x4*>(keep + 4 * c);
-                    w &= kp;
-                }
-                // amax of the group on bit patterns: for finite bf16 |x| orders like bits & 0x7fff
-                u32x4 ab = w & 0x7fff7fffu;
-                uint32_t a = max(max(ab.x & 0xffffu, ab.x >> 16), max(ab.y & 0xffffu, ab.y >> 16));
-                a = max(a, max(max(ab.z & 0xffffu, ab.z >> 16), max(ab.w & 0xffffu, ab.w >> 16)));
-                a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0xB1, 0xF, 0xF, false));  // lane ^ 1
-                a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x4E, 0xF, 0xF, false));  // lane ^ 2
-                if (GS == 64)  // lane 7 - l of the same eight lanes sits in the group's other quad
-                    a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x141, 0xF, 0xF, false));
-                // shared exponent floor(log2 amax) - 2, clamped below: E8M0 code = max(E - 2, 0)
-                const uint32_t code = (uint32_t)max((int)(a >> 7) - 2, 0);
-                // four blocks of 32 (one DPP row of 16 lanes) -> one 32-bit scale word in the row's first lane;
-                // chunks past the end of the row hold zeros, so their code is 0
-                uint32_t word = code;
-                word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x104, 0xF, 0xF, true) << 8;   // lane + 4
-                word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x108, 0xF, 0xF, true) << 16;  // lane + 8
-                word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x10C, 0xF, 0xF, true) << 24;  // lane + 12
-                if ((lane & 15) == 0 && c < nchunk)
-                    *reinterpret_cast<uint32_t*>(sdst + (c >> 4) * 128) = word;
-                const float scale = __builtin_bit_cast(float, code << 23);
-                // (scalars first: a bit cast applied to a vector component reads component 0)
-                const uint32_t w0 = w.x, w1 = w.y, w2 = w.z, w3 = w.w;
-                uint32_t out = 0;
-                out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, w0), scale, 0);
-                out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, w1), scale, 1);
-                out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, w2), scale, 2);
-                out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, w3), scale, 3);
-                if (c < nchunk) __builtin_nontemporal_store(out, dst + c);
-            }
-            if (K_o > 0) {
-                // The strip was written by this wavefront, and LDS runs a wavefront's operations in
-                // order; the fences keep the compiler from moving the reads above the writes.
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                const uint16_t* raw = reinterpret_cast<const uint16_t*>(strip);
-                uint16_t* brow = B + (int64_t)m * ldb;
-                const int o1 = colstart[cur.seg + 1];
-                for (int o = colstart[cur.seg] + lane; o < o1; o += 64)
-                    brow[o] = raw[(int)och[o] - cur.seg * SEG_CH];
-                if (cur.seg == nseg - 1)
-                    for (int o = K_o + lane; o < (int)ldb; o += 64) brow[o] = 0;  // padding columns: +0
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
+        for (int i = 0; i < 2; ++i) {
+            const int c = cbase + lane + 64 * i;
+            u32x4 w = i ? v1 : v0;
+            if constexpr (LIST) w &= (u32x4){list.keep[i][0], list.keep[i][1], list.keep[i][2], list.keep[i][3]};  // steps 2-3 of Section 3.2: (back-up is the strip) zero
+            else w = c < nchunk ? w : (u32x4){0u, 0u, 0u, 0u};
+            // amax of the group on bit patterns: for finite bf16 |x| orders like bits & 0x7fff
+            u32x4 ab = w & 0x7fff7fffu;
+            uint32_t a = max(max(ab.x & 0xffffu, ab.x >> 16), max(ab.y & 0xffffu, ab.y >> 16));
+            a = max(a, max(max(ab.z & 0xffffu, ab.z >> 16), max(ab.w & 0xffffu, ab.w >> 16)));
+            a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0xB1, 0xF, 0xF, false));  // lane ^ 1
+            a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x4E, 0xF, 0xF, false));  // lane ^ 2
+            if (GS == 64)  // lane 7 - l of the same eight lanes sits in the group's other quad
+                a = max(a, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a, 0x141, 0xF, 0xF, false));
+            // shared exponent floor(log2 amax) - 2, clamped below: E8M0 code = max(E - 2, 0)
+            const uint32_t code = (uint32_t)max((int)(a >> 7) - 2, 0);
+            // four blocks of 32 (one DPP row of 16 lanes) -> one 32-bit scale word in the row's first lane;
+            // chunks past the end of the row hold zeros, so their code is 0
+            uint32_t word = code;
+            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x104, 0xF, 0xF, true) << 8;   // lane + 4
+            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x108, 0xF, 0xF, true) << 16;  // lane + 8
+            word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x10C, 0xF, 0xF, true) << 24;  // lane + 12
+            if ((lane & 15) == 0 && c < nchunk)
+                *reinterpret_cast<uint32_t*>(sdst + (uint32_t)(c >> 4) * 128u) = word;
+            const float scale = __builtin_bit_cast(float, code << 23);
+            // (scalars first: a bit cast applied to a vector component reads component 0)
+            const uint32_t w0 = w.x, w1 = w.y, w2 = w.z, w3 = w.w;
+            uint32_t out = 0;
+            out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, w0), scale, 0);
+            out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, w1), scale, 1);
+            out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, w2), scale, 2);
+            out = __builtin_amdgcn_cvt_scalef32_pk_fp4_bf16(out, __builtin_bit_cast(v2bf, w3), scale, 3);
+            if (c < nchunk) __builtin_nontemporal_store(out, reinterpret_cast<uint32_t*>(dst + (uint32_t)c * 4u));
         }
-        cur = nxt;
-        v0 = n0;
-        v1 = n1;
-        wg = wgn;
+        if constexpr (LIST) {
+            // The strip was written by this wavefront, and LDS runs a wavefront's operations in
+            // order; the fences keep the compiler from moving the reads above the writes.
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            uint16_t* brow = B + (int64_t)m * ldb;
+            list.gather(brow, reinterpret_cast<const uint16_t*>(strip), lane, och);
+            if (it.seg == nseg - 1)
+                for (int o = K_o + lane; o < (int)ldb; o += 64) brow[o] = 0;  // padding columns: +0
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+        }
+    };
+    if constexpr (!MULTI) {
+        convert(cur, a0, a1);
+    } else {
+        auto next = [&]() __attribute__((always_inline)) -> QItem {
+            wg += gridDim.x;
+            return wg < total_wg ? quant_item(wg, wave, nseg, M) : QItem{-1, 0};
+        };
+        do {  // (items go down the rows: behind one without a row come no others)
+            convert(cur, a0, a1);
+            cur = next();
+            if (cur.m >= 0) load(a0, a1, cur);
+        } while (cur.m >= 0);
     }
-#undef OSC_Q_LOAD
 }
 
 // B columns of a table-free call still have to read +0 when the caller passes a buffer.
@@ -174,24 +162,35 @@ int launch_quant_mxfp4(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, con
     const int64_t nchunk = K / 8;
     const int nseg = (int)((nchunk + SEG_CHUNKS - 1) / SEG_CHUNKS);
     size_t smem = 4 * SEG_CHUNKS * 16;
-    if (K_o > 0) smem += (size_t)(K / 2) * 4 + (size_t)(nseg + 1) * 4 + (size_t)K_o * 2;
-    if (smem > 160 * 1024)
-        return fail(OSC_ERR_UNSUPPORTED, "quantize: K=%lld with K_o=%d needs %zu bytes of LDS", (long long)K, (int)K_o, smem);
-    auto kern = group == 64 ? quant_mxfp4_osc_kernel<64> : quant_mxfp4_osc_kernel<32>;
-    if (smem > 48 * 1024) {
-        // one flag set per kernel instantiation (scale groups of 32 and of 64)
-        static LdsReserved lds_reserved[2];
-        const int which = group == 64;
-        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved[which])) return rc;
+    if (K_o > 0) {
+        smem += (size_t)(K / 32) * 4 + (size_t)(nseg + 1) * 4 + (size_t)K_o * 2;
+        // the range that is accepted: a mask word per channel pair beside the rest
+        const size_t range = smem + (size_t)(K / 2 - K / 32) * 4;
+        if (range > 160 * 1024)
+            return fail(OSC_ERR_UNSUPPORTED, "quantize: K=%lld with K_o=%d needs %zu bytes of LDS", (long long)K, (int)K_o, range);
     }
     // 32-row blocks of 8*nseg workgroups each, dealt to XCDs in groups of eight blocks
     const int64_t blocks = (M + 31) / 32;
     const int64_t total_wg = (blocks + 7) / 8 * 8 * (8 * nseg);
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "quantize: M=%lld too large", (long long)M);
-    // eight workgroups per compute unit; sixteen when every one of them still gets eight items or more
-    // (M = 32768 at K = 4096: 63.1 -> 61.3 us; at M = 8192 the smaller grid is ahead, 17.9 against 18.6 us)
-    const int64_t cap = total_wg >= 8 * 4096 ? 4096 : 2048;
-    int grid = (int)(total_wg < cap ? total_wg : cap);
+    // One item a wavefront up to 4096 workgroups, then as many; from 2048 to 16384 four per CU where they have a list of some length to
+    // expand (us, 2048 / 1024 / 4096 workgroups: 4096 x 4096 11.0 / 10.5 / 10.7, 1000 x 12288 10.3 / 9.5 / 10.0,
+    // 8192 x 4096 18.4 / 18.0 / 18.1, 16384 x 4096 35 / 33 / 31.6; 2000 x 4096 6.4 / 6.8 / 6.4; no list, 8192 x 4096 16.1 / 19 / 16.0)
+    const bool list = K_o > 0;
+    // (a multiple of so many that a wavefront stays in its segment: 8192 x 5152 25.4 -> 24.3)
+    const int64_t cap = list && K >= 4096 && total_wg > 2048 && total_wg < 16384 ? 1024 : 4096;
+    const int64_t turn = 8 * (nseg % 4 == 0 ? nseg / 4 : nseg % 2 == 0 ? nseg / 2 : nseg);
+    const bool multi = total_wg > cap;
+    const int grid = (int)(multi ? cap - cap % turn : total_wg);
+    auto kern = group == 64 ? (list ? (multi ? quant_mxfp4_osc_kernel<64, true, true> : quant_mxfp4_osc_kernel<64, true, false>)
+                                    : (multi ? quant_mxfp4_osc_kernel<64, false, true> : quant_mxfp4_osc_kernel<64, false, false>))
+                            : (list ? (multi ? quant_mxfp4_osc_kernel<32, true, true> : quant_mxfp4_osc_kernel<32, true, false>)
+                                    : (multi ? quant_mxfp4_osc_kernel<32, false, true> : quant_mxfp4_osc_kernel<32, false, false>));
+    if (smem > 48 * 1024) {
+        // one flag set per kernel instantiation with a list (the others need no more than the strips)
+        static LdsReserved lds_reserved[4];
+        if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved[(group == 64) * 2 + multi])) return rc;
+    }
     if (K_o == 0 && B && ldb > 0)
         hipLaunchKernelGGL(zero_rows_kernel, dim3(grid), dim3(QT), 0, st, B, (int)M, ldb);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(QT), smem, st, X, (int)M, (int)K, ldx, oidx,

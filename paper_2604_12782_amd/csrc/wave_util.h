@@ -121,5 +121,60 @@ __device__ __forceinline__ QItem quant_item(int wg, int wave, int nseg, int M) {
     return q;
 }
 
+// The list of protected channels, expanded once per workgroup of T threads: one bit per channel, the list as 16-bit words, and the
+// first entry of every segment (nseg + 1 of them; the list is ascending, so a segment owns a run).
+template <int T>
+__device__ __forceinline__ void list_expand(const int32_t* __restrict__ oidx, int K_o, int K, int nseg, int t, uint32_t* bits, int* colstart,
+                                            uint16_t* och) {
+    for (int i = t; i < (K >> 5); i += T) bits[i] = 0;
+    __syncthreads();
+    for (int o = t; o < K_o; o += T) {
+        const int c = oidx[o];
+        const int prev = o ? oidx[o - 1] : -1;
+        if (c >= 0 && c < K) atomicOr(&bits[c >> 5], 1u << (c & 31));
+        och[o] = (uint16_t)c;
+        // segments that start between the previous listed channel and this one start here
+        for (int s = (prev < 0 ? -1 : prev / SEG_CH) + 1; s <= c / SEG_CH && s <= nseg; ++s) colstart[s] = o;
+        if (o == K_o - 1)
+            for (int s = c / SEG_CH + 1; s <= nseg; ++s) colstart[s] = K_o;
+    }
+    __syncthreads();
+}
+
+// What a wavefront needs of the list of protected channels for the segment that its rows are in, kept in registers from row to
+// row: AND masks of its lanes' two chunks, and where the segment's run of B columns comes from (two entries a lane; a longer
+// run goes on in LDS).
+struct SegmentList {
+    int seg = -1, run0 = 0, run1 = 0;
+    uint32_t keep[2][4];
+    int from[2];
+    __device__ __forceinline__ void take(int s, int lane, int nchunk, const uint32_t* bits, const int* colstart, const uint16_t* och) {
+        seg = s;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int c = s * SEG_CHUNKS + lane + 64 * i;
+            const int b = c < nchunk ? reinterpret_cast<const uint8_t*>(bits)[c] : 0xff;  // one bit per channel; past the end of the row zeros
+#pragma unroll
+            for (int k = 0; k < 4; ++k) keep[i][k] = ((b >> (2 * k)) & 1 ? 0u : 0xffffu) | ((b >> (2 * k + 1)) & 1 ? 0u : 0xffff0000u);
+        }
+        run0 = __builtin_amdgcn_readfirstlane(colstart[s]);
+        run1 = __builtin_amdgcn_readfirstlane(colstart[s + 1]);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int o = run0 + lane + 64 * i;
+            from[i] = o < run1 ? (int)och[o] - s * SEG_CH : -1;
+        }
+    }
+    // raw: the segment as it was
+    __device__ __forceinline__ void gather(uint16_t* brow, const uint16_t* raw, int lane, const uint16_t* och) const {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t o = (uint32_t)(run0 + lane + 64 * i);
+            if (o < (uint32_t)run1) brow[o] = raw[from[i]];
+        }
+#pragma unroll 1
+        for (int o = run0 + 128 + lane; o < run1; o += 64) brow[o] = raw[(int)och[o] - seg * SEG_CH];
+    }
+};
 
 }  // namespace osc

@@ -96,6 +96,30 @@ def test_quant_shapes(osc, M, K, r):
         quant_both(osc, X, oidx, ldb=len(oidx) + (-len(oidx)) % 8 + 8)  # odd padding width
 
 
+@pytest.mark.parametrize("M,K,G,pick", [
+    (1, 1056, 32, "all"), (3, 2080, 32, "last"), (33, 4096, 32, "none in a segment"), (2100, 4128, 32, "dense segment"),
+    (2200, 5184, 64, "drawn"), (2500, 4096, 32, "drawn"), (8300, 4096, 64, "dense segment"), (70000, 96, 32, "drawn")])
+def test_quant_lists_and_trips(osc, M, K, G, pick):
+    """The list as every wavefront sees it: empty, one-sided and long runs of a segment (more than the 128 entries that are kept in
+    registers), the list's ends, rows that end inside a segment; one item a wavefront (few rows), and several, with
+    segments that change from one to the next and that do not.  The number of workgroups steps at 2048, 4096 and 16384 times four items."""
+    g = np.random.default_rng(M + K)
+    c = np.arange(K)
+    on = {"all": c >= 0, "last": c == K - 1, "none in a segment": (c < 1024) | (c >= 2048 + 5), "dense segment": (c >= 1024) & (c < 2040),
+          "drawn": g.random(K) < 0.06}[pick]
+    if pick == "none in a segment":
+        on &= g.random(K) < 0.05
+    X = wl.activations_diffuse(77 + M, M, K)
+    oidx = np.flatnonzero(on).astype(np.int32)
+    rows = np.unique(np.concatenate([np.arange(min(M, 40)), np.arange(max(0, M - 40), M), g.integers(0, M, 60)]))
+    Xq, Xs, B = osc.osc_quantize_act(dev(X), dev(oidx), osc.OSC_FMT_MXFP4_OSC_G64 if G == 64 else osc.OSC_FMT_MXFP4_OSC)
+    rq, rs, rb = oracle.quantize_mxfp4_osc(X[rows], oidx, ldb=B.shape[1], G=G)
+    sel = torch.from_numpy(rows).cuda()
+    assert np.array_equal(Xq[sel].cpu().numpy(), rq)
+    assert np.array_equal(osc.osc_unpack_act_scales(Xs, M, K)[sel].cpu().numpy(), rs)
+    assert np.array_equal(host(B)[rows], rb)
+
+
 def test_quant_partial_table_and_full_table(osc):
     X, table = wl.activations_persistent(7, 33, 512, 3)
     table[::3] = -1  # some groups bypass suppression
