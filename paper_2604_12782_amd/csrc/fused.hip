@@ -394,12 +394,12 @@ __global__ void __launch_bounds__(FT) swiglu_quant_mxfp8_kernel(const uint16_t* 
                                                                 const uint16_t* __restrict__ U, int M, int K,
                                                                 int64_t ldg, int64_t ldu, uint8_t* __restrict__ Xq,
                                                                 uint8_t* __restrict__ Xs, uint16_t* __restrict__ Yn,
-                                                                int nseg, int total_wg) {
+                                                                int nseg, int quads, int total_wg) {
     const int Kg = K >> 5, Kg4 = (Kg + 3) >> 2;
     const int nchunk = K >> 3;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     for (int wg = blockIdx.x; wg < total_wg; wg += gridDim.x) {
-        const QItem it = quant_item(wg, wave, nseg, M);
+        const QItem it = quant_item(wg, wave, nseg, quads, M);
         if (it.m < 0) continue;  // uniform over the wavefront
         const int m = it.m;
         const u32x4* gsrc = reinterpret_cast<const u32x4*>(G + (int64_t)m * ldg);
@@ -461,8 +461,8 @@ int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, i
                               uint8_t* Xq, uint8_t* Xs, uint16_t* Yn, hipStream_t st) {
     const int64_t nchunk = K / 8;
     const int nseg = (int)((nchunk + SEG_CHUNKS - 1) / SEG_CHUNKS);
-    const int64_t blocks = (M + 31) / 32;
-    const int64_t total_wg = (blocks + 7) / 8 * 8 * (8 * nseg);
+    const RowSplit split = row_split(M, nseg);
+    const int64_t total_wg = split.wgs;
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "swiglu+quantize: M=%lld too large", (long long)M);
     // One trip per workgroup: the hardware hands out new workgroups as old ones drain, which beats walking a
     // fixed grid at every size of whole segments (8192 x 12288: 79 us, a grid of 8192 86 us, of 2048 92 us).
@@ -480,7 +480,7 @@ int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, i
     const int64_t cap = K >= SEG_CH ? MAX_GRID : 4096;
     const int grid = (int)(total_wg < cap ? total_wg : cap);
     hipLaunchKernelGGL(swiglu_quant_mxfp8_kernel, dim3(grid), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, Xq,
-                       Xs, Yn, nseg, (int)total_wg);
+                       Xs, Yn, nseg, split.quads, (int)total_wg);
     return check_launch("swiglu_quant_mxfp8_kernel");
 }
 

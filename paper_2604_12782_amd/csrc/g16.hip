@@ -35,7 +35,7 @@ constexpr int QT16 = 256;
 template <int FMT>
 __global__ void __launch_bounds__(QT16) quant_fp4_g16_kernel(
     const uint16_t* __restrict__ X, int M, int K, int64_t ldx, const int32_t* __restrict__ oidx, int K_o, float ts,
-    uint8_t* __restrict__ Xq, uint8_t* __restrict__ Xs, uint16_t* __restrict__ B, int64_t ldb, int nseg, int total_wg) {
+    uint8_t* __restrict__ Xq, uint8_t* __restrict__ Xs, uint16_t* __restrict__ B, int64_t ldb, int nseg, int quads, int total_wg) {
     extern __shared__ uint32_t smem[];
     const int nchunk = K >> 3;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -58,7 +58,7 @@ __global__ void __launch_bounds__(QT16) quant_fp4_g16_kernel(
     }
     const float d6 = __fmul_rn(6.0f, ts);
     for (int wg = blockIdx.x; wg < total_wg; wg += gridDim.x) {
-        const QItem cur = quant_item(wg, wave, nseg, M);
+        const QItem cur = quant_item(wg, wave, nseg, quads, M);
         if (cur.m < 0) continue;
         const int m = cur.m, cbase = cur.seg * SEG_CHUNKS;
         const u32x4* src = reinterpret_cast<const u32x4*>(X + (int64_t)m * ldx);
@@ -149,12 +149,12 @@ int launch_quant_fp4_g16(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, c
         static LdsReserved lds_reserved[2];
         if (int rc = reserve_lds(reinterpret_cast<const void*>(kern), smem, lds_reserved[fmt])) return rc;
     }
-    const int64_t blocks = (M + 31) / 32;
-    const int64_t total_wg = (blocks + 7) / 8 * 8 * (8 * nseg);
+    const RowSplit split = row_split(M, nseg);
+    const int64_t total_wg = split.wgs;
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "quantize: M=%lld too large", (long long)M);
     const int grid = (int)(total_wg < 2048 ? total_wg : 2048);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(QT16), smem, st, X, (int)M, (int)K, ldx, oidx, (int)K_o, ts, Xq, Xs, B, ldb,
-                       nseg, (int)total_wg);
+                       nseg, split.quads, (int)total_wg);
     return check_launch("quant_fp4_g16_kernel");
 }
 

@@ -45,7 +45,7 @@ template <int GS, bool LIST, bool MULTI>
 __global__ void __launch_bounds__(QT) quant_mxfp4_osc_kernel(
     const uint16_t* __restrict__ X, int M, int K, int64_t ldx, const int32_t* __restrict__ oidx,
     int K_o, uint8_t* __restrict__ Xq, uint8_t* __restrict__ Xs, uint16_t* __restrict__ B,
-    int64_t ldb, int nseg, int total_wg) {
+    int64_t ldb, int nseg, int quads, int total_wg) {
     extern __shared__ uint32_t smem[];
     const int Kg = K >> 5, Kg4 = (Kg + 3) >> 2;
     const int nchunk = K >> 3;
@@ -57,8 +57,8 @@ __global__ void __launch_bounds__(QT) quant_mxfp4_osc_kernel(
     uint16_t* och = reinterpret_cast<uint16_t*>(colstart + nseg + 1);
 
     int wg = blockIdx.x;
-    if (quant_item(wg, 0, nseg, M).m < 0) return;  // no row for this workgroup, nor in later trips
-    QItem cur = quant_item(wg, wave, nseg, M);
+    if (quant_item(wg, 0, nseg, quads, M).m < 0) return;  // no row for this workgroup, nor in later trips
+    QItem cur = quant_item(wg, wave, nseg, quads, M);
     // an item's two chunks a lane; without a row those of the last one, past the end of a row its last chunk (not used)
     auto load = [&](u32x4& v0, u32x4& v1, const QItem& it) __attribute__((always_inline)) {
         const uint8_t* src = reinterpret_cast<const uint8_t*>(X + (int64_t)(it.m >= 0 ? it.m : M - 1) * ldx);
@@ -135,7 +135,7 @@ __global__ void __launch_bounds__(QT) quant_mxfp4_osc_kernel(
     } else {
         auto next = [&]() __attribute__((always_inline)) -> QItem {
             wg += gridDim.x;
-            return wg < total_wg ? quant_item(wg, wave, nseg, M) : QItem{-1, 0};
+            return wg < total_wg ? quant_item(wg, wave, nseg, quads, M) : QItem{-1, 0};
         };
         do {  // (items go down the rows: behind one without a row come no others)
             convert(cur, a0, a1);
@@ -169,9 +169,8 @@ int launch_quant_mxfp4(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, con
         if (range > 160 * 1024)
             return fail(OSC_ERR_UNSUPPORTED, "quantize: K=%lld with K_o=%d needs %zu bytes of LDS", (long long)K, (int)K_o, range);
     }
-    // 32-row blocks of 8*nseg workgroups each, dealt to XCDs in groups of eight blocks
-    const int64_t blocks = (M + 31) / 32;
-    const int64_t total_wg = (blocks + 7) / 8 * 8 * (8 * nseg);
+    const RowSplit split = row_split(M, nseg);
+    const int64_t total_wg = split.wgs;
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "quantize: M=%lld too large", (long long)M);
     // One item a wavefront up to 4096 workgroups, then as many; from 2048 to 16384 four per CU where they have a list of some length to
     // expand (us, 2048 / 1024 / 4096 workgroups: 4096 x 4096 11.0 / 10.5 / 10.7, 1000 x 12288 10.3 / 9.5 / 10.0,
@@ -194,7 +193,7 @@ int launch_quant_mxfp4(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, con
     if (K_o == 0 && B && ldb > 0)
         hipLaunchKernelGGL(zero_rows_kernel, dim3(grid), dim3(QT), 0, st, B, (int)M, ldb);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(QT), smem, st, X, (int)M, (int)K, ldx, oidx,
-                       (int)K_o, Xq, Xs, B, ldb, nseg, (int)total_wg);
+                       (int)K_o, Xq, Xs, B, ldb, nseg, split.quads, (int)total_wg);
     return check_launch("quant_mxfp4_osc_kernel");
 }
 
@@ -210,14 +209,14 @@ __global__ void __launch_bounds__(QT) quant_mxfp4_dynamic_kernel(const uint16_t*
                                                                  int64_t ldx, uint8_t* __restrict__ Xq,
                                                                  uint8_t* __restrict__ Xs,
                                                                  uint16_t* __restrict__ Bd, int64_t ldb,
-                                                                 uint8_t* __restrict__ idx, int nseg,
+                                                                 uint8_t* __restrict__ idx, int nseg, int quads,
                                                                  int total_wg) {
     const int Kg = K >> 5, Kg4 = (Kg + 3) >> 2;
     const int nchunk = K >> 3;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: row and segment arithmetic stays on the scalar unit
     const uint32_t kbase = 31u - (uint32_t)((lane & 3) * 8);
     for (int wg = blockIdx.x; wg < total_wg; wg += gridDim.x) {
-        const QItem cur = quant_item(wg, wave, nseg, M);
+        const QItem cur = quant_item(wg, wave, nseg, quads, M);
         if (cur.m < 0) continue;
         const int m = cur.m;
         const u32x4* src = reinterpret_cast<const u32x4*>(X + (int64_t)m * ldx);
@@ -300,13 +299,13 @@ int launch_quant_mxfp4_dynamic(const uint16_t* X, int64_t M, int64_t K, int64_t 
     if (K > 65536) return fail(OSC_ERR_UNSUPPORTED, "quantize: K=%lld exceeds 65536", (long long)K);
     const int64_t nchunk = K / 8;
     const int nseg = (int)((nchunk + SEG_CHUNKS - 1) / SEG_CHUNKS);
-    const int64_t blocks = (M + 31) / 32;
-    const int64_t total_wg = (blocks + 7) / 8 * 8 * (8 * nseg);
+    const RowSplit split = row_split(M, nseg);
+    const int64_t total_wg = split.wgs;
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "quantize: M=%lld too large", (long long)M);
     const int64_t cap = 4096;
     const int grid = (int)(total_wg < cap ? total_wg : cap);
     hipLaunchKernelGGL(quant_mxfp4_dynamic_kernel, dim3(grid), dim3(QT), 0, st, X, (int)M, (int)K, ldx, Xq, Xs,
-                       Bd, ldb, idx, nseg, (int)total_wg);
+                       Bd, ldb, idx, nseg, split.quads, (int)total_wg);
     return check_launch("quant_mxfp4_dynamic_kernel");
 }
 
@@ -422,12 +421,12 @@ int launch_quant_fp8(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, uint8
 // ------------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(QT) quant_mxfp8_kernel(const uint16_t* __restrict__ X, int M, int K,
                                                          int64_t ldx, uint8_t* __restrict__ Xq,
-                                                         uint8_t* __restrict__ Xs, int nseg, int total_wg) {
+                                                         uint8_t* __restrict__ Xs, int nseg, int quads, int total_wg) {
     const int Kg = K >> 5, Kg4 = (Kg + 3) >> 2;
     const int nchunk = K >> 3;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);  // uniform: row and segment arithmetic stays on the scalar unit
     for (int wg = blockIdx.x; wg < total_wg; wg += gridDim.x) {
-        const QItem it = quant_item(wg, wave, nseg, M);
+        const QItem it = quant_item(wg, wave, nseg, quads, M);
         if (it.m < 0) continue;  // uniform over the wavefront
         const int m = it.m;
         const u32x4* src = reinterpret_cast<const u32x4*>(X + (int64_t)m * ldx);
@@ -477,12 +476,11 @@ int launch_quant_mxfp8(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, uin
                        hipStream_t st) {
     const int64_t nchunk = K / 8;
     const int nseg = (int)((nchunk + SEG_CHUNKS - 1) / SEG_CHUNKS);
-    const int64_t blocks = (M + 31) / 32;
-    const int64_t total_wg = (blocks + 7) / 8 * 8 * (8 * nseg);
+    const RowSplit split = row_split(M, nseg);
+    const int64_t total_wg = split.wgs;
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "quantize: M=%lld too large", (long long)M);
     const int grid = (int)(total_wg < 4096 ? total_wg : 4096);
-    hipLaunchKernelGGL(quant_mxfp8_kernel, dim3(grid), dim3(QT), 0, st, X, (int)M, (int)K, ldx, Xq, Xs, nseg,
-                       (int)total_wg);
+    hipLaunchKernelGGL(quant_mxfp8_kernel, dim3(grid), dim3(QT), 0, st, X, (int)M, (int)K, ldx, Xq, Xs, nseg, split.quads, (int)total_wg);
     return check_launch("quant_mxfp8_kernel");
 }
 

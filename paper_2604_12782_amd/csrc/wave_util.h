@@ -107,15 +107,15 @@ constexpr int SEG_CH = SEG_CHUNKS * 8;      // channels per segment
 struct QItem {
     int m, seg;
 };
-// linear work item (four per workgroup trip) -> (row, segment).  A block of 32 rows is
-// 32*nseg items; XCD x = workgroup % 8 owns blocks x, x+8, ...
-__device__ __forceinline__ QItem quant_item(int wg, int wave, int nseg, int M) {
-    const int per_block = 8 * nseg;          // workgroups per 32-row block
+// linear work item (four per workgroup trip) -> (row, segment).  A block of 4 * quads rows (row_split) is
+// 4*quads*nseg items; XCD x = workgroup % 8 owns blocks x, x+8, ...
+__device__ __forceinline__ QItem quant_item(int wg, int wave, int nseg, int quads, int M) {
+    const int per_block = quads * nseg;      // workgroups per block
     const int x = wg & 7, s = wg >> 3;
     const int block = x + 8 * (s / per_block);
     const int it = (s % per_block) * 4 + wave;  // item within the block, row-major (row, segment)
     QItem q;
-    q.m = block * 32 + it / nseg;
+    q.m = block * 4 * quads + it / nseg;
     q.seg = it % nseg;
     if (q.m >= M) q.m = -1;
     return q;

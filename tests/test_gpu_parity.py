@@ -98,11 +98,13 @@ def test_quant_shapes(osc, M, K, r):
 
 @pytest.mark.parametrize("M,K,G,pick", [
     (1, 1056, 32, "all"), (3, 2080, 32, "last"), (33, 4096, 32, "none in a segment"), (2100, 4128, 32, "dense segment"),
-    (2200, 5184, 64, "drawn"), (2500, 4096, 32, "drawn"), (8300, 4096, 64, "dense segment"), (70000, 96, 32, "drawn")])
+    (40, 12288, 32, "drawn"), (57, 4096, 32, "drawn"), (113, 4096, 64, "drawn"),
+    (223, 4096, 32, "drawn"), (2200, 5184, 64, "drawn"), (2500, 4096, 32, "drawn"), (8300, 4096, 64, "dense segment"), (70000, 96, 32, "drawn")])
 def test_quant_lists_and_trips(osc, M, K, G, pick):
     """The list as every wavefront sees it: empty, one-sided and long runs of a segment (more than the 128 entries that are kept in
     registers), the list's ends, rows that end inside a segment; one item a wavefront (few rows), and several, with
-    segments that change from one to the next and that do not.  The number of workgroups steps at 2048, 4096 and 16384 times four items."""
+    segments that change from one to the next and that do not.  The number of workgroups steps at 2048, 4096 and 16384 times four items, the
+    rows of a block at 7 times 4, 8, 16 and 32."""
     g = np.random.default_rng(M + K)
     c = np.arange(K)
     on = {"all": c >= 0, "last": c == K - 1, "none in a segment": (c < 1024) | (c >= 2048 + 5), "dense segment": (c >= 1024) & (c < 2040),
