@@ -334,10 +334,12 @@ int launch_scales_to_rowmajor(const uint8_t* S, int64_t rows, int64_t K, uint8_t
 // Per-token FP8 (e4m3).  The row lives in registers between the amax reduction and the
 // conversion, so X is read once.
 //
-// CACHED (both 8-bit quantisers): up to 64 MB of codes are stored plainly, for the GEMM that reads them next, by one trip per
-// workgroup; more go past the caches from a grid of 4096.  Quantiser + GEMM, us, streamed -> plain: FP8 1000 x 4096 x 12288
-// 64.3 -> 58.0, 8192 x 4096 x 4096 131.5 -> 127.6, MXFP8 67.1 -> 63.0 and 136.4 -> 133.8, 8192 x 256 x 4096 35.7 -> 33.9; 100 MB of codes,
-// 8192 x 256 x 12288, 98.3 -> 103.9 and 100.6 -> 104.4.
+// CACHED (both 8-bit quantisers): up to 64 MB of codes are stored plainly, for the GEMM that reads them next; more go past the
+// caches.  Quantiser + GEMM, us, streamed -> plain: FP8 8192 x 4096 x 4096 131.0 -> 126.8, 8192 x 256 x 4096 35.3 -> 31.5, 6000 x 512 x 3072
+// 30.2 -> 25.7, MXFP8 135.1 -> 132.1, 35.3 -> 32.5, 30.4 -> 26.2; 100 MB of codes, 8192 x 256 x 12288, 98.3 -> 103.9 and 100.6 -> 104.4.
+// Grid of both, at most 4096 workgroups that walk the rows: a workgroup per trip is slower from 5000 rows on, by 0 to 3 % with the
+// GEMM and by 5 to 15 % for FP8 rows of up to 1024 channels (4096 workgroups / one trip: FP8 65536 x 256 x 256 51.3 / 56.9, 32768 x 512 x 1024
+// 46.1 / 51.0, 8192 x 1024 x 4096 48.0 / 48.8, MXFP8 8192 x 1024 x 4096 48.8 / 49.7; the quantiser alone, FP8 32768 x 1024 25.5 / 29.6).
 // ------------------------------------------------------------------------------------------
 inline bool codes_cached(int64_t M, int64_t K) { return M * K <= ((int64_t)64 << 20); }
 
@@ -412,8 +414,7 @@ int launch_quant_fp8(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, uint8
     const int64_t nchunk = K / 8;
     const int cpt = (int)((nchunk + QT - 1) / QT);
     const bool cached = codes_cached(M, K);
-    const int64_t cap = cached ? 1 << 22 : 4096;
-    const int grid = (int)(M < cap ? M : cap);
+    const int grid = (int)(M < 4096 ? M : 4096);
 #define OSC_QLAUNCH(C) \
     hipLaunchKernelGGL((cached ? quant_fp8_kernel<C, true> : quant_fp8_kernel<C, false>), dim3(grid), dim3(QT), 0, st, X, (int)M, (int)K, ldx, X8, xs)
     if (cpt <= 1) OSC_QLAUNCH(1);
@@ -496,8 +497,7 @@ int launch_quant_mxfp8(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, uin
     const int64_t total_wg = split.wgs;
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "quantize: M=%lld too large", (long long)M);
     const bool cached = codes_cached(M, K);
-    const int64_t cap = cached && K >= SEG_CH ? 1 << 22 : 4096;
-    const int grid = (int)(total_wg < cap ? total_wg : cap);
+    const int grid = (int)(total_wg < 4096 ? total_wg : 4096);
     hipLaunchKernelGGL((cached ? quant_mxfp8_kernel<true> : quant_mxfp8_kernel<false>), dim3(grid), dim3(QT), 0, st, X, (int)M, (int)K, ldx, Xq, Xs, nseg, split.quads, (int)total_wg);
     return check_launch("quant_mxfp8_kernel");
 }

@@ -176,6 +176,27 @@ def test_quant_fp8(osc, M, K):
     assert np.array_equal(host(X8), r8), "e4m3 codes differ"
 
 
+@pytest.mark.parametrize("fmt", ["fp8", "mxfp8"])
+@pytest.mark.parametrize("M,K", [(4095, 96), (4097, 64), (20001, 1056), (8193, 8192), (70000, 960)])
+def test_quant_8bit_trips_and_stores(osc, M, K, fmt):
+    """Fewer rows than workgroups, and workgroups that walk several rows (segments of rows); codes on both sides of the size from which
+    on they are stored past the caches."""
+    X = wl.activations_diffuse(340 + M, M, K)
+    g = np.random.default_rng(M + K)
+    rows = np.unique(np.concatenate([np.arange(min(M, 20)), np.arange(max(0, M - 20), M), g.integers(0, M, 60), np.arange(4094, M, 4096)]))
+    sel = torch.from_numpy(rows).cuda()
+    if fmt == "fp8":
+        q, s = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_FP8_E4M3_TOKEN)
+        want, ws = oracle.quantize_fp8_rows(X[rows])
+        got, gs = q[sel].cpu().numpy(), s[sel].cpu().numpy().view(np.uint32)
+        ws = ws.view(np.uint32)
+    else:
+        q, s = osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_MXFP8)
+        want, ws = oracle.quantize_mxfp8(X[rows])
+        got, gs = q[sel].cpu().numpy(), osc.osc_unpack_act_scales(s, M, K)[sel].cpu().numpy()
+    assert np.array_equal(gs, ws) and np.array_equal(got, want)
+
+
 # ---- weights ------------------------------------------------------------------------------
 
 
