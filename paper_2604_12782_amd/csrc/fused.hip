@@ -383,7 +383,11 @@ __device__ __forceinline__ void swiglu_mxfp8_chunk(const u32x4 gv, const u32x4 u
     word |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)code, 0x10C, 0xF, 0xF, true) << 24;
     if ((lane & 15) == 0 && ok) *reinterpret_cast<uint32_t*>(sdst + (c >> 4) * 128) = word;
     const u32x2 out = mxfp8_codes(ww, code);
-    if (ok) dst[c] = out;  // (not streamed past the caches: the GEMM behind it 360 -> 339 us at 8192 x 4096 x 12288, this pass 81.7 -> 86)
+    // Stored plainly, for the GEMM that reads them next.  Pass and GEMM together, us, streamed -> plain: 32768 x 768 -> 2048 columns 88.1 -> 80.1,
+    // 262144 x 768 -> 2048 647 -> 609, 6000 x 12288 -> 512 121.5 -> 115.2, 16384 x 12288 -> 4096 847 -> 834; 24576 x 12288 -> 4096 1282 -> 1293,
+    // 100000 x 2048 -> 2048 549 -> 557.  No bound on the size: none would part the gains from the losses, which are large only where a
+    // GEMM of few columns follows many rows (16384 x 12288 -> 512 258 -> 278).  The pass by itself gets 5 to 10 % slower (8192 x 12288 78.7 -> 86.2).
+    if (ok) dst[c] = out;
 }
 
 // 4 B read and 1 B written per element.  One (row, 1024-channel segment) per wavefront and trip as in
@@ -492,8 +496,14 @@ int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, i
 // for rows of at most 2048 channels (no barrier), four for longer ones, so that a few hundred rows
 // still occupy the chip and the row's values fit few registers (with a wavefront per row and the table
 // 1000 x 12288 took 30.9 us, now 13.0; 8192 x 12288 95.5 -> 84.6 us, 32768 x 768 37.3 -> 24.7 us).
+//
+// CACHED: codes are stored plainly, for the GEMM that reads them next, but for 120 MB or more of them in rows of at most 1024 channels.
+// Pass and GEMM together, us, streamed -> plain: 32768 x 768 -> 2048 columns 89.1 -> 81.6, 150000 x 768 -> 2048 (110 MB) 377 -> 353,
+// 200000 x 768 -> 2048 (146 MB) 500 -> 513, 262144 x 768 -> 2048 651 -> 687, 262144 x 512 -> 2048 (128 MB) 501 -> 514; longer rows
+// 6000 x 12288 -> 512 122.9 -> 103.4, 8192 x 12288 -> 4096 398 -> 387, 16384 x 12288 -> 4096 820 -> 802, 100000 x 2048 -> 2048 556 -> 550.
+// The pass by itself gets 2 to 12 % slower (8192 x 12288 85.6 -> 87.6, 1000 x 12288 12.1 -> 13.6).
 // ------------------------------------------------------------------------------------------
-template <int CPT, int WPR>
+template <int CPT, int WPR, bool CACHED = true>
 __global__ void __launch_bounds__(FT) swiglu_quant_fp8_kernel(const uint16_t* __restrict__ G,
                                                               const uint16_t* __restrict__ U, int M, int K,
                                                               int64_t ldg, int64_t ldu, uint8_t* __restrict__ X8,
@@ -547,7 +557,10 @@ __global__ void __launch_bounds__(FT) swiglu_quant_fp8_kernel(const uint16_t* __
 #pragma unroll
         for (int i = 0; i < CPT; ++i) {
             const int c = t + 64 * WPR * i;
-            if (c < nchunk) dst[c] = fp8_codes(y[i], inv);  // (not streamed: block and GEMM together 895 -> 879 us at 8192 x 12288)
+            if (c < nchunk) {
+                if constexpr (CACHED) dst[c] = fp8_codes(y[i], inv);
+                else __builtin_nontemporal_store(fp8_codes(y[i], inv), dst + c);
+            }
         }
     }
 }
@@ -561,10 +574,14 @@ int launch_swiglu_quant_fp8(const uint16_t* G, const uint16_t* U, int64_t M, int
     const int64_t want = wave_rows ? (M + 3) / 4 : M;
     const int grid = (int)(want < MAX_GRID ? want : MAX_GRID);
     const int64_t cpt = wave_rows ? (nchunk + 63) / 64 : (nchunk + FT - 1) / FT;
-#define OSC_SLAUNCH(C, W)                                                                                   \
-    hipLaunchKernelGGL((swiglu_quant_fp8_kernel<C, W>), dim3(grid), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, X8, \
+    const bool streamed = K <= 1024 && M * K >= ((int64_t)120 << 20);
+#define OSC_SLAUNCH(...)                                                                                             \
+    hipLaunchKernelGGL((swiglu_quant_fp8_kernel<__VA_ARGS__>), dim3(grid), dim3(FT), 0, st, G, U, (int)M, (int)K, ldg, ldu, X8, \
                        xs, Yn)
-    if (wave_rows) {
+    if (streamed) {
+        if (cpt <= 1) OSC_SLAUNCH(1, 1, false);
+        else OSC_SLAUNCH(2, 1, false);
+    } else if (wave_rows) {
         if (cpt <= 1) OSC_SLAUNCH(1, 1);
         else if (cpt <= 2) OSC_SLAUNCH(2, 1);
         else OSC_SLAUNCH(4, 1);

@@ -138,6 +138,20 @@ def check_swiglu_fp8(osc, G, U, strided=False):
     assert none is None and torch.equal(X8b, X8) and torch.equal(xsb, xs)
 
 
+@pytest.mark.parametrize("M,K", [(122881, 1024), (122879, 1024), (245761, 512), (245759, 512)])
+def test_swiglu_fp8_many_codes(osc, M, K):
+    """Rows of one wavefront on both sides of the size from which on their codes are stored past the caches: many copies of a few rows
+    give the rows' codes and scales everywhere."""
+    gen = wl.rng(1601)
+    G, U = to_bf16_bits((gen.standard_normal((97, K)) * 3).astype(np.float32)), wl.activations_diffuse(1602, 97, K, p=0.01)
+    r8, rs = oracle.quantize_fp8_rows(oracle.swiglu(G, U))
+    row = torch.arange(M, device="cuda") % 97
+    big = lambda a: dev(a.view(np.int16))[row].view(torch.uint16)
+    X8, xs, _ = osc.osc_swiglu_quantize_act_fp8(big(G), big(U))
+    assert torch.equal(X8, dev(r8)[row])
+    assert torch.equal(xs.view(torch.int32), dev(rs.view(np.int32))[row])
+
+
 @pytest.mark.parametrize("M,K", [(1, 8), (7, 96), (40, 1056), (130, 4096), (9, 12288), (3, 16384), (5, 2056)])
 def test_swiglu_fp8_fused_matches_oracle(osc, M, K):
     gen = wl.rng(1600 + M)
