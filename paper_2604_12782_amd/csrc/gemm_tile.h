@@ -142,7 +142,12 @@ __device__ __forceinline__ int pair_col(int p) {
 }
 
 // Where lane r finds its row's scale word of a pair of weight blocks' first block: a block's words lie in the order of the rows, four
-// bytes each, `block` bytes from block to block; the second block's is the word behind it.
+// bytes each, `block` bytes from block to block; the second block's is the word behind it.  A read takes every second word of two
+// blocks, so with 32 banks lanes r and r ^ 8 meet wherever the blocks' 16-byte pieces lie (exchanging the half stages of every second block
+// changed no count): 2.3 cycles a read by the counter.  That is off the critical path: with every conflict gone (words of other rows, so
+// wrong results) attention and feed-forward blocks of 8192 tokens and the experts run 0 to 0.4 % faster, one round of 128 x 192 tiles 0.8 %.
+// Both words by one 8-byte read, which the lane halves shift: 8192 tokens, attention block 253 -> 259 us, feed-forward 892 -> 900;
+// words requested in the order of the lanes (MXFP8, persistent kernel): no conflicts, 8192 x 4096 x 12288 387 -> 391 us.
 __device__ __forceinline__ uint32_t pair_scale(int r, uint32_t block) {
     return ((uint32_t)(r >> 3) & 1) * block + (4 * ((uint32_t)r & 7) + 2 * ((uint32_t)r >> 4)) * 4;
 }
