@@ -178,7 +178,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
 #pragma unroll
         for (int i = 0; i < LA; ++i) ga[i] = (uint32_t)min(ld.m0 + (t >> 3) + RPP * i, ld.row_end - 1);
 #pragma unroll
-        for (int i = 0; i < LB; ++i) gb[i] = (uint32_t)min(ld.n0 + pair_col<TN>((t >> 3) + RPP * i), a.N - 1);
+        for (int i = 0; i < LB; ++i) gb[i] = (uint32_t)min(ld.n0 + pair_col<TN, WN>((t >> 3) + RPP * i), a.N - 1);
         int gs = min(ld.m0 + wave * 32 + r, ld.row_end - 1);
         if (mapped) {
 #pragma unroll
@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_flow_kernel(KArgs a, int nt
         // X: row r of block b.  Weights: the row that pair_col() gives to lane r; a block's words lie in the order of the rows
         const int j = b - TM;
         const bool single = TN % 2 && j == TN - 1;
-        const uint8_t* const blk = lds + s * Slot::BYTES + Slot::ROWS + (b < TM ? wm * TM + b : NBA + wn * TN + (j & ~1)) * SBB;
+        const uint8_t* const blk = lds + s * Slot::BYTES + Slot::ROWS + (b < TM ? wm * TM + b : NBA + block_col<TN, WN>(wn, single ? j : j & ~1) / 32) * SBB;
         const uint8_t* const sc = blk + (b < TM ? r * 4 : single ? (2 * (r & 15) + (r >> 4)) * 4 : pair_scale(r, SBB) + (j & 1) * 4);
         if constexpr (DUAL) S[b] = *reinterpret_cast<const uint16_t*>(sc + H * 128 + 2 * q);
         else S[b] = sc[2 * H + q];

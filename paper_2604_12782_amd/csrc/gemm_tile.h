@@ -129,17 +129,35 @@ __device__ __forceinline__ TilePos tile_at(const KArgs& a, int tile) {
     return p;
 }
 
-// Output column, relative to its wavefront's first, that lane r = p % 32 of block p / 32 (of TN) holds with store_pairs below:
-// the kernel places that weight row of the tile on LDS row p.  Blocks 2b and 2b + 1 share 64 columns: a lane's two results of
-// one row are neighbours, and lanes r and r ^ 16 hold four columns in a row.  In the last block of an odd TN those lanes
-// hold neighbours.
-template <int TN>
-__device__ __forceinline__ int pair_col(int p) {
-    const int w = TN % 2 ? p / (32 * TN) * (32 * TN) : p & ~63, o = p - w;  // the wavefront's first, or the pair's
-    const int c = o & 15, h = (o >> 4) & 1, j = o >> 5;
-    if (TN % 2 && j == TN - 1) return w + 32 * j + 2 * c + h;
-    return w + 64 * (j >> 1) + 4 * c + 2 * h + (j & 1);
+// First column in the tile of block j of wavefront column w (of WN), TN blocks each: pairs of blocks first, then the last blocks of an
+// odd TN side by side.  So every pair begins on a 128-byte line of bf16 results and two last blocks share one.  With a wavefront's blocks in a
+// row, 128 x 192 tiles had half of their pairs across two lines: 512 x 12288 x 4096 wrote 14.3 MB for 12.0, now 12.3, and 12.0 with the halves of
+// a shared line stored plainly, so that they meet in L2; 25.9 -> 25.6 us with the quantiser, 1000 x 6144 x 4096 24.0 -> 23.5.  (64 x 128 tiles, whose
+// wavefronts hold a last block each, stream it: 128 x 8192 x 4096 13.5 us, 13.6 with plain stores, 1000 x 2048 x 2048 10.1 and 10.3.)
+template <int TN, int WN>
+constexpr int block_col(int w, int j) {
+    return TN % 2 && j == TN - 1 ? 32 * (WN * (TN - 1) + w) : 32 * (w * (TN & ~1) + j);
 }
+
+// Column in the tile that lane r = p % 32 of block p / 32 (of TN * WN) holds with store_pairs below: the kernel places that weight row of the tile on
+// LDS row p.  Blocks 2b and 2b + 1 of a wavefront share 64 columns: a lane's two results of one row are neighbours, and lanes r and
+// r ^ 16 hold four columns in a row.  In the last block of an odd TN those lanes hold neighbours.
+template <int TN, int WN = 1>
+constexpr int pair_col(int p) {
+    const int w = TN % 2 ? (int)((uint32_t)p / (32 * TN)) : 0, o = TN % 2 ? (int)((uint32_t)p % (32 * TN)) : p & 63;
+    const int c = o & 15, h = (o >> 4) & 1, j = o >> 5;
+    if (TN % 2 && j == TN - 1) return block_col<TN, WN>(w, j) + 2 * c + h;
+    return (TN % 2 ? block_col<TN, WN>(w, j & ~1) : p & ~63) + 4 * c + 2 * h + (j & 1);
+}
+template <int TN, int WN>
+constexpr bool pairs_on_lines() {  // every column of the tile once, pairs of blocks on whole lines of bf16
+    uint32_t seen[TN * WN] = {};
+    for (int p = 0; p < 32 * TN * WN; ++p) seen[pair_col<TN, WN>(p) / 32] |= 1u << (pair_col<TN, WN>(p) % 32);
+    for (int b = 0; b < TN * WN; ++b)
+        if (seen[b] != ~0u || (b % TN % 2 == 0 && b % TN + 1 < TN && block_col<TN, WN>(b / TN, b % TN) % 64 != 0)) return false;
+    return true;
+}
+static_assert(pairs_on_lines<1, 4>() && pairs_on_lines<2, 2>() && pairs_on_lines<2, 4>() && pairs_on_lines<3, 2>() && pairs_on_lines<4, 2>(), "tile's columns");
 
 // Where lane r finds its row's scale word of a pair of weight blocks' first block: a block's words lie in the order of the rows, four
 // bytes each, `block` bytes from block to block; the second block's is the word behind it.  A read takes every second word of two
@@ -219,7 +237,7 @@ __device__ __forceinline__ void store_pairs(const KArgs& a, const TilePos& tp, v
                 if constexpr (BF16) {
                     const uint32_t word = __builtin_bit_cast(uint32_t, __builtin_convertvector(v, v2bf));
                     if constexpr (KIND >= 1) {
-                        store_y<WHOLE>(word, p);
+                        store_y<WHOLE || (TN > 1)>(word, p);
                     } else {
                         uint16_t* const dst = reinterpret_cast<uint16_t*>(p);
                         if (WHOLE || col < a.N) dst[0] = (uint16_t)word;
@@ -233,7 +251,7 @@ __device__ __forceinline__ void store_pairs(const KArgs& a, const TilePos& tp, v
             };
 #pragma unroll
             for (int j = 0; j < TN; j += 2) {
-                const int col0 = tp.n0 + wn * (TN * 32) + j * 32;
+                const int col0 = tp.n0 + block_col<TN, WN>(wn, j);
                 uint8_t* p = reinterpret_cast<uint8_t*>(a.Y) + SZ * ((int64_t)row0 * ldy + col0);
                 if constexpr (TN % 2 == 1)
                     if (j + 1 == TN) {
