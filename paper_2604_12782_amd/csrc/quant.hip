@@ -72,13 +72,13 @@ __global__ void __launch_bounds__(QT) quant_mxfp4_osc_kernel(
     if (cur.m < 0) return;
 
     SegmentList list;
+    if constexpr (LIST) list.take(cur.seg, lane, nchunk, bits, colstart, och);  // (of all items: walk_grid)
     auto convert = [&](const QItem& it, const u32x4& v0, const u32x4& v1) __attribute__((always_inline)) {
         const int m = it.m;
         const int cbase = it.seg * SEG_CHUNKS;
         uint8_t* dst = Xq + (int64_t)m * (K >> 1);
         uint8_t* sdst = Xs + (int64_t)(m >> 5) * Kg4 * 128 + (m & 31) * 4;
         if constexpr (LIST) {
-            if (!MULTI || it.seg != list.seg) list.take(it.seg, lane, nchunk, bits, colstart, och);
             strip[lane] = v0;
             strip[lane + 64] = v1;
         }
@@ -145,6 +145,23 @@ __global__ void __launch_bounds__(QT) quant_mxfp4_osc_kernel(
     }
 }
 
+// Workgroups, at most `cap`, that walk the items of rows of nseg segments so that a wavefront's items are of one segment: from trip to trip an
+// item's number grows by half as many, which nseg divides (8192 x 5152 25.4 us with a segment that changes, 24.3 without).
+constexpr int64_t walk_grid(int64_t cap, int nseg) {
+    const int64_t turn = 8 * (nseg % 4 == 0 ? nseg / 4 : nseg % 2 == 0 ? nseg / 2 : nseg);
+    return cap - cap % turn;
+}
+constexpr int64_t WALK_CAP = 4096, WALK_CAP_LIST = 1024;
+constexpr bool walks_in_one_segment() {
+    for (int nseg = 1; nseg <= 65536 / SEG_CH; ++nseg)
+        for (int64_t cap : {WALK_CAP, WALK_CAP_LIST}) {
+            const int64_t g = walk_grid(cap, nseg);
+            if (g <= 0 || g % 8 != 0 || g / 2 % nseg != 0) return false;
+        }
+    return true;
+}
+static_assert(walks_in_one_segment(), "segments change on the way");
+
 // B columns of a table-free call still have to read +0 when the caller passes a buffer.
 __global__ void zero_rows_kernel(uint16_t* B, int M, int64_t ldb) {
     int64_t n = (int64_t)M * (ldb >> 3);
@@ -176,11 +193,9 @@ int launch_quant_mxfp4(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, con
     // expand (us, 2048 / 1024 / 4096 workgroups: 4096 x 4096 11.0 / 10.5 / 10.7, 1000 x 12288 10.3 / 9.5 / 10.0,
     // 8192 x 4096 18.4 / 18.0 / 18.1, 16384 x 4096 35 / 33 / 31.6; 2000 x 4096 6.4 / 6.8 / 6.4; no list, 8192 x 4096 16.1 / 19 / 16.0)
     const bool list = K_o > 0;
-    // (a multiple of so many that a wavefront stays in its segment: 8192 x 5152 25.4 -> 24.3)
-    const int64_t cap = list && K >= 4096 && total_wg > 2048 && total_wg < 16384 ? 1024 : 4096;
-    const int64_t turn = 8 * (nseg % 4 == 0 ? nseg / 4 : nseg % 2 == 0 ? nseg / 2 : nseg);
+    const int64_t cap = list && K >= 4096 && total_wg > 2048 && total_wg < 16384 ? WALK_CAP_LIST : WALK_CAP;
     const bool multi = total_wg > cap;
-    const int grid = (int)(multi ? cap - cap % turn : total_wg);
+    const int grid = (int)(multi ? walk_grid(cap, nseg) : total_wg);
     auto kern = group == 64 ? (list ? (multi ? quant_mxfp4_osc_kernel<64, true, true> : quant_mxfp4_osc_kernel<64, true, false>)
                                     : (multi ? quant_mxfp4_osc_kernel<64, false, true> : quant_mxfp4_osc_kernel<64, false, false>))
                             : (list ? (multi ? quant_mxfp4_osc_kernel<32, true, true> : quant_mxfp4_osc_kernel<32, true, false>)

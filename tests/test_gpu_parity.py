@@ -102,8 +102,8 @@ def test_quant_shapes(osc, M, K, r):
     (223, 4096, 32, "drawn"), (2200, 5184, 64, "drawn"), (2500, 4096, 32, "drawn"), (8300, 4096, 64, "dense segment"), (70000, 96, 32, "drawn")])
 def test_quant_lists_and_trips(osc, M, K, G, pick):
     """The list as every wavefront sees it: empty, one-sided and long runs of a segment (more than the 128 entries that are kept in
-    registers), the list's ends, rows that end inside a segment; one item a wavefront (few rows), and several, with
-    segments that change from one to the next and that do not.  The number of workgroups steps at 2048, 4096 and 16384 times four items, the
+    registers), the list's ends, rows that end inside a segment; one item a wavefront (few rows), and several of
+    one segment, for row lengths of an even and an odd number of segments.  The number of workgroups steps at 2048, 4096 and 16384 times four items, the
     rows of a block at 7 times 4, 8, 16 and 32."""
     g = np.random.default_rng(M + K)
     c = np.arange(K)
