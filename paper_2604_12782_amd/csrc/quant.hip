@@ -181,10 +181,11 @@ int launch_quant_mxfp4(const uint16_t* X, int64_t M, int64_t K, int64_t ldx, con
     size_t smem = 4 * SEG_CHUNKS * 16;
     if (K_o > 0) {
         smem += (size_t)(K / 32) * 4 + (size_t)(nseg + 1) * 4 + (size_t)K_o * 2;
-        // the range that is accepted: a mask word per channel pair beside the rest
+        // the range of the entry point: what a mask word per channel pair beside the rest would fit (the kernel needs less)
         const size_t range = smem + (size_t)(K / 2 - K / 32) * 4;
         if (range > 160 * 1024)
-            return fail(OSC_ERR_UNSUPPORTED, "quantize: K=%lld with K_o=%d needs %zu bytes of LDS", (long long)K, (int)K_o, range);
+            return fail(OSC_ERR_UNSUPPORTED, "quantize: K=%lld with K_o=%d is out of range: 2 K + 2 K_o bytes and a little more than 8 KB may be 160 KB at most",
+                        (long long)K, (int)K_o);
     }
     const RowSplit split = row_split(M, nseg);
     const int64_t total_wg = split.wgs;

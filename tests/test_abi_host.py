@@ -112,6 +112,8 @@ def test_bad_arguments_are_rejected_on_the_host(lib):
     assert q(FAKE + 2, 4, 64, 64, None, 0, 0, FAKE, FAKE, None, 0, None) == -4
     assert q(FAKE, 4, 64, 68, None, 0, 0, FAKE, FAKE, None, 0, None) == -4  # ldx % 8
     assert q(FAKE, 4, 64, 64, FAKE, 2, 0, FAKE, FAKE, FAKE, 12, None) == -4  # ldb % 8
+    assert q(FAKE, 4, 65536, 65536, FAKE, 12159, 0, FAKE, FAKE, FAKE, 12160, None) == -4  # 2 K + 2 K_o + 8452 bytes: over 160 KB
+    assert "out of range" in osc.osc_last_error() and "K_o=12159" in osc.osc_last_error()
     # empty problems are fine and touch nothing
     assert q(None, 0, 64, 64, None, 0, 0, None, None, None, 0, None) == 0
     g = lib.osc_dual_gemm

@@ -99,7 +99,7 @@ def test_quant_shapes(osc, M, K, r):
 @pytest.mark.parametrize("M,K,G,pick", [
     (1, 1056, 32, "all"), (3, 2080, 32, "last"), (33, 4096, 32, "none in a segment"), (2100, 4128, 32, "dense segment"),
     (40, 12288, 32, "drawn"), (57, 4096, 32, "drawn"), (113, 4096, 64, "drawn"),
-    (223, 4096, 32, "drawn"), (2200, 5184, 64, "drawn"), (2500, 4096, 32, "drawn"), (8300, 4096, 64, "dense segment"), (70000, 96, 32, "drawn")])
+    (223, 4096, 32, "drawn"), (2200, 5184, 64, "drawn"), (2500, 4096, 32, "drawn"), (8300, 4096, 64, "dense segment"), (70000, 96, 32, "drawn"), (3, 65536, 32, "most")])
 def test_quant_lists_and_trips(osc, M, K, G, pick):
     """The list as every wavefront sees it: empty, one-sided and long runs of a segment (more than the 128 entries that are kept in
     registers), the list's ends, rows that end inside a segment; one item a wavefront (few rows), and several of
@@ -108,7 +108,10 @@ def test_quant_lists_and_trips(osc, M, K, G, pick):
     g = np.random.default_rng(M + K)
     c = np.arange(K)
     on = {"all": c >= 0, "last": c == K - 1, "none in a segment": (c < 1024) | (c >= 2048 + 5), "dense segment": (c >= 1024) & (c < 2040),
-          "drawn": g.random(K) < 0.06}[pick]
+          "drawn": g.random(K) < 0.06, "most": c % (K // 12158) == 0}[pick]
+    if pick == "most":  # the longest list that a row of 65536 channels may have
+        on &= np.cumsum(on) <= 12158
+        assert on.sum() == 12158
     if pick == "none in a segment":
         on &= g.random(K) < 0.05
     X = wl.activations_diffuse(77 + M, M, K)
