@@ -97,26 +97,69 @@ def test_flow_several_tiles_per_workgroup(osc, tuning, tile, mode):
     check(osc, tuning, tile, mode, M, N, 256 * (lead + 1) if mode == "dual" else 128 * (lead + 3), 2 if mode == "dual" else 0, 7700 + tile)
 
 
-@pytest.mark.parametrize("mode", ["dual", "fp8", "mx8"])
-@pytest.mark.parametrize("cfg", ["0,7", "1,7", "2,7", "3,7", "4,2", "4,1", "2,1", "1,1"])
+GUARD = 256  # rows behind a view: as many as the tallest tile
+
+
+def into_views(call, osc, M, N, Y, Yb, what, rows=None):
+    """The call's results written into views whose rows start at every residue of the store widths (16 bytes fp32, 8 bytes bf16), with
+    columns on both sides and rows behind them: the values of a buffer of their own (of the first `rows`), and not a byte beside them."""
+    n = M if rows is None else rows
+    for dt, ydt, want in ((torch.float32, osc.OSC_DT_F32, Y), (torch.bfloat16, osc.OSC_DT_BF16, Yb)):
+        for pad, col0 in ((0, 0), (4, 0), (4, 2), (8, 4), (2, 2), (3, 1), (1, 0)):
+            wide = torch.full((M + GUARD, N + pad), 7.0, dtype=dt, device="cuda")
+            call(ydt, wide[:M, col0:col0 + N])
+            assert torch.equal(wide[:n, col0:col0 + N], want[:n]), (what, dt, pad, col0)
+            wide[:n, col0:col0 + N] = 7
+            assert bool((wide == 7).all()), (what, dt, pad, col0)
+
+
+TILED = [(c, m) for c in ("0,7", "1,7", "2,7", "3,7", "4,2", "4,1", "2,1", "1,1") for m in ("dual", "fp8", "mx8")]
+TILED += [("2,2", "dual"), ("4,4", "dual"), ("2,0", "dual"), ("1,0", "dual"), ("2,0", "fp8"), ("1,0", "fp8")]  # (not built for the others)
+
+
+@pytest.mark.parametrize("cfg,mode", TILED)
 def test_output_views(osc, tuning, cfg, mode):
-    """The epilogue that all tiled kernels share, into views whose rows start at every residue of its store widths (16 bytes fp32, 8 bytes
-    bf16): the same values as in a buffer of their own, the rest of the view's buffer untouched; columns up to a
-    tile's last one, and rows past it.  The values themselves: the tests of each kernel."""
+    """The epilogue that all tiled kernels share, into views, for tiles inside the result, tiles with rows past it and tiles with columns
+    past it; the values against the oracle."""
+    tile, kern = map(int, cfg.split(","))
+    for M, N in ((256, 512), (131, 512), (131, 395), (70, 1)) if kern != 2 else ((256, 512),):
+        call, ref = problem(osc, mode, M, N, 1280, 1 if mode == "dual" else 0, 8100 + M)
+        tuning.gemm(cfg)
+        Y, Yb = call(osc.OSC_DT_F32), call(osc.OSC_DT_BF16)
+        assert osc.osc_tuning_last_gemm() == (kern, tile)
+        want = ref(np.arange(M))
+        assert np.abs(Y.cpu().numpy().astype(np.float64) - want).max() <= TOL * np.abs(want).max()
+        assert torch.equal(Yb, Y.to(torch.bfloat16))
+        into_views(call, osc, M, N, Y, Yb, (cfg, mode, M, N))
+
+
+@pytest.mark.parametrize("cfg", ["0,7", "4,1", "2,1", "1,1", "1,0"])
+def test_output_views_of_experts(osc, tuning, cfg):
+    """The same for experts, some of them empty, whose last tiles have rows of the next expert behind them, and with offsets that end before
+    the output does."""
+    sizes, N, K = [70, 0, 1, 129, 60, 0], 395, 1280
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    T, E = int(off[-1]), len(sizes)
+    X = wl.activations_diffuse(8200, T, K)
+    q, q8 = osc.osc_quantize_act(dev(X)), osc.osc_quantize_act(dev(X), None, osc.OSC_FMT_FP8_E4M3_TOKEN)
+    W = [wl.weights(8210 + e, N, K) for e in range(E)]
+    Wp, Wp8 = torch.cat([osc.osc_pack_weight(dev(w), None) for w in W]), torch.cat([osc.osc_pack_weight_fp8(dev(w)) for w in W])
+    row_map = np.random.default_rng(8201).permutation(T).astype(np.int32)
+    calls = {"dual": lambda d_off: lambda ydt, out=None: osc.osc_grouped_dual_gemm(*q, dev(row_map), d_off, T, Wp, N, K, 0, ydt, out=out),
+             "fp8": lambda d_off: lambda ydt, out=None: osc.osc_fp8_gemm(*q8, Wp8, N, K, expert_offsets=d_off, y_dtype=ydt, out=out)}
+    a, w = oracle.quantize_mxfp4_osc(X), [oracle.quantize_mxfp4_osc(x)[:2] for x in W]
+    a8, w8 = oracle.quantize_fp8_rows(X), [oracle.quantize_fp8_rows(x) for x in W]
+    refs = {"dual": oracle.grouped_dual_gemm(a[0], a[1], None, row_map, off, np.stack([x[0] for x in w]), np.stack([x[1] for x in w]), None),
+            "fp8": oracle.grouped_fp8_gemm(*a8, off, np.stack([x[0] for x in w8]), np.stack([x[1] for x in w8]))}
     tuning.gemm(cfg)
-    for M, N in ((256, 512), (131, 395), (70, 1)) if cfg != "4,2" else ((256, 512),):
-        call, _ = problem(osc, mode, M, N, 1280, 1 if mode == "dual" else 0, 8100 + M)
-        for dt, ydt in ((torch.float32, osc.OSC_DT_F32), (torch.bfloat16, osc.OSC_DT_BF16)):
-            Y = call(ydt)
-            assert osc.osc_tuning_last_gemm() == tuple(int(x) for x in reversed(cfg.split(",")))
-            for pad, col0 in ((4, 0), (4, 2), (8, 4), (2, 2), (3, 1), (1, 0)):
-                wide = torch.full((M, N + pad), 7.0, dtype=dt, device="cuda")
-                call(ydt, wide[:, col0:col0 + N])
-                assert torch.equal(wide[:, col0:col0 + N], Y), (cfg, mode, M, N, dt, pad, col0)
-                assert bool((wide[:, :col0] == 7).all()) and bool((wide[:, col0 + N:] == 7).all())
-            if dt == torch.float32:
-                Y32 = Y
-        assert torch.equal(Y, Y32.to(torch.bfloat16))
+    for name, make in calls.items():
+        call = make(dev(off))
+        Y, Yb = call(osc.OSC_DT_F32), call(osc.OSC_DT_BF16)
+        assert osc.osc_tuning_last_gemm() == tuple(int(x) for x in reversed(cfg.split(","))), name
+        assert np.abs(Y.cpu().numpy().astype(np.float64) - refs[name]).max() <= TOL * np.abs(refs[name]).max(), name
+        assert torch.equal(Yb, Y.to(torch.bfloat16)), name
+        into_views(call, osc, T, N, Y, Yb, (cfg, name))
+        into_views(make(dev(np.minimum(off, 150).astype(np.int32))), osc, T, N, Y, Yb, (cfg, name, "short"), 150)
 
 
 @pytest.mark.parametrize("stages,r", [(2, 0), (2, 1), (3, 4), (4, 0), (4, 2)])
