@@ -146,17 +146,17 @@ int launch_fp8_gemm(const GemmProblem& p, hipStream_t st);
 int launch_mxfp8_gemm(const GemmProblem& p, hipStream_t st);
 
 // Work split of the row-streaming kernels (quant_item): blocks of 4 * quads rows, dealt to the XCDs in groups of eight.  32 rows, whose
-// scale words share lines, where there are eight such blocks or only a little to read (128 segments); others take smaller
-// blocks, down to four rows, so that all XCDs and their paths to memory have some.  us, SwiGLU + MXFP8 16 x 12288 3.9 -> 3.1, 64 x
-// 12288 5.2 -> 3.7; MXFP4 quantiser 64 x 4096 3.4 -> 3.15, 16 x 12288 4.1 -> 3.7; below the line 8 x 4096 2.8 -> 2.9, MXFP8 16 x 4096
-// 3.05 -> 3.2.
+// scale words share lines, where there are eight such blocks or only a little to read (128 segments, 192 where a row has one or two); others
+// take smaller blocks, down to four rows, so that all XCDs and their paths to memory have some.  us, SwiGLU + MXFP8 16 x 12288 3.6 -> 2.85, 64 x
+// 12288 4.6 -> 3.0, 16 x 4096 3.0 -> 2.75; MXFP8 20 x 4096 2.7 -> 2.25, 64 x 8192 2.75 -> 2.4; MXFP4 quantiser 64 x 4096 3.4 -> 3.15; below the line
+// 8 x 4096 2.8 -> 2.9, MXFP8 16 x 4096 3.05 -> 3.2, 64 x 2048 2.25 -> 2.33, 80 x 1056 2.23 -> 2.31, SwiGLU + MXFP8 80 x 1056 2.67 -> 2.76.
 struct RowSplit {
     int quads;
     int64_t wgs;  // workgroups of four items
 };
 inline RowSplit row_split(int64_t M, int nseg) {
     int quads = 8;
-    while (quads > 1 && M * nseg >= 128 && (M + 4 * quads - 1) / (4 * quads) < 8) quads /= 2;
+    while (quads > 1 && M * nseg >= (nseg > 2 ? 128 : 192) && (M + 4 * quads - 1) / (4 * quads) < 8) quads /= 2;
     const int64_t blocks = (M + 4 * quads - 1) / (4 * quads);
     return RowSplit{quads, (blocks + 7) / 8 * 8 * quads * nseg};
 }
