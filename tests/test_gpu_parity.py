@@ -108,10 +108,9 @@ def test_quant_lists_and_trips(osc, M, K, G, pick):
     g = np.random.default_rng(M + K)
     c = np.arange(K)
     on = {"all": c >= 0, "last": c == K - 1, "none in a segment": (c < 1024) | (c >= 2048 + 5), "dense segment": (c >= 1024) & (c < 2040),
-          "drawn": g.random(K) < 0.06, "most": c % (K // 12158) == 0}[pick]
+          "drawn": g.random(K) < 0.06, "most": c % 5 == 0}[pick]
     if pick == "most":  # the longest list that a row of 65536 channels may have
         on &= np.cumsum(on) <= 12158
-        assert on.sum() == 12158
     if pick == "none in a segment":
         on &= g.random(K) < 0.05
     X = wl.activations_diffuse(77 + M, M, K)
