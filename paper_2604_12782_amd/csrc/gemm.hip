@@ -2128,7 +2128,10 @@ static int launch_gemm(const GemmProblem& p, hipStream_t st) {
         // being in flight instead of one: dual 512 x 4096 x 4096  17.2 -> 12.9, MXFP8 256 x 4096 x 12288  95 -> 47).
         // The 256 x 256 side costs, per round and in us, 3 + 0.83 a stage + 1.04 a stage and filled share of the CUs
         // (dual path, DMA kernel for one round and persistent kernel for more), or 7 + 1.48 a stage (8 bits,
-        // persistent kernel), from the same measurements.
+        // persistent kernel), from the same measurements.  Between the two the choice is less good than between the flowing kernel's own
+        // tiles: over 120 shapes of 2100 to 16384 rows with more than one 256 x 256 tile per CU it is 3.6 % behind the faster side
+        // on average and by more than 3 % in 30, nearly all dual path with a ragged row tail or few stages that
+        // 128 x 256 tiles would serve better (12455 x 3072 x 1280 53.7 against 41.5 us, 8209 x 13056 x 1024 89.4 against 83.1).
         double flow_cost = 0.0;
         flow_tile = flow_choose(MODE, p.M, p.N, stages, (int)ncu, &flow_cost);
         if (flow_tile >= 0) {

@@ -170,8 +170,10 @@ __device__ __forceinline__ uint32_t pair_scale(int r, uint32_t block) {
     return ((uint32_t)(r >> 3) & 1) * block + (4 * ((uint32_t)r & 7) + 2 * ((uint32_t)r >> 4)) * 4;
 }
 
-// Results are streamed past the caches, but for the persistent kernel's, whose next tiles gain by it (8192 x 24576 x 4096 dual path
-// 520 -> 501 us in a feed-forward block, the SwiGLU pass behind it 81.7 -> 79.6; 8192 x 1024 x 4096 on the flowing kernel 25.8 -> 27.3).
+// Where four bf16 columns of a row leave at once (two in the last block of 64 x 128 tiles), the flowing, DMA, staged and ring kernels stream
+// them past the caches; the persistent kernel stores plainly, which its next tiles gain by (8192 x 24576 x 4096 dual path 520 -> 501 us in a
+// feed-forward block, the SwiGLU pass behind it 81.7 -> 79.6; 8192 x 1024 x 4096 on the flowing kernel 25.8 -> 27.3).  fp32 results and those
+// that leave element by element are plain stores everywhere.
 template <bool CACHED, class T>
 __device__ __forceinline__ void store_y(T v, uint8_t* p) {
     if constexpr (CACHED) *reinterpret_cast<T*>(p) = v;
