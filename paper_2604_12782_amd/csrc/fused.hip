@@ -392,8 +392,8 @@ __device__ __forceinline__ void swiglu_mxfp8_chunk(const u32x4 gv, const u32x4 u
 
 // 4 B read and 1 B written per element.  One (row, 1024-channel segment) per wavefront and trip as in
 // the quantisers; a lane's four 16-byte loads per trip on up to eight wavefronts per SIMD keep enough
-// bytes in flight.  8192 x 12288: 98.9 -> 79.0 us (6.4 TB/s), 1000 x 12288: 16.9 -> 12.9 us, table launch
-// included in the old figures.
+// bytes in flight.  8192 x 12288: 98.9 -> 79.0 us (6.4 TB/s), 1000 x 12288: 16.9 -> 12.9 us with streaming stores, table launch
+// included in the old figures; 86 to 89 and 13.9 with the plain ones that the GEMM behind gains by.
 __global__ void __launch_bounds__(FT) swiglu_quant_mxfp8_kernel(const uint16_t* __restrict__ G,
                                                                 const uint16_t* __restrict__ U, int M, int K,
                                                                 int64_t ldg, int64_t ldu, uint8_t* __restrict__ Xq,
@@ -469,7 +469,8 @@ int launch_swiglu_quant_mxfp8(const uint16_t* G, const uint16_t* U, int64_t M, i
     const int64_t total_wg = split.wgs;
     if (total_wg > 0x7fffffff) return fail(OSC_ERR_UNSUPPORTED, "swiglu+quantize: M=%lld too large", (long long)M);
     // One trip per workgroup: the hardware hands out new workgroups as old ones drain, which beats walking a
-    // fixed grid at every size of whole segments (8192 x 12288: 79 us, a grid of 8192 86 us, of 2048 92 us).
+    // fixed grid at every size of whole segments (8192 x 12288: 79 us, a grid of 8192 86 us, of 2048 92 us; with plain stores 89, 89.6
+    // and 93, with the GEMM behind it 413, 417 and 417).
     // Rows of less than a segment are the exception.
     const int64_t flat_wg = (M * nchunk + 4 * SEG_CHUNKS - 1) / (4 * SEG_CHUNKS) + 7;
     // All rows' chunks in one line where segments would leave a fifth of the lanes or more idle, and lanes for a thousand segments
@@ -570,7 +571,7 @@ int launch_swiglu_quant_fp8(const uint16_t* G, const uint16_t* U, int64_t M, int
     const int64_t nchunk = K / 8;
     if (nchunk > 8 * FT) return fail(OSC_ERR_UNSUPPORTED, "swiglu+fp8 quantize: K=%lld exceeds 16384", (long long)K);
     const bool wave_rows = nchunk <= 4 * 64;
-    // one row (four short rows) per workgroup, as above: 8192 x 12288 85 us, 89 us on a grid of 2048
+    // one row (four short rows) per workgroup, as above: 8192 x 12288 81 us, 81.5 on a grid of 8192, 87 on one of 2048
     const int64_t want = wave_rows ? (M + 3) / 4 : M;
     const int grid = (int)(want < MAX_GRID ? want : MAX_GRID);
     const int64_t cpt = wave_rows ? (nchunk + 63) / 64 : (nchunk + FT - 1) / FT;
